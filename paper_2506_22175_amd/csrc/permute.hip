@@ -172,96 +172,90 @@ __global__ __launch_bounds__(PERM_THREADS) void zero_dropped_kernel(const int* _
     for (int c = lane; c < U; c += 64) out[c] = make_uint4(0, 0, 0, 0);
 }
 
-// dx[t] = sum_j dDI[slot[t,j]] + dL[t,:] Wg^T with the gate matrix transposed into LDS as
-// float (no conversion per token); a wavefront takes two tokens at a time, so each LDS read
-// feeds two tokens, and workgroups walk over the tokens.  Row e of W_g^T is stored so that the
-// 16 bytes a lane reads are contiguous across lanes: element d = unit*N + 4*h + r sits at
-// e*M + h*(M/N)*4 + unit*4 + r (N = elements of the storage type per 16-byte unit).
-constexpr int DXF_THREADS = 1024;
-constexpr int DXF_WAVES = DXF_THREADS / 64;
-template <typename T>
-__global__ __launch_bounds__(DXF_THREADS) void dispatch_bwd_f32lds_kernel(
-    const T* __restrict__ dDI, const int* __restrict__ slot, const float* __restrict__ dL,
-    const T* __restrict__ Wg, T* __restrict__ dx, int t_begin, int t_count, int M, int E, int k) {
-    extern __shared__ __attribute__((aligned(16))) char dxb_smem[];
-    float* wgt = reinterpret_cast<float*>(dxb_smem);
-    constexpr int N = Unit<T>::N;
-    constexpr int NH = N / 4;
-    const int U = M / N;
-#pragma unroll 8
-    for (int q = threadIdx.x; q < M * E; q += DXF_THREADS) {
-        const int e = q / M, d = q - e * M;
-        const int unit = d / N, h = (d % N) >> 2, r = d & 3;
-        wgt[e * M + h * U * 4 + unit * 4 + r] = Elem<T>::ld(Wg + (size_t)d * E + e);
+// Dispatch backward, both storage types: a workgroup owns the columns that one wavefront covers with 16
+// bytes per lane and DXB_TG token groups, one wavefront each; they share the gate weights of those columns
+// in LDS.  Tokens per group: sixteen (staging the weights then costs an eighth of the rows' traffic at 16
+// experts), fewer where that would leave compute units without a workgroup, in steps of the four that make
+// one round (2048 tokens x 512 columns, 8 experts, by HIP events: 16 workgroups of 16 tokens per wavefront
+// 12.4 us, 64 of four 6.9; 4096 x 1024: 15.8 -> 10.0).
+constexpr int DXB_CT = 64;           // column threads: one wavefront
+constexpr int DXB_TG = 8;            // token groups per workgroup
+constexpr int DXB_TOK = 16;          // most tokens per group
+constexpr int DXB_THREADS = DXB_CT * DXB_TG;
+
+// dx[t] = sum_j dDI[slot[t,j]] + dL[t,:] Wg^T for float32 storage.  A lane owns four columns; the gate
+// weights of the workgroup's 256 columns sit in LDS expert by expert (row pitch DXF_PITCH floats: the
+// transposing writes of four neighbouring experts fall into different banks), so that a lane's 16-byte read
+// feeds the multiply-adds of four tokens; the gate gradients are wave-uniform scalar loads.  Bound by
+// latency at small sizes (1024 tokens x 512 columns, 8 experts: 6.9 us, 10.8 with the whole gate matrix in
+// LDS) and by the row traffic at large ones; a column slice fits LDS at every size, up to 64 experts.
+constexpr int DXF_COLS = DXB_CT * 4;
+constexpr int DXF_PITCH = DXF_COLS + 4;
+__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(
+    const float* __restrict__ dDI, const int* __restrict__ slot, const float* __restrict__ dL,
+    const float* __restrict__ Wg, float* __restrict__ dx, int t_begin, int t_count, int tok, int M, int E, int k) {
+    extern __shared__ __attribute__((aligned(16))) char dxf_smem[];
+    float* wgt = reinterpret_cast<float*>(dxf_smem);
+    const int lane = threadIdx.x & 63;
+    const int tg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c_base = blockIdx.x * DXF_COLS;
+    const int ncols = min(DXF_COLS, M - c_base);
+    const int c = c_base + lane * 4;
+    const bool c_ok = c < M;                       // M is a multiple of eight: a lane's four columns exist or not
+    const int cc = c_ok ? c : 0;
+    const int tl0 = min((int)(blockIdx.y * DXB_TG + tg) * tok, t_count);
+    const int tl1 = min(tl0 + tok, t_count);
+    const float* wsrc = Wg + (size_t)c_base * E;
+    if ((E & 3) == 0) {
+        const int E4 = E >> 2;
+        for (int q = threadIdx.x; q < ncols * E4; q += DXB_THREADS) {
+            const int col = q / E4, e = (q - col * E4) * 4;
+            const float4 v = reinterpret_cast<const float4*>(wsrc)[q];
+            wgt[(e + 0) * DXF_PITCH + col] = v.x; wgt[(e + 1) * DXF_PITCH + col] = v.y;
+            wgt[(e + 2) * DXF_PITCH + col] = v.z; wgt[(e + 3) * DXF_PITCH + col] = v.w;
+        }
+    } else {
+        for (int q = threadIdx.x; q < ncols * E; q += DXB_THREADS) {
+            const int col = q / E;
+            wgt[(q - col * E) * DXF_PITCH + col] = wsrc[q];
+        }
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (int tl = 2 * (blockIdx.x * DXF_WAVES + wid); tl < t_count; tl += 2 * gridDim.x * DXF_WAVES) {
-        const int ntok = min(2, t_count - tl);
-        for (int c0 = 0; c0 < U; c0 += 256) {
-            float acc[2][4][N];
+    for (int tb = tl0; tb < tl1; tb += 4) {
+        float4 acc[4];
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+        for (int u = 0; u < 4; ++u) acc[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        const float* g[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) g[u] = dL + (size_t)(t_begin + min(tb + u, tl1 - 1)) * E;
+        for (int j = 0; j < k; ++j) {
+            // the four tokens' rows of choice j in flight together (a missing row is read from row 0 and not added)
+            float4 v[4];
+            int sj[4];
 #pragma unroll
-                    for (int i = 0; i < N; ++i) acc[a][u][i] = 0.0f;
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                if (a >= ntok) continue;
-                const int t = t_begin + tl + a;
-                for (int j = 0; j < k; ++j) {
-                    const int sj = slot[(size_t)t * k + j];
-                    if (sj < 0) continue;
-                    const uint4* in = reinterpret_cast<const uint4*>(dDI + (size_t)sj * M);
-                    uint4 v[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int c = c0 + u * 64 + lane;
-                        v[u] = c < U ? in[c] : make_uint4(0, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        float r[N];
-                        Unit<T>::to_float(v[u], r);
-#pragma unroll
-                        for (int i = 0; i < N; ++i) acc[a][u][i] += r[i];
-                    }
-                }
-            }
-            const float* g0 = dL + (size_t)(t_begin + tl) * E;
-            const float* g1 = dL + (size_t)(t_begin + tl + ntok - 1) * E;     // the same token again when only one is left
-            for (int e = 0; e < E; ++e) {
-                const float ge0 = g0[e], ge1 = g1[e];
-                const float* wrow = wgt + (size_t)e * M;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = c0 + u * 64 + lane;
-                    if (c < U) {
-#pragma unroll
-                        for (int h = 0; h < NH; ++h) {
-                            const float4 w4 = *reinterpret_cast<const float4*>(wrow + h * U * 4 + c * 4);
-                            const float w[4] = {w4.x, w4.y, w4.z, w4.w};
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) {
-                                acc[0][u][4 * h + r] = fmaf(ge0, w[r], acc[0][u][4 * h + r]);
-                                acc[1][u][4 * h + r] = fmaf(ge1, w[r], acc[1][u][4 * h + r]);
-                            }
-                        }
-                    }
-                }
+            for (int u = 0; u < 4; ++u) {
+                sj[u] = tb + u < tl1 ? slot[(size_t)(t_begin + tb + u) * k + j] : -1;
+                v[u] = *reinterpret_cast<const float4*>(dDI + (size_t)max(sj[u], 0) * M + cc);
             }
 #pragma unroll
-            for (int a = 0; a < 2; ++a) {
-                if (a >= ntok) continue;
-                uint4* out = reinterpret_cast<uint4*>(dx + (size_t)(t_begin + tl + a) * M);
+            for (int u = 0; u < 4; ++u)
+                if (sj[u] >= 0) { acc[u].x += v[u].x; acc[u].y += v[u].y; acc[u].z += v[u].z; acc[u].w += v[u].w; }
+        }
+        const float* wl = wgt + lane * 4;
+#pragma unroll 4
+        for (int e = 0; e < E; ++e) {
+            const float4 w = *reinterpret_cast<const float4*>(wl + e * DXF_PITCH);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int c = c0 + u * 64 + lane;
-                    if (c < U) out[c] = Unit<T>::from_float(acc[a][u]);
-                }
+            for (int u = 0; u < 4; ++u) {
+                const float ge = g[u][e];
+                acc[u].x = fmaf(ge, w.x, acc[u].x); acc[u].y = fmaf(ge, w.y, acc[u].y);
+                acc[u].z = fmaf(ge, w.z, acc[u].z); acc[u].w = fmaf(ge, w.w, acc[u].w);
             }
+        }
+        if (c_ok) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (tb + u < tl1) *reinterpret_cast<float4*>(dx + (size_t)(t_begin + tb + u) * M + c) = acc[u];
         }
     }
 }
@@ -276,25 +270,25 @@ __global__ __launch_bounds__(DXF_THREADS) void dispatch_bwd_f32lds_kernel(
 // B_b[k][j] = Wg[column of lane 4b+j][expert 4g+k], one instruction per column and expert
 // group gives a lane the gate term of four tokens at one of its columns, at 1/8 of the issue
 // slots of float FMAs.  dL is split into two bfloat16 terms (hi + lo), which keeps 16 bits of
-// its mantissa; Wg is bfloat16 already.  The kernel is bound by the latency of its row reads,
+// its mantissa; Wg is bfloat16 already.  Up to 64 experts: a slice of the gate weights is at most 65 KB, so
+// that two workgroups still fit a CU (4096 tokens x 768 columns x 64 experts: 16.4 us, 1065 with the weights
+// read from memory again for every token; 776 columns x 6 experts x 1001 tokens: 22.4 -> 11.0 by the number
+// of tokens per group).  The kernel is bound by the latency of its row reads,
 // so it is built for many wavefronts: the gate weights stay in LDS (read again every round)
 // rather than in 64 registers, which lets four wavefronts per SIMD run.
 typedef short bf16x4_hw __attribute__((ext_vector_type(4)));
 typedef float f32x4_hw __attribute__((ext_vector_type(4)));
-constexpr int DXM_TOK = 16;          // tokens per token group
-constexpr int DXM_CT = 64;           // column threads of a workgroup: one wavefront, 512 columns
-constexpr int DXM_TG = 8;            // token groups per workgroup, one wavefront each (they share the gate weights in LDS)
 template <int EG>                    // expert groups of four: E <= 4*EG
-__global__ __launch_bounds__(DXM_CT * DXM_TG, 2) void dispatch_bwd_mfma_kernel(
+__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(
     const bf16_t* __restrict__ dDI, const int* __restrict__ slot, const float* __restrict__ dL,
-    const bf16_t* __restrict__ Wg, bf16_t* __restrict__ dx, int t_begin, int t_count, int M, int E, int k) {
-    const int ct = threadIdx.x % DXM_CT;                       // column thread
-    const int tg = __builtin_amdgcn_readfirstlane(threadIdx.x / DXM_CT);
-    const int c = (blockIdx.x * DXM_CT + ct) * 8;
+    const bf16_t* __restrict__ Wg, bf16_t* __restrict__ dx, int t_begin, int t_count, int tok, int M, int E, int k) {
+    const int ct = threadIdx.x % DXB_CT;                       // column thread
+    const int tg = __builtin_amdgcn_readfirstlane(threadIdx.x / DXB_CT);
+    const int c = (blockIdx.x * DXB_CT + ct) * 8;
     const bool c_ok = c < M;                       // lanes beyond the row still feed the A operand
     const int lane = threadIdx.x & 63;
-    const int tl0 = min((blockIdx.y * DXM_TG + tg) * DXM_TOK, t_count);
-    const int tl1 = min(tl0 + DXM_TOK, t_count);
+    const int tl0 = min((int)(blockIdx.y * DXB_TG + tg) * tok, t_count);
+    const int tl1 = min(tl0 + tok, t_count);
     // The slots of the group's (token, choice) pairs, one per lane (two registers cover 16 tokens x 8
     // choices); a pair's slot is then broadcast from its lane, which costs no memory access per row.
     const int nsl = (tl1 - tl0) * k;
@@ -316,21 +310,24 @@ __global__ __launch_bounds__(DXM_CT * DXM_TG, 2) void dispatch_bwd_mfma_kernel(
                 raw[u][jj] = sj >= 0 ? v : make_uint4(0, 0, 0, 0);
             }
     };
-    // gate gradients of this lane's token (tb + lane%4) for the A operand
-    auto request_dl = [&](int tb, float4 (&dl)[EG]) {
+    // gate gradients of this lane's token (tb + lane%4) for the A operand, expert groups g0 .. g0 + GC - 1:
+    // with more than sixteen experts they come in pieces, so that they never hold more than sixteen registers
+    constexpr int GC = EG < 4 ? EG : 4;
+    auto request_dl = [&](int tb, int g0, float4 (&dl)[GC]) __attribute__((always_inline)) {
         const int ta = tb + (lane & 3);
 #pragma unroll
-        for (int g = 0; g < EG; ++g) {
-            dl[g] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int gi = 0; gi < GC; ++gi) {
+            dl[gi] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (ta < tl1) {
-                const float* row = dL + (size_t)(t_begin + ta) * E + 4 * g;
+                const int e0 = 4 * (g0 + gi);
+                const float* row = dL + (size_t)(t_begin + ta) * E + e0;
                 if (E == 4 * EG) {
-                    dl[g] = *reinterpret_cast<const float4*>(row);
+                    dl[gi] = *reinterpret_cast<const float4*>(row);
                 } else {
-                    if (4 * g + 0 < E) dl[g].x = row[0];
-                    if (4 * g + 1 < E) dl[g].y = row[1];
-                    if (4 * g + 2 < E) dl[g].z = row[2];
-                    if (4 * g + 3 < E) dl[g].w = row[3];
+                    if (e0 + 0 < E) dl[gi].x = row[0];
+                    if (e0 + 1 < E) dl[gi].y = row[1];
+                    if (e0 + 2 < E) dl[gi].z = row[2];
+                    if (e0 + 3 < E) dl[gi].w = row[3];
                 }
             }
         }
@@ -343,65 +340,66 @@ __global__ __launch_bounds__(DXM_CT * DXM_TG, 2) void dispatch_bwd_mfma_kernel(
     extern __shared__ __attribute__((aligned(16))) char dxm_smem[];
     constexpr int CHUNK = 64 * EG;
     constexpr int PITCH = CHUNK + 16;
-    const int c_base = blockIdx.x * DXM_CT * 8;
-    const int ncols = min(DXM_CT * 8, M - c_base);
-    const int pieces = ncols * EG / 2;             // 16-byte pieces of the slice: at most two per thread
-    static_assert(DXM_CT * 8 * 4 / 2 <= 2 * DXM_CT * DXM_TG, "two pieces per thread cover the slice");
-    const bool whole = E == 4 * EG;
-    uint4 piece[2];
-    if (whole) {
+    const int c_base = blockIdx.x * DXB_CT * 8;
+    const int ncols = min(DXB_CT * 8, M - c_base);
+    const int pieces = ncols * EG / 2;             // 16-byte pieces of the slice
+    constexpr int NPC = (DXB_CT * 8 * EG / 2 + DXB_THREADS - 1) / DXB_THREADS;     // at most so many per thread
+    if (E == 4 * EG) {
         const uint4* src = reinterpret_cast<const uint4*>(Wg + (size_t)c_base * E);
+        uint4 piece[NPC];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) piece[i] = src[min((int)threadIdx.x + i * DXM_CT * DXM_TG, pieces - 1)];
-    }
-    if (whole) {
+        for (int i = 0; i < NPC; ++i) piece[i] = src[min((int)threadIdx.x + i * DXB_THREADS, pieces - 1)];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int q = threadIdx.x + i * DXM_CT * DXM_TG;
+        for (int i = 0; i < NPC; ++i) {
+            const int q = threadIdx.x + i * DXB_THREADS;
             const int byte = q * 16;
             if (q < pieces) *reinterpret_cast<uint4*>(dxm_smem + (byte / CHUNK) * PITCH + byte % CHUNK) = piece[i];
         }
     } else {
-        for (int q = threadIdx.x; q < ncols * 4 * EG; q += DXM_CT * DXM_TG) {
+        for (int q = threadIdx.x; q < ncols * 4 * EG; q += DXB_THREADS) {
             const int col = q / (4 * EG), e = q % (4 * EG);
             const bf16_t v = e < E ? Wg[(size_t)(c_base + col) * E + e] : (bf16_t)0;
             *reinterpret_cast<bf16_t*>(dxm_smem + (col / 8) * PITCH + (col % 8) * 8 * EG + e * 2) = v;
         }
     }
     uint4 raw[4][2];
-    float4 dl[EG];
-    request_dl(tl0, dl);
+    float4 dl[GC];
+    request_dl(tl0, 0, dl);
     request(tl0, 0, raw);
     __syncthreads();
     for (int tb = tl0; tb < tl1; tb += 4) {
         if (tb > tl0) {
-            request_dl(tb, dl);
+            request_dl(tb, 0, dl);
             request(tb, 0, raw);
-        }
-        bf16x4_hw a_hi[EG], a_lo[EG];
-#pragma unroll
-        for (int g = 0; g < EG; ++g) {
-            const float v[4] = {dl[g].x, dl[g].y, dl[g].z, dl[g].w};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bf16_t h = f32_to_bf16(v[r]);
-                a_hi[g][r] = (short)h;
-                a_lo[g][r] = (short)f32_to_bf16(v[r] - bf16_to_f32(h));
-            }
         }
         f32x4_hw gate[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) gate[i] = f32x4_hw{0.0f, 0.0f, 0.0f, 0.0f};
         int my_off = ct * PITCH;                   // opaque: the compiler must not keep the weights in registers
         asm volatile("" : "+v"(my_off));
+#pragma unroll 1
+        for (int g0 = 0; g0 < EG; g0 += GC) {
+            bf16x4_hw a_hi[GC], a_lo[GC];
 #pragma unroll
-        for (int g = 0; g < EG; ++g)
+            for (int gi = 0; gi < GC; ++gi) {
+                const float v[4] = {dl[gi].x, dl[gi].y, dl[gi].z, dl[gi].w};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const bf16x4_hw w = *reinterpret_cast<const bf16x4_hw*>(dxm_smem + my_off + (i * EG + g) * 8);
-                gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi[g], w, gate[i], 0, 0, 0);
-                gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo[g], w, gate[i], 0, 0, 0);
+                for (int r = 0; r < 4; ++r) {
+                    const bf16_t h = f32_to_bf16(v[r]);
+                    a_hi[gi][r] = (short)h;
+                    a_lo[gi][r] = (short)f32_to_bf16(v[r] - bf16_to_f32(h));
+                }
             }
+            if (g0 + GC < EG) request_dl(tb, g0 + GC, dl);     // on its way while this piece is multiplied
+#pragma unroll
+            for (int gi = 0; gi < GC; ++gi)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const bf16x4_hw w = *reinterpret_cast<const bf16x4_hw*>(dxm_smem + my_off + (i * EG + g0 + gi) * 8);
+                    gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi[gi], w, gate[i], 0, 0, 0);
+                    gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo[gi], w, gate[i], 0, 0, 0);
+                }
+        }
         float acc[4][8];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -427,67 +425,6 @@ __global__ __launch_bounds__(DXM_CT * DXM_TG, 2) void dispatch_bwd_mfma_kernel(
             for (int u = 0; u < 4; ++u)
                 if (tb + u < tl1)
                     st_row<false>(reinterpret_cast<uint4*>(dx + (size_t)(t_begin + tb + u) * M + c), Unit<bf16_t>::from_float(acc[u]));
-        }
-    }
-}
-
-// dx[t] = sum_j dDI[slot[t,j]] + dL[t,:] Wg^T.  A thread owns eight columns and
-// keeps their gate weights in registers across TOKB tokens.
-constexpr int DXB_TOK = 32;
-template <typename T, int EC>
-__global__ __launch_bounds__(PERM_THREADS) void dispatch_bwd_kernel(
-    const T* __restrict__ dDI, const int* __restrict__ slot, const float* __restrict__ dL,
-    const T* __restrict__ Wg, T* __restrict__ dx, int t_begin, int t_count, int M, int E, int k) {
-    const int c = (blockIdx.x * PERM_THREADS + threadIdx.x) * 8;
-    if (c >= M) return;
-    float wg[8][EC];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < EC; ++e) wg[i][e] = e < E ? Elem<T>::ld(Wg + (size_t)(c + i) * E + e) : 0.0f;
-    const int tl0 = blockIdx.y * DXB_TOK;
-    const int tl1 = min(tl0 + DXB_TOK, t_count);
-    // four tokens per round so that their row reads are in flight together
-    for (int tb = tl0; tb < tl1; tb += 4) {
-        float acc[4][8];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[u][i] = 0.0f;
-            const int tl = tb + u;
-            if (tl >= tl1) continue;
-            const int t = t_begin + tl;
-            for (int j = 0; j < k; ++j) {
-                int s = slot[(size_t)t * k + j];
-                if (s < 0) continue;
-                float r[8];
-                Vec8<T>::load(dDI + (size_t)s * M + c, r);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[u][i] += r[i];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int tl = tb + u;
-            if (tl >= tl1) continue;
-            const int t = t_begin + tl;
-            for (int e0 = 0; e0 < E; e0 += EC) {
-#pragma unroll
-                for (int e = 0; e < EC; ++e) {
-                    if (e0 + e < E) {
-                        float g = dL[(size_t)t * E + e0 + e];
-                        if (E <= EC) {
-#pragma unroll
-                            for (int i = 0; i < 8; ++i) acc[u][i] = fmaf(g, wg[i][e], acc[u][i]);
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < 8; ++i)
-                                acc[u][i] = fmaf(g, Elem<T>::ld(Wg + (size_t)(c + i) * E + e0 + e), acc[u][i]);
-                        }
-                    }
-                }
-            }
-            Vec8<T>::store(dx + (size_t)t * M + c, acc[u]);
         }
     }
 }
@@ -916,53 +853,32 @@ static moe_status dispatch_t(const Dims& d, int part, const void* src, const int
 template <typename T>
 static moe_status dispatch_bwd_t(const Dims& d, int part, const void* dDI, const int* slot, const float* dL,
                                  const void* Wg, void* dx, hipStream_t s) {
-    if (sizeof(T) == 2 && d.E <= 16) {      // more experts: the gate weights no longer fit a lane's registers
-        dim3 grid((d.M / 8 + DXM_CT - 1) / DXM_CT, (d.Tp + DXM_TOK * DXM_TG - 1) / (DXM_TOK * DXM_TG));
-#define LAUNCH_DXM(EG) do { \
-        const int lds = DXM_CT * (64 * EG + 16); \
-        static bool attr_done = false; \
-        if (!attr_done) { \
-            HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(dispatch_bwd_mfma_kernel<EG>), \
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
-            attr_done = true; \
-        } \
-        hipLaunchKernelGGL((dispatch_bwd_mfma_kernel<EG>), grid, dim3(DXM_CT * DXM_TG), lds, s, \
-        (const bf16_t*)dDI, slot, dL, (const bf16_t*)Wg, (bf16_t*)dx, part * d.Tp, d.Tp, d.M, d.E, d.k); } while (0)
-        ProfScope ps(PK_DISPATCH_BWD, s);
-        if (d.E <= 4) LAUNCH_DXM(1);
-        else if (d.E <= 8) LAUNCH_DXM(2);
-        else LAUNCH_DXM(4);
-#undef LAUNCH_DXM
-        count_launch(LC_PERMUTE);
-        MOE_CHECK_LAUNCH();
-        return MOE_OK;
-    }
-    const size_t wg_float_bytes = (size_t)d.M * d.E * sizeof(float);
-    if (wg_float_bytes <= 128 * 1024) {
-        auto kern = dispatch_bwd_f32lds_kernel<T>;
-        static size_t attr_bytes = 0;                 // largest size asked for so far
-        if (wg_float_bytes > attr_bytes) {
-            HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)wg_float_bytes));
-            attr_bytes = wg_float_bytes;
-        }
-        int blocks = (d.Tp + 2 * DXF_WAVES - 1) / (2 * DXF_WAVES);
-        const int cap = wg_float_bytes > 64 * 1024 ? 256 : 512;      // workgroups that fit the chip at once
-        if (blocks > cap) blocks = cap;
-        ProfScope ps(PK_DISPATCH_BWD, s);
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(DXF_THREADS), wg_float_bytes, s, (const T*)dDI, slot, dL,
-                           (const T*)Wg, (T*)dx, part * d.Tp, d.Tp, d.M, d.E, d.k);
-        count_launch(LC_PERMUTE);
-        MOE_CHECK_LAUNCH();
-        return MOE_OK;
-    }
-    dim3 grid((d.M / 8 + PERM_THREADS - 1) / PERM_THREADS, (d.Tp + DXB_TOK - 1) / DXB_TOK);
-#define LAUNCH_DXB(EC) hipLaunchKernelGGL((dispatch_bwd_kernel<T, EC>), grid, dim3(PERM_THREADS), 0, s, \
-        (const T*)dDI, slot, dL, (const T*)Wg, (T*)dx, part * d.Tp, d.Tp, d.M, d.E, d.k)
+    constexpr bool BF16 = sizeof(T) == 2;
+    const int cols = BF16 ? DXB_CT * 8 : DXF_COLS;
+    const int slices = (d.M + cols - 1) / cols;
+    // tokens per wavefront: as many as leave every compute unit a workgroup or two
+    const int fit = (int)((long long)d.Tp * slices / (512 * DXB_TG)) / 4 * 4;
+    const int tok = fit < 4 ? 4 : fit > DXB_TOK ? DXB_TOK : fit;
+    const dim3 grid(slices, (d.Tp + tok * DXB_TG - 1) / (tok * DXB_TG));
     ProfScope ps(PK_DISPATCH_BWD, s);
-    if (d.E <= 4) LAUNCH_DXB(4);
-    else if (d.E <= 8) LAUNCH_DXB(8);
-    else LAUNCH_DXB(16);
+#define LAUNCH_DXB(KERN, T_, LDS) do { \
+        const int lds = (LDS); \
+        static int attr_bytes = 0;                  /* largest size asked for so far */ \
+        if (lds > attr_bytes) { \
+            HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
+            attr_bytes = lds; \
+        } \
+        hipLaunchKernelGGL(KERN, grid, dim3(DXB_THREADS), lds, s, (const T_*)dDI, slot, dL, (const T_*)Wg, (T_*)dx, \
+                           part * d.Tp, d.Tp, tok, d.M, d.E, d.k); } while (0)
+    if constexpr (BF16) {
+        if (d.E <= 4) LAUNCH_DXB((dispatch_bwd_mfma_kernel<1>), bf16_t, DXB_CT * (64 * 1 + 16));
+        else if (d.E <= 8) LAUNCH_DXB((dispatch_bwd_mfma_kernel<2>), bf16_t, DXB_CT * (64 * 2 + 16));
+        else if (d.E <= 16) LAUNCH_DXB((dispatch_bwd_mfma_kernel<4>), bf16_t, DXB_CT * (64 * 4 + 16));
+        else if (d.E <= 32) LAUNCH_DXB((dispatch_bwd_mfma_kernel<8>), bf16_t, DXB_CT * (64 * 8 + 16));
+        else LAUNCH_DXB((dispatch_bwd_mfma_kernel<16>), bf16_t, DXB_CT * (64 * 16 + 16));
+    } else {
+        LAUNCH_DXB(dispatch_bwd_f32_kernel, float, DXF_PITCH * d.E * (int)sizeof(float));
+    }
 #undef LAUNCH_DXB
     count_launch(LC_PERMUTE);
     MOE_CHECK_LAUNCH();
