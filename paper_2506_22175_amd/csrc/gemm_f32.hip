@@ -1,76 +1,159 @@
 // float32 grouped GEMM for the expert FFN (the two linear layers of an expert,
-// Section II-B2, and their gradients).  Plain FMA arithmetic in float, LDS-tiled;
-// this path exists for the float32 workload, whose tolerance rules out reduced
-// precision inputs.  One workgroup computes a 64x64 tile of one expert.
+// Section II-B2, and their gradients) on the float32 matrix instructions
+// (v_mfma_f32_32x32x2_f32: float operands, float accumulation; this path exists for
+// the float32 workload, whose tolerance rules out reduced precision inputs).
+//
+// One workgroup computes a 64 x 64 tile of one expert with four wavefronts of 32 x 32.
+// The matrix instruction takes 64 cycles for 32 x 32 x 2, so even this tile asks little
+// of LDS (32 of its 128 bytes per cycle) and of L2 (38 bytes per ns and CU at the full
+// rate); what counts is that small layers have enough tiles for the chip and that a
+// tile's K loop never waits: operands travel global -> LDS by DMA through a ring of three
+// 32-k stages, and three workgroups fit a CU (rings of two and of four stages measured the
+// same).  2048 rows x 512 x 2048 over 8 experts (27 us at the rate of the instruction), by
+// HIP events: first layer 57 us, second layer 79, GeLU-backward 61, input gradient 80,
+// weight gradients 52 each (the 64 x 64 float-FMA tiles before: 107, 341, 106, 307, 113).
+// The two with N = 512 have 288 tiles for 256 CUs.
 #include "common.h"
 #include "epilogue.h"
 
 namespace moe {
 
-constexpr int F_BM = 64, F_BN = 64, F_BK = 16, F_THREADS = 256;
+constexpr int F_BM = 64, F_BN = 64, F_BK = 32, F_NS = 3, F_THREADS = 256;
+constexpr int F_TILE = F_BM * F_BK * 4;            // bytes of one operand's stage
+typedef float f_acc_t __attribute__((ext_vector_type(16)));
 
-// A(m,k) = A[m*a_rs + k*a_cs], B(k,n) = B[k*b_rs + n*b_cs]
+// What a lane reads when its piece of a stage lies outside the operand.
+static __device__ __align__(16) float f_zeros[4];
+
+// 16 bytes per lane from the lane's own address to LDS at lds_off + 16*lane (lds_off wave-uniform).
+// Assembly, so that the compiler does not wait for it at the next LDS read; the loop waits with
+// s_waitcnt vmcnt(N) itself.
+__device__ __forceinline__ void f_load_to_lds(const float* p, unsigned lds_off) {
+    asm volatile("s_mov_b32 m0, %0\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dwordx4 %1, off"
+                 : : "s"(lds_off), "v"(p) : "memory");
+}
+template <int N> __device__ __forceinline__ void f_wait_loads() {
+    // (lgkmcnt: this wave's own LDS reads are through too)
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(N) : "memory");
+}
+
+// One operand of the tile: 64 rows (m or n) x 32 k per stage.
+//   KC: k is contiguous in memory.  LDS [row][32 k], 16-byte chunk c of a row at c ^ (row/2 % 8): the sixteen
+//       rows of a quarter of a 16-byte read cover all banks.
+//   NC: the rows are contiguous in memory ([k][n]).  LDS [k][64 n]; k rows 4..7 of every eight have their
+//       halves exchanged, so that the two half-wavefronts of a 4-byte read use different banks.
+// A wavefront fills two of the eight 1 KB pieces of a stage.
+template <bool KC> struct FOperand {
+    const float* p[2];          // this lane's piece in the stage requested next
+    int k[2];                   // its first k; at or beyond K it reads zeros
+    long long step;             // elements from one stage to the next
+    int K;
+    __device__ __forceinline__ void init(const float* P, long long ld, int row0, int row_limit, int K_, int wid, int lane,
+                                         const int* rows) {
+        K = K_;
+        step = KC ? F_BK : F_BK * ld;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int q = wid * 2 + j;
+            bool ok;
+            if (KC) {
+                const int row = q * 8 + (lane >> 3);
+                const int c = (lane & 7) ^ ((row >> 1) & 7);
+                ok = row0 + row < row_limit;
+                const long long src = !ok ? 0 : rows ? rows[row0 + row] : row0 + row;
+                k[j] = c * 4;
+                p[j] = P + src * ld + c * 4;
+            } else {
+                const int kr = q * 4 + (lane >> 4);
+                const int u = (lane & 15) ^ (((kr >> 2) & 1) << 3);
+                ok = row0 + u * 4 < row_limit;
+                k[j] = kr;
+                p[j] = P + (long long)kr * ld + row0 + u * 4;
+            }
+            if (!ok) k[j] = 0x40000000;            // never below K
+        }
+    }
+    __device__ __forceinline__ void request(unsigned lds, int wid) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            f_load_to_lds(k[j] < K ? p[j] : f_zeros, lds + (wid * 2 + j) * 1024);
+            p[j] += step;
+            k[j] += F_BK;
+        }
+    }
+    // operands of four matrix instructions: row rb + lane%32, k = 8*kk + 4*(lane/32) + 0..3
+    static __device__ __forceinline__ void read(const char* tile, int rb, int kk, int lane, float* o) {
+        const int row = rb + (lane & 31), h = lane >> 5;
+        if (KC) {
+            const float4 v = *reinterpret_cast<const float4*>(tile + row * 128 + (((2 * kk + h) ^ ((row >> 1) & 7)) << 4));
+            o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
+        } else {
+            const char* at = tile + (8 * kk + 4 * h) * 256 + ((row * 4) ^ (h << 7));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[j] = *reinterpret_cast<const float*>(at + j * 256);
+        }
+    }
+};
+
 template <int LAY, int EPI>
-__global__ __launch_bounds__(F_THREADS) void gemm_f32_kernel(GemmArgs g, int tiles_m, int tiles_n) {
-    __shared__ float As[F_BK][F_BM + 4];
-    __shared__ float Bs[F_BK][F_BN + 4];
+__global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_kernel(GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) char smem[F_NS * 2 * F_TILE];
     const int e = blockIdx.z;
     const int tm = blockIdx.y, tn = blockIdx.x;
     const int rows = g.counts[e];
-    int Mdim, Kdim;
-    long long a_rs, a_cs, b_rs, b_cs;
-    if (LAY == GEMM_TN) { Mdim = g.Mo; Kdim = rows; a_rs = 1; a_cs = g.lda; b_rs = g.ldb; b_cs = 1; }
-    else if (LAY == GEMM_NN) { Mdim = rows; Kdim = g.K; a_rs = g.lda; a_cs = 1; b_rs = g.ldb; b_cs = 1; }
-    else { Mdim = rows; Kdim = g.K; a_rs = g.lda; a_cs = 1; b_rs = 1; b_cs = g.ldb; }
+    const int Mdim = LAY == GEMM_TN ? g.Mo : rows, Kdim = LAY == GEMM_TN ? rows : g.K;
     const int m0 = tm * F_BM, n0 = tn * F_BN;
     if (m0 >= Mdim) return;
-    const float* A = (const float*)g.A + (size_t)e * g.a_estride;
-    const float* B = (const float*)g.B + (size_t)e * g.b_estride;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    if (EPI == EPI_ACCUM_F32 && Kdim <= 0) return;            // nothing to add
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wid >> 1, wn = wid & 1;
+    const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)smem;
 
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.0f;
+    FOperand<LAY != GEMM_TN> A;
+    FOperand<LAY == GEMM_NT> B;
+    const bool gathered = LAY != GEMM_TN && g.a_rows;         // gathered rows: one matrix for all experts
+    A.init((const float*)g.A + (gathered ? 0 : (size_t)e * g.a_estride), g.lda, m0, Mdim, Kdim, wid, lane,
+           gathered ? g.a_rows + (size_t)e * g.Cp : nullptr);
+    B.init((const float*)g.B + (size_t)e * g.b_estride, g.ldb, n0, g.N, Kdim, wid, lane, nullptr);
+    const int KT = (Kdim + F_BK - 1) / F_BK;
 
-    for (int k0 = 0; k0 < Kdim; k0 += F_BK) {
-        // 64x16 elements of A and of B: four each per thread
+    f_acc_t acc;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int idx = tid + q * F_THREADS;
-            int kk, mm;
-            if (LAY == GEMM_TN) { mm = idx & 63; kk = idx >> 6; } else { kk = idx & 15; mm = idx >> 4; }
-            float v = 0.0f;
-            if (m0 + mm < Mdim && k0 + kk < Kdim) {
-                if (LAY != GEMM_TN && g.a_rows)       // gathered rows: one matrix for all experts
-                    v = ((const float*)g.A)[(size_t)g.a_rows[(size_t)e * g.Cp + m0 + mm] * a_rs + (size_t)(k0 + kk) * a_cs];
-                else
-                    v = A[(size_t)(m0 + mm) * a_rs + (size_t)(k0 + kk) * a_cs];
-            }
-            As[kk][mm] = v;
-            int kb, nn;
-            if (LAY == GEMM_NT) { kb = idx & 15; nn = idx >> 4; } else { nn = idx & 63; kb = idx >> 6; }
-            float w = 0.0f;
-            if (n0 + nn < g.N && k0 + kb < Kdim) w = B[(size_t)(k0 + kb) * b_rs + (size_t)(n0 + nn) * b_cs];
-            Bs[kb][nn] = w;
-        }
-        __syncthreads();
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+    // stages 0 .. NS-2 on their way; past the last k they are zeros that nobody reads
 #pragma unroll
-        for (int kk = 0; kk < F_BK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-            float4 bv = *reinterpret_cast<const float4*>(&Bs[kk][tx * 4]);
-            b[0] = bv.x; b[1] = bv.y; b[2] = bv.z; b[3] = bv.w;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
+    for (int s = 0; s < F_NS - 1; ++s) {
+        A.request(lds0 + s * 2 * F_TILE, wid);
+        B.request(lds0 + s * 2 * F_TILE + F_TILE, wid);
     }
+    for (int kt = 0; kt < KT; ++kt) {
+        f_wait_loads<4 * (F_NS - 2)>();                       // this wave's part of stage kt is in
+        __builtin_amdgcn_s_barrier();                         // everybody's is, and nobody reads stage kt-1 any more
+        asm volatile("" ::: "memory");
+        const unsigned ahead = lds0 + ((kt + F_NS - 1) % F_NS) * 2 * F_TILE;
+        A.request(ahead, wid);
+        B.request(ahead + F_TILE, wid);
+        const char* as = smem + (kt % F_NS) * 2 * F_TILE;
+        const char* bs = as + F_TILE;
+        float a[F_BK / 8][4], b[F_BK / 8][4];
+#pragma unroll
+        for (int kk = 0; kk < F_BK / 8; ++kk) {
+            A.read(as, wm * 32, kk, lane, a[kk]);
+            B.read(bs, wn * 32, kk, lane, b[kk]);
+        }
+#pragma unroll
+        for (int kk = 0; kk < F_BK / 8; ++kk)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(b[kk][j], a[kk][j], acc, 0, 0, 0);
+    }
+    f_wait_loads<0>();                                        // nothing is in flight into LDS any more
 
+    // With B as the first operand a lane holds row lane%32 of its wave's block and four consecutive
+    // columns 8*q + 4*(lane/32) per register group q.
     EpiCtx<float> c;
     c.ldc = g.ldc; c.ldz = g.ldz;
     c.C = EPI == EPI_SCATTER ? (float*)g.C : (float*)g.C + (size_t)e * g.c_estride;
@@ -78,36 +161,34 @@ __global__ __launch_bounds__(F_THREADS) void gemm_f32_kernel(GemmArgs g, int til
     c.out_rows = g.c_rows ? g.c_rows + (size_t)e * g.Cp : nullptr;
     c.Z = g.Z ? (float*)g.Z + (size_t)e * g.Cp * g.ldz : nullptr;
     c.w = g.slot_w ? g.slot_w + (size_t)e * g.Cp : nullptr;
-    const int n = n0 + tx * 4;
+    const int r = m0 + wm * 32 + (lane & 31);
+    float dot = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = m0 + ty + 16 * i;
-        float dot = 0.0f;
-        if (r < Mdim && n < g.N) dot = epilogue4<float, EPI>(c, r, n, acc[i]);
-        if (EPI == EPI_DGELU && g.dw_part) {
-            // the 16 threads of a row are consecutive lanes
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-            if (tx == 0 && r < Mdim) g.dw_part[((size_t)e * g.Cp + r) * g.dw_parts + tn] = dot;
-        }
+    for (int q = 0; q < 4; ++q) {
+        const int n = n0 + wn * 32 + 8 * q + 4 * (lane >> 5);
+        const float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        if (r < Mdim && n < g.N) dot += epilogue4<float, EPI>(c, r, n, v);
+    }
+    if (EPI == EPI_DGELU && g.dw_part) {
+        // a row's 64 columns: two half-wavefronts of each of the two waves that share its rows
+        dot += __shfl_xor(dot, 32, 64);
+        float* sdot = reinterpret_cast<float*>(smem);
+        __syncthreads();                                      // the ring is no longer read
+        if (wn == 1 && lane < 32) sdot[wm * 32 + lane] = dot;
+        __syncthreads();
+        if (wn == 0 && lane < 32 && r < Mdim) g.dw_part[((size_t)e * g.Cp + r) * g.dw_parts + tn] = dot + sdot[wm * 32 + lane];
     }
 }
 
 int gemm_f32_dw_parts(int H) { return (H + F_BN - 1) / F_BN; }
 
-template <int LAY>
-static moe_status launch_f32(GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
+template <int LAY, int EPI>
+static moe_status launch_f32(const GemmArgs& a, hipStream_t s) {
     const int Mmax = (LAY == GEMM_TN) ? a.Mo : a.Cp;
     const int tiles_m = (Mmax + F_BM - 1) / F_BM, tiles_n = (a.N + F_BN - 1) / F_BN;
-    dim3 grid(tiles_n, tiles_m, a.E), block(F_THREADS);
-    ProfScope ps(gemm_prof_kind(LAY, epi), s);
-    switch (epi) {
-        case EPI_STORE: hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI_STORE>), grid, block, 0, s, a, tiles_m, tiles_n); break;
-        case EPI_GELU: hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI_GELU>), grid, block, 0, s, a, tiles_m, tiles_n); break;
-        case EPI_DGELU: hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI_DGELU>), grid, block, 0, s, a, tiles_m, tiles_n); break;
-        case EPI_ACCUM_F32: hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI_ACCUM_F32>), grid, block, 0, s, a, tiles_m, tiles_n); break;
-        case EPI_STORE_F32: hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI_STORE_F32>), grid, block, 0, s, a, tiles_m, tiles_n); break;
-        case EPI_SCATTER: hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI_SCATTER>), grid, block, 0, s, a, tiles_m, tiles_n); break;
+    {
+        ProfScope ps(gemm_prof_kind(LAY, EPI), s);
+        hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI>), dim3(tiles_n, tiles_m, a.E), dim3(F_THREADS), 0, s, a);
     }
     count_launch(LC_GEMM);
     MOE_CHECK_LAUNCH();
@@ -118,9 +199,14 @@ moe_status gemm_f32(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStre
     if (a.dw_part && a.dw_parts != gemm_f32_dw_parts(a.N)) return MOE_ERR_SHAPE;
     if (a.a_rows && (lay == GEMM_TN || a.a_row_limit <= 0)) return MOE_ERR_UNSUPPORTED;
     if (epi == EPI_SCATTER && (lay == GEMM_TN || !a.c_rows || !a.slot_w || a.c_row_limit <= 0)) return MOE_ERR_UNSUPPORTED;
-    if (lay == GEMM_NN) return launch_f32<GEMM_NN>(epi, a, s);
-    if (lay == GEMM_NT) return launch_f32<GEMM_NT>(epi, a, s);
-    return launch_f32<GEMM_TN>(epi, a, s);
+    if (lay == GEMM_NN && epi == EPI_STORE) return launch_f32<GEMM_NN, EPI_STORE>(a, s);
+    if (lay == GEMM_NN && epi == EPI_GELU) return launch_f32<GEMM_NN, EPI_GELU>(a, s);
+    if (lay == GEMM_NN && epi == EPI_SCATTER) return launch_f32<GEMM_NN, EPI_SCATTER>(a, s);
+    if (lay == GEMM_NT && epi == EPI_STORE) return launch_f32<GEMM_NT, EPI_STORE>(a, s);
+    if (lay == GEMM_NT && epi == EPI_DGELU) return launch_f32<GEMM_NT, EPI_DGELU>(a, s);
+    if (lay == GEMM_TN && epi == EPI_STORE_F32) return launch_f32<GEMM_TN, EPI_STORE_F32>(a, s);
+    if (lay == GEMM_TN && epi == EPI_ACCUM_F32) return launch_f32<GEMM_TN, EPI_ACCUM_F32>(a, s);
+    return MOE_ERR_UNSUPPORTED;
 }
 
 }  // namespace moe
