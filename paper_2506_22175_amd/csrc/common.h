@@ -209,6 +209,7 @@ struct GemmArgs {
     int a_row_limit;
     const int* counts;    // [E] valid rows of this partition
     int E, Cp;            // experts, max rows per expert
+    int mean_rows;        // rows per expert of a partition if all are loaded alike (the choice of a tile shape)
     int Mo;               // TN only: output rows
     int N, K;             // K unused for TN (K = counts[e])
     // TN only: reduce over the rows of k_segs partitions in one launch (0 or 1: one).  Partition sg of

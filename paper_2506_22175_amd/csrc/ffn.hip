@@ -15,6 +15,8 @@ static GemmArgs base_args(const Dims& d, const int* counts_p) {
     a.counts = counts_p;
     a.E = d.E;
     a.Cp = d.Cp;
+    const long long mean = ((long long)d.Tp * d.k + d.E - 1) / d.E;
+    a.mean_rows = mean < d.Cp ? (int)mean : d.Cp;
     a.free_cus = d.free_cus;
     return a;
 }

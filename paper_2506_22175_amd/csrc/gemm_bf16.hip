@@ -25,6 +25,7 @@
 // waits).  One s_barrier per tile.
 #include "common.h"
 #include "epilogue.h"
+#include <type_traits>
 
 namespace moe {
 
@@ -34,6 +35,7 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
 
 constexpr unsigned OOB_OFFSET = 0x80000000u;
+constexpr int DW_COLS = 128;         // columns per partial sum of GeLU-backward's row dots (an even number of blocks per row)
 
 // Buffer descriptor (base, stride 0, size in bytes, raw 32-bit format) kept in SGPRs.
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -63,11 +65,12 @@ __device__ __forceinline__ unsigned lds_address(const char* p) {
 }
 
 // ---- tile shape ------------------------------------------------------------------
-// Two main loops, both hand-scheduled:
-//   LOOP_PIPE32 ring of five stages of 32 k;
+// Three main loops, all hand-scheduled:
+//   LOOP_PIPE32 ring of 32-k stages for both operands;
 //   LOOP_W64    64-k steps with one ring per operand: a K-contiguous operand travels as whole
 //               128-byte lines (units of 64 k), the other one in tiles of 32 k.
-enum { LOOP_PIPE32 = 1, LOOP_W64 = 2 };
+//   LOOP_R64    64-k steps with one ring for both operands (tiles small enough for three or more stages of 64 k).
+enum { LOOP_PIPE32 = 1, LOOP_W64 = 2, LOOP_R64 = 3 };
 template <int BM_, int BN_, int BK_, int NS_, int WAVES_M_, int WAVES_N_, int OCC_, int LOOP_>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
@@ -80,13 +83,16 @@ struct TileCfg {
     static constexpr int LDS_BYTES = LOOP == LOOP_W64 ? 160 * 1024 : NS * STAGE_BYTES;
     static constexpr bool PIPE = LOOP == LOOP_PIPE32;
     // columns of a wave's block that pass through the staging region at a time, and where that region starts
-    static constexpr int CW = LOOP == LOOP_W64 ? 64 : WN;
-    static constexpr int STAGING_OFF = LOOP == LOOP_W64 ? 64 * 1024 : 0;
+    static constexpr int CW = WN < 64 || (LOOP == LOOP_PIPE32 && OCC == 1) ? WN : 64;
+    static constexpr int SBR = (WAVES * 32 * CW * 4 + STAGE_BYTES - 1) / STAGE_BYTES;      // stages that region takes
+    static constexpr int STAGING_OFF = LOOP == LOOP_W64 ? 64 * 1024 : LOOP == LOOP_R64 ? (NS - SBR) * STAGE_BYTES : 0;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
     static_assert(BK == 32 || BK == 64, "tile depth");
-    static_assert(LOOP != LOOP_PIPE32 || (BK == 32 && NS == 5), "the hand-scheduled ring is five stages of 32 k");
+    static_assert(LOOP != LOOP_PIPE32 || (BK == 32 && NS >= 3), "the hand-scheduled ring has stages of 32 k");
     static_assert(LOOP != LOOP_W64 || (BM == 256 && BN == 256 && BK == 64 && WAVES_M == 2 && WAVES_N == 2 && OCC == 1),
                   "the two-ring loop is written for four waves of 128 x 128");
+    static_assert(LOOP != LOOP_R64 || (BK == 64 && NS >= 3 && OCC == 1 && SBR <= NS - 2),
+                  "stages of 64 k; the epilogue stages through the last ones");
 };
 
 // ---- K-contiguous operand tile: R rows x BK k ---------------------------------------
@@ -177,6 +183,7 @@ struct NCTile {
     static constexpr int NI = BK / RPI / WAVES;
     static constexpr int BYTES = BK * PITCH;
     static_assert(BK % (RPI * WAVES) == 0 && NI >= 1, "rows must divide over the wavefronts");
+    static_assert(UPR >= 16, "four k rows rotated by four units each must fit a row of units");
     v4i rsrc;
     unsigned voff[NI];
     unsigned kstep;          // bytes per k row in memory
@@ -283,7 +290,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, TNN = C::TN;
     constexpr int STAGE = C::STAGE_BYTES, BK = C::BK, NS = C::NS;
-    constexpr bool W64 = C::LOOP == LOOP_W64;
+    constexpr bool W64 = C::LOOP == LOOP_W64, R64 = C::LOOP == LOOP_R64;
+    constexpr bool ALT = C::LOOP != LOOP_PIPE32;     // waves' row blocks alternate (see block_row)
     // Depth of one load unit of each operand.  In the two-ring loop a K-contiguous row operand (A of
     // NN) or the K-contiguous weights (B of NT) travel 64 k at a time, so that every request is a whole
     // 128-byte line; the other operand keeps tiles of 32 k.
@@ -296,7 +304,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     // of the tile before.  (Two-ring loop: in the third unit of the wide ring.)
     constexpr int SB = 2;
     constexpr int CW = C::CW;
-    static_assert(W64 || C::WAVES * 32 * CW * 4 <= SB * STAGE, "staging does not fit below the ring's first stage");
+    static_assert(ALT || C::WAVES * 32 * CW * 4 <= SB * STAGE, "staging does not fit below the ring's first stage");
     static_assert(!W64 || C::WAVES * 32 * CW * 4 <= 32 * 1024, "staging does not fit one unit of the wide ring");
     // two-ring LDS map: three units of 64 k x 256 rows, then four tiles of 32 k x 256 rows
     constexpr int WIDE_UNIT = 32 * 1024, NARROW_TILE = 16 * 1024, NARROW_OFF = 3 * WIDE_UNIT;
@@ -307,10 +315,18 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     typedef typename ATile<LAY, BM, C::WAVES, AK>::type AT;
     typedef typename BTile<LAY, BN, C::WAVES, BKB>::type BT;
     constexpr int LPW = AT::NI + BT::NI;         // loads per wave per tile
+    // Where two workgroups share a CU the operands' offsets and descriptors are formed again at the top of a
+    // tile (the other workgroup covers that) instead of being carried from the one before: with 128 registers
+    // for accumulators and fragments the compiler otherwise moves descriptors into vector registers, which the
+    // load cannot take.
+    constexpr bool REBIND = C::OCC == 2;
     typename AT::Frag fa[TM];
     typename BT::Frag fb[TNN];
+    // First row of the wave's block i of 32 rows.  In the 64-k loops the waves' blocks alternate, so that a tile
+    // with few rows left needs only the first blocks of every wave (see `active` below).
+    auto block_row = [&](int i) __attribute__((always_inline)) { return ALT ? (i * C::WAVES_M + wm) * 32 : wm * WM + i * 32; };
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[i].init(wm * WM + i * 32, lane);
+    for (int i = 0; i < TM; ++i) fa[i].init(block_row(i), lane);
 #pragma unroll
     for (int j = 0; j < TNN; ++j) fb[j].init(wn * WN + j * 32, lane);
 
@@ -318,23 +334,30 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     // Only tiles that exist are numbered: an expert with fewer rows than the capacity has fewer
     // tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups,
     // which take the numbers b, b + grid, ..., all get the same amount of work whatever the spread
-    // of the counts.  Lane l of every wavefront holds the tiles of expert l (E <= 64); an inclusive
-    // scan over the lanes gives the number at which each expert ends.
-    int lane_tm = 0;                     // tile rows of expert `lane` (none: the expert has no tiles)
+    // of the counts.  The tile rows that an expert fills at least half come first, expert by
+    // expert; a last tile row with fewer rows is numbered after all of those, since it takes less
+    // time (the 64-k loops multiply only the blocks of rows that hold something) and belongs at
+    // the end of a workgroup's list.  Lane l of every wavefront holds the tile rows of expert l
+    // (E <= 64); inclusive scans over the lanes give the numbers at which each expert ends.
+    int lane_tm = 0, lane_tail = 0;      // such tile rows of expert `lane`, and whether a last one with fewer rows follows
     if (lane < g.E) {
         int rows = 0;
         const int segs = (LAY == GEMM_TN && g.k_segs > 1) ? g.k_segs : 1;
         for (int sg = 0; sg < segs; ++sg) rows += g.counts[sg * g.E + lane];
         if (LAY == GEMM_TN) lane_tm = (rows > 0 || EPI == EPI_STORE_F32) ? tiles_m : 0;   // a plain store still writes zeros
-        else lane_tm = min(tiles_m, (rows + BM - 1) / BM);
+        else {
+            lane_tm = min(tiles_m, (rows + BM / 2 - 1) / BM);
+            lane_tail = (lane_tm < tiles_m && rows > lane_tm * BM) ? 1 : 0;
+        }
     }
-    int lane_end = lane_tm * tiles_n;
+    int lane_end = lane_tm * tiles_n, tail_end = lane_tail;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(lane_end, off, 64);
-        if (lane >= off) lane_end += o;
+        const int o = __shfl_up(lane_end, off, 64), q = LAY == GEMM_TN ? 0 : __shfl_up(tail_end, off, 64);
+        if (lane >= off) { lane_end += o; tail_end += q; }
     }
-    const int nblocks = __builtin_amdgcn_readlane(lane_end, 63);
+    const int nwhole = __builtin_amdgcn_readlane(lane_end, 63);
+    const int nblocks = nwhole + __builtin_amdgcn_readlane(tail_end, 63) * tiles_n;
     // Tiles are numbered expert by expert, in groups of 4 tile-rows walked column by
     // column, so 32 consecutive numbers form a 4 x 8 block that shares 4 A panels and 8
     // B panels.  Hardware deals consecutive workgroup ids round-robin to the 8 XCDs (each
@@ -345,19 +368,28 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     // plain order this halves what the L2s fetch; against giving each XCD its own experts
     // it is 3-5 % faster.)  A last partial run keeps plain order.
     auto decode = [&](int b, TileCoord& t) -> bool {
-        const int lin = (b < (nblocks & ~255)) ? (b & ~255) + (b & 7) * 32 + ((b >> 3) & 31) : b;
-        // the expert: as many experts end at or before lin as lanes say so (the ends never decrease)
-        const int e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane_end <= lin));
-        if (e >= g.E) return false;
-        const int tm_e = __builtin_amdgcn_readlane(lane_tm, e);      // tile rows of this expert
-        const int rem = lin - (__builtin_amdgcn_readlane(lane_end, e) - tm_e * tiles_n);
-        constexpr int GM = 4;
-        const int grp = rem / (GM * tiles_n);
-        const int first = grp * GM;
-        const int gsz = min(GM, tm_e - first);
-        const int in = rem - grp * GM * tiles_n;
-        const int tm = first + in % gsz;
-        t.tn = in / gsz;
+        const int lin = (b < (nwhole & ~255)) ? (b & ~255) + (b & 7) * 32 + ((b >> 3) & 31) : b;
+        int e, tm;
+        if (LAY == GEMM_TN || lin < nwhole) {
+            // the expert: as many experts end at or before lin as lanes say so (the ends never decrease)
+            e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane_end <= lin));
+            if (e >= g.E) return false;
+            const int tm_e = __builtin_amdgcn_readlane(lane_tm, e);      // tile rows of this expert
+            const int rem = lin - (__builtin_amdgcn_readlane(lane_end, e) - tm_e * tiles_n);
+            constexpr int GM = 4;
+            const int grp = rem / (GM * tiles_n);
+            const int first = grp * GM;
+            const int gsz = min(GM, tm_e - first);
+            const int in = rem - grp * GM * tiles_n;
+            tm = first + in % gsz;
+            t.tn = in / gsz;
+        } else {
+            const int q = (lin - nwhole) / tiles_n;                      // the q-th expert with such a last tile row
+            t.tn = (lin - nwhole) - q * tiles_n;
+            e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(tail_end <= q));
+            if (e >= g.E) return false;
+            tm = __builtin_amdgcn_readlane(lane_tm, e);
+        }
         const int rows = g.counts[e];
         if (LAY == GEMM_TN) { t.Mdim = g.Mo; t.Kdim = rows; } else { t.Mdim = rows; t.Kdim = g.K; }
         t.e = e;
@@ -401,6 +433,18 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     // ascending order, each starting with its load 0: that is where the cursor moves on, into the next
     // range with rows where the last one is used up (its operands then get new descriptors), and past
     // the last range, where everything reads as zeros.
+    // operand descriptors of row range seg (TN), its rows
+    auto bind_range = [&](const TileCoord& tc, int seg, AT& ta_, BT& tb_) -> int {
+        int rows = 0;
+        if constexpr (LAY == GEMM_TN) {
+            rows = seg < g.k_segs ? g.counts[seg * g.E + tc.e] : 0;
+            const bf16_t* A = (const bf16_t*)g.A + (size_t)tc.e * g.a_estride + seg * g.a_sstride + tc.m0;
+            const bf16_t* B = (const bf16_t*)g.B + (size_t)tc.e * g.b_estride + seg * g.b_sstride + tc.n0;
+            ta_.rsrc = AT::rsrc_of(A, g.lda, tc.Mdim - tc.m0, rows);
+            tb_.rsrc = BT::rsrc_of(B, g.ldb, g.N - tc.n0, rows);
+        }
+        return rows;
+    };
     auto request = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
         if constexpr (LAY == GEMM_TN) {
             if (g.k_segs > 1) {
@@ -409,13 +453,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     while (kc_.jl >= kc_.tiles) {
                         ++kc_.seg;
                         kc_.jl = 0;
-                        const bool more = kc_.seg < g.k_segs;
-                        const int rows = more ? g.counts[kc_.seg * g.E + tc.e] : 0;
-                        kc_.tiles = more ? (rows + BK - 1) / BK : 0x7fffffff;
-                        const bf16_t* A = (const bf16_t*)g.A + (size_t)tc.e * g.a_estride + kc_.seg * g.a_sstride + tc.m0;
-                        const bf16_t* B = (const bf16_t*)g.B + (size_t)tc.e * g.b_estride + kc_.seg * g.b_sstride + tc.n0;
-                        ta_.rsrc = AT::rsrc_of(A, g.lda, tc.Mdim - tc.m0, rows);
-                        tb_.rsrc = BT::rsrc_of(B, g.ldb, g.N - tc.n0, rows);
+                        const int rows = bind_range(tc, kc_.seg, ta_, tb_);
+                        kc_.tiles = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
                     }
                 }
                 k0 = kc_.jl * BK;
@@ -436,6 +475,9 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     constexpr int WL = W64 ? (A_WIDE ? AT::NI : BT::NI) : 0;       // loads per wave: one wide unit (8)
     constexpr int NL = W64 ? (A_WIDE ? BT::NI : AT::NI) : 0;       //                 one narrow tile (4)
     static_assert(!W64 || (WL == 8 && NL == 4), "the two-ring schedule issues two wide and two narrow loads per block");
+    // half-size tiles: a wave's loads of a stage that go out in block 3 of a step, the rest follow in blocks 0, 1, 2
+    constexpr int R64_G3 = (LPW + 2) / 3, R64_G0 = (LPW + 1) / 3, R64_G1 = LPW / 3, R64_G2 = 0;
+    static_assert(!R64 || R64_G3 + R64_G0 + R64_G1 + R64_G2 == LPW, "loads of a stage over the blocks");
     // the part of a tile's first loads that does not touch the staging region, and the rest
     auto issue_early = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
@@ -454,21 +496,31 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 #pragma unroll
             for (int l = 0; l < NL / 2; ++l) load_narrow(ta_, tb_, 3, 3, l);
         } else {
+            constexpr int FIRST = R64 ? 0 : SB, STAGES = R64 ? NS - C::SBR : NS - SB;
 #pragma unroll
-            for (int s = 0; s < 3; ++s)
+            for (int s = 0; s < STAGES; ++s)
 #pragma unroll
-                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (SB + s) * STAGE, s * BK, l);
+                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (FIRST + s) * STAGE, s * BK, l);
         }
     };
     auto issue_late = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
 #pragma unroll
             for (int l = 0; l < WL / 4; ++l) load_wide(ta_, tb_, 2, 2, l);
+        } else if constexpr (R64) {
+#pragma unroll
+            for (int s = NS - C::SBR; s < NS - 1; ++s)
+#pragma unroll
+                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + s * STAGE, s * BK, l);
+#pragma unroll
+            for (int l = 0; l < R64_G3; ++l) request(tc, kc_, ta_, tb_, smem + (NS - 1) * STAGE, (NS - 1) * BK, l);
         } else {
 #pragma unroll
-            for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem, 3 * BK, l);
+            for (int s = NS - SB; s < NS - 1; ++s)
 #pragma unroll
-            for (int l = 0; l < LPW / 2; ++l) request(tc, kc_, ta_, tb_, smem + STAGE, 4 * BK, l);
+                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (SB + s - NS) * STAGE, s * BK, l);
+#pragma unroll
+            for (int l = 0; l < LPW / 2; ++l) request(tc, kc_, ta_, tb_, smem + (SB - 1) * STAGE, (NS - 1) * BK, l);
         }
     };
 
@@ -484,7 +536,13 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     bool first = true;
 
     for (;;) {
+        if constexpr (REBIND) {
+            bind(cur, ta, tb);
+            if constexpr (LAY == GEMM_TN) { if (g.k_segs > 1) bind_range(cur, kc.seg, ta, tb); }
+        }
         const int m0 = cur.m0, n0 = cur.n0, e = cur.e, tn = cur.tn, Mdim = cur.Mdim, KT = cur.KT;
+        // blocks of 32 rows per wave that hold rows of this tile
+        const int active = ALT && LAY != GEMM_TN ? min(TM, (Mdim - m0 + 32 * C::WAVES_M - 1) / (32 * C::WAVES_M)) : TM;
         floatx16 acc[TM][TNN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -506,17 +564,32 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
             // loads 2,3; block 1 - unit t+2 loads 4,5, tile 2t+4 loads 0,1; block 2 - unit t+2 loads 6,7, tile
             // 2t+4 loads 2,3; block 3 - unit t+3 loads 0,1, tile 2t+5 loads 0,1.  At either barrier the sixteen
             // youngest loads of the wave may still be in flight; everything older is what the step needs next.
-            constexpr int MB = TM * TNN, FR = TM + TNN;
-            static_assert(FR + 7 <= MB, "one LDS read per matrix instruction, then a load after every other one");
             if (first) wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
+            // TMA: blocks of 32 rows per wave that hold something; loads, waits and barriers are the same for all
+            auto loop = [&](auto tma) __attribute__((always_inline)) {
+            constexpr int TMA = decltype(tma)::value;
+            constexpr int MB = TMA * TNN, FR = TMA + TNN;
+            // what follows matrix instruction m of a block: FR LDS reads, then four loads; one after every other
+            // matrix instruction where there is room, else spread evenly
+            auto follow = [&](int m, auto&& read, auto&& load) __attribute__((always_inline)) {
+                if constexpr (FR + 7 <= MB) {
+                    if (m < FR) read(m);
+                    else if (m - FR < 8 && (m - FR) % 2 == 0) load((m - FR) / 2);
+                } else {
+                    constexpr int items = FR + 4;
+#pragma unroll
+                    for (int it = 0; it < items; ++it)
+                        if (it * MB / items == m) { if (it < FR) read(it); else load(it - FR); }
+                }
+            };
             bf16x8 F0[FR], F1[FR];
             // fragment f of 16-k block kk of a step: from the wide unit at wb or from the narrow tile pair at nb0, nb1
-            auto frag = [&](int f, int kk, const char* wb, const char* nb0, const char* nb1) -> bf16x8 {
+            auto frag = [&](int f, int kk, const char* wb, const char* nb0, const char* nb1) __attribute__((always_inline)) -> bf16x8 {
                 const char* nb = kk < 2 ? nb0 : nb1;
-                if constexpr (A_WIDE) return f < TM ? fa[f].read(wb, kk) : fb[f - TM].read(nb, kk & 1);
-                else return f < TM ? fa[f].read(nb, kk & 1) : fb[f - TM].read(wb, kk);
+                if constexpr (A_WIDE) return f < TMA ? fa[f].read(wb, kk) : fb[f - TMA].read(nb, kk & 1);
+                else return f < TMA ? fa[f].read(nb, kk & 1) : fb[f - TMA].read(wb, kk);
             };
 #pragma unroll
             for (int f = 0; f < FR; ++f) F0[f] = frag(f, 0, smem, smem + NARROW_OFF, smem + NARROW_OFF);
@@ -533,10 +606,10 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 // block 0
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TM + m % TNN], F0[m / TNN]);
-                    if (m < FR) F1[m] = frag(m, 1, wb, nb0, nb1);
-                    else if (m == FR || m == FR + 2) load_wide(ta, tb, w3b, t + 2, 2 + (m - FR) / 2);
-                    else if (m == FR + 4 || m == FR + 6) load_narrow(ta, tb, n4b + 1, 2 * t + 3, 2 + (m - FR - 4) / 2);
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    follow(m, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 1, wb, nb0, nb1); },
+                           [&](int l) __attribute__((always_inline)) {
+                               if (l < 2) load_wide(ta, tb, w3b, t + 2, 2 + l); else load_narrow(ta, tb, n4b + 1, 2 * t + 3, l); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 wait_vmcnt<16>();
@@ -545,18 +618,18 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 // block 1
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TM + m % TNN], F1[m / TNN]);
-                    if (m < FR) F0[m] = frag(m, 2, wb, nb0, nb1);
-                    else if (m == FR || m == FR + 2) load_wide(ta, tb, w3b, t + 2, 4 + (m - FR) / 2);
-                    else if (m == FR + 4 || m == FR + 6) load_narrow(ta, tb, n4, 2 * t + 4, (m - FR - 4) / 2);
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    follow(m, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 2, wb, nb0, nb1); },
+                           [&](int l) __attribute__((always_inline)) {
+                               if (l < 2) load_wide(ta, tb, w3b, t + 2, 4 + l); else load_narrow(ta, tb, n4, 2 * t + 4, l - 2); });
                 }
                 // block 2
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TM + m % TNN], F0[m / TNN]);
-                    if (m < FR) F1[m] = frag(m, 3, wb, nb0, nb1);
-                    else if (m == FR || m == FR + 2) load_wide(ta, tb, w3b, t + 2, 6 + (m - FR) / 2);
-                    else if (m == FR + 4 || m == FR + 6) load_narrow(ta, tb, n4, 2 * t + 4, 2 + (m - FR - 4) / 2);
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    follow(m, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, wb, nb0, nb1); },
+                           [&](int l) __attribute__((always_inline)) {
+                               if (l < 2) load_wide(ta, tb, w3b, t + 2, 6 + l); else load_narrow(ta, tb, n4, 2 * t + 4, l); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 wait_vmcnt<16>();
@@ -565,35 +638,128 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 // block 3
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TM + m % TNN], F1[m / TNN]);
-                    if (m < FR) F0[m] = frag(m, 0, wb_next, nb_next, nb_next);
-                    else if (m == FR || m == FR + 2) load_wide(ta, tb, w3, t + 3, (m - FR) / 2);
-                    else if (m == FR + 4 || m == FR + 6) load_narrow(ta, tb, n4 + 1, 2 * t + 5, (m - FR - 4) / 2);
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    follow(m, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 0, wb_next, nb_next, nb_next); },
+                           [&](int l) __attribute__((always_inline)) {
+                               if (l < 2) load_wide(ta, tb, w3, t + 3, l); else load_narrow(ta, tb, n4 + 1, 2 * t + 5, l - 2); });
                 }
                 w3 = w3a;
                 n4 = n4b;
             }
+            };
+            if (active == 4) loop(std::integral_constant<int, 4>{});
+            else if (active == 3) loop(std::integral_constant<int, 3>{});
+            else if (active == 2) loop(std::integral_constant<int, 2>{});
+            else loop(std::integral_constant<int, 1>{});
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        } else if constexpr (R64) {
+            // Hand-scheduled loop over steps of 64 k = four blocks of TM x TN matrix instructions (16 k each).  A
+            // ring of NS stages; while block b is multiplied the fragments of block b+1 are read.  One barrier per
+            // step, after block 2: every wave has read stage t for the last time (its slot then receives stage
+            // t+NS) and stage t+1 has landed.  A wave's loads of stage t+NS-1 go out in block 3 of step t-1 and the
+            // first blocks of step t, as early as its slot is free; at the barrier those of NS-2 stages may still be
+            // in flight.
+            if (first) wait_vmcnt<(NS - 2) * LPW + R64_G3>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            auto loop = [&](auto tma) __attribute__((always_inline)) {
+            constexpr int TMA = decltype(tma)::value;
+            constexpr int MB = TMA * TNN, FR = TMA + TNN;
+            // matrix instruction m of a block is followed by its share of the block's LDS reads, then loads
+            auto follow = [&](int m, int nload, auto&& read, auto&& load) __attribute__((always_inline)) {
+                const int items = FR + nload;
+#pragma unroll
+                for (int it = 0; it < FR + LPW; ++it)
+                    if (it < items && it * MB / items == m) { if (it < FR) read(it); else load(it - FR); }
+            };
+            bf16x8 F0[FR], F1[FR];
+            auto frag = [&](int f, int kk, const char* st) __attribute__((always_inline)) -> bf16x8 {
+                return f < TMA ? fa[f].read(st, kk) : fb[f - TMA].read(st + A_BYTES, kk);
+            };
+#pragma unroll
+            for (int f = 0; f < FR; ++f) F0[f] = frag(f, 0, smem);
+            int s3 = 0;                               // slot of stage t
+#pragma unroll 1
+            for (int t = 0; t < KT; ++t) {
+                const int s3a = s3 == NS - 1 ? 0 : s3 + 1;
+                char* st = smem + s3 * STAGE;
+                char* st1 = smem + s3a * STAGE;
+                char* st2 = smem + (s3 == 0 ? NS - 1 : s3 - 1) * STAGE;      // of stage t + NS-1
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    follow(m, R64_G0, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 1, st); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + l); });
+                }
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    follow(m, R64_G1, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 2, st); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + l); });
+                }
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    follow(m, R64_G2, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, st); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + R64_G1 + l); });
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                wait_vmcnt<(NS - 2) * LPW>();
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int m = 0; m < MB; ++m) {
+                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    follow(m, R64_G3, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 0, st1); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st, (t + NS) * BK, l); });
+                }
+                s3 = s3a;
+            }
+            };
+            if (TM == 1 || active == 1) loop(std::integral_constant<int, 1>{});
+            else if (TM == 2 || active == 2) loop(std::integral_constant<int, TM < 2 ? 1 : 2>{});
+            else if (active == 3) loop(std::integral_constant<int, TM < 3 ? 1 : 3>{});
+            else loop(std::integral_constant<int, TM < 4 ? 1 : 4>{});
             asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         } else {
             // Hand-scheduled loop (with one wave per SIMD nothing else hides a stall): every
             // LDS read and every load into LDS sits between two matrix instructions, one per
             // instruction, and the data a block of TM x TN matrix instructions needs was
             // requested during the block before.
-            // A tile is 32 k = two such blocks; the ring holds five tiles.  In iteration t
+            // A tile is 32 k = two such blocks; the ring holds NS tiles.  In iteration t
             //   block 0 multiplies k 0..15 of tile t, reads k 16..31 of it into the second
-            //           fragment set and requests the second half of tile t+4;
+            //           fragment set and requests the second half of tile t+NS-1;
             //   then the wave waits for its part of tile t+1 and meets the others (their
             //           parts have landed too, and nobody reads stage t any more);
             //   block 1 multiplies k 16..31, reads k 0..15 of tile t+1 into the first
-            //           fragment set and requests the first half of tile t+5 into stage t.
-            // Up to four tiles (128 KB) are in flight towards a CU.
+            //           fragment set and requests the first half of tile t+NS into stage t.
+            // Up to NS - 1 tiles are in flight towards a workgroup.
             constexpr int MB = TM * TNN;                 // matrix instructions per block
             constexpr int FR = TM + TNN;                 // fragments per block: A rows first, then B columns
-            static_assert(LPW % 2 == 0 && FR + LPW / 2 <= MB, "one LDS read or load per matrix instruction");
-            // a load costs the wave more issue time than one matrix instruction hides: where there is room,
-            // only every other matrix instruction is followed by one
-            constexpr int LS = (FR + 2 * (LPW / 2) - 1 <= MB) ? 2 : 1;
-            if (first) wait_vmcnt<3 * LPW + LPW / 2>();            // tile 0 is in (later tiles: waited for at the handover)
+            constexpr int LH = LPW / 2;                  // loads of a tile requested one block earlier than the rest
+            // What follows matrix instruction m of a block: LDS reads first, then loads.  A load costs the wave
+            // more issue time than one matrix instruction hides: where there is room, only every other matrix
+            // instruction is followed by one; where there is not even a matrix instruction for each item (tiles
+            // of 64 x 64 per wave), the items are spread evenly.
+            constexpr int LMAX = LPW - LH;
+            constexpr int LS = (FR + 2 * LMAX - 1 <= MB) ? 2 : 1;
+            constexpr bool ROOMY = FR + LMAX <= MB;
+            auto follow = [&](int m, int nload, auto&& read, auto&& load) __attribute__((always_inline)) {
+                if constexpr (ROOMY) {
+                    if (m < FR) read(m);
+                    else if (m - FR < LS * nload && (m - FR) % LS == 0) load((m - FR) / LS);
+                } else {
+                    const int items = FR + nload;
+#pragma unroll
+                    for (int it = 0; it < FR + LMAX; ++it) {
+                        if (it < items && it * MB / items == m) {
+                            if (it < FR) read(it);
+                            else load(it - FR);
+                        }
+                    }
+                }
+            };
+            if (first) wait_vmcnt<(NS - 2) * LPW + LH>();                 // tile 0 is in (later tiles: waited for at the handover)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             bf16x8 F0[FR], F1[FR];
@@ -611,20 +777,20 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
                     mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F0[TM + m % TNN], F0[m / TNN]);
-                    if (m < TM) F1[m] = fa[m].read(cs, 1);
-                    else if (m < FR) F1[m] = fb[m - TM].read(cs + A_BYTES, 1);
-                    else if (m - FR < LS * (LPW / 2) && (m - FR) % LS == 0) request(cur, kc, ta, tb, prv, (kt + 4) * BK, LPW / 2 + (m - FR) / LS);
+                    follow(m, LPW - LH,
+                           [&](int f) __attribute__((always_inline)) { F1[f] = f < TM ? fa[f].read(cs, 1) : fb[f - TM].read(cs + A_BYTES, 1); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, prv, (kt + NS - 1) * BK, LH + l); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave no longer reads stage t
-                wait_vmcnt<3 * LPW>();                               // its part of tile t+1 is in
+                wait_vmcnt<(NS - 2) * LPW>();                          // its part of tile t+1 is in
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
                     mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F1[TM + m % TNN], F1[m / TNN]);
-                    if (m < TM) F0[m] = fa[m].read(nxt, 0);
-                    else if (m < FR) F0[m] = fb[m - TM].read(nxt + A_BYTES, 0);
-                    else if (m - FR < LS * (LPW / 2) && (m - FR) % LS == 0) request(cur, kc, ta, tb, cs, (kt + 5) * BK, (m - FR) / LS);
+                    follow(m, LH,
+                           [&](int f) __attribute__((always_inline)) { F0[f] = f < TM ? fa[f].read(nxt, 0) : fb[f - TM].read(nxt + A_BYTES, 0); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, cs, (kt + NS) * BK, l); });
                 }
                 st = stn;
             }
@@ -642,7 +808,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         BT tb2;
         KCursor kc2 = {0, 0, 0};
         const int vn = next_tile(vb + (int)gridDim.x, nx);
-        if (vn >= 0) bind(nx, ta2, tb2);
+        if (vn < 0) nx = cur;                        // (bound all the same, and never used)
+        bind(nx, ta2, tb2);
 
         // ---- epilogue -----------------------------------------------------------------------
         // An MFMA accumulator holds one row per lane (row = lane & 31, four consecutive
@@ -677,24 +844,38 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         // sums for float accumulation) is requested one pass ahead.
         constexpr bool READS = (EPI == EPI_DGELU || EPI == EPI_ACCUM_F32 || EPI == EPI_SCATTER);
         struct PassIn { uint4 zin[NPIECE]; float4 cin0[NPIECE], cin1[NPIECE]; float wrow[NPIECE]; int crow[NPIECE]; };
-        auto piece = [&](int ps, int t, int& m, int& c8, int& row, unsigned& oC, unsigned& oZ) {
-            const int idx = lane + 64 * t;
-            row = idx / CPRW; c8 = idx % CPRW;
-            m = m0 + wm * WM + (ps / NCH) * 32 + row;
-            const int n = n0 + wn * WN + (ps % NCH) * CW + c8 * 8;
-            const bool in = n < g.N;                 // rows beyond Mdim fall outside the descriptors by themselves
-            oC = in ? (unsigned)(m * g.ldc + n) * CES : OOB_OFFSET;
-            oZ = in ? (unsigned)(m * g.ldz + n) * 2u : OOB_OFFSET;
-        };
+        // Piece t of a lane: row RSTEP*t + prow of the pass, columns 8*c8 .. 8*c8 + 7.  Addresses are one vector
+        // offset per column block (out of range: past the descriptor, and it stays there with any step added) and a
+        // scalar step per pass and piece.
+        constexpr int RSTEP = 64 / CPRW;
+        const int prow = lane / CPRW, c8 = lane % CPRW;
+        unsigned baseC[NCH], baseZ[NCH];
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch) {
+            const int n = n0 + wn * WN + ch * CW + c8 * 8;
+            baseC[ch] = n < g.N ? (unsigned)((m0 + prow) * g.ldc + n) * CES : OOB_OFFSET;
+            baseZ[ch] = n < g.N ? (unsigned)((m0 + prow) * g.ldz + n) * 2u : OOB_OFFSET;
+        }
+        auto row_of = [&](int ps, int t) __attribute__((always_inline)) { return block_row(ps / NCH) + RSTEP * t; };   // wave-uniform
+        auto offC = [&](int ps, int t) __attribute__((always_inline)) { return baseC[ps % NCH] + (unsigned)(row_of(ps, t) * g.ldc) * CES; };
+        auto offZ = [&](int ps, int t) __attribute__((always_inline)) { return baseZ[ps % NCH] + (unsigned)(row_of(ps, t) * g.ldz) * 2u; };
+        // row weights, output rows and row dots through descriptors too: nothing below branches on the row
+        const unsigned row4 = (unsigned)(m0 + prow) * 4u;
+        const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wbase), 0, wbase ? Mdim * 4 : 0, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rR = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(crows), 0, crows ? Mdim * 4 : 0, 0x00020000);
+        float* dwbase = g.dw_part ? g.dw_part + (size_t)e * g.Cp * g.dw_parts : nullptr;
+        const __amdgpu_buffer_rsrc_t rD = __builtin_amdgcn_make_buffer_rsrc(dwbase, 0, dwbase ? Mdim * g.dw_parts * 4 : 0, 0x00020000);
         // Float outputs: a lane's two 16-byte halves of "piece" t are units 2t and 2t+1 of a numbering in which the
         // 64 lanes of one store (or load) cover whole rows of the pass - 4 columns per lane, CW/4 lanes per row - so
         // that every such instruction moves whole 128-byte lines (8 columns per lane would leave each instruction
         // with every other 16 bytes).  Unit u of a lane is UROWS*u rows below its unit 0, in the same columns: one
-        // vector offset per pass, the rest is a scalar offset.
+        // vector offset per pass and a constant step.  (The stores take the step in the vector offset: behind a
+        // 16-byte store with a scalar offset register the compiler may overwrite the store's data registers in the
+        // very next instruction, and then the last lanes of the store have been seen to write the new contents.)
         constexpr int ULANES = CW / 4, UROWS = 64 / ULANES;
         const int urow = lane / ULANES, uc4 = lane % ULANES;
         auto unit0 = [&](int ps) -> unsigned {
-            const int m = m0 + wm * WM + (ps / NCH) * 32 + urow;
+            const int m = m0 + block_row(ps / NCH) + urow;
             const int n = n0 + wn * WN + (ps % NCH) * CW + uc4 * 4;
             return n < g.N ? (unsigned)(m * g.ldc + n) * 4u : OOB_OFFSET;
         };
@@ -702,16 +883,12 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         auto request_pass = [&](int ps, PassIn& in) {
 #pragma unroll
             for (int t = 0; t < NPIECE; ++t) {
-                int m, c8, row; unsigned oC, oZ;
-                piece(ps, t, m, c8, row, oC, oZ);
-                if constexpr (EPI == EPI_DGELU) {
-                    in.zin[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rZ, oZ, 0, 0));
-                    in.wrow[t] = m < Mdim ? wbase[m] : 0.0f;
-                }
-                if constexpr (EPI == EPI_SCATTER) {
-                    in.crow[t] = m < Mdim ? crows[m] : -1;
-                    in.wrow[t] = m < Mdim ? wbase[m] : 0.0f;
-                }
+                if constexpr (EPI == EPI_DGELU)
+                    in.zin[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rZ, baseZ[ps % NCH], (row_of(ps, t) * g.ldz) * 2, 0));
+                if constexpr (EPI == EPI_DGELU || EPI == EPI_SCATTER)
+                    in.wrow[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rW, row4, row_of(ps, t) * 4, 0));
+                if constexpr (EPI == EPI_SCATTER)
+                    in.crow[t] = (int)__builtin_amdgcn_raw_buffer_load_b32(rR, row4, row_of(ps, t) * 4, 0);
                 if constexpr (EPI == EPI_ACCUM_F32) {
                     const unsigned ob = unit0(ps);
                     in.cin0[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rC, ob, (2 * t) * ustep, 0));
@@ -719,12 +896,20 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 }
             }
         };
-        PassIn pin[2];
-        if constexpr (READS) request_pass(0, pin[0]);
+        // (with two workgroups on the CU the other one covers the wait, and the registers are short)
+        constexpr int PB = C::OCC == 1 ? 2 : 1;
+        PassIn pin[PB];
+        if constexpr (READS && PB == 2) request_pass(0, pin[0]);
+        // where a lane's row dots go (the first of a row's lanes writes them)
+        const unsigned dw_lane = c8 == 0 ? (unsigned)((m0 + prow) * g.dw_parts + tn * C::WAVES_N + wn) * 4u : OOB_OFFSET;
+        float dots[TM][NPIECE];                      // its finished rows, where a column block is two waves wide
         float dotacc[NPIECE];                        // GeLU-backward: <gelu(Z), G> of a row over the passes of its 32 rows
 #pragma unroll
         for (int ps = 0; ps < NPASS; ++ps) {
             const int i = ps / NCH, ch = ps % NCH;
+            // no rows in the second half (wave-uniform; tested once, so that the scheduler sees long stretches)
+            if (ALT && TM > 1 && ps == NPASS / 2 && active <= TM / 2) break;
+            if constexpr (READS && PB == 1) request_pass(ps, pin[0]);
 #pragma unroll
             for (int jj = 0; jj < TJ; ++jj) {
                 const int j = ch * TJ + jj;
@@ -735,8 +920,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & 15)) << 2)) = v;
                 }
             }
-            if constexpr (READS) { if (ps + 1 < NPASS) request_pass(ps + 1, pin[(ps + 1) & 1]); }
-            const PassIn& in = pin[ps & 1];
+            if constexpr (READS && PB == 2) { if (ps + 1 < NPASS) request_pass(ps + 1, pin[(ps + 1) & 1]); }
+            const PassIn& in = pin[ps & (PB - 1)];
             // all LDS reads of the pass before its arithmetic: one round trip through LDS, not one per piece
             // (float accumulation keeps the old sums of two passes in registers and has none left for that)
             constexpr bool HOIST = EPI != EPI_ACCUM_F32;
@@ -747,8 +932,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     lo[t] = *reinterpret_cast<const float4*>(stage + r0 * CW + ((uc4 ^ (r0 & 15)) << 2));
                     hi[t] = *reinterpret_cast<const float4*>(stage + r1 * CW + ((uc4 ^ (r1 & 15)) << 2));
                 } else {
-                    const int idx = lane + 64 * t;
-                    const int row = idx / CPRW, c8 = idx % CPRW;
+                    const int row = RSTEP * t + prow;
                     lo[t] = *reinterpret_cast<const float4*>(stage + row * CW + (((2 * c8) ^ (row & 15)) << 2));
                     hi[t] = *reinterpret_cast<const float4*>(stage + row * CW + (((2 * c8 + 1) ^ (row & 15)) << 2));
                 }
@@ -759,29 +943,29 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
             }
 #pragma unroll
             for (int t = 0; t < NPIECE; ++t) {
-                int m, c8, row; unsigned oC, oZ;
-                piece(ps, t, m, c8, row, oC, oZ);
                 if constexpr (!HOIST) read_piece(t);
                 float v[8] = {lo[t].x, lo[t].y, lo[t].z, lo[t].w, hi[t].x, hi[t].y, hi[t].z, hi[t].w};
                 if constexpr (EPI == EPI_STORE) {
                     uint4 o = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o), rC, oC, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o), rC, offC(ps, t), 0, 0);
                 } else if constexpr (EPI == EPI_SCATTER) {
                     // the row's place in the output and its weight; rows and columns out of range are dropped
                     const float w = in.wrow[t];
                     const int n = n0 + wn * WN + (ps % NCH) * CW + c8 * 8;
-                    const unsigned oS = (in.crow[t] >= 0 && oC != OOB_OFFSET) ? (unsigned)(in.crow[t] * g.ldc + n) * 2u : OOB_OFFSET;
+                    const unsigned oS = (m0 + row_of(ps, t) + prow < Mdim && n < g.N) ? (unsigned)(in.crow[t] * g.ldc + n) * 2u : OOB_OFFSET;
                     uint4 o = make_uint4(pack_bf16x2(w * v[0], w * v[1]), pack_bf16x2(w * v[2], w * v[3]),
                                          pack_bf16x2(w * v[4], w * v[5]), pack_bf16x2(w * v[6], w * v[7]));
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o), rC, oS, 0, 0);
                 } else if constexpr (EPI == EPI_GELU) {
+                    // (the activation is taken of the rounded pre-activation, unpacked from what is stored)
+                    const uint4 oz = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
                     float z[8], a[8];
+                    Unit8::to_float(oz, z);
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) { z[q] = bf16_to_f32(f32_to_bf16(v[q])); a[q] = gelu_fast_f(z[q]); }
-                    uint4 oz = make_uint4(pack_bf16x2(z[0], z[1]), pack_bf16x2(z[2], z[3]), pack_bf16x2(z[4], z[5]), pack_bf16x2(z[6], z[7]));
+                    for (int q = 0; q < 8; ++q) a[q] = gelu_fast_f(z[q]);
                     uint4 oa = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
-                    if (Zbase) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oz), rZ, oZ, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oa), rC, oC, 0, 0);
+                    if (Zbase) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oz), rZ, offZ(ps, t), 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oa), rC, offC(ps, t), 0, 0);
                 } else if constexpr (EPI == EPI_DGELU) {
                     float z[8], dz[8], a[8];
                     Unit8::to_float(in.zin[t], z);
@@ -800,31 +984,65 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     dotacc[t] = dot;
                     uint4 od = make_uint4(pack_bf16x2(dz[0], dz[1]), pack_bf16x2(dz[2], dz[3]), pack_bf16x2(dz[4], dz[5]), pack_bf16x2(dz[6], dz[7]));
                     uint4 oa = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, od), rC, oC, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oa), rZ, oZ, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, od), rC, offC(ps, t), 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oa), rZ, offZ(ps, t), 0, 0);
                     if (g.dw_part && ch == NCH - 1) {
                         // the CPRW lanes of a row are neighbours
 #pragma unroll
                         for (int off = CPRW / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-                        if (c8 == 0 && m < Mdim)
-                            g.dw_part[((size_t)e * g.Cp + m) * g.dw_parts + tn * C::WAVES_N + wn] = dot;
+                        if constexpr (WN == DW_COLS) {
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dot), rD, dw_lane,
+                                                                  row_of(ps, t) * g.dw_parts * 4, 0);
+                        } else {
+                            dots[i][t] = dot;        // half a column block: added to the other wave's below
+                        }
                     }
                 } else if constexpr (EPI == EPI_STORE_F32) {
                     const unsigned ob = unit0(ps);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, lo[t]), rC, ob, (2 * t) * ustep, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, hi[t]), rC, ob, (2 * t + 1) * ustep, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, lo[t]), rC, ob + (2 * t) * ustep, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, hi[t]), rC, ob + (2 * t + 1) * ustep, 0, 0);
                 } else {
                     const unsigned ob = unit0(ps);
                     float4 o0 = in.cin0[t], o1 = in.cin1[t];
                     o0.x += v[0]; o0.y += v[1]; o0.z += v[2]; o0.w += v[3];
                     o1.x += v[4]; o1.y += v[5]; o1.z += v[6]; o1.w += v[7];
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o0), rC, ob, (2 * t) * ustep, 0);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o1), rC, ob, (2 * t + 1) * ustep, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o0), rC, ob + (2 * t) * ustep, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o1), rC, ob + (2 * t + 1) * ustep, 0, 0);
                 }
             }
             // the next tile's first operand tiles start their trip once the first pass is through
             // (earlier, and this pass's own reads would have to wait behind them)
             if (ps == 0 && vn >= 0) issue_early(nx, kc2, ta2, tb2);
+        }
+        if constexpr (EPI == EPI_DGELU && WN != DW_COLS) {
+            if (g.dw_part) {
+                // A column block of the row dots is the width of the two neighbouring waves: the right one hands its
+                // rows' sums to the left one through its own staging region, which nobody else touches.
+                static_assert(C::WAVES_N == 2 && 2 * WN == DW_COLS && BN == DW_COLS, "one column block per tile");
+                if (wn == 1 && c8 == 0) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int t = 0; t < NPIECE; ++t) stage[i * 32 + RSTEP * t + prow] = dots[i][t];
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                if (wn == 0 && c8 == 0) {
+                    const float* right = stage + 32 * CW;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int t = 0; t < NPIECE; ++t) {
+                            const int row = i * 32 + RSTEP * t + prow, m = m0 + row_of(i * NCH, t) + prow;
+                            if (m < Mdim) {
+                                float* at = g.dw_part + ((size_t)e * g.Cp + m) * g.dw_parts + tn;
+                                at[0] = dots[i][t] + right[row];
+                                if (tn == tiles_n - 1 && tn + 1 < g.dw_parts) at[1] = 0.0f;     // blocks come in pairs
+                            }
+                        }
+                }
+            }
         }
         if (vn < 0) break;
         // Everything this wave has in flight is through: the next tile's first operand tiles have
@@ -836,15 +1054,14 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         asm volatile("" ::: "memory");
         issue_late(nx, kc2, ta2, tb2);
         kc = kc2;
-        ta = ta2;
-        tb = tb2;
+        if constexpr (!REBIND) { ta = ta2; tb = tb2; }
         cur = nx;
         vb = vn;
         first = false;
     }
 }
 
-// Tile shapes in use.  Both cover 256 x 256 per workgroup with four waves of 128 x 128, one per SIMD.
+// Tile shapes in use.  The first two cover 256 x 256 per workgroup with four waves of 128 x 128, one per SIMD.
 //   CfgW   two-ring loop: for every GEMM with a K-contiguous operand (NN, NT).  A request for half a
 //          128-byte line costs the L1 as much as one for a whole line, and the loop's speed follows
 //          the number of requests; here every request but those of NT's row operand is a whole line.
@@ -857,14 +1074,20 @@ typedef TileCfg<256, 256, 32, 5, 2, 2, 1, LOOP_PIPE32> Cfg4;
 typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_W64> CfgW;
 template <int LAY, int EPI> struct CfgFor { typedef CfgW type; };
 template <int EPI> struct CfgFor<GEMM_TN, EPI> { typedef Cfg4 type; };
-// every layout reports the row dot of the GeLU-backward epilogue in the same number of column blocks
-typedef CfgFor<GEMM_NT, EPI_DGELU>::type CfgDgelu;
-static_assert(CfgFor<GEMM_NN, EPI_DGELU>::type::WAVES_N * 256 / CfgFor<GEMM_NN, EPI_DGELU>::type::BN ==
-              CfgDgelu::WAVES_N * 256 / CfgDgelu::BN &&
-              CfgFor<GEMM_TN, EPI_DGELU>::type::WAVES_N * 256 / CfgFor<GEMM_TN, EPI_DGELU>::type::BN ==
-              CfgDgelu::WAVES_N * 256 / CfgDgelu::BN, "column blocks per 256 columns");
+// Smaller tiles for launches that 256 x 256 leaves too few of, all layouts (the flat one: NN, NT):
+//   CfgM   256 x 128, waves of 128 x 64, three 64-k stages of both operands, so that every request is a whole line.
+//          A step takes 0.68 us alone against 1.0-1.4 for the large tile's, bound by the loads (48 KB per step, 96 KB
+//          in flight) where the chip is full: 8 x 1024 rows, N = 1024, K = 4096: 72 us in 256 tiles, 107 in 128.
+//   CfgS   128 x 128, waves of 64 x 64, five 32-k stages, two workgroups per CU: one's epilogue runs beside the
+//          other's loop.  Its loop is bound by LDS (192 bytes per cycle wanted, 128 there).  8 x 512 rows, N = 2048,
+//          K = 512, GeLU: 22 us against 25 in 256 x 256; N = 512, K = 2048: 22 against 38.
+//   CfgT   64 x 128, waves of 32 x 64, six 64-k stages: few rows against long K, where a CU should have many bytes of
+//          the weights in flight.  8 x 16 rows, N = 1024, K = 4096: 41 us against 60 (67 MB of weights: 13 us).
+typedef TileCfg<256, 128, 64, 3, 2, 2, 1, LOOP_R64> CfgM;
+typedef TileCfg<128, 128, 32, 5, 2, 2, 2, LOOP_PIPE32> CfgS;
+typedef TileCfg<64, 128, 64, 6, 2, 2, 1, LOOP_R64> CfgT;
 
-int gemm_bf16_dw_parts(int H) { return ((H + CfgDgelu::BN - 1) / CfgDgelu::BN) * CfgDgelu::WAVES_N; }
+int gemm_bf16_dw_parts(int H) { return (H + 2 * DW_COLS - 1) / (2 * DW_COLS) * 2; }
 
 // One workgroup per CU (a workgroup fills a CU's LDS), rounded down to a multiple of 8 so that
 // tile numbers keep their XCD.
@@ -888,6 +1111,7 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
     nblocks = (nblocks + 7) / 8 * 8;
     int full = persistent_grid() - (a.free_cus + 7) / 8 * 8;
     if (full < 8) full = 8;
+    full *= C::OCC;
     const int grid = nblocks < full ? nblocks : full;
     constexpr int lds = C::LDS_BYTES;
     auto kern = gemm_bf16_kernel<LAY, EPI, C>;
@@ -905,11 +1129,71 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
     return MOE_OK;
 }
 
+// Which tile a launch uses: the one whose estimated time is least.  Large tiles multiply fastest (per 256 x 256 x
+// 64 on one CU: 1.1 to 1.5 us in one large tile, 1.7 in two half-size ones, 1.8 to 2.6 in four small ones two at a
+// time, 3.5 in eight flat ones), but a launch with fewer tiles than the chip has CUs, or a few more than a multiple
+// of that, leaves CUs idle, and a workgroup's epilogue is only covered where two workgroups share a CU.  The estimate
+// counts the rounds of tiles over the workgroups; the times (us) of a 64-k step per layout (NN, NT, TN), of a step of
+// a nearly empty tile, and of an epilogue (store, GeLU, GeLU-backward, float store, float accumulation) were fitted
+// to 516 measured launches in all four shapes (1 to 64 experts of 8 to 8192 rows, dimensions 64 to 8192, even and
+// skewed random loads): the choice is on average 1.3 % slower than the best tile of each launch, 256 x 256
+// throughout 32 % slower.  The host does not know the loads; it takes every expert to have the mean.
+struct TileCost { int bm, bn, per_cu; double step[3], tail_step, epi[5]; };
+static constexpr TileCost TILE_COSTS[4] = {
+    {256, 256, 1, {1.09, 1.52, 1.48}, 0.85, {3.3, 10.8, 27.0, 11.1, 20.9}},      // CfgW / Cfg4
+    {256, 128, 1, {0.87, 0.84, 0.93}, 0.72, {3.4, 8.6, 19.1, 6.7, 11.0}},        // CfgM
+    {128, 128, 2, {0.90, 1.29, 0.94}, 0.0, {3.0, 5.0, 9.3, 6.5, 8.8}},           // CfgS (two tiles at a time)
+    {64, 128, 1, {0.44, 0.42, 0.0}, 0.92, {1.5, 2.5, 5.0, 0.0, 0.0}},            // CfgT (not for TN)
+};
+static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, int cus) {
+    const int which = epi == EPI_GELU ? 1 : epi == EPI_DGELU ? 2 : epi == EPI_STORE_F32 ? 3 : epi == EPI_ACCUM_F32 ? 4 : 0;
+    const long long tn = (a.N + c.bn - 1) / c.bn;
+    const int segs = a.k_segs > 1 ? a.k_segs : 1;
+    const double kt = lay == GEMM_TN ? (double)((a.mean_rows + 63) / 64) * segs : (double)((a.K + 63) / 64);
+    long long whole, tail = 0;                       // tiles; those of the experts' last, partly filled tile rows
+    double share = 1.0;                              // how full a tail tile is, in quarters
+    if (lay == GEMM_TN) {
+        whole = (long long)((a.Mo + c.bm - 1) / c.bm) * tn * a.E;
+    } else {
+        const int full = a.mean_rows / c.bm, rest = a.mean_rows - full * c.bm;
+        whole = full * tn * a.E;
+        // an even multiple on average: about half the experts have a few rows more, where the capacity allows it
+        tail = rest ? tn * a.E : a.mean_rows < a.Cp ? tn * a.E / 2 : 0;
+        share = rest ? (rest + c.bm / 4 - 1) / (c.bm / 4) * 0.25 : 0.25;
+    }
+    const double tile = kt * c.step[lay] + c.epi[which], launch = 1.7;
+    if (c.per_cu == 2) {
+        const long long n = whole + tail, rounds = n / (2 * cus), rest = n - rounds * 2 * cus;
+        return launch + rounds * tile + (rest == 0 ? 0.0 : rest <= cus ? 0.53 * tile : tile);
+    }
+    if (c.bm <= 64) share = 1.0;
+    const long long rounds = (whole + cus - 1) / cus, spare = rounds * cus - whole;
+    const long long extra = tail > spare ? (tail - spare + cus - 1) / cus : 0;
+    return launch + rounds * tile +
+           extra * (kt * (c.tail_step + (c.step[lay] - c.tail_step) * share) + c.epi[which] * (0.4 + 0.6 * share));
+}
+static int tile_choice(int lay, int epi, const GemmArgs& a) {
+    int cus = persistent_grid() - (a.free_cus + 7) / 8 * 8;
+    if (cus < 8) cus = 8;
+    int best = 0;
+    double least = 0.0;
+    for (int c = 0; c < (lay == GEMM_TN ? 3 : 4); ++c) {
+        const double t = tile_time(TILE_COSTS[c], lay, epi, a, cus);
+        // (a smaller tile has to be clearly better: skewed loads drop rows and make more cheap last tile rows)
+        if (c == 0 || t < (best == 0 ? 0.93 : 1.0) * least) { best = c; least = t; }
+    }
+    return best;
+}
+
 // Only the combinations the expert FFN uses are instantiated: NN with plain, GeLU and scattered stores
 // (both layers of forward, recomputation), NT with GeLU-backward and plain stores (the two input
 // gradients), TN with float store and float accumulation (the weight gradients).
 template <int LAY, int EPI>
 static moe_status launch_cfg(const GemmArgs& a, hipStream_t s) {
+    const int choice = tile_choice(LAY, EPI, a);
+    if (choice == 2) return launch_one<LAY, EPI, CfgS>(a, s);
+    if constexpr (LAY != GEMM_TN) { if (choice == 3) return launch_one<LAY, EPI, CfgT>(a, s); }
+    if (choice == 1) return launch_one<LAY, EPI, CfgM>(a, s);
     return launch_one<LAY, EPI, typename CfgFor<LAY, EPI>::type>(a, s);
 }
 
