@@ -114,19 +114,26 @@ struct KCTile {
     }
     v4i rsrc;
     unsigned voff[NI];       // byte offset of this lane's chunk at k0 = 0
-    int kc[NI];              // first k of this lane's chunk
+    // First k of this lane's chunk in load j: kc0 ^ 8*j for rows of eight chunks (loads of consecutive j lie eight
+    // rows apart, which the swizzle turns into the chunk number), the same for every j for rows of four.
+    int kc0;
+    static_assert((NI & (NI - 1)) == 0, "wid*NI + j is wid*NI ^ j");
+    __device__ __forceinline__ int first_k(int j) const { return CPR == 8 ? kc0 ^ (8 * j) : kc0; }
+    __device__ __forceinline__ void init_kc(int lane, int wid) {
+        kc0 = ((lane % CPR) ^ sw(wid * NI * RPI + lane / CPR)) * 8;
+    }
     int K;
     // P: operand base of this expert; rows [row0, row_limit) x [0, K) are valid
     __device__ __forceinline__ void init(const bf16_t* P, int ld, int row0, int row_limit, int K_, int lane, int wid) {
         const int valid = min(R, row_limit - row0);
         K = K_;
+        init_kc(lane, wid);
         rsrc = make_rsrc(P + (size_t)row0 * ld, K_ > 0 ? (unsigned)(((size_t)(valid - 1) * ld + K_) * 2) : 0u);
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = wid * NI + j;
             const int row = q * RPI + lane / CPR;
             const int c = (lane % CPR) ^ sw(row);
-            kc[j] = c * 8;
             voff[j] = (unsigned)(row * ld + c * 8) * 2u;
         }
     }
@@ -136,13 +143,13 @@ struct KCTile {
     __device__ __forceinline__ void init_gather(const bf16_t* P, int ld, const int* rows, int row0, int row_limit,
                                                 int n_rows, int K_, int lane, int wid) {
         K = K_;
+        init_kc(lane, wid);
         rsrc = make_rsrc(P, K_ > 0 ? (unsigned)(((size_t)(n_rows - 1) * ld + K_) * 2) : 0u);
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = wid * NI + j;
             const int row = q * RPI + lane / CPR;
             const int c = (lane % CPR) ^ sw(row);
-            kc[j] = c * 8;
             const int src = row0 + row < row_limit ? rows[row0 + row] : -1;
             voff[j] = src >= 0 ? (unsigned)(src * ld + c * 8) * 2u : OOB_OFFSET;
         }
@@ -151,7 +158,7 @@ struct KCTile {
         const int q = wid * NI + j;
         unsigned off = voff[j] + (unsigned)k0 * 2u;
         // only a tile that reaches beyond K (a wave-uniform condition) has lanes to switch off
-        if (k0 + BK > K) off = (k0 + kc[j] < K) ? off : OOB_OFFSET;
+        if (k0 + BK > K) off = (k0 + first_k(j) < K) ? off : OOB_OFFSET;
         load_to_lds(rsrc, lds_address(tile) + q * 1024, off);
     }
     __device__ __forceinline__ void load(char* tile, int k0, int wid) const {
@@ -415,7 +422,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
             if (decode(b, t)) return b;
         return -1;
     };
-    auto bind = [&](const TileCoord& t, AT& ta_, BT& tb_) {
+    auto bind = [&](const TileCoord& t, AT& ta_, BT& tb_, int lane) {
         const bf16_t* A = (const bf16_t*)g.A + (size_t)t.e * g.a_estride;
         const bf16_t* B = (const bf16_t*)g.B + (size_t)t.e * g.b_estride;
         bool gathered = false;
@@ -529,7 +536,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     if (vb < 0) return;
     AT ta;
     BT tb;
-    bind(cur, ta, tb);
+    bind(cur, ta, tb, lane);
     KCursor kc = {0, 0, 0};
     issue_early(cur, kc, ta, tb);
     issue_late(cur, kc, ta, tb);
@@ -537,7 +544,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 
     for (;;) {
         if constexpr (REBIND) {
-            bind(cur, ta, tb);
+            bind(cur, ta, tb, lane);
             if constexpr (LAY == GEMM_TN) { if (g.k_segs > 1) bind_range(cur, kc.seg, ta, tb); }
         }
         const int m0 = cur.m0, n0 = cur.n0, e = cur.e, tn = cur.tn, Mdim = cur.Mdim, KT = cur.KT;
@@ -804,12 +811,20 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 
         // ---- the tile after this one ------------------------------------------------------
         TileCoord nx;
+        // (GeLU-backward has no registers to carry the next tile's offsets through its passes: it forms them where
+        // they are used, from a lane number that the compiler cannot tell from another)
+        constexpr bool LATE_BIND = EPI == EPI_DGELU && C::OCC == 1;
         AT ta2;
         BT tb2;
+        auto bind_again = [&]() __attribute__((always_inline)) {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            bind(nx, ta2, tb2, l);
+        };
         KCursor kc2 = {0, 0, 0};
         const int vn = next_tile(vb + (int)gridDim.x, nx);
         if (vn < 0) nx = cur;                        // (bound all the same, and never used)
-        bind(nx, ta2, tb2);
+        if constexpr (!LATE_BIND) bind(nx, ta2, tb2, lane);
 
         // ---- epilogue -----------------------------------------------------------------------
         // An MFMA accumulator holds one row per lane (row = lane & 31, four consecutive
@@ -900,9 +915,10 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         constexpr int PB = C::OCC == 1 ? 2 : 1;
         PassIn pin[PB];
         if constexpr (READS && PB == 2) request_pass(0, pin[0]);
-        // where a lane's row dots go (the first of a row's lanes writes them)
-        const unsigned dw_lane = c8 == 0 ? (unsigned)((m0 + prow) * g.dw_parts + tn * C::WAVES_N + wn) * 4u : OOB_OFFSET;
-        float dots[TM][NPIECE];                      // its finished rows, where a column block is two waves wide
+        // the row of every 32 whose dot this lane ends up with, and where it goes
+        const int dw_row = RSTEP * (((c8 >> 2) & 1) * 2 + ((c8 >> 1) & 1)) + prow;
+        const unsigned dw_lane = (unsigned)((m0 + dw_row) * g.dw_parts + tn * C::WAVES_N + wn) * 4u;
+        float dots[TM];                              // its finished rows, where a column block is two waves wide
         float dotacc[NPIECE];                        // GeLU-backward: <gelu(Z), G> of a row over the passes of its 32 rows
 #pragma unroll
         for (int ps = 0; ps < NPASS; ++ps) {
@@ -920,7 +936,10 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & 15)) << 2)) = v;
                 }
             }
-            if constexpr (READS && PB == 2) { if (ps + 1 < NPASS) request_pass(ps + 1, pin[(ps + 1) & 1]); }
+            if constexpr (READS && PB == 2) {
+                if (ps + 1 < NPASS) request_pass(ps + 1, pin[(ps + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);   // (the scheduler would sink them to their uses)
+            }
             const PassIn& in = pin[ps & (PB - 1)];
             // all LDS reads of the pass before its arithmetic: one round trip through LDS, not one per piece
             // (float accumulation keeps the old sums of two passes in registers and has none left for that)
@@ -986,17 +1005,6 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     uint4 oa = make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]), pack_bf16x2(a[6], a[7]));
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, od), rC, offC(ps, t), 0, 0);
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, oa), rZ, offZ(ps, t), 0, 0);
-                    if (g.dw_part && ch == NCH - 1) {
-                        // the CPRW lanes of a row are neighbours
-#pragma unroll
-                        for (int off = CPRW / 2; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
-                        if constexpr (WN == DW_COLS) {
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dot), rD, dw_lane,
-                                                                  row_of(ps, t) * g.dw_parts * 4, 0);
-                        } else {
-                            dots[i][t] = dot;        // half a column block: added to the other wave's below
-                        }
-                    }
                 } else if constexpr (EPI == EPI_STORE_F32) {
                     const unsigned ob = unit0(ps);
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, lo[t]), rC, ob + (2 * t) * ustep, 0, 0);
@@ -1010,8 +1018,30 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, o1), rC, ob + (2 * t + 1) * ustep, 0, 0);
                 }
             }
+            if constexpr (EPI == EPI_DGELU) {
+                if (g.dw_part && ch == NCH - 1) {
+                    // The row dots of the 32 rows are spread over the eight lanes of each row in four pieces.  Folding
+                    // the lanes splits the pieces between them (lane c8 ends up with the total of piece dw_t), so that
+                    // four shuffles and one store take the place of twelve and four (large layer: 30 us of a 1230 us
+                    // launch).
+                    static_assert(NPIECE == 4 && CPRW == 8, "four pieces over eight lanes");
+                    const bool up4 = (c8 & 4) != 0, up2 = (c8 & 2) != 0;
+                    const float k0 = (up4 ? dotacc[2] : dotacc[0]) + __shfl_xor(up4 ? dotacc[0] : dotacc[2], 4, 64);
+                    const float k1 = (up4 ? dotacc[3] : dotacc[1]) + __shfl_xor(up4 ? dotacc[1] : dotacc[3], 4, 64);
+                    const float k2 = (up2 ? k1 : k0) + __shfl_xor(up2 ? k0 : k1, 2, 64);
+                    const float dot = k2 + __shfl_xor(k2, 1, 64);
+                    if constexpr (WN == DW_COLS) {
+                        if ((c8 & 1) == 0)
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dot), rD, dw_lane,
+                                                                  block_row(i) * g.dw_parts * 4, 0);
+                    } else {
+                        dots[i] = dot;           // half a column block: added to the other wave's below
+                    }
+                }
+            }
             // the next tile's first operand tiles start their trip once the first pass is through
             // (earlier, and this pass's own reads would have to wait behind them)
+            if constexpr (LATE_BIND) { if (ps == 0) bind_again(); }
             if (ps == 0 && vn >= 0) issue_early(nx, kc2, ta2, tb2);
         }
         if constexpr (EPI == EPI_DGELU && WN != DW_COLS) {
@@ -1019,28 +1049,24 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 // A column block of the row dots is the width of the two neighbouring waves: the right one hands its
                 // rows' sums to the left one through its own staging region, which nobody else touches.
                 static_assert(C::WAVES_N == 2 && 2 * WN == DW_COLS && BN == DW_COLS, "one column block per tile");
-                if (wn == 1 && c8 == 0) {
+                if (wn == 1 && (c8 & 1) == 0) {
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int t = 0; t < NPIECE; ++t) stage[i * 32 + RSTEP * t + prow] = dots[i][t];
+                    for (int i = 0; i < TM; ++i) stage[i * 32 + dw_row] = dots[i];
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                if (wn == 0 && c8 == 0) {
+                if (wn == 0 && (c8 & 1) == 0) {
                     const float* right = stage + 32 * CW;
 #pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int t = 0; t < NPIECE; ++t) {
-                            const int row = i * 32 + RSTEP * t + prow, m = m0 + row_of(i * NCH, t) + prow;
-                            if (m < Mdim) {
-                                float* at = g.dw_part + ((size_t)e * g.Cp + m) * g.dw_parts + tn;
-                                at[0] = dots[i][t] + right[row];
-                                if (tn == tiles_n - 1 && tn + 1 < g.dw_parts) at[1] = 0.0f;     // blocks come in pairs
-                            }
+                    for (int i = 0; i < TM; ++i) {
+                        const int m = m0 + block_row(i) + dw_row;
+                        if (m < Mdim) {
+                            float* at = g.dw_part + ((size_t)e * g.Cp + m) * g.dw_parts + tn;
+                            at[0] = dots[i] + right[i * 32 + dw_row];
+                            if (tn == tiles_n - 1 && tn + 1 < g.dw_parts) at[1] = 0.0f;     // blocks come in pairs
                         }
+                    }
                 }
             }
         }
@@ -1052,6 +1078,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();                // every wave is done with the staging stages
         asm volatile("" ::: "memory");
+        if constexpr (LATE_BIND) bind_again();
         issue_late(nx, kc2, ta2, tb2);
         kc = kc2;
         if constexpr (!REBIND) { ta = ta2; tb = tb2; }
@@ -1173,8 +1200,7 @@ static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, 
            extra * (kt * (c.tail_step + (c.step[lay] - c.tail_step) * share) + c.epi[which] * (0.4 + 0.6 * share));
 }
 static int tile_choice(int lay, int epi, const GemmArgs& a) {
-    int cus = persistent_grid() - (a.free_cus + 7) / 8 * 8;
-    if (cus < 8) cus = 8;
+    const int cus = persistent_grid();               // (units left free change the time of a launch, not its results)
     int best = 0;
     double least = 0.0;
     for (int c = 0; c < (lay == GEMM_TN ? 3 : 4); ++c) {
