@@ -131,11 +131,21 @@ static bool first_backward_dispatch_can_go_early(const Dims& d, const Workspace&
     return true;
 }
 
+// Cross-stream order, left out where everything runs on one stream: its own order already is the order in which
+// the events would be recorded and waited for.  A record and a wait cost about 4 us of the host and a hop between
+// streams 10 us and more of the GPU.
+struct Order {
+    bool one_stream;
+    hipError_t record(hipEvent_t e, hipStream_t s) const { return one_stream ? hipSuccess : hipEventRecord(e, s); }
+    hipError_t wait(hipStream_t s, hipEvent_t e) const { return one_stream ? hipSuccess : hipStreamWaitEvent(s, e, 0); }
+};
+
 static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws,
                           const void* x, const void* Wg, const float* gate_bias, const void* W1, const void* W2,
                           void* y, float* logits, int* topk_idx, float* topk_w, int* slot, int* counts,
                           hipStream_t s0, hipStream_t s1, const Offload* off = nullptr, const void* dy_early = nullptr) {
     const int n = d.n;
+    const Order ord = {s0 == s1 && !off};
     MOE_TRY(get_events(7 * (size_t)n + 2));
     hipEvent_t* evS = g_events.data();
     hipEvent_t* evC = evS + n;
@@ -152,8 +162,8 @@ static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace&
     const int* rows = (d.fuse || d.fcomb) ? (const int*)(ws + w.rows) : nullptr;
     if (rows) MOE_TRY(moe_slot_rows(cfg, slot, (int*)(ws + w.rows), s0));
     if (d.fcomb) MOE_TRY(zero_dropped(d, slot, y, s0));
-    HIP_TRY(hipEventRecord(evFork, s0));
-    HIP_TRY(hipStreamWaitEvent(s1, evFork, 0));
+    HIP_TRY(ord.record(evFork, s0));
+    HIP_TRY(ord.wait(s1, evFork));
 
     auto DIbuf = [&](int p) { return ws + w.DI + w.bufM * (p % w.nDI); };
     auto DObuf = [&](int p) { return w.nDO ? ws + w.DO + w.bufM * (p % w.nDO) : nullptr; };
@@ -164,30 +174,30 @@ static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace&
         if (p < n) {
             // S_p.  A shared T_DI buffer was last read by C_{p-2}; R_{p-2}, already
             // queued on this stream, waited for C_{p-2}.  Its copy to the host must be through too.
-            if (off_di && p >= w.nDI) HIP_TRY(hipStreamWaitEvent(s0, evDIout[p - w.nDI], 0));
+            if (off_di && p >= w.nDI) HIP_TRY(ord.wait(s0, evDIout[p - w.nDI]));
             // (with the gathered first GEMM there is no S kernel: C_p reads T_I through the row map)
             if (!d.fuse) MOE_TRY(moe_dispatch(cfg, p, x, slot, DIbuf(p), nullptr, nullptr, s0));
-            HIP_TRY(hipEventRecord(evS[p], s0));
+            HIP_TRY(ord.record(evS[p], s0));
             if (off_di) {
-                HIP_TRY(hipStreamWaitEvent(off->s2, evS[p], 0));
+                HIP_TRY(ord.wait(off->s2, evS[p]));
                 HIP_TRY(hipMemcpyAsync(off->host + off->DI + w.bufM * p, DIbuf(p), w.bufM, hipMemcpyDeviceToHost, off->s2));
-                HIP_TRY(hipEventRecord(evDIout[p], off->s2));
+                HIP_TRY(ord.record(evDIout[p], off->s2));
             }
             // C_p
-            HIP_TRY(hipStreamWaitEvent(s1, evS[p], 0));
-            if (w.nDO && p >= w.nDO) HIP_TRY(hipStreamWaitEvent(s1, evR[p - w.nDO], 0));   // T_DO buffer free again
-            if (off_z && p >= w.nZ) HIP_TRY(hipStreamWaitEvent(s1, evZout[p - w.nZ], 0));   // T_M buffer copied out
+            HIP_TRY(ord.wait(s1, evS[p]));
+            if (w.nDO && p >= w.nDO) HIP_TRY(ord.wait(s1, evR[p - w.nDO]));   // T_DO buffer free again
+            if (off_z && p >= w.nZ) HIP_TRY(ord.wait(s1, evZout[p - w.nZ]));   // T_M buffer copied out
             // with recomputation T_M is not kept: the activated rows go to the one
             // shared H-wide buffer and the pre-activation is not written at all
             void* Aout = keepZ ? (void*)(ws + w.HT) : (void*)Zbuf(p);
             MOE_TRY(ffn_fwd(d, p, d.fuse ? x : (const void*)DIbuf(p), d.fuse ? rows : nullptr, counts, W1, W2,
                             keepZ ? Zbuf(p) : nullptr, Aout, DObuf(p), s1,
                             d.fcomb ? rows : nullptr, (const float*)(ws + w.slot_w), y));
-            HIP_TRY(hipEventRecord(evC[p], s1));
+            HIP_TRY(ord.record(evC[p], s1));
             if (off_z) {
-                HIP_TRY(hipStreamWaitEvent(off->s2, evC[p], 0));
+                HIP_TRY(ord.wait(off->s2, evC[p]));
                 HIP_TRY(hipMemcpyAsync(off->host + off->Z + w.bufH * p, Zbuf(p), w.bufH, hipMemcpyDeviceToHost, off->s2));
-                HIP_TRY(hipEventRecord(evZout[p], off->s2));
+                HIP_TRY(ord.record(evZout[p], off->s2));
             }
         }
         if (p >= 1) {
@@ -198,16 +208,16 @@ static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace&
                 // finds its event recorded
                 const bool reuse = d.reuse != MOE_REUSE_NONE;
                 MOE_TRY(dispatch_for_backward(cfg, d, w, ws, 0, x, dy_early, slot, w.nDI < n || d.fuse, reuse || d.fcomb, s0));
-                HIP_TRY(hipEventRecord(evS[0], s0));
+                HIP_TRY(ord.record(evS[0], s0));
             }
-            HIP_TRY(hipStreamWaitEvent(s0, evC[p - 1], 0));
+            HIP_TRY(ord.wait(s0, evC[p - 1]));
             if (!d.fcomb) MOE_TRY(moe_combine(cfg, p - 1, DObuf(p - 1), slot, topk_w, y, s0));
-            HIP_TRY(hipEventRecord(evR[p - 1], s0));
+            HIP_TRY(ord.record(evR[p - 1], s0));
         }
     }
     if (off_di || off_z) {                       // the host copies belong to what stream 0 has finished
-        HIP_TRY(hipEventRecord(evCopies, off->s2));
-        HIP_TRY(hipStreamWaitEvent(s0, evCopies, 0));
+        HIP_TRY(ord.record(evCopies, off->s2));
+        HIP_TRY(ord.wait(s0, evCopies));
     }
     return MOE_OK;
 }
@@ -218,6 +228,7 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
                            const float* logits, const int* topk_idx, const int* slot, const int* counts,
                            hipStream_t s0, hipStream_t s1, const Offload* off = nullptr, bool first_dispatch_done = false) {
     const int n = d.n, G = d.G;
+    const Order ord = {s0 == s1 && !off};
     MOE_TRY(get_events(7 * (size_t)n + 2));
     hipEvent_t* evS = g_events.data();        // R'_p done (rows of dy, and of x again, are in place)
     hipEvent_t* evC = evS + n;                // backward GEMMs of p done, weight gradients apart
@@ -245,61 +256,61 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
     // forward left T_DI of every partition in place unless buffers are shared or it never wrote any
     const bool redispatch = !off_di && (w.nDI < n || d.fuse);
 
-    HIP_TRY(hipEventRecord(evFork, s0));
+    HIP_TRY(ord.record(evFork, s0));
     // (whole step with R'_0 already queued: the GEMM stream goes straight on from forward's last GEMM; what its
     // first backward GEMMs touch is ordered by R'_0's event and by the stream itself)
-    if (!first_dispatch_done) HIP_TRY(hipStreamWaitEvent(s1, evFork, 0));
+    if (!first_dispatch_done) HIP_TRY(ord.wait(s1, evFork));
     // copies back into the shared buffers must not overtake the forward GEMMs that still read them
-    if (off_di || off_z) HIP_TRY(hipStreamWaitEvent(off->s2, evFork, 0));
+    if (off_di || off_z) HIP_TRY(ord.wait(off->s2, evFork));
 
     for (int p = 0; p <= n; ++p) {
         if (p < n && !(p == 0 && first_dispatch_done)) {
             // R'_p: rows of dy to the experts.  Their buffer (and the re-dispatched T_DI buffer) was last
             // read by partition p - (number of buffers): by its GEMMs and by the weight-gradient GEMMs of
             // its group, which come last.
-            if (p >= w.ndDO) HIP_TRY(hipStreamWaitEvent(s0, evW[(p - w.ndDO) / G], 0));
-            if (redispatch && p >= w.nDI && w.nDI != w.ndDO) HIP_TRY(hipStreamWaitEvent(s0, evW[(p - w.nDI) / G], 0));
+            if (p >= w.ndDO) HIP_TRY(ord.wait(s0, evW[(p - w.ndDO) / G]));
+            if (redispatch && p >= w.nDI && w.nDI != w.ndDO) HIP_TRY(ord.wait(s0, evW[(p - w.nDI) / G]));
             MOE_TRY(dispatch_for_backward(cfg, d, w, ws, p, x, dy, slot, redispatch, dw_in_gemm, s0));
-            HIP_TRY(hipEventRecord(evS[p], s0));
+            HIP_TRY(ord.record(evS[p], s0));
         }
         if (p < n) {
             if (off_di || off_z) {
                 // what was offloaded comes back into the shared buffers, last read by the GEMMs of p-2
                 // (the copy stream runs in order, so the forward copies are through)
-                if (p >= 2) HIP_TRY(hipStreamWaitEvent(off->s2, evW[p - 2], 0));
+                if (p >= 2) HIP_TRY(ord.wait(off->s2, evW[p - 2]));
                 if (off_di)
                     HIP_TRY(hipMemcpyAsync(DIbuf(p), off->host + off->DI + w.bufM * p, w.bufM, hipMemcpyHostToDevice, off->s2));
                 if (off_z)
                     HIP_TRY(hipMemcpyAsync(Zbuf(p), off->host + off->Z + w.bufH * p, w.bufH, hipMemcpyHostToDevice, off->s2));
-                HIP_TRY(hipEventRecord(evIn[p], off->s2));
-                HIP_TRY(hipStreamWaitEvent(s1, evIn[p], 0));
+                HIP_TRY(ord.record(evIn[p], off->s2));
+                HIP_TRY(ord.wait(s1, evIn[p]));
             }
             // C'_p: everything but the weight gradients
-            HIP_TRY(hipStreamWaitEvent(s1, evS[p], 0));
-            if (p >= 2) HIP_TRY(hipStreamWaitEvent(s1, evD[p - 2], 0));
+            HIP_TRY(ord.wait(s1, evS[p]));
+            if (p >= 2) HIP_TRY(ord.wait(s1, evD[p - 2]));
             MOE_TRY(ffn_bwd_main(d, p, recompute ? 1 : 0, DIbuf(p), Zbuf(p), dDObuf(p), counts, slot_w, W1, W2,
                                  dZbuf(p), dDIbuf(p), dw_in_gemm ? dwpart(p) : nullptr, s1));
-            HIP_TRY(hipEventRecord(evC[p], s1));
+            HIP_TRY(ord.record(evC[p], s1));
             // the weight gradients of a whole group after its last partition (Section III-B's per-partition
             // schedule when G = 1)
             if (p % G == G - 1 || p == n - 1) {
                 const int p0 = p / G * G;
                 MOE_TRY(ffn_wgrad(d, p0, p - p0 + 1, d.overwrite && p0 == 0, DIbuf(p0), Zbuf(p0), dDObuf(p0), dZbuf(p0),
                                   (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s1));
-                HIP_TRY(hipEventRecord(evW[p / G], s1));
+                HIP_TRY(ord.record(evW[p / G], s1));
             }
         }
         if (p >= 1) {
             // S'_{p-1}: gate backward and rows of dDI back to token order
             const int q = p - 1;
-            HIP_TRY(hipStreamWaitEvent(s0, evC[q], 0));
+            HIP_TRY(ord.wait(s0, evC[q]));
             MOE_TRY(moe_gate_bwd(cfg, q, x, logits, topk_idx, slot, dw_in_gemm ? nullptr : dw,
                                  dw_in_gemm ? dwpart(q) : nullptr, dL, dWg, ws + w.gate_scratch, s0));
             MOE_TRY(moe_dispatch_bwd(cfg, q, dDIbuf(q), slot, dL, Wg, dx, s0));
-            HIP_TRY(hipEventRecord(evD[q], s0));
+            HIP_TRY(ord.record(evD[q], s0));
         }
     }
-    HIP_TRY(hipStreamWaitEvent(s0, evW[(n - 1) / G], 0));      // the last weight gradients belong to the step
+    HIP_TRY(ord.wait(s0, evW[(n - 1) / G]));      // the last weight gradients belong to the step
     return MOE_OK;
 }
 
@@ -315,6 +326,9 @@ static moe_status setup(const moe_config* cfg, Dims* d, Workspace* w, void* work
     if (((uintptr_t)workspace & 255) != 0) return MOE_ERR_WORKSPACE;
     *s0 = (hipStream_t)streams[0];
     *s1 = (hipStream_t)streams[1];
+    // One partition is one chain of kernels: a second stream has nothing to run beside it but the last gate kernels
+    // beside weight-gradient GEMMs that leave them no compute unit.
+    if (d->n == 1 && d->free_cus == 0 && !with_host) *s1 = *s0;
     return MOE_OK;
 }
 
