@@ -588,102 +588,91 @@ __device__ __forceinline__ void gate_block_dl(
     }
 }
 
-// One workgroup takes DWG_TOK tokens: first dL of those tokens (to global memory for the
-// dispatch-backward kernel, and to LDS), then part[b][d][e] = sum over the tokens of
-// x[t,d] * dL[t,e] in float FMAs, each thread owning eight columns d.
-template <typename T>
-__global__ __launch_bounds__(PERM_THREADS) void gate_bwd_kernel(
-    const T* __restrict__ x, const float* __restrict__ logits, const int* __restrict__ topk_idx,
-    const int* __restrict__ slot, const float* __restrict__ dw, const float* __restrict__ dw_part, int parts,
-    float* __restrict__ dL, float* __restrict__ part, int t_begin, int t_count, int M, int E, int k, int renorm) {
-    __shared__ __attribute__((aligned(16))) float sdl[DWG_TOK][DWG_LD];
-    __shared__ float sdw[DWG_TOK * 8];
-    const int tl0 = blockIdx.y * DWG_TOK;
-    const int nt = min(DWG_TOK, t_count - tl0);
-    int ids[8];
-    gate_block_ids(ids, topk_idx, t_begin + tl0, nt, k);
-    gate_block_logits(sdl, logits, t_begin + tl0, nt, E);
-    gate_block_dw(sdw, slot, dw, dw_part, parts, t_begin + tl0, nt, k);
-    __syncthreads();
-    gate_block_dl(sdl, sdw, ids, dL, nullptr, 0, t_begin + tl0, tl0, nt, E, k, renorm);
-    __syncthreads();
-    for (int c = threadIdx.x * 8; c < M; c += PERM_THREADS * 8) {
-        for (int e0 = 0; e0 < E; e0 += 16) {
-            const int ne = min(16, E - e0);
-            float acc[8][16];
+// part[s][d][e] = sum over the tokens of chunk s of x[t,d] * dL[t,e] for float32 storage, on
+// v_mfma_f32_32x32x2_f32 (float operands, float accumulation): the tokens are the reduction dimension, lane l
+// holds column l%32 of x (or expert l%32 of dL) at token l/32 of two, so both operands come straight from memory,
+// 128 bytes of a token row per half-wavefront.  A wavefront owns 32 columns, all experts and a chunk of tokens;
+// sixteen tokens are requested while the sixteen before are multiplied.  Bound by latency at small sizes, by HIP
+// events with dL and reduction: 256 tokens x 64 columns x 4 experts 16.5 us, 30.6 as float FMAs with eight columns
+// per thread (eight threads of 256 had columns); 1024 x 512 x 8: 25 against 28.
+typedef float gate_f32x16 __attribute__((ext_vector_type(16)));
+template <int EB>                    // expert blocks of 32: E <= 32*EB
+__global__ __launch_bounds__(PERM_THREADS) void gate_dwg_f32_kernel(
+    const float* __restrict__ x, const float* __restrict__ dL, float* __restrict__ part,
+    int t_begin, int t_count, int M, int E, int S, int TC) {
+    constexpr int U = 8;                          // matrix instructions of two tokens requested together
+    const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+    const int ncb = (M + 31) / 32;
+    const int w = blockIdx.x * PERM_WAVES + (threadIdx.x >> 6);
+    const int cb = w % ncb, s = w / ncb;
+    if (s >= S) return;
+    const int t0 = s * TC, t1 = min(t0 + TC, t_count);
+    const int c = cb * 32 + r;
+    const float* xcol = x + (size_t)t_begin * M + min(c, M - 1);
+    const float* dcol = dL + (size_t)t_begin * E;
+    struct Blk { float x[U], d[U][EB]; };
+    // tokens past the chunk, and experts past the last, contribute zeros through dL; their rows of x are
+    // those of the chunk's last token
+    auto request = [&](Blk& q, int tb) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+        for (int u = 0; u < U; ++u) {
+            const int t = tb + 2 * u + h, tc = min(t, t1 - 1);
+            q.x[u] = xcol[(size_t)tc * M];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][e] = 0.0f;
-            // Four token rows at a time, in two register sets in turn: the next four rows are
-            // requested before the current four are used, with no branch between request and use.
-            // Tokens past the end are clamped to the last one; their rows of sdl are zero.
-            auto request = [&](Raw8<T>* r, int i0) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) r[u].load(x + (size_t)(t_begin + tl0 + min(i0 + u, nt - 1)) * M + c);
-            };
-            auto use = [&](const Raw8<T>* r, int i0) {
-                float xv[4][8];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) r[u].to_float(xv[u]);
-                // the gradients of token u+1 are read from LDS while token u is multiplied
-                float4 g4[2][4];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) g4[0][v] = *reinterpret_cast<const float4*>(&sdl[i0][e0 + 4 * v]);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (u + 1 < 4) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            g4[(u + 1) & 1][v] = *reinterpret_cast<const float4*>(&sdl[i0 + u + 1][e0 + 4 * v]);
-                    }
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const float4 gq = g4[u & 1][v];
-                        const float gd[4] = {gq.x, gq.y, gq.z, gq.w};
-#pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4)
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) acc[q][4 * v + r4] = fmaf(xv[u][q], gd[r4], acc[q][4 * v + r4]);
-                    }
-                }
-            };
-            static_assert(DWG_TOK % 8 == 0, "the loop below walks over sdl in steps of eight rows");
-            Raw8<T> ca[4], cb[4];
-            request(ca, 0);
-            for (int i0 = 0; i0 < nt; i0 += 8) {
-                // (the barriers keep the instruction scheduler from sinking the requests to their uses)
-                request(cb, i0 + 4);
-                __builtin_amdgcn_sched_barrier(0);
-                use(ca, i0);
-                __builtin_amdgcn_sched_barrier(0);
-                request(ca, i0 + 8);
-                __builtin_amdgcn_sched_barrier(0);
-                use(cb, i0 + 4);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            float* out = part + ((size_t)blockIdx.y * M + c) * E + e0;
-            if (ne == 16 && (E & 3) == 0) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        *reinterpret_cast<float4*>(out + (size_t)q * E + 4 * v) =
-                            make_float4(acc[q][4 * v], acc[q][4 * v + 1], acc[q][4 * v + 2], acc[q][4 * v + 3]);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        if (e < ne) out[(size_t)q * E + e] = acc[q][e];
+            for (int eb = 0; eb < EB; ++eb) {
+                const int e = 32 * eb + r;
+                const float v = dcol[(size_t)tc * E + min(e, E - 1)];
+                q.d[u][eb] = (t < t1 && e < E) ? v : 0.0f;
             }
         }
+    };
+    gate_f32x16 acc[EB];
+#pragma unroll
+    for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[eb][q] = 0.0f;
+    auto use = [&](const Blk& q) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb)
+                acc[eb] = __builtin_amdgcn_mfma_f32_32x32x2f32(q.d[u][eb], q.x[u], acc[eb], 0, 0, 0);
+    };
+    Blk ka, kb;
+    request(ka, t0);
+    for (int tb = t0; tb < t1; tb += 4 * U) {
+        // (the barriers keep the instruction scheduler from sinking the requests to their uses)
+        request(kb, tb + 2 * U);
+        __builtin_amdgcn_sched_barrier(0);
+        use(ka);
+        __builtin_amdgcn_sched_barrier(0);
+        request(ka, tb + 4 * U);
+        __builtin_amdgcn_sched_barrier(0);
+        use(kb);                                  // (zeros where the chunk has ended)
+        __builtin_amdgcn_sched_barrier(0);
     }
+    // lane (r, h) holds column r and experts 8*(q/4) + 4*h + q%4 of every block
+    if (c >= M) return;
+    float* out = part + ((size_t)s * M + c) * E;
+#pragma unroll
+    for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int e0 = 32 * eb + 8 * g + 4 * h;
+            if ((E & 3) == 0) {
+                if (e0 < E)
+                    *reinterpret_cast<float4*>(out + e0) =
+                        make_float4(acc[eb][4 * g], acc[eb][4 * g + 1], acc[eb][4 * g + 2], acc[eb][4 * g + 3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (e0 + i < E) out[e0 + i] = acc[eb][4 * g + i];
+            }
+        }
 }
 
-
-// bfloat16 storage: dL of one block of tokens per workgroup, to global memory in float (for the
-// dispatch-backward kernel) and transposed as hi + lo bfloat16 terms (for the kernel below).
+// dL of one block of tokens per workgroup, to global memory in float and, for bfloat16 storage, transposed as
+// hi + lo bfloat16 terms (for the matrix-core kernel below).
 __global__ __launch_bounds__(PERM_THREADS) void gate_dl_kernel(
     const float* __restrict__ logits, const int* __restrict__ topk_idx, const int* __restrict__ slot,
     const float* __restrict__ dw, const float* __restrict__ dw_part, int parts, float* __restrict__ dL,
@@ -713,7 +702,6 @@ __global__ __launch_bounds__(PERM_THREADS) void gate_dl_kernel(
 // need more partial sums, so two it is.)
 constexpr int DWG_CPL = 2;
 typedef __bf16 gate_bf16x8 __attribute__((ext_vector_type(8)));
-typedef float gate_f32x16 __attribute__((ext_vector_type(16)));
 template <int W> struct GateWords;            // W dwords of a token row
 template <> struct GateWords<1> { typedef unsigned type; static __device__ __forceinline__ unsigned word(const unsigned& v, int) { return v; } };
 template <> struct GateWords<2> { typedef uint2 type; static __device__ __forceinline__ unsigned word(const uint2& v, int i) { return i == 0 ? v.x : v.y; } };
@@ -903,6 +891,20 @@ static GateMfmaPlan gate_mfma_plan(const Dims& d) {
     return g;
 }
 
+// Token chunks of the float32 gate-backward: about two wavefronts per SIMD (its loads are four bytes a lane), never
+// more partial sums than the scratch buffer holds, one per DWG_TOK tokens.
+struct GateF32Plan { int ncb, S, TC; };
+static GateF32Plan gate_f32_plan(const Dims& d) {
+    GateF32Plan g;
+    g.ncb = (d.M + 31) / 32;
+    const int blocks = (d.Tp + DWG_TOK - 1) / DWG_TOK;
+    int S = 2048 / g.ncb;
+    S = S < 1 ? 1 : (S > blocks ? blocks : S);
+    g.TC = (blocks + S - 1) / S * DWG_TOK;
+    g.S = (d.Tp + g.TC - 1) / g.TC;
+    return g;
+}
+
 static void launch_dwg_reduce(const Dims& d, int part, const void* scratch, float* dWg, int nblk, hipStream_t s) {
     const int ME = d.M * d.E;
     hipLaunchKernelGGL(gate_dwg_reduce_kernel, dim3((ME + 31) / 32), dim3(256), 0, s,
@@ -933,12 +935,20 @@ static moe_status gate_bwd_t(const Dims& d, int part, const void* x, const float
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     } else {
-        const int nblk = (d.Tp + DWG_TOK - 1) / DWG_TOK;
-        hipLaunchKernelGGL((gate_bwd_kernel<T>), dim3(1, nblk), dim3(PERM_THREADS), 0, s, (const T*)x, logits, idx,
-                           slot, dw, dw_part, parts, dL, (float*)scratch, part * d.Tp, d.Tp, d.M, d.E, d.k, d.renorm);
+        const GateF32Plan g = gate_f32_plan(d);
+        hipLaunchKernelGGL(gate_dl_kernel, dim3((d.Tp + DWG_TOK - 1) / DWG_TOK), dim3(PERM_THREADS), 0, s, logits, idx,
+                           slot, dw, dw_part, parts, dL, (bf16_t*)nullptr, 0, part * d.Tp, d.Tp, d.E, d.k, d.renorm);
         MOE_CHECK_LAUNCH();
-        launch_dwg_reduce(d, part, scratch, dWg, nblk, s);
-        count_launch(LC_OTHER, 2);
+        const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES);
+        if (d.E <= 32)
+            hipLaunchKernelGGL((gate_dwg_f32_kernel<1>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL,
+                               (float*)scratch, part * d.Tp, d.Tp, d.M, d.E, g.S, g.TC);
+        else
+            hipLaunchKernelGGL((gate_dwg_f32_kernel<2>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL,
+                               (float*)scratch, part * d.Tp, d.Tp, d.M, d.E, g.S, g.TC);
+        MOE_CHECK_LAUNCH();
+        launch_dwg_reduce(d, part, scratch, dWg, g.S, s);
+        count_launch(LC_OTHER, 3);
         MOE_CHECK_LAUNCH();
         return MOE_OK;
     }
