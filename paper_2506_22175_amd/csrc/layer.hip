@@ -327,8 +327,12 @@ static moe_status setup(const moe_config* cfg, Dims* d, Workspace* w, void* work
     *s0 = (hipStream_t)streams[0];
     *s1 = (hipStream_t)streams[1];
     // One partition is one chain of kernels: a second stream has nothing to run beside it but the last gate kernels
-    // beside weight-gradient GEMMs that leave them no compute unit.
-    if (d->n == 1 && d->free_cus == 0 && !with_host) *s1 = *s0;
+    // beside weight-gradient GEMMs that leave them no compute unit.  Several small partitions lose more to the hops
+    // between the streams than they gain side by side.  Whole steps, two streams / one: 0.2 GFLOP a partition 1.3-1.5,
+    // 5 GFLOP 1.2, 50-120 GFLOP 1.02-1.07, 412 GFLOP 1.00-1.01, 2.4 and 6.6 TFLOP 0.984 and 0.995; float32 takes about
+    // ten times as long per operation.
+    const double work = 12.0 * (double)d->Tp * d->k * d->M * d->H * (d->dtype == MOE_F32 ? 10.0 : 1.0);
+    if ((d->n == 1 || work < 5e11) && d->free_cus == 0 && !with_host) *s1 = *s0;
     return MOE_OK;
 }
 
