@@ -243,7 +243,8 @@ moe_status moe_dispatch_bwd(const moe_config* cfg, int32_t part, const void* dDI
  * S -> C -> R pipelined over two streams (permutations on streams[0], GEMMs on
  * streams[1]; Section III-B), then the backward pass in the same fashion, under
  * cfg->reuse (Section III-D).  Forks from streams[0] and joins back to it: the
- * caller synchronises streams[0] only.  n_streams must be >= 2 (both may be the
+ * caller synchronises streams[0] only.  A single partition, and several of less than
+ * 5e11 operations each, run on streams[0] alone (unless cfg->gemm_free_cus > 0).  n_streams must be >= 2 (both may be the
  * same stream, which serialises the schedule).
  *   x, dy [T,M]; y, dx [T,M] out; dWg [M,E], dW1 [E,M,H], dW2 [E,H,M] float,
  *   accumulated into (caller zeroes) or, with cfg->grad_overwrite, overwritten;

@@ -1163,8 +1163,8 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
 // counts the rounds of tiles over the workgroups; the times (us) of a 64-k step per layout (NN, NT, TN), of a step of
 // a nearly empty tile, and of an epilogue (store, GeLU, GeLU-backward, float store, float accumulation) were fitted
 // to 516 measured launches in all four shapes (1 to 64 experts of 8 to 8192 rows, dimensions 64 to 8192, even and
-// skewed random loads): the choice is on average 1.3 % slower than the best tile of each launch, 256 x 256
-// throughout 32 % slower.  The host does not know the loads; it takes every expert to have the mean.
+// skewed random loads): the choice is on average 2 % slower than the best tile of each launch, 256 x 256 throughout
+// 32 % slower.  The host does not know the loads; it takes every expert to have the mean.
 struct TileCost { int bm, bn, per_cu; double step[3], tail_step, epi[5]; };
 static constexpr TileCost TILE_COSTS[4] = {
     {256, 256, 1, {1.09, 1.52, 1.48}, 0.85, {3.3, 10.8, 27.0, 11.1, 20.9}},      // CfgW / Cfg4

@@ -17,14 +17,14 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
     E = len(counts)
     cfg = B.make_config(E * Cp, M, H, E, 1, 1.0, 1, B.MOE_BF16 if dtype == "bf16" else B.MOE_F32, 0, overwrite)
     assert B.moe_capacity(cfg) == Cp
-    g = torch.Generator().manual_seed(seed)
     d = "cuda:0"
-    x = torch.randn((E * Cp, M), generator=g).to(dt)
-    dy = torch.randn((E * Cp, M), generator=g).to(dt)
-    W1 = (torch.randn((E, M, H), generator=g) * 0.05).to(dt)
-    W2 = (torch.randn((E, H, M), generator=g) * 0.05).to(dt)
-    w = torch.rand((E * Cp,), generator=g) * 0.5 + 0.1
-    old1, old2 = torch.randn((E, M, H), generator=g), torch.randn((E, H, M), generator=g)
+    g = torch.Generator(d).manual_seed(seed)
+    x = torch.randn((E * Cp, M), generator=g, device=d).to(dt)
+    dy = torch.randn((E * Cp, M), generator=g, device=d).to(dt)
+    W1 = (torch.randn((E, M, H), generator=g, device=d) * 0.05).to(dt)
+    W2 = (torch.randn((E, H, M), generator=g, device=d) * 0.05).to(dt)
+    w = torch.rand((E * Cp,), generator=g, device=d) * 0.5 + 0.1
+    old1, old2 = torch.randn((E, M, H), generator=g, device=d), torch.randn((E, H, M), generator=g, device=d)
     for e in range(E):
         for t in (x, dy):
             t[e * Cp + counts[e]:(e + 1) * Cp] = float("nan")
@@ -33,19 +33,20 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
     Z, A, DO, dZ, dDI = nan(E * Cp, H), nan(E * Cp, H), nan(E * Cp, M), nan(E * Cp, H), nan(E * Cp, M)
     parts = B.moe_dw_parts(cfg)
     dw_part = nan(E * Cp, parts, dtype=torch.float32)
-    dW1, dW2 = (nan(E, M, H, dtype=torch.float32), nan(E, H, M, dtype=torch.float32)) if overwrite else (old1.to(d), old2.to(d))
+    dW1, dW2 = (nan(E, M, H, dtype=torch.float32), nan(E, H, M, dtype=torch.float32)) if overwrite else (old1.to(d, copy=True), old2.to(d, copy=True))
     c = torch.tensor([counts], dtype=torch.int32, device=d)
     xd, dyd, W1d, W2d, wd = (t.to(d) for t in (x, dy, W1, W2, w))
     B.moe_expert_ffn_fwd(cfg, 0, xd, c, W1d, W2d, None if recompute else Z, A, DO)
     B.moe_expert_ffn_bwd(cfg, 0, int(recompute), xd, Z, dyd, c, wd, W1d, W2d, dZ, dDI, dW1, dW2, dw_part)
     torch.cuda.synchronize()
-    got = {n: t.double().cpu() for n, t in (("DO", DO), ("dDI", dDI), ("dW1", dW1), ("dW2", dW2))}
-    got["dw"] = dw_part.double().cpu().sum(1)
+    got = {n: t.double() for n, t in (("DO", DO), ("dDI", dDI), ("dW1", dW1), ("dW2", dW2))}
+    got["dw"] = dw_part.double().sum(1)
+    old1, old2 = old1.to(d), old2.to(d)
     ref = {n: torch.full_like(t, float("nan")) for n, t in got.items()}
     for e in range(E):
         q = slice(e * Cp, e * Cp + counts[e])
-        xe, dye, we = x[q].double(), dy[q].double(), w[q].double()[:, None]
-        w1, w2 = W1[e].double(), W2[e].double()
+        xe, dye, we = xd[q].double(), dyd[q].double(), wd[q].double()[:, None]
+        w1, w2 = W1d[e].double(), W2d[e].double()
         z = xe @ w1
         cdf = 0.5 * (1 + torch.erf(z / math.sqrt(2)))
         a = z * cdf
@@ -61,6 +62,17 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
             assert bool(torch.isnan(got[n][~live]).all()), n + ": a padding row was written"
         err = (got[n][live] - ref[n][live]).abs().max() / ref[n][live].abs().max()
         assert err <= TOL[dtype], (n, float(err))
+
+
+# sizes that the larger bfloat16 tiles are chosen for (256 x 128 and 256 x 256 beside the small ones), with last
+# tile rows of one row, of a few blocks of 64, of half a tile and one row more, and full ones
+@pytest.mark.parametrize("M,H,counts,Cp", [
+    (1024, 4096, (1024, 1023, 897, 896, 641, 129, 64, 0), 1024),
+    (1024, 4096, (1024, 1025, 960, 1088, 1153, 1152, 897, 0), 1160),
+    (520, 4104, (4096, 4097, 4225, 4224), 4300),
+], ids=["half_size", "last_rows", "whole"])
+def test_expert_ffn_in_large_tiles(M, H, counts, Cp):
+    _run("bf16", M, H, counts, Cp, 5, 0, 0)
 
 
 @pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
