@@ -861,7 +861,9 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         struct PassIn { uint4 zin[NPIECE]; float4 cin0[NPIECE], cin1[NPIECE]; float wrow[NPIECE]; int crow[NPIECE]; };
         // Piece t of a lane: row RSTEP*t + prow of the pass, columns 8*c8 .. 8*c8 + 7.  Addresses are one vector
         // offset per column block (out of range: past the descriptor, and it stays there with any step added) and a
-        // scalar step per pass and piece.
+        // wave-uniform step per pass and piece, added to the vector offset.  (Not handed over as the scalar offset of
+        // the access: that one is no part of the bounds check, and a step beyond the last valid row, as in every last
+        // tile row, would reach whatever lies behind.)
         constexpr int RSTEP = 64 / CPRW;
         const int prow = lane / CPRW, c8 = lane % CPRW;
         unsigned baseC[NCH], baseZ[NCH];
@@ -884,9 +886,10 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         // 64 lanes of one store (or load) cover whole rows of the pass - 4 columns per lane, CW/4 lanes per row - so
         // that every such instruction moves whole 128-byte lines (8 columns per lane would leave each instruction
         // with every other 16 bytes).  Unit u of a lane is UROWS*u rows below its unit 0, in the same columns: one
-        // vector offset per pass and a constant step.  (The stores take the step in the vector offset: behind a
-        // 16-byte store with a scalar offset register the compiler may overwrite the store's data registers in the
-        // very next instruction, and then the last lanes of the store have been seen to write the new contents.)
+        // vector offset per pass and a constant step, in the vector offset as above.  (For the stores there is a
+        // second reason: behind a 16-byte store with a scalar offset register the compiler may overwrite the store's
+        // data registers in the very next instruction, and then the last lanes of the store have been seen to write
+        // the new contents.)
         constexpr int ULANES = CW / 4, UROWS = 64 / ULANES;
         const int urow = lane / ULANES, uc4 = lane % ULANES;
         auto unit0 = [&](int ps) -> unsigned {
@@ -899,15 +902,15 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 #pragma unroll
             for (int t = 0; t < NPIECE; ++t) {
                 if constexpr (EPI == EPI_DGELU)
-                    in.zin[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rZ, baseZ[ps % NCH], (row_of(ps, t) * g.ldz) * 2, 0));
+                    in.zin[t] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rZ, offZ(ps, t), 0, 0));
                 if constexpr (EPI == EPI_DGELU || EPI == EPI_SCATTER)
-                    in.wrow[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rW, row4, row_of(ps, t) * 4, 0));
+                    in.wrow[t] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rW, row4 + row_of(ps, t) * 4, 0, 0));
                 if constexpr (EPI == EPI_SCATTER)
-                    in.crow[t] = (int)__builtin_amdgcn_raw_buffer_load_b32(rR, row4, row_of(ps, t) * 4, 0);
+                    in.crow[t] = (int)__builtin_amdgcn_raw_buffer_load_b32(rR, row4 + row_of(ps, t) * 4, 0, 0);
                 if constexpr (EPI == EPI_ACCUM_F32) {
                     const unsigned ob = unit0(ps);
-                    in.cin0[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rC, ob, (2 * t) * ustep, 0));
-                    in.cin1[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rC, ob, (2 * t + 1) * ustep, 0));
+                    in.cin0[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rC, ob + (2 * t) * ustep, 0, 0));
+                    in.cin1[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rC, ob + (2 * t + 1) * ustep, 0, 0));
                 }
             }
         };
@@ -1032,8 +1035,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                     const float dot = k2 + __shfl_xor(k2, 1, 64);
                     if constexpr (WN == DW_COLS) {
                         if ((c8 & 1) == 0)
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dot), rD, dw_lane,
-                                                                  block_row(i) * g.dw_parts * 4, 0);
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, dot), rD,
+                                                                  dw_lane + block_row(i) * g.dw_parts * 4, 0, 0);
                     } else {
                         dots[i] = dot;           // half a column block: added to the other wave's below
                     }

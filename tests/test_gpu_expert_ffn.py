@@ -32,7 +32,8 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
     nan = lambda *s, dtype=dt: torch.full(s, float("nan"), dtype=dtype, device=d)  # noqa: E731
     Z, A, DO, dZ, dDI = nan(E * Cp, H), nan(E * Cp, H), nan(E * Cp, M), nan(E * Cp, H), nan(E * Cp, M)
     parts = B.moe_dw_parts(cfg)
-    dw_part = nan(E * Cp, parts, dtype=torch.float32)
+    dw_part_and_behind = nan(E * Cp + 256, parts, dtype=torch.float32)      # a tile is at most 256 rows high
+    dw_part = dw_part_and_behind[:E * Cp]
     dW1, dW2 = (nan(E, M, H, dtype=torch.float32), nan(E, H, M, dtype=torch.float32)) if overwrite else (old1.to(d, copy=True), old2.to(d, copy=True))
     c = torch.tensor([counts], dtype=torch.int32, device=d)
     xd, dyd, W1d, W2d, wd = (t.to(d) for t in (x, dy, W1, W2, w))
@@ -41,6 +42,10 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
     torch.cuda.synchronize()
     got = {n: t.double() for n, t in (("DO", DO), ("dDI", dDI), ("dW1", dW1), ("dW2", dW2))}
     got["dw"] = dw_part.double().sum(1)
+    kept = torch.zeros((E * Cp + 256,), dtype=torch.bool, device=d)
+    for e in range(E):
+        kept[e * Cp:e * Cp + counts[e]] = True
+    assert bool(torch.isnan(dw_part_and_behind[~kept]).all()), "row dots of a padding row, or past the buffer, were written"
     old1, old2 = old1.to(d), old2.to(d)
     ref = {n: torch.full_like(t, float("nan")) for n, t in got.items()}
     for e in range(E):
@@ -73,6 +78,14 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
 ], ids=["half_size", "last_rows", "whole"])
 def test_expert_ffn_in_large_tiles(M, H, counts, Cp):
     _run("bf16", M, H, counts, Cp, 5, 0, 0)
+
+
+# experts smaller than the 256 x 256 tile that they are multiplied in: the tile's last rows belong to the experts
+# behind (the last expert's to nobody), whichever rows of theirs hold something
+@pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
+def test_expert_ffn_with_experts_smaller_than_their_tile(recompute, overwrite):
+    counts = tuple([1, 10, 64, 65, 0, 127, 128, 140] + [129 + 5 * e % 12 for e in range(55)] + [129])
+    _run("bf16", 768, 3072, counts, 140, 7, recompute, overwrite)
 
 
 @pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
