@@ -233,9 +233,9 @@ moe_status moe_expert_ffn_fwd_gather(const moe_config* cfg, int32_t part, const 
 
 /* Dispatch backward S' of partition `part`:
  * dx[t] = sum over kept j of dDI[slot[t,j]] + dL[t,:] Wg^T.   dx [T,M] out.
- * Float accumulation; for bfloat16 storage the gate term runs on the matrix cores
- * with dL carried as the sum of two bfloat16 numbers (16 bits of its mantissa), for
- * float32 storage as float multiply-adds. */
+ * Float accumulation; for bfloat16 storage and E <= 16 the gate term runs on the
+ * matrix cores with dL carried as the sum of two bfloat16 numbers (16 bits of its
+ * mantissa), otherwise as float multiply-adds. */
 moe_status moe_dispatch_bwd(const moe_config* cfg, int32_t part, const void* dDI, const int32_t* slot,
                             const float* dL, const void* Wg, void* dx, void* stream);
 

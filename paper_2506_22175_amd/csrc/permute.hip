@@ -270,10 +270,13 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(
 // B_b[k][j] = Wg[column of lane 4b+j][expert 4g+k], one instruction per column and expert
 // group gives a lane the gate term of four tokens at one of its columns, at 1/8 of the issue
 // slots of float FMAs.  dL is split into two bfloat16 terms (hi + lo), which keeps 16 bits of
-// its mantissa; Wg is bfloat16 already.  Up to 64 experts: a slice of the gate weights is at most 65 KB, so
-// that two workgroups still fit a CU (4096 tokens x 768 columns x 64 experts: 16.4 us, 1065 with the weights
-// read from memory again for every token; 776 columns x 6 experts x 1001 tokens: 22.4 -> 11.0 by the number
-// of tokens per group).  The kernel is bound by the latency of its row reads,
+// its mantissa; Wg is bfloat16 already.  With more than sixteen experts the products are float ones, all of
+// dL's bits and its infinities included: v_mfma_f32_4x4x1_16B_f32, the same blocks with one expert per
+// instruction and the weights widened when they are read (4096 tokens x 768 columns x 64 experts, launches back to
+// back: 16.5 us, 11.5 with the two terms; 16384 x 2048 x 64: 97 and 68).  Up to 64 experts: a slice of the gate
+// weights is at most 65 KB, so that two workgroups still fit a CU (the former: 1065 us with the weights read from
+// memory again for every token; 776 columns x 6 experts x 1001 tokens: 22.4 -> 11.0
+// by the number of tokens per group).  The kernel is bound by the latency of its row reads,
 // so it is built for many wavefronts: the gate weights stay in LDS (read again every round)
 // rather than in 64 registers, which lets four wavefronts per SIMD run.
 typedef short bf16x4_hw __attribute__((ext_vector_type(4)));
@@ -313,6 +316,7 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(
     // gate gradients of this lane's token (tb + lane%4) for the A operand, expert groups g0 .. g0 + GC - 1:
     // with more than sixteen experts they come in pieces, so that they never hold more than sixteen registers
     constexpr int GC = EG < 4 ? EG : 4;
+    constexpr bool SPLIT = EG <= 4;                // dL as two bfloat16 terms (else float products)
     auto request_dl = [&](int tb, int g0, float4 (&dl)[GC]) __attribute__((always_inline)) {
         const int ta = tb + (lane & 3);
 #pragma unroll
@@ -379,26 +383,39 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(
         asm volatile("" : "+v"(my_off));
 #pragma unroll 1
         for (int g0 = 0; g0 < EG; g0 += GC) {
+            float v[GC][4];
             bf16x4_hw a_hi[GC], a_lo[GC];
 #pragma unroll
             for (int gi = 0; gi < GC; ++gi) {
-                const float v[4] = {dl[gi].x, dl[gi].y, dl[gi].z, dl[gi].w};
+                v[gi][0] = dl[gi].x; v[gi][1] = dl[gi].y; v[gi][2] = dl[gi].z; v[gi][3] = dl[gi].w;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const bf16_t h = f32_to_bf16(v[r]);
+                    const bf16_t h = f32_to_bf16(v[gi][r]);
                     a_hi[gi][r] = (short)h;
-                    a_lo[gi][r] = (short)f32_to_bf16(v[r] - bf16_to_f32(h));
+                    a_lo[gi][r] = (short)f32_to_bf16(v[gi][r] - bf16_to_f32(h));
                 }
             }
             if (g0 + GC < EG) request_dl(tb, g0 + GC, dl);     // on its way while this piece is multiplied
 #pragma unroll
-            for (int gi = 0; gi < GC; ++gi)
+            for (int gi = 0; gi < GC; ++gi) {
+                bf16x4_hw w[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bf16x4_hw w = *reinterpret_cast<const bf16x4_hw*>(dxm_smem + my_off + (i * EG + g0 + gi) * 8);
-                    gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi[gi], w, gate[i], 0, 0, 0);
-                    gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo[gi], w, gate[i], 0, 0, 0);
+                for (int i = 0; i < 8; ++i)
+                    w[i] = *reinterpret_cast<const bf16x4_hw*>(dxm_smem + my_off + (i * EG + g0 + gi) * 8);
+                if constexpr (SPLIT) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi[gi], w[i], gate[i], 0, 0, 0);
+                        gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo[gi], w[i], gate[i], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int i = 0; i < 8; ++i)
+                            gate[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(v[gi][r], bf16_to_f32((bf16_t)w[i][r]), gate[i], 0, 0, 0);
                 }
+            }
         }
         float acc[4][8];
 #pragma unroll
