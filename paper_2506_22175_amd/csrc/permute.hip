@@ -628,13 +628,14 @@ __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_f32_kernel(
     const float* xcol = x + (size_t)t_begin * M + min(c, M - 1);
     const float* dcol = dL + (size_t)t_begin * E;
     struct Blk { float x[U], d[U][EB]; };
-    // tokens past the chunk, and experts past the last, contribute zeros through dL; their rows of x are
-    // those of the chunk's last token
+    // tokens past the chunk contribute zeros in both operands (the last token's row instead, times zero, would turn
+    // its infinities into NaN); experts past the last have result rows of their own, which are not stored
     auto request = [&](Blk& q, int tb) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int t = tb + 2 * u + h, tc = min(t, t1 - 1);
-            q.x[u] = xcol[(size_t)tc * M];
+            const float xv = xcol[(size_t)tc * M];
+            q.x[u] = t < t1 ? xv : 0.0f;
 #pragma unroll
             for (int eb = 0; eb < EB; ++eb) {
                 const int e = 32 * eb + r;
