@@ -1232,8 +1232,10 @@ moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStr
     if (a.dw_part && a.dw_parts != gemm_bf16_dw_parts(a.N)) return MOE_ERR_SHAPE;
     // operand rows must be 16-byte aligned in memory
     if ((a.lda | a.ldb) & 7) return MOE_ERR_UNSUPPORTED;
-    // buffer offsets are 32-bit: an expert's operand must stay below 2 GiB
-    const long long ldmax = a.lda > a.ldb ? a.lda : a.ldb;
+    // buffer offsets are 32-bit: an expert's operands, and its rows of a bfloat16 output, must stay below 2 GiB
+    // (rows of two to four million elements would also take the epilogue's row steps past 2^32)
+    long long ldmax = a.lda > a.ldb ? a.lda : a.ldb;
+    if (epi != EPI_ACCUM_F32 && epi != EPI_STORE_F32 && epi != EPI_SCATTER && a.ldc > ldmax) ldmax = a.ldc;
     const long long rmax = a.Cp > a.K ? a.Cp : a.K;
     if ((rmax + 8 * 64) * ldmax * 2 >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
     if (a.k_segs > 1 && (lay != GEMM_TN || a.k_segs > MAX_KSEGS)) return MOE_ERR_UNSUPPORTED;

@@ -71,6 +71,16 @@ def test_argument_errors_are_status_codes():
     assert B.status_string(4) == "workspace too small"
 
 
+def test_oversized_rows_are_refused_before_anything_is_launched():
+    """Rows too long for 32-bit offsets: backward's first GEMM already says so (its operands are narrow, its output
+    is not), where there is no GPU as well; nothing is launched, so the pointers are never read."""
+    cfg = B.make_config(8, 8, 6_000_000, 1, 1, 1.0)
+    p = ctypes.c_void_p(4096)
+    before = B.moe_launch_counts()
+    assert B.lib().moe_expert_ffn_bwd(ctypes.byref(cfg), 0, 0, *([p] * 11), None, None) == 3
+    assert B.moe_launch_counts() == before
+
+
 def test_workspace_follows_the_memory_model(oracle):
     """saved bytes = the paper's shared-buffer bookkeeping (Section III-D) in elements
     times the element size, up to 256-byte alignment of each buffer."""
