@@ -844,15 +844,19 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         constexpr int NPASS = TM * NCH;
         float* stage = reinterpret_cast<float*>(smem + C::STAGING_OFF + wid * (32 * CW * 4));
         constexpr int CES = (EPI == EPI_ACCUM_F32 || EPI == EPI_STORE_F32) ? 4 : 2;   // bytes per output element
+        // The descriptors begin at the tile's first row: an expert's float gradients may exceed 2 GiB, and offset
+        // OOB_OFFSET would then be an element of theirs.
         // (scattered rows: the whole output matrix, every row of which some tile may write)
-        const char* Cbase = EPI == EPI_SCATTER ? (const char*)g.C : (const char*)g.C + (size_t)e * g.c_estride * CES;
+        const int trows = min(BM, Mdim - m0);
+        const char* Cbase = EPI == EPI_SCATTER ? (const char*)g.C
+                                               : (const char*)g.C + ((size_t)e * g.c_estride + (size_t)m0 * g.ldc) * CES;
         const __amdgpu_buffer_rsrc_t rC = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char*>(Cbase), 0,
-            (unsigned)(((size_t)((EPI == EPI_SCATTER ? g.c_row_limit : Mdim) - 1) * g.ldc + g.N) * CES), 0x00020000);
+            (unsigned)(((size_t)((EPI == EPI_SCATTER ? g.c_row_limit : trows) - 1) * g.ldc + g.N) * CES), 0x00020000);
         const int* crows = g.c_rows ? g.c_rows + (size_t)e * g.Cp : nullptr;
-        const bf16_t* Zbase = g.Z ? (const bf16_t*)g.Z + (size_t)e * g.Cp * g.ldz : nullptr;
+        const bf16_t* Zbase = g.Z ? (const bf16_t*)g.Z + ((size_t)e * g.Cp + m0) * g.ldz : nullptr;
         const __amdgpu_buffer_rsrc_t rZ = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<bf16_t*>(Zbase), 0, Zbase ? (unsigned)(((size_t)(Mdim - 1) * g.ldz + g.N) * 2) : 0u, 0x00020000);
+            const_cast<bf16_t*>(Zbase), 0, Zbase ? (unsigned)(((size_t)(trows - 1) * g.ldz + g.N) * 2) : 0u, 0x00020000);
         const float* wbase = g.slot_w ? g.slot_w + (size_t)e * g.Cp : nullptr;
         const int erow = lane & 31, ehalf = lane >> 5;
         // What a pass reads from memory (the pre-activation and row weight for GeLU-backward, the old
@@ -870,8 +874,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
             const int n = n0 + wn * WN + ch * CW + c8 * 8;
-            baseC[ch] = n < g.N ? (unsigned)((m0 + prow) * g.ldc + n) * CES : OOB_OFFSET;
-            baseZ[ch] = n < g.N ? (unsigned)((m0 + prow) * g.ldz + n) * 2u : OOB_OFFSET;
+            baseC[ch] = n < g.N ? (unsigned)(prow * g.ldc + n) * CES : OOB_OFFSET;
+            baseZ[ch] = n < g.N ? (unsigned)(prow * g.ldz + n) * 2u : OOB_OFFSET;
         }
         auto row_of = [&](int ps, int t) __attribute__((always_inline)) { return block_row(ps / NCH) + RSTEP * t; };   // wave-uniform
         auto offC = [&](int ps, int t) __attribute__((always_inline)) { return baseC[ps % NCH] + (unsigned)(row_of(ps, t) * g.ldc) * CES; };
@@ -893,9 +897,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         constexpr int ULANES = CW / 4, UROWS = 64 / ULANES;
         const int urow = lane / ULANES, uc4 = lane % ULANES;
         auto unit0 = [&](int ps) -> unsigned {
-            const int m = m0 + block_row(ps / NCH) + urow;
             const int n = n0 + wn * WN + (ps % NCH) * CW + uc4 * 4;
-            return n < g.N ? (unsigned)(m * g.ldc + n) * 4u : OOB_OFFSET;
+            return n < g.N ? (unsigned)((block_row(ps / NCH) + urow) * g.ldc + n) * 4u : OOB_OFFSET;
         };
         const unsigned ustep = (unsigned)(UROWS * g.ldc) * 4u;      // bytes from one unit of a lane to the next
         auto request_pass = [&](int ps, PassIn& in) {

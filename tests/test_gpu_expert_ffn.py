@@ -80,6 +80,13 @@ def test_expert_ffn_in_large_tiles(M, H, counts, Cp):
     _run("bf16", M, H, counts, Cp, 5, 0, 0)
 
 
+# float gradients of more than 2 GiB per expert, with columns that end inside a tile: the offset that stands for "out
+# of range" is then smaller than the gradients (the reference takes some 40 GB)
+@pytest.mark.parametrize("overwrite", [0, 1])
+def test_expert_ffn_with_gradients_above_two_gib(overwrite):
+    _run("bf16", 24008, 24008, (5,), 8, 3, 0, overwrite)
+
+
 # experts smaller than the 256 x 256 tile that they are multiplied in: the tile's last rows belong to the experts
 # behind (the last expert's to nobody), whichever rows of theirs hold something
 @pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
