@@ -207,7 +207,7 @@ def measure(args, workload, n, reuse, steps, warmup, brief=False, fuse=0, group=
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": shape.dtype,
         "data": "synthetic",
         "config": {"workload": f"{shape.name}: T={T} M={M} H={H} E={shape.E} k={k} cf={shape.capacity_factor}",
-                   "n_partitions": n, "reuse_mode": reuse, "streams": 1 if args.single_stream else 2,
+                   "n_partitions": n, "reuse_mode": reuse, "streams": 1 if args.single_stream else B.moe_layer_streams(st.cfg),
                    "hip_graph": bool(args.graph), "fuse_gather": int(fuse), "wgrad_group": int(group),
                    "weight_grads": "accumulated into zeroed buffers" if args.accumulate else "overwritten each step",
                    "kept_rows": R, "drop_rate": drop_rate},
@@ -363,8 +363,8 @@ def main():
         out["interference_and_cost_model"] = {
             "per_free_cus": itf, "model": model,
             "note": "alone = whole schedule on one stream, GEMMs on every compute unit; side_by_side = two streams "
-                    "with free_cus units left to the permutations; sigma, mu = time alone / time side by side. "
-                    "At free_cus = 0 mu is the time a permutation waits for a unit, not a co-run slowdown; the "
+                    "with free_cus units left to the permutations; sigma, mu = time alone / time side by side "
+                    "(null where the work is too small for a second stream). At free_cus = 0 mu is the time a permutation waits for a unit, not a co-run slowdown; the "
                     "model takes sigma and mu from the best free_cus > 0",
             "this_run": {"strategy": {0: "none", 2: "S4"}.get(args.reuse, "mode 1 (no row in Table II)"),
                          "measured_step_ms": out["ms_per_step"]}}

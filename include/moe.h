@@ -243,9 +243,10 @@ moe_status moe_dispatch_bwd(const moe_config* cfg, int32_t part, const void* dDI
  * S -> C -> R pipelined over two streams (permutations on streams[0], GEMMs on
  * streams[1]; Section III-B), then the backward pass in the same fashion, under
  * cfg->reuse (Section III-D).  Forks from streams[0] and joins back to it: the
- * caller synchronises streams[0] only.  A single partition, and several of less than
- * 5e11 operations each, run on streams[0] alone (unless cfg->gemm_free_cus > 0).  n_streams must be >= 2 (both may be the
- * same stream, which serialises the schedule).
+ * caller synchronises streams[0] only.  n_streams must be >= 2 (both may be the same
+ * stream, which serialises the schedule).  Small work runs on streams[0] alone, see
+ * moe_layer_streams: streams[1] is then not touched, and what is queued on it is not
+ * waited for.
  *   x, dy [T,M]; y, dx [T,M] out; dWg [M,E], dW1 [E,M,H], dW2 [E,H,M] float,
  *   accumulated into (caller zeroes) or, with cfg->grad_overwrite, overwritten;
  *   logits [T,E], topk_idx, topk_w, slot
@@ -256,6 +257,15 @@ moe_status moe_layer_step(const moe_config* cfg, const void* x, const void* dy,
                           float* logits, int32_t* topk_idx, float* topk_w, int32_t* slot, int32_t* counts,
                           void* workspace, size_t workspace_bytes,
                           void* const* streams, int32_t n_streams);
+
+/* Host only.  How many of the streams handed over moe_layer_step, _forward, _backward and
+ * the searches below use for cfg, at least two distinct ones given:
+ *   1  a single partition, or 12 * T_p * k * M * H < 5e11 (< 5e10 for MOE_F32, whose
+ *      operations take ten times as long; the capacity does not enter), unless
+ *      cfg->gemm_free_cus > 0;
+ *   2  otherwise;
+ *   3  always for S1..S3 (moe_layer_step_offload). */
+moe_status moe_layer_streams(const moe_config* cfg, int32_t* streams);
 
 /* moe_layer_step for the offloading strategies (cfg->reuse = MOE_REUSE_S1..S3; Section
  * III-D, Table II).  host_buffer: pinned host memory (hipHostMalloc) of at least

@@ -28,7 +28,7 @@ EXPORTS = [
     "moe_last_error", "moe_profile_enable", "moe_profile_read",
     "moe_gran_create", "moe_gran_destroy", "moe_gran_lookup", "moe_gran_record", "moe_gran_ranges",
     "moe_search_best_gran", "moe_gran_get", "moe_strategy_cost", "moe_select_strategy",
-    "moe_offload_bytes", "moe_layer_step_offload",
+    "moe_offload_bytes", "moe_layer_step_offload", "moe_layer_streams",
 ]
 
 
@@ -131,6 +131,12 @@ def moe_gate_scratch_bytes(cfg: MoEConfig) -> int:
 def moe_dw_parts(cfg: MoEConfig) -> int:
     v = ctypes.c_int32(0)
     _check(lib().moe_dw_parts(_cfg(cfg), ctypes.byref(v)), "moe_dw_parts")
+    return v.value
+
+
+def moe_layer_streams(cfg: MoEConfig) -> int:
+    v = ctypes.c_int32(0)
+    _check(lib().moe_layer_streams(_cfg(cfg), ctypes.byref(v)), "moe_layer_streams")
     return v.value
 
 

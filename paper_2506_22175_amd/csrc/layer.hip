@@ -314,6 +314,17 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
     return MOE_OK;
 }
 
+// How many of the caller's streams a schedule uses.  One partition is one chain of kernels: a second stream has
+// nothing to run beside it but the last gate kernels beside weight-gradient GEMMs that leave them no compute unit.
+// Several small partitions lose more to the hops between the streams than they gain side by side.  Whole steps, two
+// streams / one: 0.2 GFLOP a partition 1.3-1.5, 5 GFLOP 1.2, 50-120 GFLOP 1.02-1.07, 412 GFLOP 1.00-1.01, 2.4 and 6.6
+// TFLOP 0.984 and 0.995; float32 takes about ten times as long per operation.
+static int streams_used(const Dims& d) {
+    if (mode_offloads(d.reuse)) return 3;
+    const double work = 12.0 * (double)d.Tp * d.k * d.M * d.H * (d.dtype == MOE_F32 ? 10.0 : 1.0);
+    return (d.n == 1 || work < 5e11) && d.free_cus == 0 ? 1 : 2;
+}
+
 static moe_status setup(const moe_config* cfg, Dims* d, Workspace* w, void* workspace, size_t workspace_bytes,
                         void* const* streams, int n_streams, hipStream_t* s0, hipStream_t* s1,
                         bool with_host = false) {
@@ -326,13 +337,7 @@ static moe_status setup(const moe_config* cfg, Dims* d, Workspace* w, void* work
     if (((uintptr_t)workspace & 255) != 0) return MOE_ERR_WORKSPACE;
     *s0 = (hipStream_t)streams[0];
     *s1 = (hipStream_t)streams[1];
-    // One partition is one chain of kernels: a second stream has nothing to run beside it but the last gate kernels
-    // beside weight-gradient GEMMs that leave them no compute unit.  Several small partitions lose more to the hops
-    // between the streams than they gain side by side.  Whole steps, two streams / one: 0.2 GFLOP a partition 1.3-1.5,
-    // 5 GFLOP 1.2, 50-120 GFLOP 1.02-1.07, 412 GFLOP 1.00-1.01, 2.4 and 6.6 TFLOP 0.984 and 0.995; float32 takes about
-    // ten times as long per operation.
-    const double work = 12.0 * (double)d->Tp * d->k * d->M * d->H * (d->dtype == MOE_F32 ? 10.0 : 1.0);
-    if ((d->n == 1 || work < 5e11) && d->free_cus == 0 && !with_host) *s1 = *s0;
+    if (streams_used(*d) == 1) *s1 = *s0;
     return MOE_OK;
 }
 
@@ -350,6 +355,14 @@ extern "C" moe_status moe_workspace_bytes(const moe_config* cfg, size_t* total, 
     if (saved) *saved = w.saved;
     if (temp) *temp = w.temp;
     if (routing) *routing = w.routing;
+    return MOE_OK;
+}
+
+extern "C" moe_status moe_layer_streams(const moe_config* cfg, int32_t* streams) {
+    Dims d;
+    MOE_TRY(make_dims(cfg, &d));
+    if (!streams) return MOE_ERR_NULL;
+    *streams = streams_used(d);
     return MOE_OK;
 }
 

@@ -46,7 +46,8 @@ def interference(shape, inp, n: int, reuse: int, free_cus: Sequence[int] = (0, 8
     free by the GEMMs.  sigma(r) = GEMM time alone / GEMM time in the two-stream step, mu(r) likewise
     for the permutations (both are relative speeds, at most 1 up to timing noise).  With r = 0 a
     permutation kernel queued beside a GEMM mostly waits for a compute unit, so mu(0) measures that
-    wait; with r > 0 it runs on the free units while the GEMM runs."""
+    wait; with r > 0 it runs on the free units while the GEMM runs.  Small work runs on one stream at
+    r = 0 (the row's "streams" says so): nothing ran side by side then, and sigma and mu are None."""
     def state(r, two_streams):
         st = runner.LayerState(shape.T, shape.M, shape.H, shape.E, shape.k, shape.capacity_factor, n, shape.dtype,
                                reuse, second_stream=two_streams, grad_overwrite=1, wgrad_group=wgrad_group,
@@ -61,9 +62,11 @@ def interference(shape, inp, n: int, reuse: int, free_cus: Sequence[int] = (0, 8
     for r in free_cus:
         st = state(r, True)
         t = timed_steps(st, steps)
+        used = B.moe_layer_streams(st.cfg)
         del st
-        rows.append({"free_cus": r, "step_ms": t["step_ms"], "gemm_ms": t["gemm_ms"], "perm_ms": t["perm_ms"],
-                     "sigma": alone["gemm_ms"] / t["gemm_ms"], "mu": alone["perm_ms"] / t["perm_ms"],
+        rows.append({"free_cus": r, "streams": used, "step_ms": t["step_ms"], "gemm_ms": t["gemm_ms"],
+                     "perm_ms": t["perm_ms"], "sigma": alone["gemm_ms"] / t["gemm_ms"] if used > 1 else None,
+                     "mu": alone["perm_ms"] / t["perm_ms"] if used > 1 else None,
                      "exposed_ms": t["step_ms"] - t["gemm_ms"]})
     torch.cuda.empty_cache()
     best = min(rows, key=lambda x: x["step_ms"])

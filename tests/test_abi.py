@@ -71,6 +71,23 @@ def test_argument_errors_are_status_codes():
     assert B.status_string(4) == "workspace too small"
 
 
+def test_number_of_streams_follows_the_work():
+    def used(T, M, H, E, k, n, dtype=B.MOE_BF16, reuse=0, **kw):
+        return B.moe_layer_streams(B.make_config(T, M, H, E, k, 1.0, n, dtype, reuse, **kw))
+    assert used(32768, 2048, 8192, 16, 2, 1) == 1                       # one partition
+    assert used(32768, 2048, 8192, 16, 2, 2) == 2                       # 6.6e12 each
+    assert used(16384, 1024, 4096, 8, 2, 2) == 2                        # 8.2e11
+    assert used(16384, 1024, 4096, 8, 2, 4) == 1                        # 4.1e11
+    assert used(16384, 1024, 4096, 8, 2, 4, gemm_free_cus=8) == 2
+    assert used(4096, 512, 2048, 8, 2, 1, gemm_free_cus=8) == 2
+    assert used(4096, 512, 2048, 8, 2, 2, B.MOE_F32) == 2               # 5.15e10: counted tenfold
+    assert used(4096, 512, 2040, 8, 2, 2, B.MOE_F32) == 2
+    assert used(4096, 512, 1984, 8, 2, 2, B.MOE_F32) == 1               # 4.99e10
+    for mode in (B.MOE_REUSE_S1, B.MOE_REUSE_S2, B.MOE_REUSE_S3):
+        assert used(256, 64, 128, 4, 1, 1, reuse=mode) == 3
+    assert B.lib().moe_layer_streams(None, None) == 1
+
+
 def test_oversized_rows_are_refused_before_anything_is_launched():
     """Rows too long for 32-bit offsets: backward's first GEMM already says so (its operands are narrow, its output
     is not), where there is no GPU as well; nothing is launched, so the pointers are never read."""

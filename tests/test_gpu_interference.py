@@ -31,6 +31,9 @@ def test_measured_slowdown_factors_and_strategy_selection():
     n = 4
     itf = measure.interference(s, d, n, 2, free_cus=(0, 8, 16), steps=4)
     rows = {r["free_cus"]: r for r in itf["side_by_side"]}
+    # with every unit to the GEMMs this work runs on one stream: no relative speed to report
+    assert rows[0]["streams"] == 1 and rows[0]["sigma"] is None and rows[0]["mu"] is None
+    assert rows[8]["streams"] == rows[16]["streams"] == 2
     for r in (8, 16):
         # relative speeds: positive, and at most 1 up to timing noise
         assert 0.0 < rows[r]["sigma"] <= 1.05, rows[r]
