@@ -273,18 +273,59 @@ def test_results_do_not_depend_on_streams_or_reuse_mode(runner):
     s = synth.WORKLOADS["small"]
     d = synth.make_inputs(s, seed=1)
     base = runner.run_layer_step(s, d, 4, 0, second_stream=False)
+    # (so little work runs on one stream unless the GEMMs are to leave units free)
     for mode, two in ((0, True), (1, True), (2, True), (2, False)):
-        g = runner.run_layer_step(s, d, 4, mode, second_stream=two)
+        g = runner.run_layer_step(s, d, 4, mode, second_stream=two, gemm_free_cus=8 if two else 0)
         for k_ in ("idx", "slot", "counts"):
             assert np.array_equal(g[k_], base[k_])
         assert np.array_equal(g["y"], base["y"])                 # forward never differs
         for k_ in ("dx", "dWg", "dW1", "dW2"):
             assert relerr(g[k_], base[k_]) <= 1e-2
     # recomputed T_M is the stored T_M: modes 1 and 2 agree exactly
-    g1 = runner.run_layer_step(s, d, 4, 1)
-    g2 = runner.run_layer_step(s, d, 4, 2)
+    g1 = runner.run_layer_step(s, d, 4, 1, gemm_free_cus=8)
+    g2 = runner.run_layer_step(s, d, 4, 2, gemm_free_cus=8)
     for k_ in ("dx", "dWg", "dW1", "dW2"):
         assert np.array_equal(g1[k_], g2[k_]), k_
+
+
+# name, (T, M, H, E, k, cf, dtype), n, options: more partitions than buffers throughout, so that every ring of
+# buffers is used again across the streams
+STREAM_CASES = [
+    ("plain", (4096, 512, 2048, 8, 2, 1.25, "bf16"), 8, {}),
+    ("f32", (1024, 256, 512, 8, 2, 1.25, "f32"), 4, {}),
+    ("gathered", (4096, 512, 2048, 8, 2, 1.25, "bf16"), 4, dict(fuse_gather=1)),
+    ("grouped2", (4096, 512, 2048, 8, 2, 1.0, "bf16"), 8, dict(wgrad_group=2)),
+    ("grouped3", (4096, 512, 2048, 8, 2, 0.6, "bf16"), 8, dict(wgrad_group=3)),
+    ("combined", (4096, 512, 2048, 8, 1, 0.75, "bf16"), 4, dict(fuse_combine=1)),
+    ("combined_gathered_grouped", (4096, 512, 2048, 16, 1, 1.0, "bf16"), 8, dict(fuse_combine=1, fuse_gather=1, wgrad_group=2)),
+]
+
+
+@pytest.mark.parametrize("mode", [0, 1, 2])
+@pytest.mark.parametrize("case", STREAM_CASES, ids=[c[0] for c in STREAM_CASES])
+def test_two_streams_equal_one_stream_bit_for_bit(runner, case, mode):
+    """The same kernels in the same order per buffer: a step on two streams leaves what a step on one does, also
+    when the next step follows at once and finds the last one's leftovers."""
+    from paper_2506_22175_amd import binding as B
+    name, (T, M, H, E, k, cf, dt), n, opts = case
+    s = synth.custom_shape(T, M, H, E, k, cf, dtype=dt, x_std=1.0, w_std=0.05, name=name)
+    d = synth.make_inputs(s, seed=21)
+    base = runner.run_layer_step(s, d, n, mode, second_stream=False, grad_overwrite=1, **opts)
+    st = runner.LayerState(T, M, H, E, k, cf, n, dt, mode, grad_overwrite=1, gemm_free_cus=8, **opts)
+    assert B.moe_layer_streams(st.cfg) == 2 and st.s1 != st.s0
+    st.upload(d)
+    st.poison()
+    for steps in (1, 3):
+        for _ in range(steps):
+            st.step()
+        g = st.results()
+        for k_ in ("y", "dx", "dWg", "dW1", "dW2", "idx", "slot", "counts"):
+            assert np.array_equal(g[k_], base[k_]), (steps, k_)
+    st.forward()
+    st.backward()
+    g = st.results()
+    for k_ in ("y", "dx", "dWg", "dW1", "dW2"):
+        assert np.array_equal(g[k_], base[k_]), ("in two calls", k_)
 
 
 def test_repeated_steps_reuse_the_workspace_cleanly(oracle, runner):
@@ -756,12 +797,16 @@ def test_kernel_timing_hooks_see_every_gemm(runner):
     assert all(ms > 0 for cnt, ms in prof.values() if cnt)
 
 
-def test_graph_replay_equals_eager_every_time(runner):
+@pytest.mark.parametrize("free_cus", [0, 8], ids=["one_stream", "two_streams"])
+def test_graph_replay_equals_eager_every_time(runner, free_cus):
     """A captured step replayed several times, with eager steps and synchronisations
-    between the replays, gives the eager result each time."""
+    between the replays, gives the eager result each time; as one chain and with the fork to the
+    GEMMs' stream and the join back."""
+    from paper_2506_22175_amd import binding as B
     s = synth.WORKLOADS["small"]
     d = synth.make_inputs(s, seed=4)
-    st = runner.LayerState(s.T, s.M, s.H, s.E, s.k, s.capacity_factor, 4, s.dtype, 2)
+    st = runner.LayerState(s.T, s.M, s.H, s.E, s.k, s.capacity_factor, 4, s.dtype, 2, gemm_free_cus=free_cus)
+    assert B.moe_layer_streams(st.cfg) == (2 if free_cus else 1)
     st.upload(d)
     st.zero_grads()
     st.step()
