@@ -200,6 +200,15 @@ moe_status moe_expert_ffn_bwd(const moe_config* cfg, int32_t part, int32_t recom
                               void* dZ, void* dDI, float* dW1, float* dW2, float* dw_part, void* stream);
 moe_status moe_dw_parts(const moe_config* cfg, int32_t* parts);
 
+/* Host only.  Rows and columns of the output tiles in which a GEMM of partition `part` is
+ * computed when moe_layer_step runs it under cfg (the moe_expert_ffn_* calls: as with
+ * wgrad_group = 0 and fuse_combine = 0).  Which shape a launch uses depends on cfg alone;
+ * a product's terms are added in the same order in all of them. */
+typedef enum { MOE_GEMM_FIRST = 0 /* T_DI W1, GeLU */, MOE_GEMM_SECOND = 1 /* A W2 */,
+               MOE_GEMM_RECOMPUTE = 2 /* T_DI W1 again */, MOE_GEMM_DGELU = 3 /* dDO W2^T, GeLU backward */,
+               MOE_GEMM_DGRAD = 4 /* dZ W1^T */, MOE_GEMM_DW2 = 5, MOE_GEMM_DW1 = 6 } moe_gemm;
+moe_status moe_gemm_tile(const moe_config* cfg, int32_t part, int32_t gemm, int32_t* rows, int32_t* cols);
+
 /* Combine R of partition `part` (Fig. 1: T_DO -> T_O): for the partition's tokens
  * y[t] = sum over kept j of topk_w[t,j] * DO[slot[t,j]], float accumulation in
  * ascending j; exactly zero when every choice was dropped.  y [T,M] out. */

@@ -29,6 +29,7 @@ EXPORTS = [
     "moe_gran_create", "moe_gran_destroy", "moe_gran_lookup", "moe_gran_record", "moe_gran_ranges",
     "moe_search_best_gran", "moe_gran_get", "moe_strategy_cost", "moe_select_strategy",
     "moe_offload_bytes", "moe_layer_step_offload", "moe_layer_streams",
+    "moe_gemm_tile",
 ]
 
 
@@ -138,6 +139,17 @@ def moe_layer_streams(cfg: MoEConfig) -> int:
     v = ctypes.c_int32(0)
     _check(lib().moe_layer_streams(_cfg(cfg), ctypes.byref(v)), "moe_layer_streams")
     return v.value
+
+
+GEMMS = ("first", "second", "recompute", "dgelu", "dgrad", "dW2", "dW1")
+
+
+def moe_gemm_tile(cfg: MoEConfig, part: int, gemm: str):
+    """(rows, columns) of the output tiles of one of GEMMS for partition `part`."""
+    r, c = ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(lib().moe_gemm_tile(_cfg(cfg), ctypes.c_int32(part), ctypes.c_int32(GEMMS.index(gemm)), ctypes.byref(r),
+                               ctypes.byref(c)), "moe_gemm_tile")
+    return r.value, c.value
 
 
 def moe_launch_counts(reset: bool = False):

@@ -208,7 +208,8 @@ moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStr
 moe_status gemm_f32(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 int gemm_bf16_dw_parts(int H);   // column blocks the DGELU epilogue reports per row
 int gemm_f32_dw_parts(int H);
-
+void gemm_bf16_tile(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, int* rows, int* cols);   // of a launch; host only
+void gemm_f32_tile(int* rows, int* cols);
 
 // ---- one partition's expert FFN (ffn.hip) ---------------------------------------
 // rows != NULL: DI is the token-major input [T, M] and rows[part] maps expert rows to its rows

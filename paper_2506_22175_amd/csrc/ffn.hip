@@ -143,6 +143,34 @@ extern "C" moe_status moe_dw_parts(const moe_config* cfg, int32_t* parts) {
     return MOE_OK;
 }
 
+extern "C" moe_status moe_gemm_tile(const moe_config* cfg, int32_t part, int32_t gemm, int32_t* rows, int32_t* cols) {
+    Dims d;
+    MOE_TRY(make_dims(cfg, &d));
+    MOE_TRY(check_part(d, part));
+    if (!rows || !cols) return MOE_ERR_NULL;
+    if (gemm < MOE_GEMM_FIRST || gemm > MOE_GEMM_DW1) return MOE_ERR_SHAPE;
+    if (d.dtype == MOE_F32) { gemm_f32_tile(rows, cols); return MOE_OK; }
+    GemmArgs a = base_args(d, nullptr);
+    const bool wide = gemm == MOE_GEMM_FIRST || gemm == MOE_GEMM_RECOMPUTE || gemm == MOE_GEMM_DGELU || gemm == MOE_GEMM_DW1;
+    a.N = wide ? d.H : d.M;
+    a.K = wide ? d.M : d.H;
+    a.Mo = a.K;                                       // the weight gradients' output rows
+    GemmLayout lay = gemm <= MOE_GEMM_RECOMPUTE ? GEMM_NN : GEMM_NT;
+    GemmEpilogue epi = EPI_STORE;
+    if (gemm == MOE_GEMM_FIRST) epi = EPI_GELU;
+    else if (gemm == MOE_GEMM_SECOND && d.fcomb) epi = EPI_SCATTER;
+    else if (gemm == MOE_GEMM_DGELU) epi = EPI_DGELU;
+    else if (gemm >= MOE_GEMM_DW2) {
+        const int p0 = part / d.G * d.G;              // first partition of the group
+        lay = GEMM_TN;
+        epi = d.overwrite && p0 == 0 ? EPI_STORE_F32 : EPI_ACCUM_F32;
+        a.k_segs = d.n - p0 < d.G ? d.n - p0 : d.G;
+        a.K = 0;
+    }
+    gemm_bf16_tile(lay, epi, a, rows, cols);
+    return MOE_OK;
+}
+
 extern "C" moe_status moe_expert_ffn_fwd(const moe_config* cfg, int32_t part, const void* DI, const int32_t* counts,
                                          const void* W1, const void* W2, void* Z, void* A, void* DO, void* stream) {
     Dims d;

@@ -1229,8 +1229,12 @@ static moe_status launch_cfg(const GemmArgs& a, hipStream_t s) {
     return launch_one<LAY, EPI, typename CfgFor<LAY, EPI>::type>(a, s);
 }
 
-}  // namespace moe
-namespace moe {
+void gemm_bf16_tile(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, int* rows, int* cols) {
+    const TileCost& c = TILE_COSTS[tile_choice(lay, epi, a)];
+    *rows = c.bm;
+    *cols = c.bn;
+}
+
 moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
     if (a.dw_part && a.dw_parts != gemm_bf16_dw_parts(a.N)) return MOE_ERR_SHAPE;
     // operand rows must be 16-byte aligned in memory

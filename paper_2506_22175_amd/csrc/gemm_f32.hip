@@ -180,6 +180,8 @@ __global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_kernel(GemmArgs g) {
     }
 }
 
+void gemm_f32_tile(int* rows, int* cols) { *rows = F_BM; *cols = F_BN; }
+
 int gemm_f32_dw_parts(int H) { return (H + F_BN - 1) / F_BN; }
 
 template <int LAY, int EPI>

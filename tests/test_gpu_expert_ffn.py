@@ -11,12 +11,16 @@ pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-4, "bf16": 2e-2}          # max|gpu - ref| / max|ref|, as everywhere in these tests
 
 
-def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
+def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite, mean=None, tiles=None):
+    """mean: rows per expert when all are loaded alike (the capacity unless given); tiles: the output tiles, by GEMM,
+    that the case is meant to be computed in."""
     from paper_2506_22175_amd import binding as B
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     E = len(counts)
-    cfg = B.make_config(E * Cp, M, H, E, 1, 1.0, 1, B.MOE_BF16 if dtype == "bf16" else B.MOE_F32, 0, overwrite)
+    cfg = B.make_config(E * (mean or Cp), M, H, E, 1, Cp / (mean or Cp), 1, B.MOE_BF16 if dtype == "bf16" else B.MOE_F32, 0, overwrite)
     assert B.moe_capacity(cfg) == Cp
+    for gemm, tile in (tiles or {}).items():
+        assert B.moe_gemm_tile(cfg, 0, gemm) == tile, gemm
     d = "cuda:0"
     g = torch.Generator(d).manual_seed(seed)
     x = torch.randn((E * Cp, M), generator=g, device=d).to(dt)
@@ -69,15 +73,41 @@ def _run(dtype, M, H, counts, Cp, seed, recompute, overwrite):
         assert err <= TOL[dtype], (n, float(err))
 
 
-# sizes that the larger bfloat16 tiles are chosen for (256 x 128 and 256 x 256 beside the small ones), with last
-# tile rows of one row, of a few blocks of 64, of half a tile and one row more, and full ones
-@pytest.mark.parametrize("M,H,counts,Cp", [
-    (1024, 4096, (1024, 1023, 897, 896, 641, 129, 64, 0), 1024),
-    (1024, 4096, (1024, 1025, 960, 1088, 1153, 1152, 897, 0), 1160),
-    (520, 4104, (4096, 4097, 4225, 4224), 4300),
+LARGE, HALF, SMALL, FLAT = (256, 256), (256, 128), (128, 128), (64, 128)       # the bfloat16 GEMM's tiles
+GEMMS = ("first", "second", "recompute", "dgelu", "dgrad", "dW2", "dW1")
+
+
+# sizes that the larger bfloat16 tiles are chosen for (the small ones too, for single GEMMs), with last tile rows of
+# one row, of a few blocks of 64, of half a tile and one row more, and full ones
+@pytest.mark.parametrize("M,H,counts,Cp,tiles", [
+    (1024, 4096, (1024, 1023, 897, 896, 641, 129, 64, 0), 1024,
+     dict(first=LARGE, second=HALF, dgelu=LARGE, dgrad=HALF, dW2=LARGE, dW1=LARGE)),
+    (1024, 4096, (1024, 1025, 960, 1088, 1153, 1152, 897, 0), 1160, dict.fromkeys(GEMMS, LARGE)),
+    (520, 4104, (4096, 4097, 4225, 4224), 4300,
+     dict(first=LARGE, second=LARGE, dgelu=SMALL, dgrad=LARGE, dW2=SMALL, dW1=SMALL)),
 ], ids=["half_size", "last_rows", "whole"])
-def test_expert_ffn_in_large_tiles(M, H, counts, Cp):
-    _run("bf16", M, H, counts, Cp, 5, 0, 0)
+def test_expert_ffn_in_large_tiles(M, H, counts, Cp, tiles):
+    _run("bf16", M, H, counts, Cp, 5, 0, 0, tiles=tiles)
+
+
+# every tile with every epilogue of the expert FFN (256 x 128 accumulates over several partitions only: see the
+# layer's tests), dimensions and loads that end inside a tile
+@pytest.mark.parametrize("M,H,counts,Cp,mean,recompute,overwrite,tiles", [
+    (784, 1312, (160, 1, 0, 128, 129, 64, 65, 32, 33, 127, 160, 96, 97, 31, 130, 159), 160, 128, 1, 0,
+     dict(first=HALF, recompute=HALF, second=SMALL, dgelu=FLAT, dgrad=SMALL)),
+    (1544, 1544, (1500, 1281), 1500, None, 1, 1,
+     dict(first=SMALL, second=HALF, recompute=HALF, dgelu=HALF, dgrad=HALF, dW2=HALF, dW1=HALF)),
+    (1544, 1544, (1409, 897), 1500, None, 0, 0, dict(second=HALF, dgelu=HALF, dgrad=HALF, dW2=SMALL, dW1=SMALL)),
+    (768, 1032, (700, 513, 640, 641, 1, 0, 257, 384, 385, 128, 129, 639, 577, 576, 512, 64), 700, None, 1, 1,
+     dict.fromkeys(GEMMS, LARGE)),
+    (768, 1032, (700, 513, 640, 641, 1, 0, 257, 384, 385, 128, 129, 639, 577, 576, 512, 64), 700, None, 0, 0,
+     dict.fromkeys(GEMMS, LARGE)),
+    (136, 136, (1030, 1025, 1024, 129, 0, 1, 897, 961), 1030, None, 1, 1, dict.fromkeys(GEMMS, SMALL)),
+    (136, 136, (1030, 1025, 1024, 129, 0, 1, 897, 961), 1030, None, 0, 0, dict.fromkeys(GEMMS, SMALL)),
+    (136, 264, (100,), 100, None, 1, 0, dict.fromkeys(GEMMS[:5], FLAT)),
+], ids=["half_gelu", "half", "half_tails", "large_store", "large_add", "small_store", "small_add", "flat"])
+def test_expert_ffn_in_every_tile_shape(M, H, counts, Cp, mean, recompute, overwrite, tiles):
+    _run("bf16", M, H, counts, Cp, 13, recompute, overwrite, mean, tiles)
 
 
 # float gradients of more than 2 GiB per expert, with columns that end inside a tile: the offset that stands for "out
@@ -92,7 +122,7 @@ def test_expert_ffn_with_gradients_above_two_gib(overwrite):
 @pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
 def test_expert_ffn_with_experts_smaller_than_their_tile(recompute, overwrite):
     counts = tuple([1, 10, 64, 65, 0, 127, 128, 140] + [129 + 5 * e % 12 for e in range(55)] + [129])
-    _run("bf16", 768, 3072, counts, 140, 7, recompute, overwrite)
+    _run("bf16", 768, 3072, counts, 140, 7, recompute, overwrite, tiles=dict.fromkeys(GEMMS[:5], LARGE))
 
 
 @pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
