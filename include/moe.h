@@ -34,8 +34,8 @@
  *   - host-side state (a pool of events, the launch counters, the timing
  *     records) is process-wide and unsynchronised: call the library from one
  *     host thread at a time.  Calls on different streams may overlap on the GPU;
- *     the bf16 GEMMs launch one persistent workgroup per CU, so two GEMMs that
- *     overlap share the CUs by whole workgroups.
+ *     the bf16 GEMMs launch one persistent workgroup per CU (two in 128 x 128
+ *     tiles), so two GEMMs that overlap share the CUs by whole workgroups.
  */
 #ifndef MOE_H
 #define MOE_H
@@ -100,11 +100,12 @@ typedef struct {
                                G partition-sized buffers each of T_DI, dT_DO, T_M and dT_M alive in
                                backward instead of two (one for T_M, dT_M).  Values above n count as
                                n.  Not with S1..S3. */
-    int32_t gemm_free_cus;  /* The bfloat16 expert GEMMs launch one persistent workgroup per compute unit,
-                               which leaves no room for a kernel of another stream until a GEMM ends.
-                               r > 0 launches them on r compute units fewer (rounded up to a multiple of 8,
-                               at least 8 stay), so that the permutation kernels of Section III-B's other
-                               stream run beside them on the units left free.  0: every unit. */
+    int32_t gemm_free_cus;  /* The bfloat16 expert GEMMs launch one persistent workgroup per compute unit (in
+                               128 x 128 tiles two, which fill it as well), which leaves no room for a kernel
+                               of another stream until a GEMM ends.  r > 0 launches the workgroups of r compute
+                               units fewer (rounded up to a multiple of 8, at least 8 units' stay), so that the
+                               permutation kernels of Section III-B's other stream run beside them in the room
+                               left free.  0: every unit. */
     int32_t fuse_combine;   /* 1 (only with k = 1, the paper's own gate, Section IV-A): the second expert
                                GEMM writes each kept row, times its combine weight, straight into its
                                token's row of y, and the rows of dropped tokens are zeroed beforehand.

@@ -286,7 +286,7 @@ constexpr int MAX_KSEGS = 8;
 struct TileCoord { int e, tn, m0, n0, Mdim, Kdim, KT; };
 struct KCursor { int seg, jl, tiles; };
 
-// Persistent workgroups: the grid has one workgroup per CU, and workgroup b works through
+// Persistent workgroups: the grid has one workgroup per CU (two where two fit), and workgroup b works through
 // the tiles b, b + grid, b + 2 grid, ...  While a tile's epilogue runs (it needs only the
 // staging part of LDS and no matrix instructions), the first operand tiles of the next
 // tile are already on their way into the rest of the ring, so neither the launch of a new
@@ -341,8 +341,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     // Only tiles that exist are numbered: an expert with fewer rows than the capacity has fewer
     // tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups,
     // which take the numbers b, b + grid, ..., all get the same amount of work whatever the spread
-    // of the counts.  The tile rows that an expert fills at least half come first, expert by
-    // expert; a last tile row with fewer rows is numbered after all of those, since it takes less
+    // of the counts.  The tile rows that an expert fills by more than half come first, expert
+    // by expert; a last tile row with fewer rows is numbered after all of those, since it takes less
     // time (the 64-k loops multiply only the blocks of rows that hold something) and belongs at
     // the end of a workgroup's list.  Lane l of every wavefront holds the tile rows of expert l
     // (E <= 64); inclusive scans over the lanes give the numbers at which each expert ends.
@@ -1122,8 +1122,8 @@ typedef TileCfg<64, 128, 64, 6, 2, 2, 1, LOOP_R64> CfgT;
 
 int gemm_bf16_dw_parts(int H) { return (H + 2 * DW_COLS - 1) / (2 * DW_COLS) * 2; }
 
-// One workgroup per CU (a workgroup fills a CU's LDS), rounded down to a multiple of 8 so that
-// tile numbers keep their XCD.
+// Workgroups of a full grid: one per CU (times TileCfg::OCC; together they fill a CU's LDS), rounded down to a
+// multiple of 8 so that tile numbers keep their XCD.
 static int persistent_grid() {
     static int grid = 0;
     if (grid == 0) {
