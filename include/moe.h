@@ -313,15 +313,17 @@ moe_status moe_layer_backward(const moe_config* cfg, const void* x, const void* 
                               void* const* streams, int32_t n_streams);
 
 /* Counters of kernels launched by this process since the last reset, by class:
- * out[0] GEMM launches, out[1] permutation launches (dispatch, combine,
- * dispatch-backward), out[2] everything else.  Host only. */
+ * out[0] GEMMs, out[1] permutations (dispatch, combine, dispatch-backward),
+ * out[2] everything else.  A launch that does the work of several counts as
+ * all of them.  Host only. */
 moe_status moe_launch_counts(int64_t out[3], int32_t reset);
 
 /* Optional timing of the library's kernels with HIP events recorded on the
  * stream each kernel is launched on.  moe_profile_enable(1) clears earlier
  * records and starts recording; moe_profile_enable(0) stops.  moe_profile_read
  * waits for the recorded events and returns, per kernel kind, the number of
- * launches and the summed duration in milliseconds.  Kinds: 0 first FFN GEMM
+ * launches and the summed duration in milliseconds (of one launch for several
+ * GEMMs, which are of the same size: one each, and equal shares).  Kinds: 0 first FFN GEMM
  * (GeLU epilogue), 1 second FFN GEMM and recomputation, 2 GEMM with the
  * GeLU-backward epilogue, 3 input-gradient GEMM, 4 weight-gradient GEMMs,
  * 5 dispatch, 6 combine, 7 dispatch backward, 8 gate, 9 slot assignment,

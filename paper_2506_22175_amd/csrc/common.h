@@ -149,7 +149,8 @@ enum ProfKind {
 };
 struct ProfScope {
     int idx; hipStream_t s;
-    ProfScope(int kind, hipStream_t stream);
+    // one launch may do the work of several: `units` of `kind`, and one of `also`
+    ProfScope(int kind, hipStream_t stream, int units = 1, int also = -1);
     ~ProfScope();
 };
 
@@ -206,6 +207,11 @@ inline int gemm_prof_kind(int lay, int epi) {
 
 moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 moe_status gemm_f32(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
+// The two weight gradients (TN, epi) and, unless NULL, the input gradient (NT, store) in one launch.  The bfloat16 one
+// does so where the tile shapes fit together, else it launches nothing and says so.
+moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s,
+                              bool* done);
+moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s);
 int gemm_bf16_dw_parts(int H);   // column blocks the DGELU epilogue reports per row
 int gemm_f32_dw_parts(int H);
 void gemm_bf16_tile(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, int* rows, int* cols);   // of a launch; host only
@@ -220,14 +226,15 @@ moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, con
 moe_status ffn_bwd(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                    const int* counts, const float* slot_w, const void* W1, const void* W2,
                    void* dZ, void* dDI, float* dW1, float* dW2, float* dw_part, hipStream_t s);
-// its two halves: everything but the weight gradients of one partition, and the weight gradients of
-// nparts consecutive partitions at once
+// its two halves: everything but the weight gradients of one partition (without the input gradient on request), and
+// the weight gradients of nparts consecutive partitions at once
 moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                         const int* counts, const float* slot_w, const void* W1, const void* W2,
-                        void* dZ, void* dDI, float* dw_part, hipStream_t s);
+                        void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad = true);
+// dgrad_W1 != NULL: and the input gradient of the last of the partitions (which ffn_bwd_main left out) into dDI
 moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void* DI, const void* A, const void* dDO,
                      const void* dZ, long long strideM, long long strideH, const int* counts,
-                     float* dW1, float* dW2, hipStream_t s);
+                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1 = nullptr, void* dDI = nullptr);
 
 // k = 1 with the fused combine: rows of y of dropped tokens <- 0 (permute.hip)
 moe_status zero_dropped(const Dims& d, const int* slot, void* y, hipStream_t s);

@@ -55,7 +55,7 @@ static std::atomic<long long> g_launches[3];
 void count_launch(LaunchClass c, int n) { g_launches[c].fetch_add(n, std::memory_order_relaxed); }
 
 // ---- optional kernel timing ---------------------------------------------------------
-struct ProfRec { int kind; hipEvent_t a, b; };
+struct ProfRec { int kind, units, also; hipEvent_t a, b; };
 static bool g_prof_on = false;
 static std::vector<ProfRec> g_prof_recs;      // records of the current session
 static std::vector<hipEvent_t> g_prof_pool;   // timing events, reused across sessions
@@ -72,10 +72,12 @@ static bool prof_event(hipEvent_t* e) {
     return true;
 }
 
-ProfScope::ProfScope(int kind, hipStream_t stream) : idx(-1), s(stream) {
+ProfScope::ProfScope(int kind, hipStream_t stream, int units, int also) : idx(-1), s(stream) {
     if (!g_prof_on || g_prof_recs.size() >= PROF_MAX_RECS) return;
     ProfRec r;
     r.kind = kind;
+    r.units = units;
+    r.also = also;
     if (!prof_event(&r.a) || !prof_event(&r.b)) return;
     if (hipEventRecord(r.a, s) != hipSuccess) return;
     idx = (int)g_prof_recs.size();
@@ -101,8 +103,14 @@ extern "C" moe_status moe_profile_read(int32_t kinds, int64_t* launches, double*
         HIP_TRY(hipEventSynchronize(r.b));
         float ms = 0.0f;
         HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
-        launches[r.kind] += 1;
-        total_ms[r.kind] += ms;
+        // (units of one launch are of the same number of operations)
+        const int all = r.units + (r.also >= 0 ? 1 : 0);
+        launches[r.kind] += r.units;
+        total_ms[r.kind] += ms * r.units / all;
+        if (r.also >= 0 && r.also < kinds) {
+            launches[r.also] += 1;
+            total_ms[r.also] += ms / all;
+        }
     }
     return MOE_OK;
 }

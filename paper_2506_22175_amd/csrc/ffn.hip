@@ -51,9 +51,19 @@ moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, con
     return run_gemm(d, GEMM_NN, EPI_STORE, b, s);
 }
 
+// dDI = dZ W1^T
+static GemmArgs dgrad_args(const Dims& d, const int* cp, const void* dZ, const void* W1, void* dDI) {
+    GemmArgs a = base_args(d, cp);
+    a.A = dZ; a.lda = d.H; a.a_estride = (long long)d.Cp * d.H;
+    a.B = W1; a.ldb = d.H; a.b_estride = (long long)d.M * d.H;
+    a.C = dDI; a.ldc = d.M; a.c_estride = (long long)d.Cp * d.M;
+    a.N = d.M; a.K = d.H;
+    return a;
+}
+
 moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                         const int* counts, const float* slot_w, const void* W1, const void* W2,
-                        void* dZ, void* dDI, float* dw_part, hipStream_t s) {
+                        void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad) {
     const int* cp = counts + (size_t)part * d.E;
     const long long eM = (long long)d.Cp * d.M, eH = (long long)d.Cp * d.H, wMH = (long long)d.M * d.H;
     if (recompute) {
@@ -77,14 +87,7 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
         a.dw_parts = d.dtype == MOE_F32 ? gemm_f32_dw_parts(d.H) : gemm_bf16_dw_parts(d.H);
         MOE_TRY(run_gemm(d, GEMM_NT, EPI_DGELU, a, s));
     }
-    {   // dDI = dZ W1^T
-        GemmArgs a = base_args(d, cp);
-        a.A = dZ; a.lda = d.H; a.a_estride = eH;
-        a.B = W1; a.ldb = d.H; a.b_estride = wMH;
-        a.C = dDI; a.ldc = d.M; a.c_estride = eM;
-        a.N = d.M; a.K = d.H;
-        MOE_TRY(run_gemm(d, GEMM_NT, EPI_STORE, a, s));
-    }
+    if (with_dgrad) MOE_TRY(run_gemm(d, GEMM_NT, EPI_STORE, dgrad_args(d, cp, dZ, W1, dDI), s));
     return MOE_OK;
 }
 
@@ -94,7 +97,7 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
 // are read and written once per group instead of once per partition.
 moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void* DI, const void* A, const void* dDO,
                      const void* dZ, long long strideM, long long strideH, const int* counts,
-                     float* dW1, float* dW2, hipStream_t s) {
+                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1, void* dDI) {
     const long long eM = (long long)d.Cp * d.M, eH = (long long)d.Cp * d.H, wMH = (long long)d.M * d.H;
     // the float GEMM reduces one partition per launch
     const int per_launch = d.dtype == MOE_F32 ? 1 : nparts;
@@ -102,23 +105,39 @@ moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void*
         const int* cp = counts + (size_t)(part + q) * d.E;
         const GemmEpilogue epi = (store && q == 0) ? EPI_STORE_F32 : EPI_ACCUM_F32;
         const size_t oM = (size_t)q * strideM * d.es, oH = (size_t)q * strideH * d.es;
-        {   // dW2[e] += (w gelu(Z))^T dDO
-            GemmArgs a = base_args(d, cp);
-            a.A = (const char*)A + oH; a.lda = d.H; a.a_estride = eH; a.Mo = d.H;
-            a.B = (const char*)dDO + oM; a.ldb = d.M; a.b_estride = eM;
-            a.C = dW2; a.ldc = d.M; a.c_estride = wMH;
-            a.N = d.M;
-            a.k_segs = per_launch; a.a_sstride = strideH; a.b_sstride = strideM;
-            MOE_TRY(run_gemm(d, GEMM_TN, epi, a, s));
+        // dW2[e] += (w gelu(Z))^T dDO
+        GemmArgs w2 = base_args(d, cp);
+        w2.A = (const char*)A + oH; w2.lda = d.H; w2.a_estride = eH; w2.Mo = d.H;
+        w2.B = (const char*)dDO + oM; w2.ldb = d.M; w2.b_estride = eM;
+        w2.C = dW2; w2.ldc = d.M; w2.c_estride = wMH;
+        w2.N = d.M;
+        w2.k_segs = per_launch; w2.a_sstride = strideH; w2.b_sstride = strideM;
+        // dW1[e] += DI^T dZ
+        GemmArgs w1 = base_args(d, cp);
+        w1.A = (const char*)DI + oM; w1.lda = d.M; w1.a_estride = eM; w1.Mo = d.M;
+        w1.B = (const char*)dZ + oH; w1.ldb = d.H; w1.b_estride = eH;
+        w1.C = dW1; w1.ldc = d.H; w1.c_estride = wMH;
+        w1.N = d.H;
+        w1.k_segs = per_launch; w1.a_sstride = strideM; w1.b_sstride = strideH;
+        // all three GEMMs that are left of the last partition in one launch, or both weight gradients, or one by one
+        const bool with_dgrad = dgrad_W1 && q + per_launch >= nparts;
+        const int last = part + nparts - 1;
+        const GemmArgs dg = with_dgrad ? dgrad_args(d, counts + (size_t)last * d.E,
+                                                    (const char*)dZ + (size_t)(nparts - 1) * strideH * d.es, dgrad_W1, dDI)
+                                       : GemmArgs{};
+        if (d.dtype == MOE_F32) {
+            MOE_TRY(gemm_f32_backward(with_dgrad ? &dg : nullptr, w2, w1, epi, s));
+            continue;
         }
-        {   // dW1[e] += DI^T dZ
-            GemmArgs a = base_args(d, cp);
-            a.A = (const char*)DI + oM; a.lda = d.M; a.a_estride = eM; a.Mo = d.M;
-            a.B = (const char*)dZ + oH; a.ldb = d.H; a.b_estride = eH;
-            a.C = dW1; a.ldc = d.H; a.c_estride = wMH;
-            a.N = d.H;
-            a.k_segs = per_launch; a.a_sstride = strideM; a.b_sstride = strideH;
-            MOE_TRY(run_gemm(d, GEMM_TN, epi, a, s));
+        bool done = false;
+        if (with_dgrad) {
+            MOE_TRY(gemm_bf16_backward(&dg, w2, w1, epi, s, &done));
+            if (!done) MOE_TRY(gemm_bf16(GEMM_NT, EPI_STORE, dg, s));
+        }
+        if (!done) MOE_TRY(gemm_bf16_backward(nullptr, w2, w1, epi, s, &done));
+        if (!done) {
+            MOE_TRY(gemm_bf16(GEMM_TN, epi, w2, s));
+            MOE_TRY(gemm_bf16(GEMM_TN, epi, w1, s));
         }
     }
     return MOE_OK;
@@ -127,8 +146,8 @@ moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void*
 moe_status ffn_bwd(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                    const int* counts, const float* slot_w, const void* W1, const void* W2,
                    void* dZ, void* dDI, float* dW1, float* dW2, float* dw_part, hipStream_t s) {
-    MOE_TRY(ffn_bwd_main(d, part, recompute, DI, Z, dDO, counts, slot_w, W1, W2, dZ, dDI, dw_part, s));
-    return ffn_wgrad(d, part, 1, d.overwrite && part == 0, DI, Z, dDO, dZ, 0, 0, counts, dW1, dW2, s);
+    MOE_TRY(ffn_bwd_main(d, part, recompute, DI, Z, dDO, counts, slot_w, W1, W2, dZ, dDI, dw_part, s, false));
+    return ffn_wgrad(d, part, 1, d.overwrite && part == 0, DI, Z, dDO, dZ, 0, 0, counts, dW1, dW2, s, W1, dDI);
 }
 
 }  // namespace moe

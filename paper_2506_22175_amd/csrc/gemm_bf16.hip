@@ -83,7 +83,7 @@ struct TileCfg {
     static constexpr int LDS_BYTES = LOOP == LOOP_W64 ? 160 * 1024 : NS * STAGE_BYTES;
     static constexpr bool PIPE = LOOP == LOOP_PIPE32;
     // columns of a wave's block that pass through the staging region at a time, and where that region starts
-    static constexpr int CW = WN < 64 || (LOOP == LOOP_PIPE32 && OCC == 1) ? WN : 64;
+    static constexpr int CW = WN < 64 || (LOOP == LOOP_PIPE32 && OCC == 1) ? WN : LOOP == LOOP_R64 && OCC == 2 ? 32 : 64;
     static constexpr int SBR = (WAVES * 32 * CW * 4 + STAGE_BYTES - 1) / STAGE_BYTES;      // stages that region takes
     static constexpr int STAGING_OFF = LOOP == LOOP_W64 ? 64 * 1024 : LOOP == LOOP_R64 ? (NS - SBR) * STAGE_BYTES : 0;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
@@ -91,7 +91,7 @@ struct TileCfg {
     static_assert(LOOP != LOOP_PIPE32 || (BK == 32 && NS >= 3), "the hand-scheduled ring has stages of 32 k");
     static_assert(LOOP != LOOP_W64 || (BM == 256 && BN == 256 && BK == 64 && WAVES_M == 2 && WAVES_N == 2 && OCC == 1),
                   "the two-ring loop is written for four waves of 128 x 128");
-    static_assert(LOOP != LOOP_R64 || (BK == 64 && NS >= 3 && OCC == 1 && SBR <= NS - 2),
+    static_assert(LOOP != LOOP_R64 || (BK == 64 && NS >= 3 && SBR <= NS - 2),
                   "stages of 64 k; the epilogue stages through the last ones");
 };
 
@@ -286,14 +286,53 @@ constexpr int MAX_KSEGS = 8;
 struct TileCoord { int e, tn, m0, n0, Mdim, Kdim, KT; };
 struct KCursor { int seg, jl, tiles; };
 
-// Persistent workgroups: the grid has one workgroup per CU (two where two fit), and workgroup b works through
-// the tiles b, b + grid, b + 2 grid, ...  While a tile's epilogue runs (it needs only the
+// Numbers of the tiles of a launch.  Only tiles that exist are numbered: an expert with fewer rows than the capacity
+// has fewer tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups, which take
+// the numbers b, b + grid, ..., all get the same amount of work whatever the spread of the counts.  The tile rows that
+// an expert fills by more than half come first, expert by expert; a last tile row with fewer rows is numbered after
+// all of those, since it takes less time (the 64-k loops multiply only the blocks of rows that hold something) and
+// belongs at the end of a workgroup's list.  Lane l of every wavefront holds the tile rows of expert l (E <= 64);
+// inclusive scans over the lanes give the numbers at which each expert ends.
+struct TileNumbers {
+    int lane_tm;                         // such tile rows of expert `lane`
+    int lane_end, tail_end;              // numbers of whole tiles / of last tile rows up to and including this expert
+    int nwhole, nblocks;                 // whole tiles; all tiles
+};
+template <int LAY, int EPI, typename C>
+__device__ __forceinline__ TileNumbers number_tiles(const GemmArgs& g, int tiles_m, int tiles_n, int lane) {
+    constexpr int BM = C::BM;
+    TileNumbers t;
+    t.lane_tm = 0;
+    int lane_tail = 0;                   // whether a last tile row with fewer rows follows
+    if (lane < g.E) {
+        int rows = 0;
+        const int segs = (LAY == GEMM_TN && g.k_segs > 1) ? g.k_segs : 1;
+        for (int sg = 0; sg < segs; ++sg) rows += g.counts[sg * g.E + lane];
+        if (LAY == GEMM_TN) t.lane_tm = (rows > 0 || EPI == EPI_STORE_F32) ? tiles_m : 0;   // a plain store still writes zeros
+        else {
+            t.lane_tm = min(tiles_m, (rows + BM / 2 - 1) / BM);
+            lane_tail = (t.lane_tm < tiles_m && rows > t.lane_tm * BM) ? 1 : 0;
+        }
+    }
+    t.lane_end = t.lane_tm * tiles_n;
+    t.tail_end = lane_tail;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(t.lane_end, off, 64), q = LAY == GEMM_TN ? 0 : __shfl_up(t.tail_end, off, 64);
+        if (lane >= off) { t.lane_end += o; t.tail_end += q; }
+    }
+    t.nwhole = __builtin_amdgcn_readlane(t.lane_end, 63);
+    t.nblocks = t.nwhole + __builtin_amdgcn_readlane(t.tail_end, 63) * tiles_n;
+    return t;
+}
+
+// The tiles b0, b0 + step, b0 + 2 step, ... of one GEMM.  While a tile's epilogue runs (it needs only the
 // staging part of LDS and no matrix instructions), the first operand tiles of the next
 // tile are already on their way into the rest of the ring, so neither the launch of a new
 // workgroup nor the first trip to memory stands between two main loops.
-template <int LAY, int EPI, typename C>
-__global__ __launch_bounds__(C::THREADS) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
-void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+// ONE: tile b0 only.
+template <int LAY, int EPI, typename C, bool ONE>
+__device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int tiles_n, const TileNumbers& tiles, int b0, int step) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, TNN = C::TN;
     constexpr int STAGE = C::STAGE_BYTES, BK = C::BK, NS = C::NS;
@@ -326,7 +365,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     // tile (the other workgroup covers that) instead of being carried from the one before: with 128 registers
     // for accumulators and fragments the compiler otherwise moves descriptors into vector registers, which the
     // load cannot take.
-    constexpr bool REBIND = C::OCC == 2;
+    constexpr bool REBIND = C::OCC == 2 && !ONE;
     typename AT::Frag fa[TM];
     typename BT::Frag fb[TNN];
     // First row of the wave's block i of 32 rows.  In the 64-k loops the waves' blocks alternate, so that a tile
@@ -338,33 +377,8 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     for (int j = 0; j < TNN; ++j) fb[j].init(wn * WN + j * 32, lane);
 
     // ---- tile number -> (expert, tile) -----------------------------------------------
-    // Only tiles that exist are numbered: an expert with fewer rows than the capacity has fewer
-    // tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups,
-    // which take the numbers b, b + grid, ..., all get the same amount of work whatever the spread
-    // of the counts.  The tile rows that an expert fills by more than half come first, expert
-    // by expert; a last tile row with fewer rows is numbered after all of those, since it takes less
-    // time (the 64-k loops multiply only the blocks of rows that hold something) and belongs at
-    // the end of a workgroup's list.  Lane l of every wavefront holds the tile rows of expert l
-    // (E <= 64); inclusive scans over the lanes give the numbers at which each expert ends.
-    int lane_tm = 0, lane_tail = 0;      // such tile rows of expert `lane`, and whether a last one with fewer rows follows
-    if (lane < g.E) {
-        int rows = 0;
-        const int segs = (LAY == GEMM_TN && g.k_segs > 1) ? g.k_segs : 1;
-        for (int sg = 0; sg < segs; ++sg) rows += g.counts[sg * g.E + lane];
-        if (LAY == GEMM_TN) lane_tm = (rows > 0 || EPI == EPI_STORE_F32) ? tiles_m : 0;   // a plain store still writes zeros
-        else {
-            lane_tm = min(tiles_m, (rows + BM / 2 - 1) / BM);
-            lane_tail = (lane_tm < tiles_m && rows > lane_tm * BM) ? 1 : 0;
-        }
-    }
-    int lane_end = lane_tm * tiles_n, tail_end = lane_tail;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(lane_end, off, 64), q = LAY == GEMM_TN ? 0 : __shfl_up(tail_end, off, 64);
-        if (lane >= off) { lane_end += o; tail_end += q; }
-    }
-    const int nwhole = __builtin_amdgcn_readlane(lane_end, 63);
-    const int nblocks = nwhole + __builtin_amdgcn_readlane(tail_end, 63) * tiles_n;
+    const int lane_tm = tiles.lane_tm, lane_end = tiles.lane_end, tail_end = tiles.tail_end;
+    const int nwhole = tiles.nwhole, nblocks = tiles.nblocks;
     // Tiles are numbered expert by expert, in groups of 4 tile-rows walked column by
     // column, so 32 consecutive numbers form a 4 x 8 block that shares 4 A panels and 8
     // B panels.  Hardware deals consecutive workgroup ids round-robin to the 8 XCDs (each
@@ -418,7 +432,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         return true;
     };
     auto next_tile = [&](int b, TileCoord& t) -> int {          // first tile of this workgroup at or after b, or -1
-        for (; b < nblocks; b += (int)gridDim.x)
+        for (; b < nblocks; b += step)
             if (decode(b, t)) return b;
         return -1;
     };
@@ -532,7 +546,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
     };
 
     TileCoord cur;
-    int vb = next_tile(blockIdx.x, cur);
+    int vb = next_tile(b0, cur);
     if (vb < 0) return;
     AT ta;
     BT tb;
@@ -694,19 +708,19 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 char* st2 = smem + (s3 == 0 ? NS - 1 : s3 - 1) * STAGE;      // of stage t + NS-1
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
                     follow(m, R64_G0, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 1, st); },
                            [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + l); });
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
                     follow(m, R64_G1, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 2, st); },
                            [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + l); });
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
                     follow(m, R64_G2, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, st); },
                            [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + R64_G1 + l); });
                 }
@@ -716,7 +730,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
                     follow(m, R64_G3, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 0, st1); },
                            [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st, (t + NS) * BK, l); });
                 }
@@ -822,9 +836,12 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
             bind(nx, ta2, tb2, l);
         };
         KCursor kc2 = {0, 0, 0};
-        const int vn = next_tile(vb + (int)gridDim.x, nx);
-        if (vn < 0) nx = cur;                        // (bound all the same, and never used)
-        if constexpr (!LATE_BIND) bind(nx, ta2, tb2, lane);
+        int vn = -1;
+        if constexpr (!ONE) {
+            vn = next_tile(vb + step, nx);
+            if (vn < 0) nx = cur;                    // (bound all the same, and never used)
+            if constexpr (!LATE_BIND) bind(nx, ta2, tb2, lane);
+        }
 
         // ---- epilogue -----------------------------------------------------------------------
         // An MFMA accumulator holds one row per lane (row = lane & 31, four consecutive
@@ -839,6 +856,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         // A pass moves 32 rows x CW columns of the wave's block (CW = the block's width, or 64 where the
         // staging region is one ring unit).
         constexpr int CPRW = CW / 8;                 // 8-column pieces per row of a pass
+        constexpr int SW = CW >= 64 ? 15 : CW / 4 - 1;       // the row bits that the 16-byte chunks of a staged row are swizzled by
         constexpr int NPIECE = 32 * CPRW / 64;       // pieces per lane
         constexpr int NCH = WN / CW, TJ = CW / 32;   // passes per 32 rows; 32-column accumulator blocks per pass
         constexpr int NPASS = TM * NCH;
@@ -939,7 +957,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 for (int g4 = 0; g4 < 4; ++g4) {
                     const int cch = (jj * 32 + g4 * 8 + ehalf * 4) >> 2;
                     float4 v = make_float4(acc[i][j][g4 * 4 + 0], acc[i][j][g4 * 4 + 1], acc[i][j][g4 * 4 + 2], acc[i][j][g4 * 4 + 3]);
-                    *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & 15)) << 2)) = v;
+                    *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & SW)) << 2)) = v;
                 }
             }
             if constexpr (READS && PB == 2) {
@@ -954,12 +972,12 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
             auto read_piece = [&](int t) {
                 if constexpr (CES == 4) {
                     const int r0 = urow + UROWS * (2 * t), r1 = r0 + UROWS;
-                    lo[t] = *reinterpret_cast<const float4*>(stage + r0 * CW + ((uc4 ^ (r0 & 15)) << 2));
-                    hi[t] = *reinterpret_cast<const float4*>(stage + r1 * CW + ((uc4 ^ (r1 & 15)) << 2));
+                    lo[t] = *reinterpret_cast<const float4*>(stage + r0 * CW + ((uc4 ^ (r0 & SW)) << 2));
+                    hi[t] = *reinterpret_cast<const float4*>(stage + r1 * CW + ((uc4 ^ (r1 & SW)) << 2));
                 } else {
                     const int row = RSTEP * t + prow;
-                    lo[t] = *reinterpret_cast<const float4*>(stage + row * CW + (((2 * c8) ^ (row & 15)) << 2));
-                    hi[t] = *reinterpret_cast<const float4*>(stage + row * CW + (((2 * c8 + 1) ^ (row & 15)) << 2));
+                    lo[t] = *reinterpret_cast<const float4*>(stage + row * CW + (((2 * c8) ^ (row & SW)) << 2));
+                    hi[t] = *reinterpret_cast<const float4*>(stage + row * CW + (((2 * c8 + 1) ^ (row & SW)) << 2));
                 }
             };
             if constexpr (HOIST) {
@@ -1047,8 +1065,10 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
             }
             // the next tile's first operand tiles start their trip once the first pass is through
             // (earlier, and this pass's own reads would have to wait behind them)
-            if constexpr (LATE_BIND) { if (ps == 0) bind_again(); }
-            if (ps == 0 && vn >= 0) issue_early(nx, kc2, ta2, tb2);
+            if constexpr (!ONE) {
+                if constexpr (LATE_BIND) { if (ps == 0) bind_again(); }
+                if (ps == 0 && vn >= 0) issue_early(nx, kc2, ta2, tb2);
+            }
         }
         if constexpr (EPI == EPI_DGELU && WN != DW_COLS) {
             if (g.dw_part) {
@@ -1076,7 +1096,7 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
                 }
             }
         }
-        if (vn < 0) break;
+        if (ONE || vn < 0) break;
         // Everything this wave has in flight is through: the next tile's first operand tiles have
         // landed and the epilogue's stores are written.  (Counting on the stores being younger than
         // the loads would save waiting for the last of them, but the main loop's third wait would
@@ -1092,6 +1112,52 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
         vb = vn;
         first = false;
     }
+}
+
+// Persistent workgroups: the grid has one workgroup per CU (two where two fit), and workgroup b works through
+// the tiles b, b + grid, b + 2 grid, ...
+template <int LAY, int EPI, typename C>
+__global__ __launch_bounds__(C::THREADS) __attribute__((amdgpu_waves_per_eu(C::OCC, C::OCC)))
+void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+    gemm_tiles<LAY, EPI, C, false>(g, tiles_m, tiles_n, number_tiles<LAY, EPI, C>(g, tiles_m, tiles_n, threadIdx.x & 63),
+                                   (int)blockIdx.x, (int)gridDim.x);
+}
+
+// What follows GeLU-backward - the input gradient dZ W1^T (NT) and the two weight gradients (TN), which do not depend
+// on each other - in one launch, a tile per workgroup: whichever CU is free takes the next one.  Alone, each
+// of the three ends in a round of tiles that leaves most of the chip idle (a launch of 128 or 144 tiles of 256 x 256 all
+// the way through), and a tile's time varies with the rows of its expert.  The tiles with the longest reduction, those
+// of the input gradient, come first.  A workgroup's first operand loads are not covered by another tile's epilogue as in
+// the persistent launches (2 to 3 us of a tile), so this is for launches of a few rounds.
+struct BackwardArgs {
+    GemmArgs d;                          // input gradient; not there if tiles_d == 0
+    GemmArgs w[2];                       // weight gradients
+    int tiles_dm, tiles_dn, tiles_wm[2], tiles_wn[2];
+};
+template <int EPI, typename CN, typename CT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT::OCC, CT::OCC)))
+void gemm_bf16_backward_kernel(BackwardArgs a) {
+    static_assert(CN::OCC == CT::OCC && CN::THREADS == 256 && CT::THREADS == 256, "tiles of one launch share its shape");
+    const int lane = threadIdx.x & 63;
+    int b = blockIdx.x;
+    if (a.tiles_dm > 0) {
+        const TileNumbers t = number_tiles<GEMM_NT, EPI_STORE, CN>(a.d, a.tiles_dm, a.tiles_dn, lane);
+        const int n = (t.nblocks + 7) & ~7;                // (a number keeps its place modulo the eight XCDs)
+        if (b < n) {
+            gemm_tiles<GEMM_NT, EPI_STORE, CN, true>(a.d, a.tiles_dm, a.tiles_dn, t, b, 1 << 30);
+            return;
+        }
+        b -= n;
+    }
+    TileNumbers t = number_tiles<GEMM_TN, EPI, CT>(a.w[0], a.tiles_wm[0], a.tiles_wn[0], lane);
+    int q = 0;
+    const int n = (t.nblocks + 7) & ~7;
+    if (b >= n) {
+        b -= n;
+        q = 1;
+        t = number_tiles<GEMM_TN, EPI, CT>(a.w[1], a.tiles_wm[1], a.tiles_wn[1], lane);
+    }
+    gemm_tiles<GEMM_TN, EPI, CT, true>(a.w[q], a.tiles_wm[q], a.tiles_wn[q], t, b, 1 << 30);
 }
 
 // Tile shapes in use.  The first two cover 256 x 256 per workgroup with four waves of 128 x 128, one per SIMD.
@@ -1119,6 +1185,8 @@ template <int EPI> struct CfgFor<GEMM_TN, EPI> { typedef Cfg4 type; };
 typedef TileCfg<256, 128, 64, 3, 2, 2, 1, LOOP_R64> CfgM;
 typedef TileCfg<128, 128, 32, 5, 2, 2, 2, LOOP_PIPE32> CfgS;
 typedef TileCfg<64, 128, 64, 6, 2, 2, 1, LOOP_R64> CfgT;
+//   CfgT2  CfgT with three stages, two workgroups per CU: beside CfgS in one launch.
+typedef TileCfg<64, 128, 64, 3, 2, 2, 2, LOOP_R64> CfgT2;
 
 int gemm_bf16_dw_parts(int H) { return (H + 2 * DW_COLS - 1) / (2 * DW_COLS) * 2; }
 
@@ -1235,7 +1303,7 @@ void gemm_bf16_tile(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, int* ro
     *cols = c.bn;
 }
 
-moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
+static moe_status check_args(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a) {
     if (a.dw_part && a.dw_parts != gemm_bf16_dw_parts(a.N)) return MOE_ERR_SHAPE;
     // operand rows must be 16-byte aligned in memory
     if ((a.lda | a.ldb) & 7) return MOE_ERR_UNSUPPORTED;
@@ -1255,6 +1323,79 @@ moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStr
         if (lay == GEMM_TN || a.a_row_limit <= 0) return MOE_ERR_UNSUPPORTED;
         if (((long long)a.a_row_limit + 1) * a.lda * 2 >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
     }
+    return MOE_OK;
+}
+
+// Rounds of tiles from which on the persistent launches one by one are the faster ones: of 32 768 tokens, 2048/8192, 16
+// experts, two partitions (2 x 16 rounds) the step takes 14.55 ms with them and 14.64 with both weight gradients
+// together; 8192 tokens, 768/3072, 64 experts (18 rounds of weight gradients, 3 of the input gradient) 1.35 and 1.33 ms.
+// Below: 16 384 tokens, 1024/4096, 8 experts, four partitions (0.6 + 4 rounds; 108 + 97 + 94 us one by one) 3.03 and 2.85
+// ms, 16 unevenly loaded experts 2.94 and 2.72, 4096 tokens, 512/2048 435 and 397 us.
+constexpr int BACKWARD_ROUNDS = 24;
+
+template <int EPI, typename CN, typename CT>
+static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, hipStream_t s, bool* done) {
+    BackwardArgs b = {};
+    b.w[0] = w2;
+    b.w[1] = w1;
+    int blocks = 0;
+    if (dgrad) {
+        b.d = *dgrad;
+        b.tiles_dm = (dgrad->Cp + CN::BM - 1) / CN::BM;
+        b.tiles_dn = (dgrad->N + CN::BN - 1) / CN::BN;
+        blocks += (dgrad->E * b.tiles_dm * b.tiles_dn + 7) / 8 * 8;
+    }
+    for (int q = 0; q < 2; ++q) {
+        b.tiles_wm[q] = (b.w[q].Mo + CT::BM - 1) / CT::BM;
+        b.tiles_wn[q] = (b.w[q].N + CT::BN - 1) / CT::BN;
+        blocks += (b.w[q].E * b.tiles_wm[q] * b.tiles_wn[q] + 7) / 8 * 8;
+    }
+    *done = blocks <= BACKWARD_ROUNDS * CT::OCC * persistent_grid();
+    if (!*done) return MOE_OK;
+    constexpr int lds = CN::LDS_BYTES > CT::LDS_BYTES ? CN::LDS_BYTES : CT::LDS_BYTES;
+    auto kern = gemm_bf16_backward_kernel<EPI, CN, CT>;
+    static bool attr_done = false;
+    if (!attr_done) {
+        HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        attr_done = true;
+    }
+    {
+        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, b);
+    }
+    count_launch(LC_GEMM, dgrad ? 3 : 2);
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
+}
+
+template <int EPI>
+static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, hipStream_t s, bool* done) {
+    // (the shapes are those of the launches by themselves; shapes with one workgroup per CU and with two do not mix)
+    const int cw = tile_choice(GEMM_TN, EPI, w2), cd = dgrad ? tile_choice(GEMM_NT, EPI_STORE, *dgrad) : cw;
+    if (cw == 1 || tile_choice(GEMM_TN, EPI, w1) != cw || w2.free_cus > 0) return MOE_OK;
+    if (cw == 2) {
+        if (cd < 2) return MOE_OK;
+        if (cd == 3) return launch_backward<EPI, CfgT2, CfgS>(dgrad, w2, w1, s, done);
+        return launch_backward<EPI, CfgS, CfgS>(dgrad, w2, w1, s, done);
+    }
+    if (cd == 2) return MOE_OK;
+    if (cd == 1) return launch_backward<EPI, CfgM, Cfg4>(dgrad, w2, w1, s, done);
+    if (cd == 3) return launch_backward<EPI, CfgT, Cfg4>(dgrad, w2, w1, s, done);
+    return launch_backward<EPI, CfgW, Cfg4>(dgrad, w2, w1, s, done);
+}
+
+moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s,
+                              bool* done) {
+    *done = false;
+    if (dgrad) MOE_TRY(check_args(GEMM_NT, EPI_STORE, *dgrad));
+    MOE_TRY(check_args(GEMM_TN, epi, w2));
+    MOE_TRY(check_args(GEMM_TN, epi, w1));
+    return epi == EPI_STORE_F32 ? backward_cfg<EPI_STORE_F32>(dgrad, w2, w1, s, done)
+                                : backward_cfg<EPI_ACCUM_F32>(dgrad, w2, w1, s, done);
+}
+
+moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {
+    MOE_TRY(check_args(lay, epi, a));
     if (lay == GEMM_NN && epi == EPI_STORE) return launch_cfg<GEMM_NN, EPI_STORE>(a, s);
     if (lay == GEMM_NN && epi == EPI_GELU) return launch_cfg<GEMM_NN, EPI_GELU>(a, s);
     if (lay == GEMM_NN && epi == EPI_SCATTER) return launch_cfg<GEMM_NN, EPI_SCATTER>(a, s);

@@ -97,11 +97,9 @@ template <bool KC> struct FOperand {
     }
 };
 
+// Tile (tm, tn) of expert e
 template <int LAY, int EPI>
-__global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_kernel(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) char smem[F_NS * 2 * F_TILE];
-    const int e = blockIdx.z;
-    const int tm = blockIdx.y, tn = blockIdx.x;
+__device__ __forceinline__ void gemm_f32_one(const GemmArgs& g, int e, int tm, int tn, char* smem) {
     const int rows = g.counts[e];
     const int Mdim = LAY == GEMM_TN ? g.Mo : rows, Kdim = LAY == GEMM_TN ? rows : g.K;
     const int m0 = tm * F_BM, n0 = tn * F_BN;
@@ -180,6 +178,36 @@ __global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_kernel(GemmArgs g) {
     }
 }
 
+template <int LAY, int EPI>
+__global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_kernel(GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) char smem[F_NS * 2 * F_TILE];
+    gemm_f32_one<LAY, EPI>(g, blockIdx.z, blockIdx.y, blockIdx.x, smem);
+}
+
+// The input gradient (tiles_dm = 0: not there) and the two weight gradients, which do not depend on each other, in one
+// launch: the tiles of the first, which take longest, fill up with those of the others instead of leaving the chip
+// half idle in a last round.
+struct F32BackwardArgs {
+    GemmArgs d, w[2];
+    int tiles_dm, tiles_dn, tiles_wm[2], tiles_wn[2];
+};
+template <int EPI>
+__global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_backward_kernel(F32BackwardArgs a) {
+    __shared__ __attribute__((aligned(16))) char smem[F_NS * 2 * F_TILE];
+    int b = blockIdx.x;
+    const int nd = a.d.E * a.tiles_dm * a.tiles_dn;
+    if (b < nd) {
+        const int per = a.tiles_dm * a.tiles_dn, e = b / per, r = b - e * per, tm = r / a.tiles_dn;
+        gemm_f32_one<GEMM_NT, EPI_STORE>(a.d, e, tm, r - tm * a.tiles_dn, smem);
+        return;
+    }
+    b -= nd;
+    const int n2 = a.w[0].E * a.tiles_wm[0] * a.tiles_wn[0], q = b >= n2 ? 1 : 0;
+    b -= q * n2;
+    const int tn = a.tiles_wn[q], per = a.tiles_wm[q] * tn, e = b / per, r = b - e * per, tm = r / tn;
+    gemm_f32_one<GEMM_TN, EPI>(a.w[q], e, tm, r - tm * tn, smem);
+}
+
 void gemm_f32_tile(int* rows, int* cols) { *rows = F_BM; *cols = F_BN; }
 
 int gemm_f32_dw_parts(int H) { return (H + F_BN - 1) / F_BN; }
@@ -193,6 +221,36 @@ static moe_status launch_f32(const GemmArgs& a, hipStream_t s) {
         hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI>), dim3(tiles_n, tiles_m, a.E), dim3(F_THREADS), 0, s, a);
     }
     count_launch(LC_GEMM);
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
+}
+
+moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s) {
+    F32BackwardArgs b = {};
+    b.w[0] = w2;
+    b.w[1] = w1;
+    auto tiles = [](int n, int t) { return (n + t - 1) / t; };
+    if (dgrad) { b.d = *dgrad; b.tiles_dm = tiles(dgrad->Cp, F_BM); b.tiles_dn = tiles(dgrad->N, F_BN); }
+    long long blocks = (long long)b.d.E * b.tiles_dm * b.tiles_dn;
+    for (int q = 0; q < 2; ++q) {
+        b.tiles_wm[q] = tiles(b.w[q].Mo, F_BM);
+        b.tiles_wn[q] = tiles(b.w[q].N, F_BN);
+        blocks += (long long)b.w[q].E * b.tiles_wm[q] * b.tiles_wn[q];
+    }
+    // (one linear grid: beyond what one launch takes, the three are launched one by one)
+    if (blocks > 0x7fffffff / F_THREADS) {
+        if (dgrad) MOE_TRY(gemm_f32(GEMM_NT, EPI_STORE, *dgrad, s));
+        MOE_TRY(gemm_f32(GEMM_TN, epi, w2, s));
+        return gemm_f32(GEMM_TN, epi, w1, s);
+    }
+    {
+        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1);
+        if (epi == EPI_STORE_F32)
+            hipLaunchKernelGGL((gemm_f32_backward_kernel<EPI_STORE_F32>), dim3((unsigned)blocks), dim3(F_THREADS), 0, s, b);
+        else
+            hipLaunchKernelGGL((gemm_f32_backward_kernel<EPI_ACCUM_F32>), dim3((unsigned)blocks), dim3(F_THREADS), 0, s, b);
+    }
+    count_launch(LC_GEMM, dgrad ? 3 : 2);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

@@ -288,15 +288,18 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
             // C'_p: everything but the weight gradients
             HIP_TRY(ord.wait(s1, evS[p]));
             if (p >= 2) HIP_TRY(ord.wait(s1, evD[p - 2]));
+            // (the weight gradients of a whole group come after its last partition: Section III-B's per-partition
+            // schedule when G = 1.  On one stream the last partition's input gradient shares their launch; on two S'_p
+            // is to start as soon as it is there.)
+            const bool group_ends = p % G == G - 1 || p == n - 1, together = group_ends && ord.one_stream;
             MOE_TRY(ffn_bwd_main(d, p, recompute ? 1 : 0, DIbuf(p), Zbuf(p), dDObuf(p), counts, slot_w, W1, W2,
-                                 dZbuf(p), dDIbuf(p), dw_in_gemm ? dwpart(p) : nullptr, s1));
+                                 dZbuf(p), dDIbuf(p), dw_in_gemm ? dwpart(p) : nullptr, s1, !together));
             HIP_TRY(ord.record(evC[p], s1));
-            // the weight gradients of a whole group after its last partition (Section III-B's per-partition
-            // schedule when G = 1)
-            if (p % G == G - 1 || p == n - 1) {
+            if (group_ends) {
                 const int p0 = p / G * G;
                 MOE_TRY(ffn_wgrad(d, p0, p - p0 + 1, d.overwrite && p0 == 0, DIbuf(p0), Zbuf(p0), dDObuf(p0), dZbuf(p0),
-                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s1));
+                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s1,
+                                  together ? W1 : nullptr, dDIbuf(p)));
                 HIP_TRY(ord.record(evW[p / G], s1));
             }
         }

@@ -110,6 +110,21 @@ def test_expert_ffn_in_every_tile_shape(M, H, counts, Cp, mean, recompute, overw
     _run("bf16", M, H, counts, Cp, 13, recompute, overwrite, mean, tiles)
 
 
+# backward's last three GEMMs share a launch where their tiles go together (the tests above: two workgroups per CU, and
+# 256 x 256 with 256 x 256 and 256 x 128): flat input-gradient tiles beside large ones, and tiles that do not go together
+@pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("M,H,E,Cp,dgrad,dw", [
+    (136, 3080, 16, 70, FLAT, LARGE),
+    (136, 520, 64, 257, HALF, LARGE),
+    (136, 1032, 32, 257, SMALL, LARGE),         # one workgroup per CU and two: the input gradient by itself
+    (1032, 264, 16, 129, HALF, SMALL),
+], ids=["flat_large", "half_large", "small_large", "half_small"])
+def test_last_gradients_in_one_launch(M, H, E, Cp, dgrad, dw, recompute, overwrite):
+    counts = tuple((0, Cp, 1, 64, 65, Cp - 1, 33)[e % 7] for e in range(E))
+    dw = dw if overwrite else SMALL              # sums that are added to go into smaller tiles at these sizes
+    _run("bf16", M, H, counts, Cp, 17, recompute, overwrite, tiles=dict(dgrad=dgrad, dW2=dw, dW1=dw))
+
+
 # float gradients of more than 2 GiB per expert, with columns that end inside a tile: the offset that stands for "out
 # of range" is then smaller than the gradients (the reference takes some 40 GB)
 @pytest.mark.parametrize("overwrite", [0, 1])
