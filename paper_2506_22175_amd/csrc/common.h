@@ -149,8 +149,8 @@ enum ProfKind {
 };
 struct ProfScope {
     int idx; hipStream_t s;
-    // one launch may do the work of several: `units` of `kind`, and one of `also`
-    ProfScope(int kind, hipStream_t stream, int units = 1, int also = -1);
+    // one launch may do the work of several: `units` of `kind`, and `also_units` of `also`
+    ProfScope(int kind, hipStream_t stream, int units = 1, int also = -1, int also_units = 1);
     ~ProfScope();
 };
 
@@ -236,7 +236,36 @@ moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void*
                      const void* dZ, long long strideM, long long strideH, const int* counts,
                      float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1 = nullptr, void* dDI = nullptr);
 
-// k = 1 with the fused combine: rows of y of dropped tokens <- 0 (permute.hip)
-moe_status zero_dropped(const Dims& d, const int* slot, void* y, hipStream_t s);
+// ---- row permutations and gate backward of np consecutive partitions from p0 on (permute.hip) ----
+// Pointers are partition p0's, strides lead from one partition's buffer to the next one's.
+struct RowMove { const void* src; void* dst; long long stride; };      // token-major rows, partition buffer, bytes
+// S: rows of up to two sources to the experts.  dw != NULL (one source): dw = <src, DO row> on the way; y != NULL: and
+// the combine of the same DO rows with weights w.
+moe_status dispatch_rows(const Dims& d, int p0, int np, const RowMove* moves, int n_moves, const int* slot,
+                         const void* DO, long long DO_stride, float* dw, const float* w, void* y, hipStream_t s);
+moe_status combine_rows(const Dims& d, int p0, int np, const void* DO, long long DO_stride, const int* slot, const float* w,
+                        void* y, hipStream_t s);
+// Partial sums of the gate-weight gradient, part[b][i] per partition, and where their totals go.
+struct GateSums {
+    const float* part;
+    long long part_stride;               // floats from one partition's partial sums to the next one's
+    float* dWg;
+    int nblk, ME, np, store;             // blocks per partition, outputs, partitions; store: the first total is stored, not added
+};
+// Gate backward.  part: gate_part_bytes per partition, part_stride floats apart; dLt (bfloat16): gate_dlt_bytes per
+// partition, one behind the other.  sums != NULL: the partial sums are left for dispatch_bwd_rows to add up.
+moe_status gate_bwd_rows(const Dims& d, int p0, int np, const void* x, const float* logits, const int* idx, const int* slot,
+                         const float* dw, const float* dw_part, long long dw_part_stride, int parts, float* dL, float* dWg,
+                         float* part, long long part_stride, void* dLt, hipStream_t s, GateSums* sums);
+size_t gate_part_bytes(const Dims& d);
+size_t gate_dlt_bytes(const Dims& d);
+size_t gate_dlt_offset(const Dims& d);           // of the first partition's dLt in the buffer of moe_gate_scratch_bytes
+moe_status dispatch_bwd_rows(const Dims& d, int p0, int np, const void* dDI, long long dDI_stride, const int* slot,
+                             const float* dL, const void* Wg, void* dx, const GateSums* sums, hipStream_t s);
+
+// Slots of every partition (slots.hip); may be NULL: slot_w, rows (the map of moe_slot_rows), y (k = 1 with the fused
+// combine: rows of y of dropped tokens <- 0)
+moe_status assign_slots(const Dims& d, const int* topk_idx, const float* topk_w, int* slot, int* counts, float* slot_w,
+                        int* rows, void* y, int* hist, hipStream_t s);
 
 }  // namespace moe

@@ -31,6 +31,7 @@ struct Workspace {
     // routing-class data
     size_t slot_w, dw, dw_part, dL, gate_scratch, slot_scratch, rows;
     size_t bufM, bufH, dw_part_bytes;
+    bool gate_pairs;                  // gate backward may take two partitions in one launch (one stream)
     size_t total, saved, temp, routing;
 };
 
@@ -46,6 +47,17 @@ struct Offload {
     size_t DI = 0, Z = 0;        // offsets in host; n buffers each (when offloaded)
     hipStream_t s2 = nullptr;
 };
+
+// How many of the caller's streams a schedule uses.  One partition is one chain of kernels: a second stream has
+// nothing to run beside it but the last gate kernels beside weight-gradient GEMMs that leave them no compute unit.
+// Several small partitions lose more to the hops between the streams than they gain side by side.  Whole steps, two
+// streams / one: 0.2 GFLOP a partition 1.3-1.5, 5 GFLOP 1.2, 50-120 GFLOP 1.02-1.07, 412 GFLOP 1.00-1.01, 2.4 and 6.6
+// TFLOP 0.984 and 0.995; float32 takes about ten times as long per operation.
+static int streams_used(const Dims& d) {
+    if (mode_offloads(d.reuse)) return 3;
+    const double work = 12.0 * (double)d.Tp * d.k * d.M * d.H * (d.dtype == MOE_F32 ? 10.0 : 1.0);
+    return (d.n == 1 || work < 5e11) && d.free_cus == 0 ? 1 : 2;
+}
 
 static moe_status plan(const moe_config* cfg, const Dims& d, Workspace* w) {
     w->bufM = align_up((size_t)d.Rp * d.M * d.es);
@@ -81,7 +93,9 @@ static moe_status plan(const moe_config* cfg, const Dims& d, Workspace* w) {
     w->dw_part_bytes = align_up((size_t)d.Rp * parts * sizeof(float));
     w->dw_part = take(w->dw_part_bytes * 2);
     w->dL = take((size_t)d.T * d.E * sizeof(float));
-    w->gate_scratch = take(gs);
+    // (two partitions at a time: two transposed dL; where their second partial sums go, see gate_sums_space)
+    w->gate_pairs = d.n > 1 && streams_used(d) == 1;
+    w->gate_scratch = take(gs + (w->gate_pairs ? gate_dlt_bytes(d) : 0));
     w->slot_scratch = take(ss);
     w->rows = take((d.fuse || d.fcomb) ? (size_t)d.n * d.Rp * sizeof(int) : 0);
     w->routing = off - r0;
@@ -131,21 +145,136 @@ static bool first_backward_dispatch_can_go_early(const Dims& d, const Workspace&
     return true;
 }
 
-// Cross-stream order, left out where everything runs on one stream: its own order already is the order in which
-// the events would be recorded and waited for.  A record and a wait cost about 4 us of the host and a hop between
-// streams 10 us and more of the GPU.
-struct Order {
-    bool one_stream;
-    hipError_t record(hipEvent_t e, hipStream_t s) const { return one_stream ? hipSuccess : hipEventRecord(e, s); }
-    hipError_t wait(hipStream_t s, hipEvent_t e) const { return one_stream ? hipSuccess : hipStreamWaitEvent(s, e, 0); }
-};
+// S'_p of partitions p0 .. p0 + np - 1: gate backward, then rows of dDI back to token order (in whose launch the partial
+// sums of the gate-weight gradient are added up).  part: see gate_bwd_rows.
+static moe_status back_to_tokens(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws, int p0, int np,
+                                 const void* x, const float* logits, const int* topk_idx, const int* slot, const void* Wg,
+                                 bool dw_in_gemm, void* dx, float* dWg, const float* second_part, hipStream_t s0) {
+    int parts = 0;
+    MOE_TRY(moe_dw_parts(cfg, &parts));
+    const int turn = p0 % 2 == 0 ? 1 : -1;           // from p0's buffer of two to the next partition's
+    float* part = (float*)(ws + w.gate_scratch);
+    GateSums sums;
+    MOE_TRY(gate_bwd_rows(d, p0, np, x, logits, topk_idx, slot, dw_in_gemm ? nullptr : (const float*)(ws + w.dw),
+                          dw_in_gemm ? (const float*)(ws + w.dw_part + w.dw_part_bytes * (p0 % 2)) : nullptr,
+                          turn * (long long)(w.dw_part_bytes / sizeof(float)), parts, (float*)(ws + w.dL), dWg, part,
+                          second_part ? second_part - part : 0, ws + w.gate_scratch + gate_dlt_offset(d), s0, &sums));
+    return dispatch_bwd_rows(d, p0, np, ws + w.dDI + w.bufM * (p0 % 2), turn * (long long)w.bufM, slot,
+                             (const float*)(ws + w.dL), Wg, dx, &sums, s0);
+}
+
+// ---- everything on one stream ---------------------------------------------------------
+//
+// The order of the stream is all the order there is: no events (a record and a wait cost about 4 us of the host and a hop
+// between streams 10 us and more of the GPU).  A launch costs 4.6 us of the GPU however little it does, and a permutation
+// of a small partition little more, so the permutations run for as many partitions at once as there are buffers:
+// forward sends the rows of a whole ring of T_DI buffers, then runs their GEMMs, then combines; backward takes
+// partitions two by two (dT_DI has two buffers).  What a partition's kernels compute does not
+// depend on it.  4096 tokens, 512/2048, two partitions with recomputation: 27 launches and 367 us one by one, 16 and 344
+// so; 3003 tokens, 776/2600, three partitions: 39 and 695, 22 and 644.
+
+// buffers of consecutive partitions in a ring: bytes from p's to the next one's
+static long long ring_step(int p, int ring, size_t bytes) {
+    return ((long long)((p + 1) % ring) - p % ring) * (long long)bytes;
+}
+
+// later: the combine is left to backward, whose dispatch of dy reads the same rows (see chain_backward)
+static moe_status chain_forward(const Dims& d, const Workspace& w, char* ws, const void* x, const void* W1, const void* W2,
+                                void* y, const float* topk_w, const int* slot, const int* counts, bool later, hipStream_t s) {
+    const int n = d.n;
+    const int* rows = (d.fuse || d.fcomb) ? (const int*)(ws + w.rows) : nullptr;
+    auto DIbuf = [&](int p) { return ws + w.DI + w.bufM * (p % w.nDI); };
+    auto DObuf = [&](int p) { return w.nDO ? ws + w.DO + w.bufM * (p % w.nDO) : nullptr; };
+    auto Zbuf = [&](int p) { return ws + w.Z + w.bufH * (p % w.nZ); };
+    const bool keepZ = !mode_recomputes(d.reuse);
+    const int unit_S = d.fuse ? n : w.nDI, unit_R = w.nDO && !later ? w.nDO : n;
+    const int unit = unit_S < unit_R ? unit_S : unit_R;       // (a ring each: all of n buffers, or the same number)
+    for (int p0 = 0; p0 < n; p0 += unit) {
+        const int np = n - p0 < unit ? n - p0 : unit;
+        if (!d.fuse) {
+            const RowMove m = {x, DIbuf(p0), (long long)w.bufM};
+            MOE_TRY(dispatch_rows(d, p0, np, &m, 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
+        }
+        for (int p = p0; p < p0 + np; ++p)
+            MOE_TRY(ffn_fwd(d, p, d.fuse ? x : (const void*)DIbuf(p), d.fuse ? rows : nullptr, counts, W1, W2,
+                            keepZ ? Zbuf(p) : nullptr, keepZ ? (void*)(ws + w.HT) : (void*)Zbuf(p), DObuf(p), s,
+                            d.fcomb ? rows : nullptr, (const float*)(ws + w.slot_w), y));
+        if (w.nDO && !later) MOE_TRY(combine_rows(d, p0, np, DObuf(p0), (long long)w.bufM, slot, topk_w, y, s));
+    }
+    return MOE_OK;
+}
+
+// Where the second of two partitions' partial sums of the gate-weight gradient can go: the first has the scratch buffer;
+// the second the partition's T_DO buffer, which nobody reads after its dispatch of dy (where T_DO is kept), or the row
+// dots of the GeLU-backward GEMM, which gate backward's first kernel has consumed by then.  NULL: too small.
+static float* gate_sums_space(const Dims& d, const Workspace& w, char* ws, int p, bool dw_in_gemm) {
+    const size_t need = gate_part_bytes(d);
+    if (!w.gate_pairs) return nullptr;
+    if (dw_in_gemm) return need <= 2 * w.dw_part_bytes ? (float*)(ws + w.dw_part) : nullptr;
+    return need <= w.bufM ? (float*)(ws + w.DO + w.bufM * (p % w.nDO)) : nullptr;
+}
+
+// y != NULL: forward's combine is still to be done, in the dispatch of dy.
+static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws,
+                                 const void* x, const void* dy, const void* Wg, const void* W1, const void* W2,
+                                 void* dx, float* dWg, float* dW1, float* dW2,
+                                 const float* logits, const int* topk_idx, const float* topk_w, const int* slot,
+                                 const int* counts, void* y, hipStream_t s) {
+    const int n = d.n, G = d.G;
+    const bool dw_in_gemm = d.reuse != MOE_REUSE_NONE || d.fcomb;     // (see backward)
+    const bool recompute = mode_recomputes(d.reuse);
+    const bool redispatch = w.nDI < n || d.fuse;
+    auto DIbuf = [&](int p) { return ws + w.DI + w.bufM * (p % w.nDI); };
+    auto DObuf = [&](int p) { return ws + w.DO + w.bufM * (p % w.nDO); };
+    auto Zbuf = [&](int p) { return ws + w.Z + w.bufH * (p % w.nZ); };
+    auto dZbuf = [&](int p) { return ws + w.HT + w.bufH * (p % G); };
+    auto dDObuf = [&](int p) { return ws + w.dDO + w.bufM * (p % w.ndDO); };
+    auto dDIbuf = [&](int p) { return ws + w.dDI + w.bufM * (p % 2); };
+    // partition p's buffer in a ring is free before the GEMMs of partition `now`: whoever had it last has had its weight
+    // gradients taken, which happens at the end of a group
+    auto is_free = [&](int p, int ring, int now) {
+        const int last = p - ring;
+        return last < 0 || (last / G + 1) * G <= now;
+    };
+    for (int p0 = 0; p0 < n;) {
+        const int np = p0 + 1 < n && w.ndDO >= 2 && is_free(p0 + 1, w.ndDO, p0) &&
+                       (!redispatch || (w.nDI >= 2 && is_free(p0 + 1, w.nDI, p0))) ? 2 : 1;
+        // R': rows of dy to the experts, rows of x again
+        const RowMove m[2] = {{dy, dDObuf(p0), ring_step(p0, w.ndDO, w.bufM)}, {x, DIbuf(p0), ring_step(p0, w.nDI, w.bufM)}};
+        if (dw_in_gemm) {
+            MOE_TRY(dispatch_rows(d, p0, np, m, redispatch ? 2 : 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
+        } else {
+            MOE_TRY(dispatch_rows(d, p0, np, m, 1, slot, DObuf(p0), ring_step(p0, w.nDO, w.bufM), (float*)(ws + w.dw), topk_w, y, s));
+            if (d.fuse) MOE_TRY(dispatch_rows(d, p0, np, m + 1, 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
+        }
+        for (int p = p0; p < p0 + np; ++p) {
+            // the last partition's input gradient shares the launch of its group's weight gradients
+            const bool group_ends = p % G == G - 1 || p == n - 1;
+            MOE_TRY(ffn_bwd_main(d, p, recompute ? 1 : 0, DIbuf(p), Zbuf(p), dDObuf(p), counts, (const float*)(ws + w.slot_w),
+                                 W1, W2, dZbuf(p), dDIbuf(p),
+                                 dw_in_gemm ? (float*)(ws + w.dw_part + w.dw_part_bytes * (p % 2)) : nullptr, s, !group_ends));
+            if (group_ends) {
+                const int g0 = p / G * G;
+                MOE_TRY(ffn_wgrad(d, g0, p - g0 + 1, d.overwrite && g0 == 0, DIbuf(g0), Zbuf(g0), dDObuf(g0), dZbuf(g0),
+                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s, W1, dDIbuf(p)));
+            }
+        }
+        float* second = np == 2 ? gate_sums_space(d, w, ws, p0 + 1, dw_in_gemm) : nullptr;
+        const int together = second ? 2 : 1;
+        for (int p = p0; p < p0 + np; p += together)
+            MOE_TRY(back_to_tokens(cfg, d, w, ws, p, together, x, logits, topk_idx, slot, Wg, dw_in_gemm, dx, dWg, second, s));
+        p0 += np;
+    }
+    return MOE_OK;
+}
+
+// ---- two streams (and a third for copies to the host) --------------------------------------
 
 static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws,
-                          const void* x, const void* Wg, const float* gate_bias, const void* W1, const void* W2,
-                          void* y, float* logits, int* topk_idx, float* topk_w, int* slot, int* counts,
-                          hipStream_t s0, hipStream_t s1, const Offload* off = nullptr, const void* dy_early = nullptr) {
+                          const void* x, const void* W1, const void* W2, void* y, const float* topk_w, const int* slot,
+                          const int* counts, hipStream_t s0, hipStream_t s1, const Offload* off = nullptr,
+                          const void* dy_early = nullptr) {
     const int n = d.n;
-    const Order ord = {s0 == s1 && !off};
     MOE_TRY(get_events(7 * (size_t)n + 2));
     hipEvent_t* evS = g_events.data();
     hipEvent_t* evC = evS + n;
@@ -156,14 +285,9 @@ static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace&
     hipEvent_t evCopies = g_events[7 * (size_t)n + 1];
     const bool off_di = off && mode_offloads_di(d.reuse), off_z = off && mode_offloads_z(d.reuse);
 
-    MOE_TRY(moe_route(cfg, x, Wg, gate_bias, logits, topk_idx, topk_w, s0));
-    MOE_TRY(moe_assign_slots(cfg, topk_idx, topk_w, slot, counts, (float*)(ws + w.slot_w),
-                             ws + w.slot_scratch, s0));
     const int* rows = (d.fuse || d.fcomb) ? (const int*)(ws + w.rows) : nullptr;
-    if (rows) MOE_TRY(moe_slot_rows(cfg, slot, (int*)(ws + w.rows), s0));
-    if (d.fcomb) MOE_TRY(zero_dropped(d, slot, y, s0));
-    HIP_TRY(ord.record(evFork, s0));
-    HIP_TRY(ord.wait(s1, evFork));
+    HIP_TRY(hipEventRecord(evFork, s0));
+    HIP_TRY(hipStreamWaitEvent(s1, evFork, 0));
 
     auto DIbuf = [&](int p) { return ws + w.DI + w.bufM * (p % w.nDI); };
     auto DObuf = [&](int p) { return w.nDO ? ws + w.DO + w.bufM * (p % w.nDO) : nullptr; };
@@ -174,30 +298,30 @@ static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace&
         if (p < n) {
             // S_p.  A shared T_DI buffer was last read by C_{p-2}; R_{p-2}, already
             // queued on this stream, waited for C_{p-2}.  Its copy to the host must be through too.
-            if (off_di && p >= w.nDI) HIP_TRY(ord.wait(s0, evDIout[p - w.nDI]));
+            if (off_di && p >= w.nDI) HIP_TRY(hipStreamWaitEvent(s0, evDIout[p - w.nDI], 0));
             // (with the gathered first GEMM there is no S kernel: C_p reads T_I through the row map)
             if (!d.fuse) MOE_TRY(moe_dispatch(cfg, p, x, slot, DIbuf(p), nullptr, nullptr, s0));
-            HIP_TRY(ord.record(evS[p], s0));
+            HIP_TRY(hipEventRecord(evS[p], s0));
             if (off_di) {
-                HIP_TRY(ord.wait(off->s2, evS[p]));
+                HIP_TRY(hipStreamWaitEvent(off->s2, evS[p], 0));
                 HIP_TRY(hipMemcpyAsync(off->host + off->DI + w.bufM * p, DIbuf(p), w.bufM, hipMemcpyDeviceToHost, off->s2));
-                HIP_TRY(ord.record(evDIout[p], off->s2));
+                HIP_TRY(hipEventRecord(evDIout[p], off->s2));
             }
             // C_p
-            HIP_TRY(ord.wait(s1, evS[p]));
-            if (w.nDO && p >= w.nDO) HIP_TRY(ord.wait(s1, evR[p - w.nDO]));   // T_DO buffer free again
-            if (off_z && p >= w.nZ) HIP_TRY(ord.wait(s1, evZout[p - w.nZ]));   // T_M buffer copied out
+            HIP_TRY(hipStreamWaitEvent(s1, evS[p], 0));
+            if (w.nDO && p >= w.nDO) HIP_TRY(hipStreamWaitEvent(s1, evR[p - w.nDO], 0));   // T_DO buffer free again
+            if (off_z && p >= w.nZ) HIP_TRY(hipStreamWaitEvent(s1, evZout[p - w.nZ], 0));   // T_M buffer copied out
             // with recomputation T_M is not kept: the activated rows go to the one
             // shared H-wide buffer and the pre-activation is not written at all
             void* Aout = keepZ ? (void*)(ws + w.HT) : (void*)Zbuf(p);
             MOE_TRY(ffn_fwd(d, p, d.fuse ? x : (const void*)DIbuf(p), d.fuse ? rows : nullptr, counts, W1, W2,
                             keepZ ? Zbuf(p) : nullptr, Aout, DObuf(p), s1,
                             d.fcomb ? rows : nullptr, (const float*)(ws + w.slot_w), y));
-            HIP_TRY(ord.record(evC[p], s1));
+            HIP_TRY(hipEventRecord(evC[p], s1));
             if (off_z) {
-                HIP_TRY(ord.wait(off->s2, evC[p]));
+                HIP_TRY(hipStreamWaitEvent(off->s2, evC[p], 0));
                 HIP_TRY(hipMemcpyAsync(off->host + off->Z + w.bufH * p, Zbuf(p), w.bufH, hipMemcpyDeviceToHost, off->s2));
-                HIP_TRY(ord.record(evZout[p], off->s2));
+                HIP_TRY(hipEventRecord(evZout[p], off->s2));
             }
         }
         if (p >= 1) {
@@ -208,16 +332,16 @@ static moe_status forward(const moe_config* cfg, const Dims& d, const Workspace&
                 // finds its event recorded
                 const bool reuse = d.reuse != MOE_REUSE_NONE;
                 MOE_TRY(dispatch_for_backward(cfg, d, w, ws, 0, x, dy_early, slot, w.nDI < n || d.fuse, reuse || d.fcomb, s0));
-                HIP_TRY(ord.record(evS[0], s0));
+                HIP_TRY(hipEventRecord(evS[0], s0));
             }
-            HIP_TRY(ord.wait(s0, evC[p - 1]));
+            HIP_TRY(hipStreamWaitEvent(s0, evC[p - 1], 0));
             if (!d.fcomb) MOE_TRY(moe_combine(cfg, p - 1, DObuf(p - 1), slot, topk_w, y, s0));
-            HIP_TRY(ord.record(evR[p - 1], s0));
+            HIP_TRY(hipEventRecord(evR[p - 1], s0));
         }
     }
     if (off_di || off_z) {                       // the host copies belong to what stream 0 has finished
-        HIP_TRY(ord.record(evCopies, off->s2));
-        HIP_TRY(ord.wait(s0, evCopies));
+        HIP_TRY(hipEventRecord(evCopies, off->s2));
+        HIP_TRY(hipStreamWaitEvent(s0, evCopies, 0));
     }
     return MOE_OK;
 }
@@ -228,7 +352,6 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
                            const float* logits, const int* topk_idx, const int* slot, const int* counts,
                            hipStream_t s0, hipStream_t s1, const Offload* off = nullptr, bool first_dispatch_done = false) {
     const int n = d.n, G = d.G;
-    const Order ord = {s0 == s1 && !off};
     MOE_TRY(get_events(7 * (size_t)n + 2));
     hipEvent_t* evS = g_events.data();        // R'_p done (rows of dy, and of x again, are in place)
     hipEvent_t* evC = evS + n;                // backward GEMMs of p done, weight gradients apart
@@ -250,82 +373,64 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
     auto dDObuf = [&](int p) { return ws + w.dDO + w.bufM * (p % w.ndDO); };
     auto dDIbuf = [&](int p) { return ws + w.dDI + w.bufM * (p % 2); };
     auto dwpart = [&](int p) { return (float*)(ws + w.dw_part + w.dw_part_bytes * (p % 2)); };
-    float* dw = (float*)(ws + w.dw);
-    float* dL = (float*)(ws + w.dL);
     const float* slot_w = (const float*)(ws + w.slot_w);
     // forward left T_DI of every partition in place unless buffers are shared or it never wrote any
     const bool redispatch = !off_di && (w.nDI < n || d.fuse);
 
-    HIP_TRY(ord.record(evFork, s0));
+    HIP_TRY(hipEventRecord(evFork, s0));
     // (whole step with R'_0 already queued: the GEMM stream goes straight on from forward's last GEMM; what its
     // first backward GEMMs touch is ordered by R'_0's event and by the stream itself)
-    if (!first_dispatch_done) HIP_TRY(ord.wait(s1, evFork));
+    if (!first_dispatch_done) HIP_TRY(hipStreamWaitEvent(s1, evFork, 0));
     // copies back into the shared buffers must not overtake the forward GEMMs that still read them
-    if (off_di || off_z) HIP_TRY(ord.wait(off->s2, evFork));
+    if (off_di || off_z) HIP_TRY(hipStreamWaitEvent(off->s2, evFork, 0));
 
     for (int p = 0; p <= n; ++p) {
         if (p < n && !(p == 0 && first_dispatch_done)) {
             // R'_p: rows of dy to the experts.  Their buffer (and the re-dispatched T_DI buffer) was last
             // read by partition p - (number of buffers): by its GEMMs and by the weight-gradient GEMMs of
             // its group, which come last.
-            if (p >= w.ndDO) HIP_TRY(ord.wait(s0, evW[(p - w.ndDO) / G]));
-            if (redispatch && p >= w.nDI && w.nDI != w.ndDO) HIP_TRY(ord.wait(s0, evW[(p - w.nDI) / G]));
+            if (p >= w.ndDO) HIP_TRY(hipStreamWaitEvent(s0, evW[(p - w.ndDO) / G], 0));
+            if (redispatch && p >= w.nDI && w.nDI != w.ndDO) HIP_TRY(hipStreamWaitEvent(s0, evW[(p - w.nDI) / G], 0));
             MOE_TRY(dispatch_for_backward(cfg, d, w, ws, p, x, dy, slot, redispatch, dw_in_gemm, s0));
-            HIP_TRY(ord.record(evS[p], s0));
+            HIP_TRY(hipEventRecord(evS[p], s0));
         }
         if (p < n) {
             if (off_di || off_z) {
                 // what was offloaded comes back into the shared buffers, last read by the GEMMs of p-2
                 // (the copy stream runs in order, so the forward copies are through)
-                if (p >= 2) HIP_TRY(ord.wait(off->s2, evW[p - 2]));
+                if (p >= 2) HIP_TRY(hipStreamWaitEvent(off->s2, evW[p - 2], 0));
                 if (off_di)
                     HIP_TRY(hipMemcpyAsync(DIbuf(p), off->host + off->DI + w.bufM * p, w.bufM, hipMemcpyHostToDevice, off->s2));
                 if (off_z)
                     HIP_TRY(hipMemcpyAsync(Zbuf(p), off->host + off->Z + w.bufH * p, w.bufH, hipMemcpyHostToDevice, off->s2));
-                HIP_TRY(ord.record(evIn[p], off->s2));
-                HIP_TRY(ord.wait(s1, evIn[p]));
+                HIP_TRY(hipEventRecord(evIn[p], off->s2));
+                HIP_TRY(hipStreamWaitEvent(s1, evIn[p], 0));
             }
             // C'_p: everything but the weight gradients
-            HIP_TRY(ord.wait(s1, evS[p]));
-            if (p >= 2) HIP_TRY(ord.wait(s1, evD[p - 2]));
-            // (the weight gradients of a whole group come after its last partition: Section III-B's per-partition
-            // schedule when G = 1.  On one stream the last partition's input gradient shares their launch; on two S'_p
-            // is to start as soon as it is there.)
-            const bool group_ends = p % G == G - 1 || p == n - 1, together = group_ends && ord.one_stream;
+            HIP_TRY(hipStreamWaitEvent(s1, evS[p], 0));
+            if (p >= 2) HIP_TRY(hipStreamWaitEvent(s1, evD[p - 2], 0));
             MOE_TRY(ffn_bwd_main(d, p, recompute ? 1 : 0, DIbuf(p), Zbuf(p), dDObuf(p), counts, slot_w, W1, W2,
-                                 dZbuf(p), dDIbuf(p), dw_in_gemm ? dwpart(p) : nullptr, s1, !together));
-            HIP_TRY(ord.record(evC[p], s1));
-            if (group_ends) {
+                                 dZbuf(p), dDIbuf(p), dw_in_gemm ? dwpart(p) : nullptr, s1));
+            HIP_TRY(hipEventRecord(evC[p], s1));
+            // the weight gradients of a whole group after its last partition (Section III-B's per-partition
+            // schedule when G = 1)
+            if (p % G == G - 1 || p == n - 1) {
                 const int p0 = p / G * G;
                 MOE_TRY(ffn_wgrad(d, p0, p - p0 + 1, d.overwrite && p0 == 0, DIbuf(p0), Zbuf(p0), dDObuf(p0), dZbuf(p0),
-                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s1,
-                                  together ? W1 : nullptr, dDIbuf(p)));
-                HIP_TRY(ord.record(evW[p / G], s1));
+                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s1));
+                HIP_TRY(hipEventRecord(evW[p / G], s1));
             }
         }
         if (p >= 1) {
             // S'_{p-1}: gate backward and rows of dDI back to token order
             const int q = p - 1;
-            HIP_TRY(ord.wait(s0, evC[q]));
-            MOE_TRY(moe_gate_bwd(cfg, q, x, logits, topk_idx, slot, dw_in_gemm ? nullptr : dw,
-                                 dw_in_gemm ? dwpart(q) : nullptr, dL, dWg, ws + w.gate_scratch, s0));
-            MOE_TRY(moe_dispatch_bwd(cfg, q, dDIbuf(q), slot, dL, Wg, dx, s0));
-            HIP_TRY(ord.record(evD[q], s0));
+            HIP_TRY(hipStreamWaitEvent(s0, evC[q], 0));
+            MOE_TRY(back_to_tokens(cfg, d, w, ws, q, 1, x, logits, topk_idx, slot, Wg, dw_in_gemm, dx, dWg, nullptr, s0));
+            HIP_TRY(hipEventRecord(evD[q], s0));
         }
     }
-    HIP_TRY(ord.wait(s0, evW[(n - 1) / G]));      // the last weight gradients belong to the step
+    HIP_TRY(hipStreamWaitEvent(s0, evW[(n - 1) / G], 0));      // the last weight gradients belong to the step
     return MOE_OK;
-}
-
-// How many of the caller's streams a schedule uses.  One partition is one chain of kernels: a second stream has
-// nothing to run beside it but the last gate kernels beside weight-gradient GEMMs that leave them no compute unit.
-// Several small partitions lose more to the hops between the streams than they gain side by side.  Whole steps, two
-// streams / one: 0.2 GFLOP a partition 1.3-1.5, 5 GFLOP 1.2, 50-120 GFLOP 1.02-1.07, 412 GFLOP 1.00-1.01, 2.4 and 6.6
-// TFLOP 0.984 and 0.995; float32 takes about ten times as long per operation.
-static int streams_used(const Dims& d) {
-    if (mode_offloads(d.reuse)) return 3;
-    const double work = 12.0 * (double)d.Tp * d.k * d.M * d.H * (d.dtype == MOE_F32 ? 10.0 : 1.0);
-    return (d.n == 1 || work < 5e11) && d.free_cus == 0 ? 1 : 2;
 }
 
 static moe_status setup(const moe_config* cfg, Dims* d, Workspace* w, void* workspace, size_t workspace_bytes,
@@ -342,6 +447,15 @@ static moe_status setup(const moe_config* cfg, Dims* d, Workspace* w, void* work
     *s1 = (hipStream_t)streams[1];
     if (streams_used(*d) == 1) *s1 = *s0;
     return MOE_OK;
+}
+
+// The gate and the slots of every partition.
+static moe_status gate(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws, const void* x, const void* Wg,
+                       const float* gate_bias, void* y, float* logits, int* topk_idx, float* topk_w, int* slot, int* counts,
+                       hipStream_t s) {
+    MOE_TRY(moe_route(cfg, x, Wg, gate_bias, logits, topk_idx, topk_w, s));
+    return assign_slots(d, topk_idx, topk_w, slot, counts, (float*)(ws + w.slot_w),
+                        d.fuse || d.fcomb ? (int*)(ws + w.rows) : nullptr, d.fcomb ? y : nullptr, (int*)(ws + w.slot_scratch), s);
 }
 
 }  // namespace moe
@@ -378,8 +492,9 @@ extern "C" moe_status moe_layer_forward(const moe_config* cfg, const void* x,
     Dims d; Workspace w; hipStream_t s0, s1;
     MOE_TRY(setup(cfg, &d, &w, workspace, workspace_bytes, streams, n_streams, &s0, &s1));
     if (!x || !Wg || !W1 || !W2 || !y || !logits || !topk_idx || !topk_w || !slot || !counts) return MOE_ERR_NULL;
-    return forward(cfg, d, w, (char*)workspace, x, Wg, gate_bias, W1, W2, y, logits, topk_idx, topk_w, slot,
-                   counts, s0, s1);
+    MOE_TRY(gate(cfg, d, w, (char*)workspace, x, Wg, gate_bias, y, logits, topk_idx, topk_w, slot, counts, s0));
+    if (s0 == s1) return chain_forward(d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, false, s0);
+    return forward(cfg, d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, s0, s1);
 }
 
 extern "C" moe_status moe_layer_backward(const moe_config* cfg, const void* x, const void* dy,
@@ -393,6 +508,9 @@ extern "C" moe_status moe_layer_backward(const moe_config* cfg, const void* x, c
     MOE_TRY(setup(cfg, &d, &w, workspace, workspace_bytes, streams, n_streams, &s0, &s1));
     if (!x || !dy || !Wg || !W1 || !W2 || !dx || !dWg || !dW1 || !dW2 || !logits || !topk_idx || !topk_w ||
         !slot || !counts) return MOE_ERR_NULL;
+    if (s0 == s1)
+        return chain_backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
+                              slot, counts, nullptr, s0);
     return backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, slot,
                     counts, s0, s1);
 }
@@ -407,9 +525,16 @@ extern "C" moe_status moe_layer_step(const moe_config* cfg, const void* x, const
     MOE_TRY(setup(cfg, &d, &w, workspace, workspace_bytes, streams, n_streams, &s0, &s1));
     if (!x || !dy || !Wg || !W1 || !W2 || !y || !dx || !dWg || !dW1 || !dW2 || !logits || !topk_idx ||
         !topk_w || !slot || !counts) return MOE_ERR_NULL;
+    MOE_TRY(gate(cfg, d, w, (char*)workspace, x, Wg, gate_bias, y, logits, topk_idx, topk_w, slot, counts, s0));
+    if (s0 == s1) {
+        // with every T_DO kept, the combine and the dispatch of dy with its row dots read the same rows: one kernel
+        const bool later = d.reuse == MOE_REUSE_NONE && !d.fcomb;
+        MOE_TRY(chain_forward(d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, later, s0));
+        return chain_backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
+                              slot, counts, later ? y : nullptr, s0);
+    }
     const bool early = first_backward_dispatch_can_go_early(d, w, false);
-    MOE_TRY(forward(cfg, d, w, (char*)workspace, x, Wg, gate_bias, W1, W2, y, logits, topk_idx, topk_w, slot,
-                    counts, s0, s1, nullptr, early ? dy : nullptr));
+    MOE_TRY(forward(cfg, d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, s0, s1, nullptr, early ? dy : nullptr));
     return backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, slot,
                     counts, s0, s1, nullptr, early);
 }
@@ -458,8 +583,8 @@ extern "C" moe_status moe_layer_step_offload(const moe_config* cfg, const void* 
     }
     o.host = (char*)host_buffer;
     o.s2 = (hipStream_t)streams[2];
-    MOE_TRY(forward(cfg, d, w, (char*)workspace, x, Wg, gate_bias, W1, W2, y, logits, topk_idx, topk_w, slot,
-                    counts, s0, s1, &o));
+    MOE_TRY(gate(cfg, d, w, (char*)workspace, x, Wg, gate_bias, y, logits, topk_idx, topk_w, slot, counts, s0));
+    MOE_TRY(forward(cfg, d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, s0, s1, &o));
     return backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, slot,
                     counts, s0, s1, &o);
 }

@@ -4,7 +4,9 @@
 // token-ordered tensors T_I / T_O and the expert-contiguous T_DI / T_DO.  They
 // are bound by HBM: every kernel moves whole rows with 16-byte accesses, one
 // wavefront per token, and reads each token row once however many experts it
-// goes to.
+// goes to.  A launch does one partition, or the partition blockIdx.z of several
+// (a launch takes 4.6 us of the GPU however little it does): partition buffers then
+// lie a constant number of bytes apart.
 #include "common.h"
 
 namespace moe {
@@ -35,57 +37,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// DI[slot[t,j]] = src[t]; optionally dw[t,j] = <src[t], saved[slot[t,j]]>.
-// U = 16-byte units per row.
-template <typename T, bool WITH_DW>
-__global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(
-    const T* __restrict__ src, const int* __restrict__ slot, T* __restrict__ dst,
-    const T* __restrict__ saved, float* __restrict__ dw, int t_begin, int t_count, int M, int k) {
-    const int lane = threadIdx.x & 63;
-    const int tl = blockIdx.x * PERM_WAVES + (threadIdx.x >> 6);
-    if (tl >= t_count) return;
-    const int t = t_begin + tl;
-    constexpr int EPU = 16 / sizeof(T);            // elements per 16-byte unit
-    const int U = M / EPU;
-    int s[8];
-    for (int j = 0; j < k; ++j) s[j] = slot[(size_t)t * k + j];
-    const uint4* in = reinterpret_cast<const uint4*>(src + (size_t)t * M);
-    float dot[8];
-    if (WITH_DW) for (int j = 0; j < k; ++j) dot[j] = 0.0f;
-    for (int c0 = 0; c0 < U; c0 += 256) {
-        uint4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            int c = c0 + u * 64 + lane;
-            if (c < U) v[u] = ld_row<true>(in + c);
-        }
-        for (int j = 0; j < k; ++j) {
-            if (s[j] < 0) continue;
-            uint4* out = reinterpret_cast<uint4*>(dst + (size_t)s[j] * M);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                int c = c0 + u * 64 + lane;
-                if (c < U) {
-                    st_row<false>(out + c, v[u]);
-                    if (WITH_DW) {
-                        uint4 o = reinterpret_cast<const uint4*>(saved + (size_t)s[j] * M)[c];
-                        const T* a = reinterpret_cast<const T*>(&v[u]);
-                        const T* b = reinterpret_cast<const T*>(&o);
-#pragma unroll
-                        for (int i = 0; i < EPU; ++i) dot[j] = fmaf(Elem<T>::ld(a + i), Elem<T>::ld(b + i), dot[j]);
-                    }
-                }
-            }
-        }
-    }
-    if (WITH_DW) {
-        for (int j = 0; j < k; ++j) {
-            float d = wave_sum(dot[j]);
-            if (lane == 0) dw[(size_t)t * k + j] = s[j] >= 0 ? d : 0.0f;
-        }
-    }
-}
-
 // 16 bytes <-> floats (8 bf16 or 4 float)
 template <typename T> struct Unit;
 template <> struct Unit<bf16_t> {
@@ -112,22 +63,129 @@ template <> struct Unit<float> {
     }
 };
 
-// y[t] = sum_j w[t,j] * DO[slot[t,j]]  (float accumulation, ascending j).  One wavefront per
-// token; four 16-byte units per lane are in flight per source row.
-template <typename T>
-__global__ __launch_bounds__(PERM_THREADS) void combine_kernel(
-    const T* __restrict__ DO, const int* __restrict__ slot, const float* __restrict__ w,
-    T* __restrict__ y, int t_begin, int t_count, int M, int k) {
+// What the row permutations of one or several consecutive partitions work on.  Pointers are those of partition p0;
+// strides are bytes from one partition's buffer to the next one's and may be negative (buffers used in turn).
+struct RowArgs {
+    const void* src[2];              // token-major rows that go to the experts; blockIdx.y chooses
+    char* dst[2];                    // partition buffers they go to
+    long long dst_stride[2];
+    const char* rows;                // T_DO buffer: the combine's source; with `dw` also its gradient's
+    long long rows_stride;
+    const int* slot;
+    const float* w;
+    float* dw;
+    void* y;
+    int p0, Tp, M, k;
+};
+
+// dst[slot[t,j]] = src[t]; optionally on the way dw[t,j] = <src[t], rows[slot[t,j]]> (backward's dispatch of dy where
+// T_DO was kept) and y[t] = sum_j w[t,j] rows[slot[t,j]] (forward's combine, which reads the same rows, in a step that
+// has not run it yet).  One wavefront per token.  KM: choices per token at most.  All reads of a piece of the row - the
+// token's and its experts' - are in flight before the first is used: 32768 tokens x 2048, two choices, with dw, 62 us a
+// partition of 16384 and 72 with the experts' rows read one after another.
+// (float accumulation, ascending j; a lane's part of a dot in ascending column order)
+template <typename T, int KM, bool DW, bool COMB>
+__global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
     const int lane = threadIdx.x & 63;
     const int tl = blockIdx.x * PERM_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (tl >= t_count) return;
-    const int t = t_begin + tl;
+    if (tl >= a.Tp) return;
+    const int z = blockIdx.z, which = blockIdx.y, k = a.k, M = a.M;
+    const size_t t = (size_t)(a.p0 + z) * a.Tp + tl;
     constexpr int N = Unit<T>::N;
+    constexpr int UN = DW && KM > 4 ? 1 : DW && KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
     const int U = M / N;
+    T* dst = reinterpret_cast<T*>(a.dst[which] + z * a.dst_stride[which]);
+    const T* rows = DW || COMB ? reinterpret_cast<const T*>(a.rows + z * a.rows_stride) : nullptr;
+    int s[KM];
+    float ws[KM], dot[KM];
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+        s[j] = j < k ? a.slot[t * k + j] : -1;
+        ws[j] = COMB && s[j] >= 0 ? a.w[t * k + j] : 0.0f;
+        dot[j] = 0.0f;
+    }
+    const uint4* in = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.src[which]) + t * M);
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    for (int c0 = 0; c0 < U; c0 += 64 * UN) {
+        uint4 v[UN], r[KM][UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int c = c0 + u * 64 + lane;
+            if (c < U) v[u] = ld_row<true>(in + c);
+        }
+        if constexpr (DW || COMB) {
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                const uint4* row = reinterpret_cast<const uint4*>(rows + (size_t)max(s[j], 0) * M);
+#pragma unroll
+                for (int u = 0; u < UN; ++u) {
+                    const int c = c0 + u * 64 + lane;
+                    r[j][u] = zero;
+                    if (c < U && s[j] >= 0) r[j][u] = ld_row<true>(row + c);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            if (s[j] < 0) continue;
+            uint4* out = reinterpret_cast<uint4*>(dst + (size_t)s[j] * M);
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int c = c0 + u * 64 + lane;
+                if (c < U) st_row<false>(out + c, v[u]);
+            }
+        }
+        if constexpr (DW || COMB) {
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int c = c0 + u * 64 + lane;
+                float x[N], acc[N];
+                Unit<T>::to_float(c < U ? v[u] : zero, x);
+#pragma unroll
+                for (int i = 0; i < N; ++i) acc[i] = 0.0f;
+#pragma unroll
+                for (int j = 0; j < KM; ++j) {
+                    float q[N];
+                    Unit<T>::to_float(r[j][u], q);
+#pragma unroll
+                    for (int i = 0; i < N; ++i) {
+                        if constexpr (DW) dot[j] = fmaf(x[i], q[i], dot[j]);
+                        if constexpr (COMB) acc[i] = fmaf(ws[j], q[i], acc[i]);
+                    }
+                }
+                if constexpr (COMB) {
+                    if (c < U) st_row<false>(reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * M) + c, Unit<T>::from_float(acc));
+                }
+            }
+        }
+    }
+    if constexpr (DW) {
+#pragma unroll
+        for (int j = 0; j < KM; ++j) {
+            if (j < k) {
+                const float d = wave_sum(dot[j]);
+                if (lane == 0) a.dw[t * k + j] = s[j] >= 0 ? d : 0.0f;
+            }
+        }
+    }
+}
+
+// y[t] = sum_j w[t,j] * rows[slot[t,j]]  (float accumulation, ascending j).  One wavefront per
+// token; four 16-byte units per lane are in flight per source row.
+template <typename T>
+__global__ __launch_bounds__(PERM_THREADS) void combine_kernel(RowArgs a) {
+    const int lane = threadIdx.x & 63;
+    const int tl = blockIdx.x * PERM_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (tl >= a.Tp) return;
+    const int k = a.k;
+    const size_t t = (size_t)(a.p0 + blockIdx.z) * a.Tp + tl;
+    const T* DO = reinterpret_cast<const T*>(a.rows + blockIdx.z * a.rows_stride);
+    constexpr int N = Unit<T>::N;
+    const int U = a.M / N;
     int s[8];
     float ws[8];
-    for (int j = 0; j < k; ++j) { s[j] = slot[(size_t)t * k + j]; ws[j] = w[(size_t)t * k + j]; }
-    uint4* out = reinterpret_cast<uint4*>(y + (size_t)t * M);
+    for (int j = 0; j < k; ++j) { s[j] = a.slot[t * k + j]; ws[j] = a.w[t * k + j]; }
+    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * a.M);
     for (int c0 = 0; c0 < U; c0 += 256) {
         float acc[4][N];
 #pragma unroll
@@ -136,7 +194,7 @@ __global__ __launch_bounds__(PERM_THREADS) void combine_kernel(
             for (int i = 0; i < N; ++i) acc[u][i] = 0.0f;
         for (int j = 0; j < k; ++j) {
             if (s[j] < 0) continue;
-            const uint4* in = reinterpret_cast<const uint4*>(DO + (size_t)s[j] * M);
+            const uint4* in = reinterpret_cast<const uint4*>(DO + (size_t)s[j] * a.M);
             uint4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -159,17 +217,31 @@ __global__ __launch_bounds__(PERM_THREADS) void combine_kernel(
     }
 }
 
-// One choice per token and the combine fused into the second expert GEMM: a dropped token has no row
-// that would write its output, so its row of y is zeroed here.  One wavefront per token.
-template <typename T>
-__global__ __launch_bounds__(PERM_THREADS) void zero_dropped_kernel(const int* __restrict__ slot, T* __restrict__ y,
-                                                                    int Ttot, int M) {
-    const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * PERM_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (t >= Ttot || slot[t] >= 0) return;
-    const int U = M / Unit<T>::N;
-    uint4* out = reinterpret_cast<uint4*>(y + (size_t)t * M);
-    for (int c = lane; c < U; c += 64) out[c] = make_uint4(0, 0, 0, 0);
+// dWg[i] += sum_b part[b][i], partition by partition: THREADS/8 consecutive outputs per workgroup, eight threads per
+// output each taking every eighth partial block, then a fixed-order sum of the eight.
+template <int THREADS>
+__device__ __forceinline__ void gate_dwg_reduce(const GateSums& g, int block, float* red) {
+    constexpr int COLS = THREADS / 8;
+    const int col = threadIdx.x % COLS, sl = threadIdx.x / COLS;
+    const int i = block * COLS + col;
+    float total = 0.0f;
+    if (sl == 0 && i < g.ME && !g.store) total = g.dWg[i];
+    for (int q = 0; q < g.np; ++q) {
+        const float* part = g.part + q * g.part_stride;
+        float s = 0.0f;
+        if (i < g.ME)
+            for (int b = sl; b < g.nblk; b += 8) s += part[(size_t)b * g.ME + i];
+        if (q) __syncthreads();
+        red[sl * COLS + col] = s;
+        __syncthreads();
+        if (sl == 0) {
+            float tot = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) tot += red[r * COLS + col];
+            total = q == 0 && g.store ? tot : total + tot;
+        }
+    }
+    if (sl == 0 && i < g.ME) g.dWg[i] = total;
 }
 
 // Dispatch backward, both storage types: a workgroup owns the columns that one wavefront covers with 16
@@ -183,6 +255,26 @@ constexpr int DXB_TG = 8;            // token groups per workgroup
 constexpr int DXB_TOK = 16;          // most tokens per group
 constexpr int DXB_THREADS = DXB_CT * DXB_TG;
 
+// Partitions p0 .. p0 + gridDim.z - 1.  Blocks from token_rows on (in y) do not belong to dispatch backward: they add up
+// the gate-weight gradient's partial sums, which saves that its own launch.
+struct DispatchBwdArgs {
+    const char* dDI;
+    long long dDI_stride;                // bytes
+    const int* slot;
+    const float* dL;
+    const void* Wg;
+    void* dx;
+    int p0, Tp, tok, M, E, k, token_rows;
+    GateSums sums;
+};
+template <int THREADS>
+__device__ __forceinline__ bool dispatch_bwd_sums(const DispatchBwdArgs& a, char* smem) {
+    if ((int)blockIdx.y < a.token_rows) return false;
+    if (blockIdx.z == 0)
+        gate_dwg_reduce<THREADS>(a.sums, ((int)blockIdx.y - a.token_rows) * gridDim.x + blockIdx.x, reinterpret_cast<float*>(smem));
+    return true;
+}
+
 // dx[t] = sum_j dDI[slot[t,j]] + dL[t,:] Wg^T for float32 storage.  A lane owns four columns; the gate
 // weights of the workgroup's 256 columns sit in LDS expert by expert (row pitch DXF_PITCH floats: the
 // transposing writes of four neighbouring experts fall into different banks), so that a lane's 16-byte read
@@ -191,10 +283,15 @@ constexpr int DXB_THREADS = DXB_CT * DXB_TG;
 // LDS) and by the row traffic at large ones; a column slice fits LDS at every size, up to 64 experts.
 constexpr int DXF_COLS = DXB_CT * 4;
 constexpr int DXF_PITCH = DXF_COLS + 4;
-__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(
-    const float* __restrict__ dDI, const int* __restrict__ slot, const float* __restrict__ dL,
-    const float* __restrict__ Wg, float* __restrict__ dx, int t_begin, int t_count, int tok, int M, int E, int k) {
+__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(DispatchBwdArgs a) {
     extern __shared__ __attribute__((aligned(16))) char dxf_smem[];
+    if (dispatch_bwd_sums<DXB_THREADS>(a, dxf_smem)) return;
+    const float* __restrict__ dDI = reinterpret_cast<const float*>(a.dDI + blockIdx.z * a.dDI_stride);
+    const int* __restrict__ slot = a.slot;
+    const float* __restrict__ dL = a.dL;
+    const float* __restrict__ Wg = (const float*)a.Wg;
+    float* __restrict__ dx = (float*)a.dx;
+    const int t_begin = (a.p0 + (int)blockIdx.z) * a.Tp, t_count = a.Tp, tok = a.tok, M = a.M, E = a.E, k = a.k;
     float* wgt = reinterpret_cast<float*>(dxf_smem);
     const int lane = threadIdx.x & 63;
     const int tg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -282,9 +379,15 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(
 typedef short bf16x4_hw __attribute__((ext_vector_type(4)));
 typedef float f32x4_hw __attribute__((ext_vector_type(4)));
 template <int EG>                    // expert groups of four: E <= 4*EG
-__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(
-    const bf16_t* __restrict__ dDI, const int* __restrict__ slot, const float* __restrict__ dL,
-    const bf16_t* __restrict__ Wg, bf16_t* __restrict__ dx, int t_begin, int t_count, int tok, int M, int E, int k) {
+__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(DispatchBwdArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char dxm_smem[];
+    if (dispatch_bwd_sums<DXB_THREADS>(a, dxm_smem)) return;
+    const bf16_t* __restrict__ dDI = reinterpret_cast<const bf16_t*>(a.dDI + blockIdx.z * a.dDI_stride);
+    const int* __restrict__ slot = a.slot;
+    const float* __restrict__ dL = a.dL;
+    const bf16_t* __restrict__ Wg = (const bf16_t*)a.Wg;
+    bf16_t* __restrict__ dx = (bf16_t*)a.dx;
+    const int t_begin = (a.p0 + (int)blockIdx.z) * a.Tp, t_count = a.Tp, tok = a.tok, M = a.M, E = a.E, k = a.k;
     const int ct = threadIdx.x % DXB_CT;                       // column thread
     const int tg = __builtin_amdgcn_readfirstlane(threadIdx.x / DXB_CT);
     const int c = (blockIdx.x * DXB_CT + ct) * 8;
@@ -341,7 +444,6 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(
     // wavefront spread over all banks.  The weights are staged before the first rows are requested:
     // an LDS write waits for every load issued before it, and the rows take several times longer
     // to arrive than the weights.
-    extern __shared__ __attribute__((aligned(16))) char dxm_smem[];
     constexpr int CHUNK = 64 * EG;
     constexpr int PITCH = CHUNK + 16;
     const int c_base = blockIdx.x * DXB_CT * 8;
@@ -616,7 +718,9 @@ typedef float gate_f32x16 __attribute__((ext_vector_type(16)));
 template <int EB>                    // expert blocks of 32: E <= 32*EB
 __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ dL, float* __restrict__ part,
-    int t_begin, int t_count, int M, int E, int S, int TC) {
+    long long part_stride, int p0, int t_count, int M, int E, int S, int TC) {
+    const int t_begin = (p0 + (int)blockIdx.z) * t_count;
+    part += blockIdx.z * part_stride;
     constexpr int U = 8;                          // matrix instructions of two tokens requested together
     const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
     const int ncb = (M + 31) / 32;
@@ -693,8 +797,12 @@ __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_f32_kernel(
 // hi + lo bfloat16 terms (for the matrix-core kernel below).
 __global__ __launch_bounds__(PERM_THREADS) void gate_dl_kernel(
     const float* __restrict__ logits, const int* __restrict__ topk_idx, const int* __restrict__ slot,
-    const float* __restrict__ dw, const float* __restrict__ dw_part, int parts, float* __restrict__ dL,
-    bf16_t* __restrict__ dLt, int tp_pad, int t_begin, int t_count, int E, int k, int renorm) {
+    const float* __restrict__ dw, const float* __restrict__ dw_part, long long dw_part_stride, int parts,
+    float* __restrict__ dL, bf16_t* __restrict__ dLt, long long dLt_stride, int tp_pad, int p0, int t_count, int E, int k,
+    int renorm) {
+    const int t_begin = (p0 + (int)blockIdx.z) * t_count;
+    if (dw_part) dw_part += blockIdx.z * dw_part_stride;
+    if (dLt) dLt += blockIdx.z * dLt_stride;
     __shared__ __attribute__((aligned(16))) float sdl[DWG_TOK][DWG_LD];
     __shared__ float sdw[DWG_TOK * 8];
     const int tl0 = blockIdx.x * DWG_TOK;
@@ -726,8 +834,11 @@ template <> struct GateWords<2> { typedef uint2 type; static __device__ __forcei
 template <> struct GateWords<4> { typedef uint4 type; static __device__ __forceinline__ unsigned word(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; } };
 template <int EB, int CPL>           // expert blocks of sixteen: E <= 16*EB; columns per lane
 __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_mfma_kernel(
-    const bf16_t* __restrict__ x, const bf16_t* __restrict__ dLt, float* __restrict__ part,
-    int t_begin, int t_count, int tp_pad, int M, int E, int S, int TC) {
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ dLt, long long dLt_stride, float* __restrict__ part,
+    long long part_stride, int p0, int t_count, int tp_pad, int M, int E, int S, int TC) {
+    const int t_begin = (p0 + (int)blockIdx.z) * t_count;
+    dLt += blockIdx.z * dLt_stride;
+    part += blockIdx.z * part_stride;
     constexpr int U = (EB * CPL <= 4) ? 4 : 2;      // MFMA steps of 16 tokens requested together
     constexpr int BT = 16 * U;
     constexpr int W = CPL / 2;
@@ -820,73 +931,98 @@ __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_mfma_kernel(
     }
 }
 
-// dWg[i] += sum_b part[b][i]: 32 consecutive outputs per workgroup, eight threads per output
-// each taking every eighth partial block, then a fixed-order sum of the eight.
-__global__ __launch_bounds__(256) void gate_dwg_reduce_kernel(
-    const float* __restrict__ part, float* __restrict__ dWg, int nblk, int ME, int store) {
-    __shared__ float red[8][32];
-    const int col = threadIdx.x & 31, sl = threadIdx.x >> 5;
-    const int i = blockIdx.x * 32 + col;
-    float s = 0.0f;
-    if (i < ME)
-        for (int b = sl; b < nblk; b += 8) s += part[(size_t)b * ME + i];
-    red[sl][col] = s;
-    __syncthreads();
-    if (sl == 0 && i < ME) {
-        float tot = 0.0f;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) tot += red[q][col];
-        dWg[i] = store ? tot : dWg[i] + tot;
-    }
+__global__ __launch_bounds__(256) void gate_dwg_reduce_kernel(GateSums g) {
+    __shared__ float red[256];
+    gate_dwg_reduce<256>(g, blockIdx.x, red);
 }
 
+template <typename T, bool DW, bool COMB>
+static moe_status launch_dispatch(const RowArgs& a, int sources, int np, hipStream_t s) {
+    const dim3 grid((a.Tp + PERM_WAVES - 1) / PERM_WAVES, sources, np);
+    if (a.k == 1) hipLaunchKernelGGL((dispatch_kernel<T, 1, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
+    else if (a.k == 2) hipLaunchKernelGGL((dispatch_kernel<T, 2, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
+    else if (a.k <= 4) hipLaunchKernelGGL((dispatch_kernel<T, 4, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
+    else hipLaunchKernelGGL((dispatch_kernel<T, 8, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
+}
 template <typename T>
-static moe_status dispatch_t(const Dims& d, int part, const void* src, const int* slot, void* DI,
-                             const void* saved, float* dw, hipStream_t s) {
-    dim3 grid((d.Tp + PERM_WAVES - 1) / PERM_WAVES);
-    ProfScope ps(PK_DISPATCH, s);
-    if (saved && dw)
-        hipLaunchKernelGGL((dispatch_kernel<T, true>), grid, dim3(PERM_THREADS), 0, s, (const T*)src, slot,
-                           (T*)DI, (const T*)saved, dw, part * d.Tp, d.Tp, d.M, d.k);
-    else
-        hipLaunchKernelGGL((dispatch_kernel<T, false>), grid, dim3(PERM_THREADS), 0, s, (const T*)src, slot,
-                           (T*)DI, (const T*)nullptr, (float*)nullptr, part * d.Tp, d.Tp, d.M, d.k);
-    count_launch(LC_PERMUTE);
+static moe_status dispatch_t(const RowArgs& a, int sources, int np, hipStream_t s) {
+    if (a.y) return launch_dispatch<T, true, true>(a, sources, np, s);
+    if (a.dw) return launch_dispatch<T, true, false>(a, sources, np, s);
+    return launch_dispatch<T, false, false>(a, sources, np, s);
+}
+
+moe_status dispatch_rows(const Dims& d, int p0, int np, const RowMove* moves, int n_moves, const int* slot,
+                         const void* DO, long long DO_stride, float* dw, const float* w, void* y, hipStream_t s) {
+    RowArgs a = {};
+    for (int i = 0; i < n_moves; ++i) { a.src[i] = moves[i].src; a.dst[i] = (char*)moves[i].dst; a.dst_stride[i] = moves[i].stride; }
+    a.rows = (const char*)DO; a.rows_stride = DO_stride;
+    a.slot = slot; a.w = w; a.dw = dw; a.y = y;
+    a.p0 = p0; a.Tp = d.Tp; a.M = d.M; a.k = d.k;
+    {
+        ProfScope ps(PK_DISPATCH, s, n_moves * np, y ? PK_COMBINE : -1, np);
+        MOE_TRY(d.dtype == MOE_F32 ? dispatch_t<float>(a, n_moves, np, s) : dispatch_t<bf16_t>(a, n_moves, np, s));
+    }
+    count_launch(LC_PERMUTE, (n_moves + (y ? 1 : 0)) * np);
+    return MOE_OK;
+}
+
+moe_status combine_rows(const Dims& d, int p0, int np, const void* DO, long long DO_stride, const int* slot, const float* w,
+                        void* y, hipStream_t s) {
+    RowArgs a = {};
+    a.rows = (const char*)DO; a.rows_stride = DO_stride;
+    a.slot = slot; a.w = w; a.y = y;
+    a.p0 = p0; a.Tp = d.Tp; a.M = d.M; a.k = d.k;
+    const dim3 grid((d.Tp + PERM_WAVES - 1) / PERM_WAVES, 1, np);
+    {
+        ProfScope ps(PK_COMBINE, s, np);
+        if (d.dtype == MOE_F32) hipLaunchKernelGGL((combine_kernel<float>), grid, dim3(PERM_THREADS), 0, s, a);
+        else hipLaunchKernelGGL((combine_kernel<bf16_t>), grid, dim3(PERM_THREADS), 0, s, a);
+    }
+    count_launch(LC_PERMUTE, np);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
 
-template <typename T>
-static moe_status dispatch_bwd_t(const Dims& d, int part, const void* dDI, const int* slot, const float* dL,
-                                 const void* Wg, void* dx, hipStream_t s) {
-    constexpr bool BF16 = sizeof(T) == 2;
-    const int cols = BF16 ? DXB_CT * 8 : DXF_COLS;
+moe_status dispatch_bwd_rows(const Dims& d, int p0, int np, const void* dDI, long long dDI_stride, const int* slot,
+                             const float* dL, const void* Wg, void* dx, const GateSums* sums, hipStream_t s) {
+    const bool bf16 = d.dtype == MOE_BF16;
+    const int cols = bf16 ? DXB_CT * 8 : DXF_COLS;
     const int slices = (d.M + cols - 1) / cols;
     // tokens per wavefront: as many as leave every compute unit a workgroup or two
-    const int fit = (int)((long long)d.Tp * slices / (512 * DXB_TG)) / 4 * 4;
+    const int fit = (int)((long long)d.Tp * np * slices / (512 * DXB_TG)) / 4 * 4;
     const int tok = fit < 4 ? 4 : fit > DXB_TOK ? DXB_TOK : fit;
-    const dim3 grid(slices, (d.Tp + tok * DXB_TG - 1) / (tok * DXB_TG));
-    ProfScope ps(PK_DISPATCH_BWD, s);
-#define LAUNCH_DXB(KERN, T_, LDS) do { \
-        const int lds = (LDS); \
+    DispatchBwdArgs a = {};
+    a.dDI = (const char*)dDI; a.dDI_stride = dDI_stride;
+    a.slot = slot; a.dL = dL; a.Wg = Wg; a.dx = dx;
+    a.p0 = p0; a.Tp = d.Tp; a.tok = tok; a.M = d.M; a.E = d.E; a.k = d.k;
+    a.token_rows = (d.Tp + tok * DXB_TG - 1) / (tok * DXB_TG);
+    int sum_rows = 0;
+    if (sums) {
+        a.sums = *sums;
+        const int blocks = (sums->ME + DXB_THREADS / 8 - 1) / (DXB_THREADS / 8);
+        sum_rows = (blocks + slices - 1) / slices;
+    }
+    const dim3 grid(slices, a.token_rows + sum_rows, np);
+    ProfScope ps(PK_DISPATCH_BWD, s, np);
+#define LAUNCH_DXB(KERN, LDS) do { \
+        int lds = (LDS); \
+        if (lds < DXB_THREADS * (int)sizeof(float)) lds = DXB_THREADS * (int)sizeof(float);     /* (the sums') */ \
         static int attr_bytes = 0;                  /* largest size asked for so far */ \
         if (lds > attr_bytes) { \
             HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(KERN), hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
             attr_bytes = lds; \
         } \
-        hipLaunchKernelGGL(KERN, grid, dim3(DXB_THREADS), lds, s, (const T_*)dDI, slot, dL, (const T_*)Wg, (T_*)dx, \
-                           part * d.Tp, d.Tp, tok, d.M, d.E, d.k); } while (0)
-    if constexpr (BF16) {
-        if (d.E <= 4) LAUNCH_DXB((dispatch_bwd_mfma_kernel<1>), bf16_t, DXB_CT * (64 * 1 + 16));
-        else if (d.E <= 8) LAUNCH_DXB((dispatch_bwd_mfma_kernel<2>), bf16_t, DXB_CT * (64 * 2 + 16));
-        else if (d.E <= 16) LAUNCH_DXB((dispatch_bwd_mfma_kernel<4>), bf16_t, DXB_CT * (64 * 4 + 16));
-        else if (d.E <= 32) LAUNCH_DXB((dispatch_bwd_mfma_kernel<8>), bf16_t, DXB_CT * (64 * 8 + 16));
-        else LAUNCH_DXB((dispatch_bwd_mfma_kernel<16>), bf16_t, DXB_CT * (64 * 16 + 16));
-    } else {
-        LAUNCH_DXB(dispatch_bwd_f32_kernel, float, DXF_PITCH * d.E * (int)sizeof(float));
-    }
+        hipLaunchKernelGGL(KERN, grid, dim3(DXB_THREADS), lds, s, a); } while (0)
+    if (!bf16) LAUNCH_DXB(dispatch_bwd_f32_kernel, DXF_PITCH * d.E * (int)sizeof(float));
+    else if (d.E <= 4) LAUNCH_DXB((dispatch_bwd_mfma_kernel<1>), DXB_CT * (64 * 1 + 16));
+    else if (d.E <= 8) LAUNCH_DXB((dispatch_bwd_mfma_kernel<2>), DXB_CT * (64 * 2 + 16));
+    else if (d.E <= 16) LAUNCH_DXB((dispatch_bwd_mfma_kernel<4>), DXB_CT * (64 * 4 + 16));
+    else if (d.E <= 32) LAUNCH_DXB((dispatch_bwd_mfma_kernel<8>), DXB_CT * (64 * 8 + 16));
+    else LAUNCH_DXB((dispatch_bwd_mfma_kernel<16>), DXB_CT * (64 * 16 + 16));
 #undef LAUNCH_DXB
-    count_launch(LC_PERMUTE);
+    count_launch(LC_PERMUTE, np);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
@@ -923,53 +1059,59 @@ static GateF32Plan gate_f32_plan(const Dims& d) {
     return g;
 }
 
-static void launch_dwg_reduce(const Dims& d, int part, const void* scratch, float* dWg, int nblk, hipStream_t s) {
-    const int ME = d.M * d.E;
-    hipLaunchKernelGGL(gate_dwg_reduce_kernel, dim3((ME + 31) / 32), dim3(256), 0, s,
-                       (const float*)scratch, dWg, nblk, ME, (d.overwrite && part == 0) ? 1 : 0);
+size_t gate_part_bytes(const Dims& d) {
+    const int S = d.dtype == MOE_BF16 ? gate_mfma_plan(d).S : gate_f32_plan(d).S;
+    return (size_t)S * d.M * d.E * sizeof(float);
 }
+size_t gate_dlt_bytes(const Dims& d) {
+    if (d.dtype != MOE_BF16) return 0;
+    const GateMfmaPlan g = gate_mfma_plan(d);
+    return (size_t)g.EB * 32 * g.tp_pad * sizeof(bf16_t);
+}
+size_t gate_dlt_offset(const Dims& d) { return d.dtype == MOE_BF16 ? gate_mfma_plan(d).dlt_off : 0; }
 
-template <typename T>
-static moe_status gate_bwd_t(const Dims& d, int part, const void* x, const float* logits, const int* idx,
-                             const int* slot, const float* dw, const float* dw_part, int parts,
-                             float* dL, float* dWg, void* scratch, hipStream_t s) {
-    ProfScope ps(PK_GATE_BWD, s);
-    if constexpr (sizeof(T) == 2) {
+moe_status gate_bwd_rows(const Dims& d, int p0, int np, const void* x, const float* logits, const int* idx, const int* slot,
+                         const float* dw, const float* dw_part, long long dw_part_stride, int parts, float* dL, float* dWg,
+                         float* part, long long part_stride, void* dLt, hipStream_t s, GateSums* sums) {
+    ProfScope ps(PK_GATE_BWD, s, np);
+    const int blocks = (d.Tp + DWG_TOK - 1) / DWG_TOK;
+    GateSums t = {};
+    t.part = part; t.part_stride = part_stride; t.dWg = dWg;
+    t.ME = d.M * d.E; t.np = np; t.store = d.overwrite && p0 == 0;
+    if (d.dtype == MOE_BF16) {
         const GateMfmaPlan g = gate_mfma_plan(d);
-        bf16_t* dLt = reinterpret_cast<bf16_t*>((char*)scratch + g.dlt_off);
-        hipLaunchKernelGGL(gate_dl_kernel, dim3(g.tp_pad / DWG_TOK), dim3(PERM_THREADS), 0, s, logits, idx, slot, dw,
-                           dw_part, parts, dL, dLt, g.tp_pad, part * d.Tp, d.Tp, d.E, d.k, d.renorm);
+        const long long dlt_stride = (long long)(gate_dlt_bytes(d) / sizeof(bf16_t));
+        hipLaunchKernelGGL(gate_dl_kernel, dim3(blocks, 1, np), dim3(PERM_THREADS), 0, s, logits, idx, slot, dw,
+                           dw_part, dw_part_stride, parts, dL, (bf16_t*)dLt, dlt_stride, g.tp_pad, p0, d.Tp, d.E, d.k, d.renorm);
         MOE_CHECK_LAUNCH();
-        const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES);
+        const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES, 1, np);
 #define LAUNCH_DWG(EB) hipLaunchKernelGGL((gate_dwg_mfma_kernel<EB, DWG_CPL>), grid, dim3(PERM_THREADS), 0, s, (const bf16_t*)x, \
-                           dLt, (float*)scratch, part * d.Tp, d.Tp, g.tp_pad, d.M, d.E, g.S, g.TC)
+                           (const bf16_t*)dLt, dlt_stride, part, part_stride, p0, d.Tp, g.tp_pad, d.M, d.E, g.S, g.TC)
         if (g.EB == 1) LAUNCH_DWG(1);
         else if (g.EB == 2) LAUNCH_DWG(2);
         else LAUNCH_DWG(4);
 #undef LAUNCH_DWG
-        MOE_CHECK_LAUNCH();
-        launch_dwg_reduce(d, part, scratch, dWg, g.S, s);
-        count_launch(LC_OTHER, 3);
-        MOE_CHECK_LAUNCH();
-        return MOE_OK;
+        t.nblk = g.S;
     } else {
         const GateF32Plan g = gate_f32_plan(d);
-        hipLaunchKernelGGL(gate_dl_kernel, dim3((d.Tp + DWG_TOK - 1) / DWG_TOK), dim3(PERM_THREADS), 0, s, logits, idx,
-                           slot, dw, dw_part, parts, dL, (bf16_t*)nullptr, 0, part * d.Tp, d.Tp, d.E, d.k, d.renorm);
+        hipLaunchKernelGGL(gate_dl_kernel, dim3(blocks, 1, np), dim3(PERM_THREADS), 0, s, logits, idx, slot, dw, dw_part,
+                           dw_part_stride, parts, dL, (bf16_t*)nullptr, 0ll, 0, p0, d.Tp, d.E, d.k, d.renorm);
         MOE_CHECK_LAUNCH();
-        const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES);
+        const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES, 1, np);
         if (d.E <= 32)
-            hipLaunchKernelGGL((gate_dwg_f32_kernel<1>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL,
-                               (float*)scratch, part * d.Tp, d.Tp, d.M, d.E, g.S, g.TC);
+            hipLaunchKernelGGL((gate_dwg_f32_kernel<1>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL, part, part_stride,
+                               p0, d.Tp, d.M, d.E, g.S, g.TC);
         else
-            hipLaunchKernelGGL((gate_dwg_f32_kernel<2>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL,
-                               (float*)scratch, part * d.Tp, d.Tp, d.M, d.E, g.S, g.TC);
-        MOE_CHECK_LAUNCH();
-        launch_dwg_reduce(d, part, scratch, dWg, g.S, s);
-        count_launch(LC_OTHER, 3);
-        MOE_CHECK_LAUNCH();
-        return MOE_OK;
+            hipLaunchKernelGGL((gate_dwg_f32_kernel<2>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL, part, part_stride,
+                               p0, d.Tp, d.M, d.E, g.S, g.TC);
+        t.nblk = g.S;
     }
+    MOE_CHECK_LAUNCH();
+    count_launch(LC_OTHER, 3 * np);
+    if (sums) { *sums = t; return MOE_OK; }
+    hipLaunchKernelGGL(gate_dwg_reduce_kernel, dim3((t.ME + 31) / 32), dim3(256), 0, s, t);
+    MOE_CHECK_LAUNCH();
+    return MOE_OK;
 }
 
 }  // namespace moe
@@ -982,8 +1124,10 @@ extern "C" moe_status moe_dispatch(const moe_config* cfg, int32_t part, const vo
     MOE_TRY(make_dims(cfg, &d));
     MOE_TRY(check_part(d, part));
     if (!src || !slot || !DI) return MOE_ERR_NULL;
-    if (d.dtype == MOE_F32) return dispatch_t<float>(d, part, src, slot, DI, dO_saved, dw, (hipStream_t)stream);
-    return dispatch_t<bf16_t>(d, part, src, slot, DI, dO_saved, dw, (hipStream_t)stream);
+    const RowMove m = {src, DI, 0};
+    const bool with_dw = dO_saved && dw;
+    return dispatch_rows(d, part, 1, &m, 1, slot, with_dw ? dO_saved : nullptr, 0, with_dw ? dw : nullptr, nullptr, nullptr,
+                         (hipStream_t)stream);
 }
 
 extern "C" moe_status moe_combine(const moe_config* cfg, int32_t part, const void* DO, const int32_t* slot,
@@ -992,32 +1136,8 @@ extern "C" moe_status moe_combine(const moe_config* cfg, int32_t part, const voi
     MOE_TRY(make_dims(cfg, &d));
     MOE_TRY(check_part(d, part));
     if (!DO || !slot || !topk_w || !y) return MOE_ERR_NULL;
-    dim3 grid((d.Tp + PERM_WAVES - 1) / PERM_WAVES);
-    hipStream_t s = (hipStream_t)stream;
-    ProfScope ps(PK_COMBINE, s);
-    if (d.dtype == MOE_F32)
-        hipLaunchKernelGGL((combine_kernel<float>), grid, dim3(PERM_THREADS), 0, s, (const float*)DO, slot,
-                           topk_w, (float*)y, part * d.Tp, d.Tp, d.M, d.k);
-    else
-        hipLaunchKernelGGL((combine_kernel<bf16_t>), grid, dim3(PERM_THREADS), 0, s, (const bf16_t*)DO, slot,
-                           topk_w, (bf16_t*)y, part * d.Tp, d.Tp, d.M, d.k);
-    count_launch(LC_PERMUTE);
-    MOE_CHECK_LAUNCH();
-    return MOE_OK;
+    return combine_rows(d, part, 1, DO, 0, slot, topk_w, y, (hipStream_t)stream);
 }
-
-namespace moe {
-moe_status zero_dropped(const Dims& d, const int* slot, void* y, hipStream_t s) {
-    dim3 grid((d.T + PERM_WAVES - 1) / PERM_WAVES);
-    if (d.dtype == MOE_F32)
-        hipLaunchKernelGGL((zero_dropped_kernel<float>), grid, dim3(PERM_THREADS), 0, s, slot, (float*)y, d.T, d.M);
-    else
-        hipLaunchKernelGGL((zero_dropped_kernel<bf16_t>), grid, dim3(PERM_THREADS), 0, s, slot, (bf16_t*)y, d.T, d.M);
-    count_launch(LC_OTHER);
-    MOE_CHECK_LAUNCH();
-    return MOE_OK;
-}
-}  // namespace moe
 
 extern "C" moe_status moe_dispatch_bwd(const moe_config* cfg, int32_t part, const void* dDI, const int32_t* slot,
                                        const float* dL, const void* Wg, void* dx, void* stream) {
@@ -1025,8 +1145,7 @@ extern "C" moe_status moe_dispatch_bwd(const moe_config* cfg, int32_t part, cons
     MOE_TRY(make_dims(cfg, &d));
     MOE_TRY(check_part(d, part));
     if (!dDI || !slot || !dL || !Wg || !dx) return MOE_ERR_NULL;
-    if (d.dtype == MOE_F32) return dispatch_bwd_t<float>(d, part, dDI, slot, dL, Wg, dx, (hipStream_t)stream);
-    return dispatch_bwd_t<bf16_t>(d, part, dDI, slot, dL, Wg, dx, (hipStream_t)stream);
+    return dispatch_bwd_rows(d, part, 1, dDI, 0, slot, dL, Wg, dx, nullptr, (hipStream_t)stream);
 }
 
 extern "C" moe_status moe_gate_scratch_bytes(const moe_config* cfg, size_t* bytes) {
@@ -1048,9 +1167,6 @@ extern "C" moe_status moe_gate_bwd(const moe_config* cfg, int32_t part, const vo
     if (!dw && !dw_part) return MOE_ERR_NULL;
     int parts = 0;
     MOE_TRY(moe_dw_parts(cfg, &parts));
-    if (d.dtype == MOE_F32)
-        return gate_bwd_t<float>(d, part, x, logits, topk_idx, slot, dw, dw_part, parts, dL, dWg, scratch,
-                                 (hipStream_t)stream);
-    return gate_bwd_t<bf16_t>(d, part, x, logits, topk_idx, slot, dw, dw_part, parts, dL, dWg, scratch,
-                              (hipStream_t)stream);
+    return gate_bwd_rows(d, part, 1, x, logits, topk_idx, slot, dw, dw_part, 0, parts, dL, dWg, (float*)scratch, 0,
+                         (char*)scratch + gate_dlt_offset(d), (hipStream_t)stream, nullptr);
 }

@@ -1,0 +1,118 @@
+"""Slot assignment and the row permutations by themselves, at the edges of their launches: assignments around the number
+that one kernel counts by itself, workgroups of 1024 tokens that end early, every number of choices, rows that end
+inside a wavefront's piece; and the whole step with its combine in backward's dispatch."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_22175_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+D = "cuda:0"
+
+
+def _choices(T, E, k, seed):
+    """k different experts per token, the low ones more often."""
+    rng = np.random.default_rng(seed)
+    p = 1.0 / (np.arange(E) + 1.0)
+    return np.argsort(-(np.log(p) + rng.gumbel(size=(T, E))), axis=1)[:, :k].astype(np.int32)
+
+
+def _slots(idx, n, E, Cp):
+    """Choice-major, then token order, inside each partition."""
+    T, k = idx.shape
+    Tp = T // n
+    slot, counts = np.full((T, k), -1, np.int32), np.zeros((n, E), np.int32)
+    for p in range(n):
+        for j in range(k):
+            for t in range(p * Tp, (p + 1) * Tp):
+                e = idx[t, j]
+                if counts[p, e] < Cp:
+                    slot[t, j] = e * Cp + counts[p, e]
+                    counts[p, e] += 1
+    return slot, counts
+
+
+@pytest.mark.parametrize("T,n,E,k", [
+    (1, 1, 1, 1), (63, 1, 3, 2), (64, 1, 64, 8), (384, 1, 9, 8), (385, 1, 9, 8), (1023, 1, 33, 3), (1024, 1, 33, 3),
+    (1025, 1, 33, 3), (3072, 1, 64, 1), (3073, 1, 64, 1), (6144, 2, 64, 1), (5120, 1, 2, 2), (9000, 3, 17, 4),
+    (33000, 1, 16, 2),
+])
+def test_slots(T, n, E, k):
+    cfg = B.make_config(T, 8, 8, E, k, 0.75, n, B.MOE_BF16, 0)
+    Cp = B.moe_capacity(cfg)
+    idx = _choices(T, E, k, T + E)
+    ref, counts = _slots(idx, n, E, Cp)
+    assert (ref < 0).any() or k == E
+    w = np.random.default_rng(1).random((T, k), dtype=np.float32)
+    ti, tw = torch.from_numpy(idx).to(D), torch.from_numpy(w).to(D)
+    slot, c = torch.full((T, k), -9, dtype=torch.int32, device=D), torch.full((n, E), -9, dtype=torch.int32, device=D)
+    slot_w = torch.full((n * E * Cp,), -1.0, device=D)
+    scratch = torch.full((B.moe_slot_scratch_bytes(cfg),), 0xFF, dtype=torch.uint8, device=D)
+    B.moe_assign_slots(cfg, ti, tw, slot, c, slot_w, scratch)
+    assert np.array_equal(slot.cpu().numpy(), ref) and np.array_equal(c.cpu().numpy(), counts)
+    want = np.full((n * E * Cp,), -1.0, np.float32)
+    part = np.arange(T)[:, None] // (T // n) * (E * Cp) + ref
+    want[part[ref >= 0]] = w[ref >= 0]
+    assert np.array_equal(slot_w.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("M", [8, 520, 2056])
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_dispatch_with_row_dots(dtype, k, M):
+    """Rows land bit for bit and nowhere else; the dots are float sums of M products: M units of rounding at most."""
+    T, n, E = 52, 2, 9
+    dt, mt = (torch.bfloat16, B.MOE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_F32)
+    cfg = B.make_config(T, M, 8, E, k, 0.7, n, mt, 0)
+    Cp = B.moe_capacity(cfg)
+    ref, _ = _slots(_choices(T, E, k, k), n, E, Cp)
+    assert (ref < 0).any()
+    g = torch.Generator(D).manual_seed(M)
+    src = torch.randn((T, M), generator=g, device=D).to(dt)
+    saved = torch.randn((E * Cp, M), generator=g, device=D).to(dt)
+    slot = torch.from_numpy(ref).to(D)
+    dw = torch.full((T, k), float("nan"), device=D)
+    for p in range(n):
+        held = torch.zeros((E * Cp,), dtype=torch.bool, device=D)
+        q = slice(p * T // n, (p + 1) * T // n)
+        s = slot[q].long()
+        held[s[s >= 0]] = True
+        kept = saved.clone()
+        kept[~held] = float("nan")
+        for with_dw in (False, True):
+            out = torch.full((E * Cp, M), float("nan"), device=D).to(dt)
+            B.moe_dispatch(cfg, p, src, slot, out, kept if with_dw else None, dw if with_dw else None)
+            want = torch.full_like(out, float("nan"))
+            t, j = torch.nonzero(s >= 0, as_tuple=True)
+            want[s[t, j]] = src[q][t]
+            assert torch.equal(out.isnan(), want.isnan()) and torch.equal(out[held], want[held])
+        rows = torch.where((s >= 0)[..., None], saved[s.clamp(min=0)].double(), 0.0)
+        prod = src[q].double()[:, None] * rows
+        err = (dw[q].double() - prod.sum(2)).abs()
+        assert bool((err <= prod.abs().sum(2) * M * 2.0 ** -24).all())
+
+
+@pytest.mark.parametrize("T,M,H,E,k,n,dtype", [
+    (120, 72, 136, 5, 3, 5, "bf16"), (96, 520, 264, 9, 8, 1, "bf16"), (90, 264, 136, 3, 1, 3, "f32"), (128, 2056, 72, 4, 2, 2, "bf16"),
+])
+def test_step_equals_its_two_halves(T, M, H, E, k, n, dtype):
+    """In a whole step that keeps T_DO the combine shares backward's dispatch of dy: the same bits as by itself."""
+    from paper_2506_22175_amd import runner, synth
+    s = synth.custom_shape(T, M, H, E, k, 0.75, dtype=dtype, x_std=1.0, w_std=0.05, name="halves")
+    st = runner.LayerState(T, M, H, E, k, 0.75, n, dtype, 0, grad_overwrite=1)
+    assert B.moe_layer_streams(st.cfg) == 1
+    st.upload(synth.make_inputs(s, seed=5))
+    out = []
+    for halves in (False, True):
+        st.poison()
+        if halves:
+            st.forward()
+            st.backward()
+        else:
+            st.step()
+        out.append(st.results())
+    assert (out[0]["slot"] < 0).any()
+    for name in ("y", "dx", "dWg", "dW1", "dW2"):
+        assert np.isfinite(out[0][name]).all() and np.array_equal(out[0][name], out[1][name]), name
