@@ -41,6 +41,10 @@ template <> struct Raw8<bf16_t> {
     uint4 u;
     __device__ __forceinline__ void load(const bf16_t* p) { u = *reinterpret_cast<const uint4*>(p); }
     __device__ __forceinline__ void zero() { u = make_uint4(0, 0, 0, 0); }
+    __device__ __forceinline__ float at(int i) const {
+        const unsigned w = i < 2 ? u.x : i < 4 ? u.y : i < 6 ? u.z : u.w;
+        return __uint_as_float((i & 1) ? w & 0xffff0000u : w << 16);
+    }
     __device__ __forceinline__ void to_float(float* o) const {
         const unsigned w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
@@ -57,6 +61,10 @@ template <> struct Raw8<float> {
         b = *reinterpret_cast<const float4*>(p + 4);
     }
     __device__ __forceinline__ void zero() { a = make_float4(0, 0, 0, 0); b = a; }
+    __device__ __forceinline__ float at(int i) const {
+        const float4 q = i < 4 ? a : b;
+        return (i & 3) == 0 ? q.x : (i & 3) == 1 ? q.y : (i & 3) == 2 ? q.z : q.w;
+    }
     __device__ __forceinline__ void to_float(float* o) const {
         o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
         o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;

@@ -1,0 +1,52 @@
+"""The gate by itself at the edges of its kernels: tokens that end inside a wavefront's or a workgroup's set, around
+the numbers at which a wavefront takes more of them, experts that do not fill a power of two, gate weights that are not
+16-byte aligned, rows that end inside a span of 512, equal logits, infinities and NaN."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle
+from paper_2506_22175_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+D = "cuda:0"
+
+
+@pytest.mark.parametrize("T,M,E,k,dtype", [
+    (1, 8, 64, 8, "bf16"), (3, 520, 33, 2, "bf16"), (9, 1032, 64, 8, "f32"), (50, 512, 17, 3, "f32"), (17, 72, 32, 1, "bf16"),
+    (2047, 136, 64, 2, "bf16"), (2049, 136, 64, 2, "bf16"), (4095, 72, 32, 2, "f32"), (4097, 72, 32, 2, "bf16"), (4097, 72, 27, 2, "f32"),
+    (2050, 520, 48, 4, "f32"), (16385, 8, 32, 1, "f32"),
+    (1, 8, 1, 1, "f32"), (15, 520, 4, 2, "bf16"), (8191, 24, 8, 2, "bf16"), (8193, 24, 7, 2, "f32"), (4095, 24, 16, 3, "f32"), (4097, 24, 11, 3, "bf16"),
+])
+@pytest.mark.parametrize("renorm", [0, 1])
+def test_gate(T, M, E, k, dtype, renorm):
+    """Logits, choices bit for bit; weights to float32 rounding of E exponentials and their sum."""
+    if renorm and k == 1:
+        pytest.skip("one choice: nothing to renormalise")
+    dt, mt = (torch.bfloat16, B.MOE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_F32)
+    g = torch.Generator().manual_seed(T + E)
+    x, Wg = torch.randn((T, M), generator=g).to(dt), (torch.randn((M, E), generator=g) * 0.2).to(dt)
+    if E > 4:
+        Wg[:, E // 2] = Wg[:, 1]                    # equal logits: the lower index wins
+        Wg[:, E - 1] = Wg[:, 1]
+    bias = None if renorm else torch.randn((E,), generator=g)
+    if bias is not None and E > 4:
+        bias[E // 2] = bias[E - 1] = bias[1]
+    if T > 8:
+        x[4, 0], x[6, 1] = float("inf"), float("nan")
+    cfg = B.make_config(T, M, 8, E, k, 1.0, 1, mt, 0, gate_renormalize=renorm)
+    ref, _, idx, w = moe_oracle.route(x.float().numpy(), Wg.float().numpy(), k, None if bias is None else bias.numpy(), bool(renorm))
+    odd = torch.empty((M * E + 1,), dtype=dt, device=D)
+    odd[1:] = Wg.reshape(-1).to(D)
+    for weights in (Wg.to(D), odd[1:].view(M, E)):
+        lo = torch.full((T, E), 7.0, device=D)
+        ti, tw = torch.full((T, k), -9, dtype=torch.int32, device=D), torch.full((T, k), -9.0, device=D)
+        B.moe_route(cfg, x.to(D), weights, None if bias is None else bias.to(D), lo, ti, tw)
+        got = lo.cpu().numpy()
+        assert np.array_equal(got, ref, equal_nan=True)
+        assert np.array_equal(ti.cpu().numpy(), idx)
+        fine = np.isfinite(ref).all(axis=1)
+        assert fine.any()
+        # expf within 2 units, logit - max rounded once (half a unit of a difference of up to 60), a sum of 64, a quotient
+        assert np.abs(tw.cpu().numpy() / w - 1.0)[fine].max() <= 2.0 ** -23 * (60 + 64 + 6)
