@@ -186,6 +186,10 @@ struct GemmArgs {
     int a_row_limit;
     const int* counts;    // [E] valid rows of this partition
     int E, Cp;            // experts, max rows per expert
+    // NN / NT: np consecutive partitions in one launch (0 or 1: one; E * np <= 64), whose partition buffers lie a_pstride,
+    // c_pstride, z_pstride elements and dw_pstride floats apart; row arrays and counts of partitions follow one another.
+    int np;
+    long long a_pstride, c_pstride, z_pstride, dw_pstride;
     int mean_rows;        // rows per expert of a partition if all are loaded alike (the choice of a tile shape)
     int Mo;               // TN only: output rows
     int N, K;             // K unused for TN (K = counts[e])
@@ -204,6 +208,16 @@ struct GemmArgs {
     float* dw_part;       // EPI_DGELU: [E*Cp, dw_parts] or NULL
     int dw_parts;
 };
+
+// Experts of all partitions of a launch are numbered so that those that share their weights are neighbours:
+// number v is expert v / np of the launch's partition v % np.
+struct ExpertOf { int e, q; };
+__host__ __device__ __forceinline__ int launch_experts(const GemmArgs& g) { return g.np > 1 ? g.E * g.np : g.E; }
+__device__ __forceinline__ ExpertOf expert_of(const GemmArgs& g, int v) {
+    if (g.np <= 1) return {v, 0};
+    const int e = v / g.np;
+    return {e, v - e * g.np};
+}
 
 inline int gemm_prof_kind(int lay, int epi) {
     if (epi == EPI_GELU) return PK_GEMM_FWD1;
@@ -228,9 +242,11 @@ void gemm_f32_tile(int* rows, int* cols);
 // ---- one partition's expert FFN (ffn.hip) ---------------------------------------
 // rows != NULL: DI is the token-major input [T, M] and rows[part] maps expert rows to its rows
 // y_rows != NULL (k = 1): the second GEMM writes slot_w * row into y[y_rows[...]] instead of DO
+// step: np partitions from `part` on, whose buffers lie so many elements (dw_part: floats) apart
+struct PartStep { int np = 1; long long DI = 0, Z = 0, A = 0, DO = 0, dDO = 0, dZ = 0, dDI = 0, dw_part = 0; };
 moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, const int* counts,
                    const void* W1, const void* W2, void* Z, void* A, void* DO, hipStream_t s,
-                   const int* y_rows = nullptr, const float* slot_w = nullptr, void* y = nullptr);
+                   const int* y_rows = nullptr, const float* slot_w = nullptr, void* y = nullptr, const PartStep& step = PartStep());
 moe_status ffn_bwd(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                    const int* counts, const float* slot_w, const void* W1, const void* W2,
                    void* dZ, void* dDI, float* dW1, float* dW2, float* dw_part, hipStream_t s);
@@ -238,11 +254,14 @@ moe_status ffn_bwd(const Dims& d, int part, int recompute, const void* DI, void*
 // the weight gradients of nparts consecutive partitions at once
 moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                         const int* counts, const float* slot_w, const void* W1, const void* W2,
-                        void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad = true);
-// dgrad_W1 != NULL: and the input gradient of the last of the partitions (which ffn_bwd_main left out) into dDI
+                        void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad = true,
+                        const PartStep& step = PartStep());
+// dgrad_W1 != NULL: and the input gradient of the last step.np of the partitions (which ffn_bwd_main left out) into dDI,
+// that of the first of them
 moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void* DI, const void* A, const void* dDO,
                      const void* dZ, long long strideM, long long strideH, const int* counts,
-                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1 = nullptr, void* dDI = nullptr);
+                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1 = nullptr, void* dDI = nullptr,
+                     const PartStep& step = PartStep());
 
 // ---- row permutations and gate backward of np consecutive partitions from p0 on (permute.hip) ----
 // Pointers are partition p0's, strides lead from one partition's buffer to the next one's.

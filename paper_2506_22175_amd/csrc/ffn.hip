@@ -23,7 +23,7 @@ static GemmArgs base_args(const Dims& d, const int* counts_p) {
 
 moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, const int* counts,
                    const void* W1, const void* W2, void* Z, void* A, void* DO, hipStream_t s,
-                   const int* y_rows, const float* slot_w, void* y) {
+                   const int* y_rows, const float* slot_w, void* y, const PartStep& step) {
     const int* cp = counts + (size_t)part * d.E;
     // T_M = T_DI W1 ; A = gelu(T_M)
     GemmArgs a = base_args(d, cp);
@@ -33,6 +33,7 @@ moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, con
     a.C = A; a.ldc = d.H; a.c_estride = (long long)d.Cp * d.H;
     a.N = d.H; a.K = d.M;
     a.Z = Z; a.ldz = d.H;
+    a.np = step.np; a.a_pstride = rows ? 0 : step.DI; a.c_pstride = step.A; a.z_pstride = step.Z;
     MOE_TRY(run_gemm(d, GEMM_NN, EPI_GELU, a, s));
     // T_DO = A W2
     GemmArgs b = base_args(d, cp);
@@ -40,10 +41,11 @@ moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, con
     b.B = W2; b.ldb = d.M; b.b_estride = (long long)d.H * d.M;
     b.C = DO; b.ldc = d.M; b.c_estride = (long long)d.Cp * d.M;
     b.N = d.M; b.K = d.H;
+    b.np = step.np; b.a_pstride = step.A; b.c_pstride = step.DO;
     if (y_rows) {
         // one choice per token: a kept row is its token's whole output, weighted (Fig. 1: T_DO -> T_O with
         // no T_DO in between)
-        b.C = y; b.c_estride = 0;
+        b.C = y; b.c_estride = 0; b.c_pstride = 0;
         b.c_rows = y_rows + (size_t)part * d.Rp; b.c_row_limit = d.T;
         b.slot_w = slot_w + (size_t)part * d.Rp;
         return run_gemm(d, GEMM_NN, EPI_SCATTER, b, s);
@@ -52,18 +54,19 @@ moe_status ffn_fwd(const Dims& d, int part, const void* DI, const int* rows, con
 }
 
 // dDI = dZ W1^T
-static GemmArgs dgrad_args(const Dims& d, const int* cp, const void* dZ, const void* W1, void* dDI) {
+static GemmArgs dgrad_args(const Dims& d, const int* cp, const void* dZ, const void* W1, void* dDI, const PartStep& step) {
     GemmArgs a = base_args(d, cp);
     a.A = dZ; a.lda = d.H; a.a_estride = (long long)d.Cp * d.H;
     a.B = W1; a.ldb = d.H; a.b_estride = (long long)d.M * d.H;
     a.C = dDI; a.ldc = d.M; a.c_estride = (long long)d.Cp * d.M;
     a.N = d.M; a.K = d.H;
+    a.np = step.np; a.a_pstride = step.dZ; a.c_pstride = step.dDI;
     return a;
 }
 
 moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, void* Z, const void* dDO,
                         const int* counts, const float* slot_w, const void* W1, const void* W2,
-                        void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad) {
+                        void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad, const PartStep& step) {
     const int* cp = counts + (size_t)part * d.E;
     const long long eM = (long long)d.Cp * d.M, eH = (long long)d.Cp * d.H, wMH = (long long)d.M * d.H;
     if (recompute) {
@@ -73,6 +76,7 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
         a.B = W1; a.ldb = d.H; a.b_estride = wMH;
         a.C = Z; a.ldc = d.H; a.c_estride = eH;
         a.N = d.H; a.K = d.M;
+        a.np = step.np; a.a_pstride = step.DI; a.c_pstride = step.Z;
         MOE_TRY(run_gemm(d, GEMM_NN, EPI_STORE, a, s));
     }
     {   // G = dDO W2^T ; dZ = w G gelu'(Z) ; Z <- w gelu(Z) ; dw_part = <gelu(Z), G>
@@ -85,9 +89,10 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
         a.slot_w = slot_w + (size_t)part * d.Rp;
         a.dw_part = dw_part;
         a.dw_parts = d.dtype == MOE_F32 ? gemm_f32_dw_parts(d.H) : gemm_bf16_dw_parts(d.H);
+        a.np = step.np; a.a_pstride = step.dDO; a.c_pstride = step.dZ; a.z_pstride = step.Z; a.dw_pstride = step.dw_part;
         MOE_TRY(run_gemm(d, GEMM_NT, EPI_DGELU, a, s));
     }
-    if (with_dgrad) MOE_TRY(run_gemm(d, GEMM_NT, EPI_STORE, dgrad_args(d, cp, dZ, W1, dDI), s));
+    if (with_dgrad) MOE_TRY(run_gemm(d, GEMM_NT, EPI_STORE, dgrad_args(d, cp, dZ, W1, dDI, step), s));
     return MOE_OK;
 }
 
@@ -97,7 +102,7 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
 // are read and written once per group instead of once per partition.
 moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void* DI, const void* A, const void* dDO,
                      const void* dZ, long long strideM, long long strideH, const int* counts,
-                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1, void* dDI) {
+                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1, void* dDI, const PartStep& step) {
     const long long eM = (long long)d.Cp * d.M, eH = (long long)d.Cp * d.H, wMH = (long long)d.M * d.H;
     // the float GEMM reduces one partition per launch
     const int per_launch = d.dtype == MOE_F32 ? 1 : nparts;
@@ -121,9 +126,9 @@ moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void*
         w1.k_segs = per_launch; w1.a_sstride = strideM; w1.b_sstride = strideH;
         // all three GEMMs that are left of the last partition in one launch, or both weight gradients, or one by one
         const bool with_dgrad = dgrad_W1 && q + per_launch >= nparts;
-        const int last = part + nparts - 1;
-        const GemmArgs dg = with_dgrad ? dgrad_args(d, counts + (size_t)last * d.E,
-                                                    (const char*)dZ + (size_t)(nparts - 1) * strideH * d.es, dgrad_W1, dDI)
+        const int first = nparts - step.np;
+        const GemmArgs dg = with_dgrad ? dgrad_args(d, counts + (size_t)(part + first) * d.E,
+                                                    (const char*)dZ + (size_t)first * strideH * d.es, dgrad_W1, dDI, step)
                                        : GemmArgs{};
         if (d.dtype == MOE_F32) {
             MOE_TRY(gemm_f32_backward(with_dgrad ? &dg : nullptr, w2, w1, epi, s));

@@ -283,7 +283,7 @@ __device__ __forceinline__ void mfma_pinned(floatx16& acc, const bf16x8& a, cons
 // ranges, one per partition buffer); tiles of 32 k never straddle two ranges.  KCursor says which range
 // the tile that is being requested lies in and where.
 constexpr int MAX_KSEGS = 8;
-struct TileCoord { int e, tn, m0, n0, Mdim, Kdim, KT; };
+struct TileCoord { int e, q, er, tn, m0, n0, Mdim, Kdim, KT; };      // expert, partition of the launch, their place in row arrays
 struct KCursor { int seg, jl, tiles; };
 
 // Numbers of the tiles of a launch.  Only tiles that exist are numbered: an expert with fewer rows than the capacity
@@ -291,7 +291,8 @@ struct KCursor { int seg, jl, tiles; };
 // the numbers b, b + grid, ..., all get the same amount of work whatever the spread of the counts.  The tile rows that
 // an expert fills by more than half come first, expert by expert; a last tile row with fewer rows is numbered after
 // all of those, since it takes less time (the 64-k loops multiply only the blocks of rows that hold something) and
-// belongs at the end of a workgroup's list.  Lane l of every wavefront holds the tile rows of expert l (E <= 64);
+// belongs at the end of a workgroup's list.  Lane l of every wavefront holds the tile rows of expert l (of expert
+// l / np of partition l % np where the launch covers several; at most 64 in all);
 // inclusive scans over the lanes give the numbers at which each expert ends.
 struct TileNumbers {
     int lane_tm;                         // such tile rows of expert `lane`
@@ -304,10 +305,15 @@ __device__ __forceinline__ TileNumbers number_tiles(const GemmArgs& g, int tiles
     TileNumbers t;
     t.lane_tm = 0;
     int lane_tail = 0;                   // whether a last tile row with fewer rows follows
-    if (lane < g.E) {
+    if (lane < (LAY == GEMM_TN ? g.E : launch_experts(g))) {
         int rows = 0;
-        const int segs = (LAY == GEMM_TN && g.k_segs > 1) ? g.k_segs : 1;
-        for (int sg = 0; sg < segs; ++sg) rows += g.counts[sg * g.E + lane];
+        if constexpr (LAY == GEMM_TN) {
+            const int segs = g.k_segs > 1 ? g.k_segs : 1;
+            for (int sg = 0; sg < segs; ++sg) rows += g.counts[sg * g.E + lane];
+        } else {
+            const ExpertOf x = expert_of(g, lane);
+            rows = g.counts[x.q * g.E + x.e];
+        }
         if (LAY == GEMM_TN) t.lane_tm = (rows > 0 || EPI == EPI_STORE_F32) ? tiles_m : 0;   // a plain store still writes zeros
         else {
             t.lane_tm = min(tiles_m, (rows + BM / 2 - 1) / BM);
@@ -390,11 +396,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     // it is 3-5 % faster.)  A last partial run keeps plain order.
     auto decode = [&](int b, TileCoord& t) -> bool {
         const int lin = (b < (nwhole & ~255)) ? (b & ~255) + (b & 7) * 32 + ((b >> 3) & 31) : b;
+        const int all = LAY == GEMM_TN ? g.E : launch_experts(g);
         int e, tm;
         if (LAY == GEMM_TN || lin < nwhole) {
             // the expert: as many experts end at or before lin as lanes say so (the ends never decrease)
             e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane_end <= lin));
-            if (e >= g.E) return false;
+            if (e >= all) return false;
             const int tm_e = __builtin_amdgcn_readlane(lane_tm, e);      // tile rows of this expert
             const int rem = lin - (__builtin_amdgcn_readlane(lane_end, e) - tm_e * tiles_n);
             constexpr int GM = 4;
@@ -408,12 +415,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             const int q = (lin - nwhole) / tiles_n;                      // the q-th expert with such a last tile row
             t.tn = (lin - nwhole) - q * tiles_n;
             e = __builtin_popcountll(__builtin_amdgcn_ballot_w64(tail_end <= q));
-            if (e >= g.E) return false;
+            if (e >= all) return false;
             tm = __builtin_amdgcn_readlane(lane_tm, e);
         }
-        const int rows = g.counts[e];
+        const ExpertOf x = LAY == GEMM_TN ? ExpertOf{e, 0} : expert_of(g, e);
+        t.er = x.q * g.E + x.e;
+        const int rows = g.counts[t.er];
         if (LAY == GEMM_TN) { t.Mdim = g.Mo; t.Kdim = rows; } else { t.Mdim = rows; t.Kdim = g.K; }
-        t.e = e;
+        t.e = x.e;
+        t.q = x.q;
         t.m0 = tm * BM;
         t.n0 = t.tn * BN;
         t.KT = (t.Kdim + BK - 1) / BK;
@@ -421,7 +431,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             if (g.k_segs > 1) {
                 t.Kdim = 0; t.KT = 0;
                 for (int sg = 0; sg < g.k_segs; ++sg) {
-                    const int r = g.counts[sg * g.E + e];
+                    const int r = g.counts[sg * g.E + t.e];
                     t.Kdim += r;
                     t.KT += (r + BK - 1) / BK;
                 }
@@ -437,12 +447,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         return -1;
     };
     auto bind = [&](const TileCoord& t, AT& ta_, BT& tb_, int lane) {
-        const bf16_t* A = (const bf16_t*)g.A + (size_t)t.e * g.a_estride;
+        const bf16_t* A = (const bf16_t*)g.A + (size_t)t.e * g.a_estride + (LAY == GEMM_TN ? 0 : t.q * g.a_pstride);
         const bf16_t* B = (const bf16_t*)g.B + (size_t)t.e * g.b_estride;
         bool gathered = false;
         if constexpr (LAY != GEMM_TN) {
             if (g.a_rows) {
-                ta_.init_gather((const bf16_t*)g.A, g.lda, g.a_rows + (size_t)t.e * g.Cp, t.m0, t.Mdim, g.a_row_limit,
+                ta_.init_gather((const bf16_t*)g.A, g.lda, g.a_rows + (size_t)t.er * g.Cp, t.m0, t.Mdim, g.a_row_limit,
                                 t.Kdim, lane, wid);
                 gathered = true;
             }
@@ -561,7 +571,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             bind(cur, ta, tb, lane);
             if constexpr (LAY == GEMM_TN) { if (g.k_segs > 1) bind_range(cur, kc.seg, ta, tb); }
         }
-        const int m0 = cur.m0, n0 = cur.n0, e = cur.e, tn = cur.tn, Mdim = cur.Mdim, KT = cur.KT;
+        const int m0 = cur.m0, n0 = cur.n0, e = cur.e, q = cur.q, er = cur.er, tn = cur.tn, Mdim = cur.Mdim, KT = cur.KT;
         // blocks of 32 rows per wave that hold rows of this tile
         const int active = ALT && LAY != GEMM_TN ? min(TM, (Mdim - m0 + 32 * C::WAVES_M - 1) / (32 * C::WAVES_M)) : TM;
         floatx16 acc[TM][TNN];
@@ -867,15 +877,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         // (scattered rows: the whole output matrix, every row of which some tile may write)
         const int trows = min(BM, Mdim - m0);
         const char* Cbase = EPI == EPI_SCATTER ? (const char*)g.C
-                                               : (const char*)g.C + ((size_t)e * g.c_estride + (size_t)m0 * g.ldc) * CES;
+                                               : (const char*)g.C + ((size_t)e * g.c_estride + (size_t)m0 * g.ldc + (LAY == GEMM_TN ? 0 : q * g.c_pstride)) * CES;
         const __amdgpu_buffer_rsrc_t rC = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char*>(Cbase), 0,
             (unsigned)(((size_t)((EPI == EPI_SCATTER ? g.c_row_limit : trows) - 1) * g.ldc + g.N) * CES), 0x00020000);
-        const int* crows = g.c_rows ? g.c_rows + (size_t)e * g.Cp : nullptr;
-        const bf16_t* Zbase = g.Z ? (const bf16_t*)g.Z + ((size_t)e * g.Cp + m0) * g.ldz : nullptr;
+        const int* crows = g.c_rows ? g.c_rows + (size_t)er * g.Cp : nullptr;
+        const bf16_t* Zbase = g.Z ? (const bf16_t*)g.Z + ((size_t)e * g.Cp + m0) * g.ldz + q * g.z_pstride : nullptr;
         const __amdgpu_buffer_rsrc_t rZ = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<bf16_t*>(Zbase), 0, Zbase ? (unsigned)(((size_t)(trows - 1) * g.ldz + g.N) * 2) : 0u, 0x00020000);
-        const float* wbase = g.slot_w ? g.slot_w + (size_t)e * g.Cp : nullptr;
+        const float* wbase = g.slot_w ? g.slot_w + (size_t)er * g.Cp : nullptr;
         const int erow = lane & 31, ehalf = lane >> 5;
         // What a pass reads from memory (the pre-activation and row weight for GeLU-backward, the old
         // sums for float accumulation) is requested one pass ahead.
@@ -902,7 +912,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         const unsigned row4 = (unsigned)(m0 + prow) * 4u;
         const __amdgpu_buffer_rsrc_t rW = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(wbase), 0, wbase ? Mdim * 4 : 0, 0x00020000);
         const __amdgpu_buffer_rsrc_t rR = __builtin_amdgcn_make_buffer_rsrc(const_cast<int*>(crows), 0, crows ? Mdim * 4 : 0, 0x00020000);
-        float* dwbase = g.dw_part ? g.dw_part + (size_t)e * g.Cp * g.dw_parts : nullptr;
+        float* dwbase = g.dw_part ? g.dw_part + (size_t)e * g.Cp * g.dw_parts + q * g.dw_pstride : nullptr;
         const __amdgpu_buffer_rsrc_t rD = __builtin_amdgcn_make_buffer_rsrc(dwbase, 0, dwbase ? Mdim * g.dw_parts * 4 : 0, 0x00020000);
         // Float outputs: a lane's two 16-byte halves of "piece" t are units 2t and 2t+1 of a numbering in which the
         // 64 lanes of one store (or load) cover whole rows of the pass - 4 columns per lane, CW/4 lanes per row - so
@@ -1088,7 +1098,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                     for (int i = 0; i < TM; ++i) {
                         const int m = m0 + block_row(i) + dw_row;
                         if (m < Mdim) {
-                            float* at = g.dw_part + ((size_t)e * g.Cp + m) * g.dw_parts + tn;
+                            float* at = dwbase + (size_t)m * g.dw_parts + tn;
                             at[0] = dots[i] + right[i * 32 + dw_row];
                             if (tn == tiles_n - 1 && tn + 1 < g.dw_parts) at[1] = 0.0f;     // blocks come in pairs
                         }
@@ -1208,7 +1218,7 @@ template <int LAY, int EPI, typename C>
 static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
     const int Mmax = (LAY == GEMM_TN) ? a.Mo : a.Cp;
     const int tiles_m = (Mmax + C::BM - 1) / C::BM, tiles_n = (a.N + C::BN - 1) / C::BN;
-    int nblocks = a.E * tiles_m * tiles_n;
+    int nblocks = launch_experts(a) * tiles_m * tiles_n;
     nblocks = (nblocks + 7) / 8 * 8;
     int full = persistent_grid() - (a.free_cus + 7) / 8 * 8;
     if (full < 8) full = 8;
@@ -1222,10 +1232,10 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
         attr_done = true;
     }
     {
-        ProfScope ps(gemm_prof_kind(LAY, EPI), s);
+        ProfScope ps(gemm_prof_kind(LAY, EPI), s, a.np > 1 ? a.np : 1);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(C::THREADS), lds, s, a, tiles_m, tiles_n);
     }
-    count_launch(LC_GEMM);
+    count_launch(LC_GEMM, a.np > 1 ? a.np : 1);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
@@ -1238,7 +1248,8 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
 // a nearly empty tile, and of an epilogue (store, GeLU, GeLU-backward, float store, float accumulation) were fitted
 // to 516 measured launches in all four shapes (1 to 64 experts of 8 to 8192 rows, dimensions 64 to 8192, even and
 // skewed random loads): the choice is on average 2 % slower than the best tile of each launch, 256 x 256 throughout
-// 32 % slower.  The host does not know the loads; it takes every expert to have the mean.
+// 32 % slower.  The host does not know the loads; it takes every expert to have the mean.  A launch for several
+// partitions has the shape of one for a single partition.
 struct TileCost { int bm, bn, per_cu; double step[3], tail_step, epi[5]; };
 static constexpr TileCost TILE_COSTS[4] = {
     {256, 256, 1, {1.09, 1.52, 1.48}, 0.85, {3.3, 10.8, 27.0, 11.1, 20.9}},      // CfgW / Cfg4
@@ -1314,6 +1325,7 @@ static moe_status check_args(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a
     const long long rmax = a.Cp > a.K ? a.Cp : a.K;
     if ((rmax + 8 * 64) * ldmax * 2 >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
     if (a.k_segs > 1 && (lay != GEMM_TN || a.k_segs > MAX_KSEGS)) return MOE_ERR_UNSUPPORTED;
+    if (a.np > 1 && (lay == GEMM_TN || launch_experts(a) > 64)) return MOE_ERR_UNSUPPORTED;
     if (epi == EPI_SCATTER) {
         if (lay == GEMM_TN || !a.c_rows || !a.slot_w || a.c_row_limit <= 0) return MOE_ERR_UNSUPPORTED;
         if (((long long)a.c_row_limit + 1) * a.ldc * 2 >= (1ll << 31)) return MOE_ERR_UNSUPPORTED;
@@ -1343,7 +1355,7 @@ static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, con
         b.d = *dgrad;
         b.tiles_dm = (dgrad->Cp + CN::BM - 1) / CN::BM;
         b.tiles_dn = (dgrad->N + CN::BN - 1) / CN::BN;
-        blocks += (dgrad->E * b.tiles_dm * b.tiles_dn + 7) / 8 * 8;
+        blocks += (launch_experts(*dgrad) * b.tiles_dm * b.tiles_dn + 7) / 8 * 8;
     }
     for (int q = 0; q < 2; ++q) {
         b.tiles_wm[q] = (b.w[q].Mo + CT::BM - 1) / CT::BM;
@@ -1360,10 +1372,10 @@ static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, con
         attr_done = true;
     }
     {
-        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1);
+        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1, dgrad && dgrad->np > 1 ? dgrad->np : 1);
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, b);
     }
-    count_launch(LC_GEMM, dgrad ? 3 : 2);
+    count_launch(LC_GEMM, 2 + (!dgrad ? 0 : dgrad->np > 1 ? dgrad->np : 1));
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

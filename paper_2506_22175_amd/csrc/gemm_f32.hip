@@ -97,10 +97,12 @@ template <bool KC> struct FOperand {
     }
 };
 
-// Tile (tm, tn) of expert e
+// Tile (tm, tn) of expert number v
 template <int LAY, int EPI>
-__device__ __forceinline__ void gemm_f32_one(const GemmArgs& g, int e, int tm, int tn, char* smem) {
-    const int rows = g.counts[e];
+__device__ __forceinline__ void gemm_f32_one(const GemmArgs& g, int v, int tm, int tn, char* smem) {
+    const ExpertOf x = LAY == GEMM_TN ? ExpertOf{v, 0} : expert_of(g, v);
+    const int e = x.e, er = x.q * g.E + e;
+    const int rows = g.counts[er];
     const int Mdim = LAY == GEMM_TN ? g.Mo : rows, Kdim = LAY == GEMM_TN ? rows : g.K;
     const int m0 = tm * F_BM, n0 = tn * F_BN;
     if (m0 >= Mdim) return;
@@ -113,8 +115,8 @@ __device__ __forceinline__ void gemm_f32_one(const GemmArgs& g, int e, int tm, i
     FOperand<LAY != GEMM_TN> A;
     FOperand<LAY == GEMM_NT> B;
     const bool gathered = LAY != GEMM_TN && g.a_rows;         // gathered rows: one matrix for all experts
-    A.init((const float*)g.A + (gathered ? 0 : (size_t)e * g.a_estride), g.lda, m0, Mdim, Kdim, wid, lane,
-           gathered ? g.a_rows + (size_t)e * g.Cp : nullptr);
+    A.init((const float*)g.A + (gathered ? 0 : (size_t)e * g.a_estride + (LAY == GEMM_TN ? 0 : x.q * g.a_pstride)), g.lda, m0, Mdim, Kdim, wid, lane,
+           gathered ? g.a_rows + (size_t)er * g.Cp : nullptr);
     B.init((const float*)g.B + (size_t)e * g.b_estride, g.ldb, n0, g.N, Kdim, wid, lane, nullptr);
     const int KT = (Kdim + F_BK - 1) / F_BK;
 
@@ -154,11 +156,11 @@ __device__ __forceinline__ void gemm_f32_one(const GemmArgs& g, int e, int tm, i
     // columns 8*q + 4*(lane/32) per register group q.
     EpiCtx<float> c;
     c.ldc = g.ldc; c.ldz = g.ldz;
-    c.C = EPI == EPI_SCATTER ? (float*)g.C : (float*)g.C + (size_t)e * g.c_estride;
+    c.C = EPI == EPI_SCATTER ? (float*)g.C : (float*)g.C + (size_t)e * g.c_estride + (LAY == GEMM_TN ? 0 : x.q * g.c_pstride);
     c.Cf = c.C;
-    c.out_rows = g.c_rows ? g.c_rows + (size_t)e * g.Cp : nullptr;
-    c.Z = g.Z ? (float*)g.Z + (size_t)e * g.Cp * g.ldz : nullptr;
-    c.w = g.slot_w ? g.slot_w + (size_t)e * g.Cp : nullptr;
+    c.out_rows = g.c_rows ? g.c_rows + (size_t)er * g.Cp : nullptr;
+    c.Z = g.Z ? (float*)g.Z + (size_t)e * g.Cp * g.ldz + x.q * g.z_pstride : nullptr;
+    c.w = g.slot_w ? g.slot_w + (size_t)er * g.Cp : nullptr;
     const int r = m0 + wm * 32 + (lane & 31);
     float dot = 0.0f;
 #pragma unroll
@@ -174,7 +176,7 @@ __device__ __forceinline__ void gemm_f32_one(const GemmArgs& g, int e, int tm, i
         __syncthreads();                                      // the ring is no longer read
         if (wn == 1 && lane < 32) sdot[wm * 32 + lane] = dot;
         __syncthreads();
-        if (wn == 0 && lane < 32 && r < Mdim) g.dw_part[((size_t)e * g.Cp + r) * g.dw_parts + tn] = dot + sdot[wm * 32 + lane];
+        if (wn == 0 && lane < 32 && r < Mdim) g.dw_part[x.q * g.dw_pstride + ((size_t)e * g.Cp + r) * g.dw_parts + tn] = dot + sdot[wm * 32 + lane];
     }
 }
 
@@ -195,7 +197,7 @@ template <int EPI>
 __global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_backward_kernel(F32BackwardArgs a) {
     __shared__ __attribute__((aligned(16))) char smem[F_NS * 2 * F_TILE];
     int b = blockIdx.x;
-    const int nd = a.d.E * a.tiles_dm * a.tiles_dn;
+    const int nd = launch_experts(a.d) * a.tiles_dm * a.tiles_dn;
     if (b < nd) {
         const int per = a.tiles_dm * a.tiles_dn, e = b / per, r = b - e * per, tm = r / a.tiles_dn;
         gemm_f32_one<GEMM_NT, EPI_STORE>(a.d, e, tm, r - tm * a.tiles_dn, smem);
@@ -217,10 +219,10 @@ static moe_status launch_f32(const GemmArgs& a, hipStream_t s) {
     const int Mmax = (LAY == GEMM_TN) ? a.Mo : a.Cp;
     const int tiles_m = (Mmax + F_BM - 1) / F_BM, tiles_n = (a.N + F_BN - 1) / F_BN;
     {
-        ProfScope ps(gemm_prof_kind(LAY, EPI), s);
-        hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI>), dim3(tiles_n, tiles_m, a.E), dim3(F_THREADS), 0, s, a);
+        ProfScope ps(gemm_prof_kind(LAY, EPI), s, a.np > 1 ? a.np : 1);
+        hipLaunchKernelGGL((gemm_f32_kernel<LAY, EPI>), dim3(tiles_n, tiles_m, launch_experts(a)), dim3(F_THREADS), 0, s, a);
     }
-    count_launch(LC_GEMM);
+    count_launch(LC_GEMM, a.np > 1 ? a.np : 1);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }
@@ -231,7 +233,7 @@ moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const Ge
     b.w[1] = w1;
     auto tiles = [](int n, int t) { return (n + t - 1) / t; };
     if (dgrad) { b.d = *dgrad; b.tiles_dm = tiles(dgrad->Cp, F_BM); b.tiles_dn = tiles(dgrad->N, F_BN); }
-    long long blocks = (long long)b.d.E * b.tiles_dm * b.tiles_dn;
+    long long blocks = (long long)launch_experts(b.d) * b.tiles_dm * b.tiles_dn;
     for (int q = 0; q < 2; ++q) {
         b.tiles_wm[q] = tiles(b.w[q].Mo, F_BM);
         b.tiles_wn[q] = tiles(b.w[q].N, F_BN);
@@ -244,13 +246,13 @@ moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const Ge
         return gemm_f32(GEMM_TN, epi, w1, s);
     }
     {
-        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1);
+        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1, dgrad && dgrad->np > 1 ? dgrad->np : 1);
         if (epi == EPI_STORE_F32)
             hipLaunchKernelGGL((gemm_f32_backward_kernel<EPI_STORE_F32>), dim3((unsigned)blocks), dim3(F_THREADS), 0, s, b);
         else
             hipLaunchKernelGGL((gemm_f32_backward_kernel<EPI_ACCUM_F32>), dim3((unsigned)blocks), dim3(F_THREADS), 0, s, b);
     }
-    count_launch(LC_GEMM, dgrad ? 3 : 2);
+    count_launch(LC_GEMM, 2 + (!dgrad ? 0 : dgrad->np > 1 ? dgrad->np : 1));
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

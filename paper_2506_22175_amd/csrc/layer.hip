@@ -178,6 +178,35 @@ static long long ring_step(int p, int ring, size_t bytes) {
     return ((long long)((p + 1) % ring) - p % ring) * (long long)bytes;
 }
 
+// Forward's GEMMs take several partitions in one launch - twice the tiles, half the last rounds that leave the chip idle,
+// and a partition's experts share the weights that the other's have just read - as far as their activated rows find room
+// in what forward does not need otherwise: backward's temporaries (where T_M is kept) and, with recomputation, the T_M
+// buffer, which come one after another in the workspace.
+static size_t forward_activations(const Dims& d, const Workspace& w) { return mode_recomputes(d.reuse) ? w.Z : w.HT; }
+static int forward_batch(const Dims& d, const Workspace& w) {
+    const size_t room = (w.saved + w.temp - forward_activations(d, w)) / w.bufH;
+    const int lanes = 64 / d.E;                      // (experts of a launch: one per lane)
+    return room < 1 ? 1 : room < (size_t)lanes ? (int)room : lanes;
+}
+
+// Partitions whose rows forward sends and combines at once: a ring of buffers.
+static int forward_unit(const Dims& d, const Workspace& w) {
+    const int S = d.fuse ? d.n : w.nDI, R = w.nDO ? w.nDO : d.n;
+    return S < R ? S : R;                            // (a ring each: all of n buffers, or the same number)
+}
+// Backward's next partitions, one or two: two where the second's buffers of dT_DO (and of T_DI) are free, which the
+// last holder's are once its weight gradients have been taken, at the end of its group.
+static int backward_unit(const Dims& d, const Workspace& w, int p0) {
+    auto is_free = [&](int p, int ring) {
+        const int last = p - ring;
+        return ring >= 2 && (last < 0 || (last / d.G + 1) * d.G <= p0);
+    };
+    const bool redispatch = w.nDI < d.n || d.fuse;
+    return p0 + 1 < d.n && is_free(p0 + 1, w.ndDO) && (!redispatch || is_free(p0 + 1, w.nDI)) ? 2 : 1;
+}
+// Two partitions of one group of weight gradients have T_M and dT_M buffers of their own: one launch for both.
+static int backward_batch(const Dims& d, int p0, int np) { return np == 2 && p0 / d.G == (p0 + 1) / d.G && 2 * d.E <= 64 ? 2 : 1; }
+
 // later: the combine is left to backward, whose dispatch of dy reads the same rows (see chain_backward)
 static moe_status chain_forward(const Dims& d, const Workspace& w, char* ws, const void* x, const void* W1, const void* W2,
                                 void* y, const float* topk_w, const int* slot, const int* counts, bool later, hipStream_t s) {
@@ -187,18 +216,23 @@ static moe_status chain_forward(const Dims& d, const Workspace& w, char* ws, con
     auto DObuf = [&](int p) { return w.nDO ? ws + w.DO + w.bufM * (p % w.nDO) : nullptr; };
     auto Zbuf = [&](int p) { return ws + w.Z + w.bufH * (p % w.nZ); };
     const bool keepZ = !mode_recomputes(d.reuse);
-    const int unit_S = d.fuse ? n : w.nDI, unit_R = w.nDO && !later ? w.nDO : n;
-    const int unit = unit_S < unit_R ? unit_S : unit_R;       // (a ring each: all of n buffers, or the same number)
+    const int unit = forward_unit(d, w), batch = forward_batch(d, w);
+    const size_t activations = forward_activations(d, w);
     for (int p0 = 0; p0 < n; p0 += unit) {
         const int np = n - p0 < unit ? n - p0 : unit;
         if (!d.fuse) {
             const RowMove m = {x, DIbuf(p0), (long long)w.bufM};
             MOE_TRY(dispatch_rows(d, p0, np, &m, 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
         }
-        for (int p = p0; p < p0 + np; ++p)
+        for (int p = p0; p < p0 + np; p += batch) {
+            PartStep step;
+            step.np = p0 + np - p < batch ? p0 + np - p : batch;
+            step.DI = step.DO = (long long)(w.bufM / d.es);
+            step.Z = step.A = (long long)(w.bufH / d.es);
             MOE_TRY(ffn_fwd(d, p, d.fuse ? x : (const void*)DIbuf(p), d.fuse ? rows : nullptr, counts, W1, W2,
-                            keepZ ? Zbuf(p) : nullptr, keepZ ? (void*)(ws + w.HT) : (void*)Zbuf(p), DObuf(p), s,
-                            d.fcomb ? rows : nullptr, (const float*)(ws + w.slot_w), y));
+                            keepZ ? Zbuf(p) : nullptr, ws + activations, DObuf(p), s,
+                            d.fcomb ? rows : nullptr, (const float*)(ws + w.slot_w), y, step));
+        }
         if (w.nDO && !later) MOE_TRY(combine_rows(d, p0, np, DObuf(p0), (long long)w.bufM, slot, topk_w, y, s));
     }
     return MOE_OK;
@@ -230,15 +264,8 @@ static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Wor
     auto dZbuf = [&](int p) { return ws + w.HT + w.bufH * (p % G); };
     auto dDObuf = [&](int p) { return ws + w.dDO + w.bufM * (p % w.ndDO); };
     auto dDIbuf = [&](int p) { return ws + w.dDI + w.bufM * (p % 2); };
-    // partition p's buffer in a ring is free before the GEMMs of partition `now`: whoever had it last has had its weight
-    // gradients taken, which happens at the end of a group
-    auto is_free = [&](int p, int ring, int now) {
-        const int last = p - ring;
-        return last < 0 || (last / G + 1) * G <= now;
-    };
     for (int p0 = 0; p0 < n;) {
-        const int np = p0 + 1 < n && w.ndDO >= 2 && is_free(p0 + 1, w.ndDO, p0) &&
-                       (!redispatch || (w.nDI >= 2 && is_free(p0 + 1, w.nDI, p0))) ? 2 : 1;
+        const int np = backward_unit(d, w, p0), batch = backward_batch(d, p0, np);
         // R': rows of dy to the experts, rows of x again
         const RowMove m[2] = {{dy, dDObuf(p0), ring_step(p0, w.ndDO, w.bufM)}, {x, DIbuf(p0), ring_step(p0, w.nDI, w.bufM)}};
         if (dw_in_gemm) {
@@ -247,16 +274,24 @@ static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Wor
             MOE_TRY(dispatch_rows(d, p0, np, m, 1, slot, DObuf(p0), ring_step(p0, w.nDO, w.bufM), (float*)(ws + w.dw), topk_w, y, s));
             if (d.fuse) MOE_TRY(dispatch_rows(d, p0, np, m + 1, 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
         }
-        for (int p = p0; p < p0 + np; ++p) {
-            // the last partition's input gradient shares the launch of its group's weight gradients
-            const bool group_ends = p % G == G - 1 || p == n - 1;
+        for (int p = p0; p < p0 + np; p += batch) {
+            // the last partitions' input gradients share the launch of their group's weight gradients
+            const int last = p + batch - 1;
+            const bool group_ends = last % G == G - 1 || last == n - 1;
+            PartStep step;
+            step.np = batch;
+            step.DI = ring_step(p, w.nDI, w.bufM) / (long long)d.es;
+            step.dDO = ring_step(p, w.ndDO, w.bufM) / (long long)d.es;
+            step.dDI = ring_step(p, 2, w.bufM) / (long long)d.es;
+            step.Z = step.dZ = (long long)(w.bufH / d.es);
+            step.dw_part = ring_step(p, 2, w.dw_part_bytes) / (long long)sizeof(float);
             MOE_TRY(ffn_bwd_main(d, p, recompute ? 1 : 0, DIbuf(p), Zbuf(p), dDObuf(p), counts, (const float*)(ws + w.slot_w),
                                  W1, W2, dZbuf(p), dDIbuf(p),
-                                 dw_in_gemm ? (float*)(ws + w.dw_part + w.dw_part_bytes * (p % 2)) : nullptr, s, !group_ends));
+                                 dw_in_gemm ? (float*)(ws + w.dw_part + w.dw_part_bytes * (p % 2)) : nullptr, s, !group_ends, step));
             if (group_ends) {
                 const int g0 = p / G * G;
-                MOE_TRY(ffn_wgrad(d, g0, p - g0 + 1, d.overwrite && g0 == 0, DIbuf(g0), Zbuf(g0), dDObuf(g0), dZbuf(g0),
-                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s, W1, dDIbuf(p)));
+                MOE_TRY(ffn_wgrad(d, g0, last - g0 + 1, d.overwrite && g0 == 0, DIbuf(g0), Zbuf(g0), dDObuf(g0), dZbuf(g0),
+                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s, W1, dDIbuf(p), step));
             }
         }
         float* second = np == 2 ? gate_sums_space(d, w, ws, p0 + 1, dw_in_gemm) : nullptr;

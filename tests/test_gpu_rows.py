@@ -116,3 +116,24 @@ def test_step_equals_its_two_halves(T, M, H, E, k, n, dtype):
     assert (out[0]["slot"] < 0).any()
     for name in ("y", "dx", "dWg", "dW1", "dW2"):
         assert np.isfinite(out[0][name]).all() and np.array_equal(out[0][name], out[1][name]), name
+
+
+@pytest.mark.parametrize("T,M,H,E,k,n,dtype,mode,opts", [
+    (1024, 72, 136, 32, 2, 4, "bf16", 0, {}),                                 # two partitions fill the 64 expert numbers
+    (1023, 72, 136, 21, 2, 3, "bf16", 2, dict(wgrad_group=3)),                # three in forward
+    (1056, 72, 264, 33, 2, 4, "bf16", 1, dict(wgrad_group=2)),                # one at a time
+    (512, 136, 72, 5, 1, 8, "bf16", 2, dict(fuse_gather=1, fuse_combine=1, wgrad_group=4)),
+    (512, 136, 72, 5, 1, 8, "f32", 0, dict(fuse_gather=1, fuse_combine=1, wgrad_group=2)),
+    (600, 72, 1032, 3, 2, 3, "f32", 0, {}),                                   # no room for a second activation buffer
+], ids=["two", "three", "one", "gathered_combined", "gathered_combined_f32", "no_room"])
+def test_gemms_of_several_partitions_in_one_launch(T, M, H, E, k, n, dtype, mode, opts):
+    """One stream runs the GEMMs of several partitions at once where their buffers allow it, two streams one by one: the
+    same bits."""
+    from paper_2506_22175_amd import runner, synth
+    s = synth.custom_shape(T, M, H, E, k, 0.8, dtype=dtype, x_std=1.0, w_std=0.05, zipf_s=1.2, zipf_tau=0.3, name="batch")
+    d = synth.make_inputs(s, seed=6)
+    one = runner.run_layer_step(s, d, n, mode, second_stream=False, grad_overwrite=1, **opts)
+    two = runner.run_layer_step(s, d, n, mode, grad_overwrite=1, gemm_free_cus=8, **opts)
+    assert (one["slot"] < 0).any()
+    for name in ("y", "dx", "dWg", "dW1", "dW2", "slot", "counts"):
+        assert np.isfinite(one[name]).all() and np.array_equal(one[name], two[name]), name
