@@ -65,12 +65,14 @@ __device__ __forceinline__ unsigned lds_address(const char* p) {
 }
 
 // ---- tile shape ------------------------------------------------------------------
-// Three main loops, all hand-scheduled:
+// Four main loops, all hand-scheduled:
 //   LOOP_PIPE32 ring of 32-k stages for both operands;
 //   LOOP_W64    64-k steps with one ring per operand: a K-contiguous operand travels as whole
 //               128-byte lines (units of 64 k), the other one in tiles of 32 k.
-//   LOOP_R64    64-k steps with one ring for both operands (tiles small enough for three or more stages of 64 k).
-enum { LOOP_PIPE32 = 1, LOOP_W64 = 2, LOOP_R64 = 3 };
+//   LOOP_R64    64-k steps with one ring for both operands (tiles small enough for three or more stages of 64 k);
+//   LOOP_N64    256 x 256 of two K-contiguous operands: both travel as whole lines in units of 64 k, of which five fit;
+//               the weights of a whole step are held in registers, so that their unit is free half a step early.
+enum { LOOP_PIPE32 = 1, LOOP_W64 = 2, LOOP_R64 = 3, LOOP_N64 = 4 };
 template <int BM_, int BN_, int BK_, int NS_, int WAVES_M_, int WAVES_N_, int OCC_, int LOOP_>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
@@ -80,17 +82,17 @@ struct TileCfg {
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     static constexpr int TM = WM / 32, TN = WN / 32;
     static constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-    static constexpr int LDS_BYTES = LOOP == LOOP_W64 ? 160 * 1024 : NS * STAGE_BYTES;
+    static constexpr int LDS_BYTES = LOOP == LOOP_W64 || LOOP == LOOP_N64 ? 160 * 1024 : NS * STAGE_BYTES;
     static constexpr bool PIPE = LOOP == LOOP_PIPE32;
     // columns of a wave's block that pass through the staging region at a time, and where that region starts
     static constexpr int CW = WN < 64 || (LOOP == LOOP_PIPE32 && OCC == 1) ? WN : LOOP == LOOP_R64 && OCC == 2 ? 32 : 64;
     static constexpr int SBR = (WAVES * 32 * CW * 4 + STAGE_BYTES - 1) / STAGE_BYTES;      // stages that region takes
-    static constexpr int STAGING_OFF = LOOP == LOOP_W64 ? 64 * 1024 : LOOP == LOOP_R64 ? (NS - SBR) * STAGE_BYTES : 0;
+    static constexpr int STAGING_OFF = LOOP == LOOP_W64 ? 64 * 1024 : LOOP == LOOP_N64 ? 128 * 1024 : LOOP == LOOP_R64 ? (NS - SBR) * STAGE_BYTES : 0;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
     static_assert(BK == 32 || BK == 64, "tile depth");
     static_assert(LOOP != LOOP_PIPE32 || (BK == 32 && NS >= 3), "the hand-scheduled ring has stages of 32 k");
-    static_assert(LOOP != LOOP_W64 || (BM == 256 && BN == 256 && BK == 64 && WAVES_M == 2 && WAVES_N == 2 && OCC == 1),
-                  "the two-ring loop is written for four waves of 128 x 128");
+    static_assert((LOOP != LOOP_W64 && LOOP != LOOP_N64) || (BM == 256 && BN == 256 && BK == 64 && WAVES_M == 2 && WAVES_N == 2 && OCC == 1),
+                  "the two-ring and the five-unit loop are written for four waves of 128 x 128");
     static_assert(LOOP != LOOP_R64 || (BK == 64 && NS >= 3 && SBR <= NS - 2),
                   "stages of 64 k; the epilogue stages through the last ones");
 };
@@ -190,7 +192,7 @@ struct NCTile {
     static constexpr int NI = BK / RPI / WAVES;
     static constexpr int BYTES = BK * PITCH;
     static_assert(BK % (RPI * WAVES) == 0 && NI >= 1, "rows must divide over the wavefronts");
-    static_assert(UPR >= 16, "four k rows rotated by four units each must fit a row of units");
+    static_assert(UPR >= 16 || UPR == 8, "four k rows rotated by four units each must fit a row of units (or two rows)");
     v4i rsrc;
     unsigned voff[NI];
     unsigned kstep;          // bytes per k row in memory
@@ -207,7 +209,7 @@ struct NCTile {
         for (int j = 0; j < NI; ++j) {
             const int q = wid * NI + j;
             const int row = q * RPI + lane / UPR;
-            const int u = ((lane % UPR) - 4 * (row & 3) + UPR) % UPR;
+            const int u = ((lane % UPR) - 4 * (row & 3) + 4 * UPR) % UPR;
             voff[j] = (u * 8 < n_valid) ? (unsigned)(row * ld + u * 8) * 2u : OOB_OFFSET;
         }
     }
@@ -295,7 +297,7 @@ struct KCursor { int seg, jl, tiles; };
 // l / np of partition l % np where the launch covers several; at most 64 in all);
 // inclusive scans over the lanes give the numbers at which each expert ends.
 struct TileNumbers {
-    int lane_tm;                         // such tile rows of expert `lane`
+    int lane_rows, lane_tm;              // rows, such tile rows of expert `lane`
     int lane_end, tail_end;              // numbers of whole tiles / of last tile rows up to and including this expert
     int nwhole, nblocks;                 // whole tiles; all tiles
 };
@@ -303,7 +305,7 @@ template <int LAY, int EPI, typename C>
 __device__ __forceinline__ TileNumbers number_tiles(const GemmArgs& g, int tiles_m, int tiles_n, int lane) {
     constexpr int BM = C::BM;
     TileNumbers t;
-    t.lane_tm = 0;
+    t.lane_rows = t.lane_tm = 0;
     int lane_tail = 0;                   // whether a last tile row with fewer rows follows
     if (lane < (LAY == GEMM_TN ? g.E : launch_experts(g))) {
         int rows = 0;
@@ -314,6 +316,7 @@ __device__ __forceinline__ TileNumbers number_tiles(const GemmArgs& g, int tiles
             const ExpertOf x = expert_of(g, lane);
             rows = g.counts[x.q * g.E + x.e];
         }
+        t.lane_rows = rows;
         if (LAY == GEMM_TN) t.lane_tm = (rows > 0 || EPI == EPI_STORE_F32) ? tiles_m : 0;   // a plain store still writes zeros
         else {
             t.lane_tm = min(tiles_m, (rows + BM / 2 - 1) / BM);
@@ -342,7 +345,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, TNN = C::TN;
     constexpr int STAGE = C::STAGE_BYTES, BK = C::BK, NS = C::NS;
-    constexpr bool W64 = C::LOOP == LOOP_W64, R64 = C::LOOP == LOOP_R64;
+    constexpr bool W64 = C::LOOP == LOOP_W64, R64 = C::LOOP == LOOP_R64, N64 = C::LOOP == LOOP_N64;
+    static_assert(!N64 || LAY == GEMM_NT, "units of 64 k of both operands");
     constexpr bool ALT = C::LOOP != LOOP_PIPE32;     // waves' row blocks alternate (see block_row)
     // Depth of one load unit of each operand.  In the two-ring loop a K-contiguous row operand (A of
     // NN) or the K-contiguous weights (B of NT) travel 64 k at a time, so that every request is a whole
@@ -357,7 +361,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     constexpr int SB = 2;
     constexpr int CW = C::CW;
     static_assert(ALT || C::WAVES * 32 * CW * 4 <= SB * STAGE, "staging does not fit below the ring's first stage");
-    static_assert(!W64 || C::WAVES * 32 * CW * 4 <= 32 * 1024, "staging does not fit one unit of the wide ring");
+    static_assert(!(W64 || N64) || C::WAVES * 32 * CW * 4 <= 32 * 1024, "staging does not fit one unit of the wide ring");
     // two-ring LDS map: three units of 64 k x 256 rows, then four tiles of 32 k x 256 rows
     constexpr int WIDE_UNIT = 32 * 1024, NARROW_TILE = 16 * 1024, NARROW_OFF = 3 * WIDE_UNIT;
 
@@ -420,7 +424,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         }
         const ExpertOf x = LAY == GEMM_TN ? ExpertOf{e, 0} : expert_of(g, e);
         t.er = x.q * g.E + x.e;
-        const int rows = g.counts[t.er];
+        const int rows = __builtin_amdgcn_readlane(tiles.lane_rows, e);
         if (LAY == GEMM_TN) { t.Mdim = g.Mo; t.Kdim = rows; } else { t.Mdim = rows; t.Kdim = g.K; }
         t.e = x.e;
         t.q = x.q;
@@ -429,12 +433,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         t.KT = (t.Kdim + BK - 1) / BK;
         if constexpr (LAY == GEMM_TN) {
             if (g.k_segs > 1) {
-                t.Kdim = 0; t.KT = 0;
-                for (int sg = 0; sg < g.k_segs; ++sg) {
-                    const int r = g.counts[sg * g.E + t.e];
-                    t.Kdim += r;
-                    t.KT += (r + BK - 1) / BK;
-                }
+                t.KT = 0;
+                for (int sg = 0; sg < g.k_segs; ++sg) t.KT += (g.counts[sg * g.E + t.e] + BK - 1) / BK;
             }
         }
         if (t.m0 >= t.Mdim) return false;
@@ -509,6 +509,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     // half-size tiles: a wave's loads of a stage that go out in block 3 of a step, the rest follow in blocks 0, 1, 2
     constexpr int R64_G3 = (LPW + 2) / 3, R64_G0 = (LPW + 1) / 3, R64_G1 = LPW / 3, R64_G2 = 0;
     static_assert(!R64 || R64_G3 + R64_G0 + R64_G1 + R64_G2 == LPW, "loads of a stage over the blocks");
+    // five-unit loop: load l of the weights' / the rows' unit of step t into a unit slot
+    constexpr int UL = N64 ? 8 : 0;
+    static_assert(!N64 || (AT::NI == 8 && BT::NI == 8), "eight loads per wave and unit");
+    auto load_b = [&](const BT& tb_, int slot, int t, int l) { tb_.load_one(smem + slot * WIDE_UNIT, t * 64, wid, l); };
+    auto load_a = [&](const AT& ta_, int slot, int t, int l) { ta_.load_one(smem + slot * WIDE_UNIT, t * 64, wid, l); };
     // the part of a tile's first loads that does not touch the staging region, and the rest
     auto issue_early = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
@@ -526,6 +531,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             for (int l = 0; l < NL; ++l) load_narrow(ta_, tb_, 2, 2, l);
 #pragma unroll
             for (int l = 0; l < NL / 2; ++l) load_narrow(ta_, tb_, 3, 3, l);
+        } else if constexpr (N64) {
+            // units 0 to 3: weights and rows of steps 0 and 1
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int l = 0; l < UL; ++l) load_b(tb_, 2 * t, t, l);
+#pragma unroll
+                for (int l = 0; l < UL; ++l) load_a(ta_, 2 * t + 1, t, l);
+            }
         } else {
             constexpr int FIRST = R64 ? 0 : SB, STAGES = R64 ? NS - C::SBR : NS - SB;
 #pragma unroll
@@ -538,6 +552,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         if constexpr (W64) {
 #pragma unroll
             for (int l = 0; l < WL / 4; ++l) load_wide(ta_, tb_, 2, 2, l);
+        } else if constexpr (N64) {
+#pragma unroll
+            for (int l = 0; l < UL / 4; ++l) load_b(tb_, 4, 2, l);
         } else if constexpr (R64) {
 #pragma unroll
             for (int s = NS - C::SBR; s < NS - 1; ++s)
@@ -676,6 +693,91 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 }
                 w3 = w3a;
                 n4 = n4b;
+            }
+            };
+            if (active == 4) loop(std::integral_constant<int, 4>{});
+            else if (active == 3) loop(std::integral_constant<int, 3>{});
+            else if (active == 2) loop(std::integral_constant<int, 2>{});
+            else loop(std::integral_constant<int, 1>{});
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+        } else if constexpr (N64) {
+            // Hand-scheduled loop over steps of 64 k = eight blocks of 2 x TN matrix instructions: blocks 0 to 3 the wave's
+            // first two blocks of rows over the four 16 k, blocks 4 to 7 the other two.  Unit 2t holds the weights of
+            // step t, unit 2t+1 its rows, unit u lies in slot u mod 5.  All weights of a step are in registers when it
+            // begins; in blocks 4 to 7 those of the next step take their places, each behind the last matrix instruction
+            // that needs the old ones.  Rows are read one block ahead.  Two barriers per step:
+            //   after block 3: every wave has read the weights of step t for the last time (block 7 of step t-1), their
+            //           slot receives the rows of step t+2 (blocks 4 to 6); and the weights of step t+1 have landed;
+            //   after block 6: every wave has read the rows of step t for the last time, their slot receives the weights
+            //           of step t+3 (block 7 and blocks 0 to 2 of the next step); and the rows of step t+1 have landed.
+            // So a unit is requested 1.4 (rows) or 1.6 steps (weights) before it has to be there, and at either barrier
+            // the sixteen youngest loads of a wave may still be in flight.  (LOOP_W64 has this layout's rows in tiles of
+            // 32 k, that is in half lines.  Input gradient in launches by itself, 12 x 1400 rows x 640, K = 2560: 79.6 us with
+            // LOOP_W64, 73.3 so; 16 x 2048 x 2048, K = 8192: 998 and 976; 8 x 4096 x 1024, K = 4096, with the weight gradients:
+            // 242 and 235 per GEMM.)
+            if (first) wait_vmcnt<16 + UL / 4>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            auto loop = [&](auto tma) __attribute__((always_inline)) {
+            constexpr int TMA = decltype(tma)::value;
+            bf16x8 W[4][TNN], R[2][2];               // weights per 16 k; rows of this block and of the next one
+            const auto row_frag = [&](int b, int i, const char* unit) __attribute__((always_inline)) -> bf16x8 {
+                return fa[(b < 4 ? 0 : 2) + i].read(unit, b & 3);
+            };
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                for (int j = 0; j < TNN; ++j) W[kk][j] = fb[j].read(smem, kk);
+#pragma unroll
+            for (int i = 0; i < (TMA < 2 ? TMA : 2); ++i) R[0][i] = row_frag(0, i, smem + WIDE_UNIT);
+            int s5 = 0;                              // slot of the weights of step t
+            const auto slot = [&](int add) __attribute__((always_inline)) { const int v = s5 + add; return v >= 5 ? v - 5 : v; };
+#pragma unroll 1
+            for (int t = 0; t < KT; ++t) {
+                const char* rows = smem + slot(1) * WIDE_UNIT;
+                const char* w_next = smem + slot(2) * WIDE_UNIT;
+                const char* rows_next = smem + slot(3) * WIDE_UNIT;
+                const int to_a = s5, to_b2 = slot(4), to_b3 = slot(1);
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    const int i0 = b < 4 ? 0 : 2, nr = TMA - i0 < 0 ? 0 : TMA - i0 > 2 ? 2 : TMA - i0;      // rows' blocks of this block
+                    const int bn = (b + 1) & 7, n0r = bn < 4 ? 0 : 2;
+                    const int nn = TMA - n0r < 0 ? 0 : TMA - n0r > 2 ? 2 : TMA - n0r;                       // and of the next one
+                    const char* rn = b == 7 ? rows_next : rows;
+                    // what follows matrix instruction m of the block (all of it where the block has none)
+                    auto rows_ahead = [&](int i) __attribute__((always_inline)) { if (i < nn) R[bn & 1][i] = row_frag(bn, i, rn); };
+                    auto weights_ahead = [&](int j) __attribute__((always_inline)) { if (b >= 4) W[b - 4][j] = fb[j].read(w_next, b - 4); };
+                    auto load = [&](int l) __attribute__((always_inline)) {
+                        if (b < 3) { if (l < 2) load_b(tb, to_b2, t + 2, 2 * (b + 1) + l); }
+                        else if (b == 7) { if (l < 2) load_b(tb, to_b3, t + 3, l); }
+                        else if (b >= 4) { if (l < (b == 6 ? 2 : 3)) load_a(ta, to_a, t + 2, 3 * (b - 4) + l); }
+                    };
+                    if (nr == 0) {
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) rows_ahead(i);
+#pragma unroll
+                        for (int j = 0; j < TNN; ++j) weights_ahead(j);
+#pragma unroll
+                        for (int l = 0; l < 3; ++l) load(l);
+                    }
+#pragma unroll
+                    for (int m = 0; m < 2 * TNN; ++m) {
+                        if (m >= nr * TNN) continue;
+                        const int i = m / TNN, j = m % TNN;
+                        mfma_pinned<true>(acc[i0 + i][j], W[b & 3][j], R[b & 1][i]);
+                        if (m < 2) rows_ahead(m);
+                        else if (m < 4) load(m - 2);
+                        if (m == nr * TNN - 1) load(2);
+                        if (i == nr - 1) weights_ahead(j);
+                    }
+                    if (b == 3 || b == 6) {
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        wait_vmcnt<16>();
+                        __builtin_amdgcn_s_barrier();
+                        asm volatile("" ::: "memory");
+                    }
+                }
+                s5 = slot(2);
             }
             };
             if (active == 4) loop(std::integral_constant<int, 4>{});
@@ -1170,10 +1272,13 @@ void gemm_bf16_backward_kernel(BackwardArgs a) {
     gemm_tiles<GEMM_TN, EPI, CT, true>(a.w[q], a.tiles_wm[q], a.tiles_wn[q], t, b, 1 << 30);
 }
 
-// Tile shapes in use.  The first two cover 256 x 256 per workgroup with four waves of 128 x 128, one per SIMD.
-//   CfgW   two-ring loop: for every GEMM with a K-contiguous operand (NN, NT).  A request for half a
+// Tile shapes in use.  The first three cover 256 x 256 per workgroup with four waves of 128 x 128, one per SIMD.
+//   CfgW   two-ring loop: NN, and NT with the GeLU-backward epilogue.  A request for half a
 //          128-byte line costs the L1 as much as one for a whole line, and the loop's speed follows
 //          the number of requests; here every request but those of NT's row operand is a whole line.
+//   CfgN   five-unit loop: NT with a plain store (the input gradient); every request is a whole line.  With the
+//          GeLU-backward epilogue it needs more registers than there are (11 spilled) and is 1 % faster on the large layer
+//          (1283 -> 1269 us), 3 % slower on mid-size ones (8 x 4096 x 4096, K = 1024: 411 -> 424).
 //   Cfg4   ring of 5 x 32 k: the weight-gradient GEMMs (TN), whose two operands are N-contiguous
 //          and come in whole lines anyway.
 // (Shapes with two waves of 128 x 64 per SIMD - TileCfg<256, 256, 32, 5, 2, 4, 2, LOOP_PIPE32> - ran the GeLU
@@ -1181,7 +1286,9 @@ void gemm_bf16_backward_kernel(BackwardArgs a) {
 // arithmetic the four-wave shapes win everywhere.)
 typedef TileCfg<256, 256, 32, 5, 2, 2, 1, LOOP_PIPE32> Cfg4;
 typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_W64> CfgW;
+typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_N64> CfgN;
 template <int LAY, int EPI> struct CfgFor { typedef CfgW type; };
+template <> struct CfgFor<GEMM_NT, EPI_STORE> { typedef CfgN type; };
 template <int EPI> struct CfgFor<GEMM_TN, EPI> { typedef Cfg4 type; };
 // Smaller tiles for launches that 256 x 256 leaves too few of, all layouts (the flat one: NN, NT):
 //   CfgM   256 x 128, waves of 128 x 64, three 64-k stages of both operands, so that every request is a whole line.
@@ -1197,6 +1304,11 @@ typedef TileCfg<128, 128, 32, 5, 2, 2, 2, LOOP_PIPE32> CfgS;
 typedef TileCfg<64, 128, 64, 6, 2, 2, 1, LOOP_R64> CfgT;
 //   CfgT2  CfgT with three stages, two workgroups per CU: beside CfgS in one launch.
 typedef TileCfg<64, 128, 64, 3, 2, 2, 2, LOOP_R64> CfgT2;
+//   CfgU   64 x 64, waves of 32 x 32, ten 64-k stages, for plain stores over a long K: where CfgT has tiles for half of
+//          the CUs at most, its steps wait for loads that were requested five steps before.  8 rows of 16, N = 1024,
+//          K = 4096: 22 us in 64 tiles of CfgT, 13 in 128; 8 x 128 rows: 38.9 and 29.3; K = 2048: the same either way.
+typedef TileCfg<64, 64, 64, 10, 2, 2, 1, LOOP_R64> CfgU;
+constexpr int CFG_U_MIN_K = 1024;
 
 int gemm_bf16_dw_parts(int H) { return (H + 2 * DW_COLS - 1) / (2 * DW_COLS) * 2; }
 
@@ -1251,11 +1363,12 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
 // 32 % slower.  The host does not know the loads; it takes every expert to have the mean.  A launch for several
 // partitions has the shape of one for a single partition.
 struct TileCost { int bm, bn, per_cu; double step[3], tail_step, epi[5]; };
-static constexpr TileCost TILE_COSTS[4] = {
+static constexpr TileCost TILE_COSTS[5] = {
     {256, 256, 1, {1.09, 1.52, 1.48}, 0.85, {3.3, 10.8, 27.0, 11.1, 20.9}},      // CfgW / Cfg4
     {256, 128, 1, {0.87, 0.84, 0.93}, 0.72, {3.4, 8.6, 19.1, 6.7, 11.0}},        // CfgM
     {128, 128, 2, {0.90, 1.29, 0.94}, 0.0, {3.0, 5.0, 9.3, 6.5, 8.8}},           // CfgS (two tiles at a time)
     {64, 128, 1, {0.44, 0.42, 0.0}, 0.92, {1.5, 2.5, 5.0, 0.0, 0.0}},            // CfgT (not for TN)
+    {64, 64, 1, {0.24, 0.0, 0.0}, 0.24, {1.2, 0.0, 0.0, 0.0, 0.0}},              // CfgU (NN stores)
 };
 static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, int cus) {
     const int which = epi == EPI_GELU ? 1 : epi == EPI_DGELU ? 2 : epi == EPI_STORE_F32 ? 3 : epi == EPI_ACCUM_F32 ? 4 : 0;
@@ -1288,7 +1401,8 @@ static int tile_choice(int lay, int epi, const GemmArgs& a) {
     const int cus = persistent_grid();               // (units left free change the time of a launch, not its results)
     int best = 0;
     double least = 0.0;
-    for (int c = 0; c < (lay == GEMM_TN ? 3 : 4); ++c) {
+    const bool u = lay == GEMM_NN && (epi == EPI_STORE || epi == EPI_SCATTER) && a.K >= CFG_U_MIN_K;
+    for (int c = 0; c < (lay == GEMM_TN ? 3 : u ? 5 : 4); ++c) {
         const double t = tile_time(TILE_COSTS[c], lay, epi, a, cus);
         // (a smaller tile has to be clearly better: skewed loads drop rows and make more cheap last tile rows)
         if (c == 0 || t < (best == 0 ? 0.93 : 1.0) * least) { best = c; least = t; }
@@ -1304,6 +1418,7 @@ static moe_status launch_cfg(const GemmArgs& a, hipStream_t s) {
     const int choice = tile_choice(LAY, EPI, a);
     if (choice == 2) return launch_one<LAY, EPI, CfgS>(a, s);
     if constexpr (LAY != GEMM_TN) { if (choice == 3) return launch_one<LAY, EPI, CfgT>(a, s); }
+    if constexpr (LAY == GEMM_NN && EPI != EPI_GELU) { if (choice == 4) return launch_one<LAY, EPI, CfgU>(a, s); }
     if (choice == 1) return launch_one<LAY, EPI, CfgM>(a, s);
     return launch_one<LAY, EPI, typename CfgFor<LAY, EPI>::type>(a, s);
 }
@@ -1393,7 +1508,7 @@ static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const 
     if (cd == 2) return MOE_OK;
     if (cd == 1) return launch_backward<EPI, CfgM, Cfg4>(dgrad, w2, w1, s, done);
     if (cd == 3) return launch_backward<EPI, CfgT, Cfg4>(dgrad, w2, w1, s, done);
-    return launch_backward<EPI, CfgW, Cfg4>(dgrad, w2, w1, s, done);
+    return launch_backward<EPI, CfgN, Cfg4>(dgrad, w2, w1, s, done);
 }
 
 moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s,

@@ -125,6 +125,14 @@ def test_last_gradients_in_one_launch(M, H, E, Cp, dgrad, dw, recompute, overwri
     _run("bf16", M, H, counts, Cp, 17, recompute, overwrite, tiles=dict(dgrad=dgrad, dW2=dw, dW1=dw))
 
 
+# 64 x 64 tiles of the second layer: few rows against a long reduction that ends inside a step, columns inside a tile
+@pytest.mark.parametrize("M,H,counts,Cp", [
+    (296, 1592, (1, 0, 18, 17, 64, 65, 33, 128), 128), (8, 1024, (1, 3), 3), (72, 4104, (129,), 129), (136, 1288, (64, 63, 31, 32), 64),
+], ids=["many", "min", "one", "k_tail"])
+def test_expert_ffn_in_the_smallest_tiles(M, H, counts, Cp):
+    _run("bf16", M, H, counts, Cp, 19, 1, 1, tiles=dict(second=(64, 64)))
+
+
 # float gradients of more than 2 GiB per expert, with columns that end inside a tile: the offset that stands for "out
 # of range" is then smaller than the gradients (the reference takes some 40 GB)
 @pytest.mark.parametrize("overwrite", [0, 1])

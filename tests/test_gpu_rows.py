@@ -137,3 +137,21 @@ def test_gemms_of_several_partitions_in_one_launch(T, M, H, E, k, n, dtype, mode
     assert (one["slot"] < 0).any()
     for name in ("y", "dx", "dWg", "dW1", "dW2", "slot", "counts"):
         assert np.isfinite(one[name]).all() and np.array_equal(one[name], two[name]), name
+
+
+@pytest.mark.parametrize("T,M,H,E,n", [(404, 136, 1288, 4, 2), (130, 72, 2056, 3, 1)])
+def test_scattered_rows_in_the_smallest_tiles(T, M, H, E, n):
+    """The fused combine from 64 x 64 tiles: what the combine kernel gives up to one rounding, zeros for dropped tokens."""
+    from paper_2506_22175_amd import runner, synth
+    s = synth.custom_shape(T, M, H, E, 1, 0.9, dtype="bf16", x_std=1.0, w_std=0.05, zipf_s=1.2, zipf_tau=0.5, name="k1")
+    d = synth.make_inputs(s, seed=17)
+    cfg = B.make_config(T, M, H, E, 1, 0.9, n, B.MOE_BF16, 0, 1, fuse_combine=1)
+    assert B.moe_gemm_tile(cfg, 0, "second") == (64, 64)
+    plain = runner.run_layer_step(s, d, n, 0, grad_overwrite=1)
+    fused = runner.run_layer_step(s, d, n, 0, grad_overwrite=1, fuse_combine=1)
+    dropped = (fused["slot"] < 0).all(axis=1)
+    assert dropped.any() and np.all(fused["y"][dropped] == 0.0)
+    # row by row: both round w * row to bfloat16 (2^-8 of it), the plain combine after a rounding of the row
+    scale = np.abs(plain["y"]).max(axis=1, keepdims=True)
+    assert np.all(np.abs(fused["y"] - plain["y"]) <= 2.0 ** -6 * scale)
+    assert np.array_equal(fused["dW1"], plain["dW1"])
