@@ -229,11 +229,26 @@ inline int gemm_prof_kind(int lay, int epi) {
 
 moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
 moe_status gemm_f32(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s);
-// The two weight gradients (TN, epi) and, unless NULL, the input gradient (NT, store) in one launch.  The bfloat16 one
-// does so where the tile shapes fit together, else it launches nothing and says so.
-moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s,
-                              bool* done);
-moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s);
+// dL of np partitions' gates, blocks of 64 tokens (gate_bwd.h)
+struct GateDlArgs {
+    const float* logits; const int* topk_idx; const int* slot;
+    const float* dw;                     // given combine-weight gradients, or
+    const float* dw_part;                // the GeLU-backward GEMM's row dots, `parts` per row
+    long long dw_part_stride;            // floats from one partition's to the next one's
+    int parts;
+    float* dL;
+    bf16_t* dLt;                         // transposed, bfloat16 storage
+    long long dLt_stride;
+    int tp_pad, p0, Tp, E, k, renorm;
+    int per_part, blocks;                // blocks of a partition, of all
+};
+
+// The two weight gradients (TN, epi) and, unless NULL, the input gradient (NT, store) and a gate's dL in one launch.  The
+// bfloat16 one does so where the tile shapes fit together, else it launches nothing; *done says so.
+moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi,
+                              const GateDlArgs* gate, hipStream_t s, bool* done);
+moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi,
+                             const GateDlArgs* gate, hipStream_t s, bool* done);
 int gemm_bf16_dw_parts(int H);   // column blocks the DGELU epilogue reports per row
 int gemm_f32_dw_parts(int H);
 void gemm_bf16_tile(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, int* rows, int* cols);   // of a launch; host only
@@ -257,17 +272,17 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
                         void* dZ, void* dDI, float* dw_part, hipStream_t s, bool with_dgrad = true,
                         const PartStep& step = PartStep());
 // dgrad_W1 != NULL: and the input gradient of the last step.np of the partitions (which ffn_bwd_main left out) into dDI,
-// that of the first of them
+// that of the first of them; gate != NULL: and that dL, if all this fits one launch (*gate_done)
 moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void* DI, const void* A, const void* dDO,
                      const void* dZ, long long strideM, long long strideH, const int* counts,
                      float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1 = nullptr, void* dDI = nullptr,
-                     const PartStep& step = PartStep());
+                     const PartStep& step = PartStep(), const GateDlArgs* gate = nullptr, bool* gate_done = nullptr);
 
 // ---- row permutations and gate backward of np consecutive partitions from p0 on (permute.hip) ----
 // Pointers are partition p0's, strides lead from one partition's buffer to the next one's.
 struct RowMove { const void* src; void* dst; long long stride; };      // token-major rows, partition buffer, bytes
-// S: rows of up to two sources to the experts.  dw != NULL (one source): dw = <src, DO row> on the way; y != NULL: and
-// the combine of the same DO rows with weights w.
+// S: rows of up to two sources to the experts.  dw != NULL (one source): dw = <src, DO row> on the way; y != NULL: the
+// combine of the same DO rows with weights w (which the first source's may replace).
 moe_status dispatch_rows(const Dims& d, int p0, int np, const RowMove* moves, int n_moves, const int* slot,
                          const void* DO, long long DO_stride, float* dw, const float* w, void* y, hipStream_t s);
 moe_status combine_rows(const Dims& d, int p0, int np, const void* DO, long long DO_stride, const int* slot, const float* w,
@@ -279,11 +294,13 @@ struct GateSums {
     float* dWg;
     int nblk, ME, np, store;             // blocks per partition, outputs, partitions; store: the first total is stored, not added
 };
-// Gate backward.  part: gate_part_bytes per partition, part_stride floats apart; dLt (bfloat16): gate_dlt_bytes per
-// partition, one behind the other.  sums != NULL: the partial sums are left for dispatch_bwd_rows to add up.
-moe_status gate_bwd_rows(const Dims& d, int p0, int np, const void* x, const float* logits, const int* idx, const int* slot,
-                         const float* dw, const float* dw_part, long long dw_part_stride, int parts, float* dL, float* dWg,
-                         float* part, long long part_stride, void* dLt, hipStream_t s, GateSums* sums);
+// Gate backward: dL (which may have been computed beside the last GEMMs, dl_done), then the gate-weight gradient.  dLt
+// (bfloat16): gate_dlt_bytes per partition, one behind the other; part: gate_part_bytes per partition, part_stride floats
+// apart.  sums != NULL: the partial sums are left for dispatch_bwd_rows to add up.
+GateDlArgs gate_dl_args(const Dims& d, int p0, int np, const float* logits, const int* idx, const int* slot, const float* dw,
+                        const float* dw_part, long long dw_part_stride, int parts, float* dL, void* dLt);
+moe_status gate_bwd_rows(const Dims& d, int np, const void* x, const GateDlArgs& dl, bool dl_done, float* dWg,
+                         float* part, long long part_stride, hipStream_t s, GateSums* sums);
 size_t gate_part_bytes(const Dims& d);
 size_t gate_dlt_bytes(const Dims& d);
 size_t gate_dlt_offset(const Dims& d);           // of the first partition's dLt in the buffer of moe_gate_scratch_bytes

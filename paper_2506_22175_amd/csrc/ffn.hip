@@ -102,7 +102,8 @@ moe_status ffn_bwd_main(const Dims& d, int part, int recompute, const void* DI, 
 // are read and written once per group instead of once per partition.
 moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void* DI, const void* A, const void* dDO,
                      const void* dZ, long long strideM, long long strideH, const int* counts,
-                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1, void* dDI, const PartStep& step) {
+                     float* dW1, float* dW2, hipStream_t s, const void* dgrad_W1, void* dDI, const PartStep& step,
+                     const GateDlArgs* gate, bool* gate_done) {
     const long long eM = (long long)d.Cp * d.M, eH = (long long)d.Cp * d.H, wMH = (long long)d.M * d.H;
     // the float GEMM reduces one partition per launch
     const int per_launch = d.dtype == MOE_F32 ? 1 : nparts;
@@ -130,19 +131,21 @@ moe_status ffn_wgrad(const Dims& d, int part, int nparts, int store, const void*
         const GemmArgs dg = with_dgrad ? dgrad_args(d, counts + (size_t)(part + first) * d.E,
                                                     (const char*)dZ + (size_t)first * strideH * d.es, dgrad_W1, dDI, step)
                                        : GemmArgs{};
-        if (d.dtype == MOE_F32) {
-            MOE_TRY(gemm_f32_backward(with_dgrad ? &dg : nullptr, w2, w1, epi, s));
-            continue;
-        }
+        const bool f32 = d.dtype == MOE_F32;
+        const GateDlArgs* g = q + per_launch >= nparts ? gate : nullptr;
+        auto together = [&](const GemmArgs* in, bool* done) {
+            return f32 ? gemm_f32_backward(in, w2, w1, epi, g, s, done) : gemm_bf16_backward(in, w2, w1, epi, g, s, done);
+        };
         bool done = false;
         if (with_dgrad) {
-            MOE_TRY(gemm_bf16_backward(&dg, w2, w1, epi, s, &done));
-            if (!done) MOE_TRY(gemm_bf16(GEMM_NT, EPI_STORE, dg, s));
+            MOE_TRY(together(&dg, &done));
+            if (!done) MOE_TRY(run_gemm(d, GEMM_NT, EPI_STORE, dg, s));
         }
-        if (!done) MOE_TRY(gemm_bf16_backward(nullptr, w2, w1, epi, s, &done));
+        if (!done) MOE_TRY(together(nullptr, &done));
+        if (g && done) *gate_done = true;
         if (!done) {
-            MOE_TRY(gemm_bf16(GEMM_TN, epi, w2, s));
-            MOE_TRY(gemm_bf16(GEMM_TN, epi, w1, s));
+            MOE_TRY(run_gemm(d, GEMM_TN, epi, w2, s));
+            MOE_TRY(run_gemm(d, GEMM_TN, epi, w1, s));
         }
     }
     return MOE_OK;

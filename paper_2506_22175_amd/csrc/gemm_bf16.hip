@@ -25,6 +25,7 @@
 // waits).  One s_barrier per tile.
 #include "common.h"
 #include "epilogue.h"
+#include "gate_bwd.h"
 #include <type_traits>
 
 namespace moe {
@@ -1245,11 +1246,14 @@ struct BackwardArgs {
     GemmArgs d;                          // input gradient; not there if tiles_d == 0
     GemmArgs w[2];                       // weight gradients
     int tiles_dm, tiles_dn, tiles_wm[2], tiles_wn[2];
+    GateDlArgs gate;                     // in the blocks after the last tile (blocks = 0: not there)
 };
 template <int EPI, typename CN, typename CT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CT::OCC, CT::OCC)))
 void gemm_bf16_backward_kernel(BackwardArgs a) {
-    static_assert(CN::OCC == CT::OCC && CN::THREADS == 256 && CT::THREADS == 256, "tiles of one launch share its shape");
+    static_assert(CN::OCC == CT::OCC && CN::THREADS == 256 && CT::THREADS == 256 && GATE_THREADS == 256 && GATE_DL_LDS <= CT::LDS_BYTES,
+                  "tiles of one launch share its shape");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63;
     int b = blockIdx.x;
     if (a.tiles_dm > 0) {
@@ -1268,6 +1272,11 @@ void gemm_bf16_backward_kernel(BackwardArgs a) {
         b -= n;
         q = 1;
         t = number_tiles<GEMM_TN, EPI, CT>(a.w[1], a.tiles_wm[1], a.tiles_wn[1], lane);
+    }
+    if (q == 1 && b >= t.nblocks) {
+        // the gate's dL, which only needs the row dots of the GeLU-backward GEMM: a launch of its own takes 4 to 6 us
+        if (b - t.nblocks < a.gate.blocks) gate_dl(a.gate, b - t.nblocks, smem);
+        return;
     }
     gemm_tiles<GEMM_TN, EPI, CT, true>(a.w[q], a.tiles_wm[q], a.tiles_wn[q], t, b, 1 << 30);
 }
@@ -1461,7 +1470,8 @@ static moe_status check_args(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a
 constexpr int BACKWARD_ROUNDS = 24;
 
 template <int EPI, typename CN, typename CT>
-static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, hipStream_t s, bool* done) {
+static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, const GateDlArgs* gate,
+                                  hipStream_t s, bool* done) {
     BackwardArgs b = {};
     b.w[0] = w2;
     b.w[1] = w1;
@@ -1479,6 +1489,7 @@ static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, con
     }
     *done = blocks <= BACKWARD_ROUNDS * CT::OCC * persistent_grid();
     if (!*done) return MOE_OK;
+    if (gate) { b.gate = *gate; blocks += gate->blocks; }
     constexpr int lds = CN::LDS_BYTES > CT::LDS_BYTES ? CN::LDS_BYTES : CT::LDS_BYTES;
     auto kern = gemm_bf16_backward_kernel<EPI, CN, CT>;
     static bool attr_done = false;
@@ -1496,29 +1507,30 @@ static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, con
 }
 
 template <int EPI>
-static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, hipStream_t s, bool* done) {
+static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, const GateDlArgs* gate,
+                               hipStream_t s, bool* done) {
     // (the shapes are those of the launches by themselves; shapes with one workgroup per CU and with two do not mix)
     const int cw = tile_choice(GEMM_TN, EPI, w2), cd = dgrad ? tile_choice(GEMM_NT, EPI_STORE, *dgrad) : cw;
     if (cw == 1 || tile_choice(GEMM_TN, EPI, w1) != cw || w2.free_cus > 0) return MOE_OK;
     if (cw == 2) {
         if (cd < 2) return MOE_OK;
-        if (cd == 3) return launch_backward<EPI, CfgT2, CfgS>(dgrad, w2, w1, s, done);
-        return launch_backward<EPI, CfgS, CfgS>(dgrad, w2, w1, s, done);
+        if (cd == 3) return launch_backward<EPI, CfgT2, CfgS>(dgrad, w2, w1, gate, s, done);
+        return launch_backward<EPI, CfgS, CfgS>(dgrad, w2, w1, gate, s, done);
     }
     if (cd == 2) return MOE_OK;
-    if (cd == 1) return launch_backward<EPI, CfgM, Cfg4>(dgrad, w2, w1, s, done);
-    if (cd == 3) return launch_backward<EPI, CfgT, Cfg4>(dgrad, w2, w1, s, done);
-    return launch_backward<EPI, CfgN, Cfg4>(dgrad, w2, w1, s, done);
+    if (cd == 1) return launch_backward<EPI, CfgM, Cfg4>(dgrad, w2, w1, gate, s, done);
+    if (cd == 3) return launch_backward<EPI, CfgT, Cfg4>(dgrad, w2, w1, gate, s, done);
+    return launch_backward<EPI, CfgN, Cfg4>(dgrad, w2, w1, gate, s, done);
 }
 
-moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s,
-                              bool* done) {
+moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi,
+                              const GateDlArgs* gate, hipStream_t s, bool* done) {
     *done = false;
     if (dgrad) MOE_TRY(check_args(GEMM_NT, EPI_STORE, *dgrad));
     MOE_TRY(check_args(GEMM_TN, epi, w2));
     MOE_TRY(check_args(GEMM_TN, epi, w1));
-    return epi == EPI_STORE_F32 ? backward_cfg<EPI_STORE_F32>(dgrad, w2, w1, s, done)
-                                : backward_cfg<EPI_ACCUM_F32>(dgrad, w2, w1, s, done);
+    return epi == EPI_STORE_F32 ? backward_cfg<EPI_STORE_F32>(dgrad, w2, w1, gate, s, done)
+                                : backward_cfg<EPI_ACCUM_F32>(dgrad, w2, w1, gate, s, done);
 }
 
 moe_status gemm_bf16(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a, hipStream_t s) {

@@ -15,6 +15,7 @@
 // The two with N = 512 have 288 tiles for 256 CUs.
 #include "common.h"
 #include "epilogue.h"
+#include "gate_bwd.h"
 
 namespace moe {
 
@@ -192,6 +193,7 @@ __global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_kernel(GemmArgs g) {
 struct F32BackwardArgs {
     GemmArgs d, w[2];
     int tiles_dm, tiles_dn, tiles_wm[2], tiles_wn[2];
+    GateDlArgs gate;                     // in the last blocks (blocks = 0: not there)
 };
 template <int EPI>
 __global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_backward_kernel(F32BackwardArgs a) {
@@ -206,6 +208,10 @@ __global__ __launch_bounds__(F_THREADS, 2) void gemm_f32_backward_kernel(F32Back
     b -= nd;
     const int n2 = a.w[0].E * a.tiles_wm[0] * a.tiles_wn[0], q = b >= n2 ? 1 : 0;
     b -= q * n2;
+    if (q == 1 && b >= a.w[1].E * a.tiles_wm[1] * a.tiles_wn[1]) {
+        gate_dl(a.gate, b - a.w[1].E * a.tiles_wm[1] * a.tiles_wn[1], smem);
+        return;
+    }
     const int tn = a.tiles_wn[q], per = a.tiles_wm[q] * tn, e = b / per, r = b - e * per, tm = r / tn;
     gemm_f32_one<GEMM_TN, EPI>(a.w[q], e, tm, r - tm * tn, smem);
 }
@@ -227,7 +233,9 @@ static moe_status launch_f32(const GemmArgs& a, hipStream_t s) {
     return MOE_OK;
 }
 
-moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi, hipStream_t s) {
+moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi,
+                             const GateDlArgs* gate, hipStream_t s, bool* done) {
+    static_assert(GATE_DL_LDS <= F_NS * 2 * F_TILE && GATE_THREADS == F_THREADS, "a block of the gate in a tile's workgroup");
     F32BackwardArgs b = {};
     b.w[0] = w2;
     b.w[1] = w1;
@@ -239,12 +247,10 @@ moe_status gemm_f32_backward(const GemmArgs* dgrad, const GemmArgs& w2, const Ge
         b.tiles_wn[q] = tiles(b.w[q].N, F_BN);
         blocks += (long long)b.w[q].E * b.tiles_wm[q] * b.tiles_wn[q];
     }
+    if (gate) { b.gate = *gate; blocks += gate->blocks; }
     // (one linear grid: beyond what one launch takes, the three are launched one by one)
-    if (blocks > 0x7fffffff / F_THREADS) {
-        if (dgrad) MOE_TRY(gemm_f32(GEMM_NT, EPI_STORE, *dgrad, s));
-        MOE_TRY(gemm_f32(GEMM_TN, epi, w2, s));
-        return gemm_f32(GEMM_TN, epi, w1, s);
-    }
+    *done = blocks <= 0x7fffffff / F_THREADS;
+    if (!*done) return MOE_OK;
     {
         ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1, dgrad && dgrad->np > 1 ? dgrad->np : 1);
         if (epi == EPI_STORE_F32)

@@ -31,6 +31,7 @@ struct Workspace {
     // routing-class data
     size_t slot_w, dw, dw_part, dL, gate_scratch, slot_scratch, rows;
     size_t bufM, bufH, dw_part_bytes;
+    int parts;                        // row dots of the GeLU-backward GEMM per row
     bool gate_pairs;                  // gate backward may take two partitions in one launch (one stream)
     size_t total, saved, temp, routing;
 };
@@ -83,14 +84,13 @@ static moe_status plan(const moe_config* cfg, const Dims& d, Workspace* w) {
     w->dDI = take(w->bufM * 2);
     w->temp = off - w->saved;
     const size_t r0 = off;
-    int parts = 0;
-    MOE_TRY(moe_dw_parts(cfg, &parts));
+    MOE_TRY(moe_dw_parts(cfg, &w->parts));
     size_t gs = 0, ss = 0;
     MOE_TRY(moe_gate_scratch_bytes(cfg, &gs));
     MOE_TRY(moe_slot_scratch_bytes(cfg, &ss));
     w->slot_w = take((size_t)d.n * d.Rp * sizeof(float));
     w->dw = take((size_t)d.T * d.k * sizeof(float));
-    w->dw_part_bytes = align_up((size_t)d.Rp * parts * sizeof(float));
+    w->dw_part_bytes = align_up((size_t)d.Rp * w->parts * sizeof(float));
     w->dw_part = take(w->dw_part_bytes * 2);
     w->dL = take((size_t)d.T * d.E * sizeof(float));
     // (two partitions at a time: two transposed dL; where their second partial sums go, see gate_sums_space)
@@ -147,18 +147,21 @@ static bool first_backward_dispatch_can_go_early(const Dims& d, const Workspace&
 
 // S'_p of partitions p0 .. p0 + np - 1: gate backward, then rows of dDI back to token order (in whose launch the partial
 // sums of the gate-weight gradient are added up).  part: see gate_bwd_rows.
-static moe_status back_to_tokens(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws, int p0, int np,
-                                 const void* x, const float* logits, const int* topk_idx, const int* slot, const void* Wg,
-                                 bool dw_in_gemm, void* dx, float* dWg, const float* second_part, hipStream_t s0) {
-    int parts = 0;
-    MOE_TRY(moe_dw_parts(cfg, &parts));
+static GateDlArgs gate_dl_of(const Dims& d, const Workspace& w, char* ws, int p0, int np, const float* logits,
+                             const int* topk_idx, const int* slot, bool dw_in_gemm) {
     const int turn = p0 % 2 == 0 ? 1 : -1;           // from p0's buffer of two to the next partition's
+    return gate_dl_args(d, p0, np, logits, topk_idx, slot, dw_in_gemm ? nullptr : (const float*)(ws + w.dw),
+                        dw_in_gemm ? (const float*)(ws + w.dw_part + w.dw_part_bytes * (p0 % 2)) : nullptr,
+                        turn * (long long)(w.dw_part_bytes / sizeof(float)), w.parts, (float*)(ws + w.dL),
+                        ws + w.gate_scratch + gate_dlt_offset(d));
+}
+static moe_status back_to_tokens(const Dims& d, const Workspace& w, char* ws, int np, const GateDlArgs& dl, bool dl_done,
+                                 const void* x, const int* slot, const void* Wg, void* dx, float* dWg,
+                                 const float* second_part, hipStream_t s0) {
+    const int p0 = dl.p0, turn = p0 % 2 == 0 ? 1 : -1;
     float* part = (float*)(ws + w.gate_scratch);
     GateSums sums;
-    MOE_TRY(gate_bwd_rows(d, p0, np, x, logits, topk_idx, slot, dw_in_gemm ? nullptr : (const float*)(ws + w.dw),
-                          dw_in_gemm ? (const float*)(ws + w.dw_part + w.dw_part_bytes * (p0 % 2)) : nullptr,
-                          turn * (long long)(w.dw_part_bytes / sizeof(float)), parts, (float*)(ws + w.dL), dWg, part,
-                          second_part ? second_part - part : 0, ws + w.gate_scratch + gate_dlt_offset(d), s0, &sums));
+    MOE_TRY(gate_bwd_rows(d, np, x, dl, dl_done, dWg, part, second_part ? second_part - part : 0, s0, &sums));
     return dispatch_bwd_rows(d, p0, np, ws + w.dDI + w.bufM * (p0 % 2), turn * (long long)w.bufM, slot,
                              (const float*)(ws + w.dL), Wg, dx, &sums, s0);
 }
@@ -207,7 +210,7 @@ static int backward_unit(const Dims& d, const Workspace& w, int p0) {
 // Two partitions of one group of weight gradients have T_M and dT_M buffers of their own: one launch for both.
 static int backward_batch(const Dims& d, int p0, int np) { return np == 2 && p0 / d.G == (p0 + 1) / d.G && 2 * d.E <= 64 ? 2 : 1; }
 
-// later: the combine is left to backward, whose dispatch of dy reads the same rows (see chain_backward)
+// later: the combine is left to backward (see chain_backward)
 static moe_status chain_forward(const Dims& d, const Workspace& w, char* ws, const void* x, const void* W1, const void* W2,
                                 void* y, const float* topk_w, const int* slot, const int* counts, bool later, hipStream_t s) {
     const int n = d.n;
@@ -269,11 +272,17 @@ static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Wor
         // R': rows of dy to the experts, rows of x again
         const RowMove m[2] = {{dy, dDObuf(p0), ring_step(p0, w.ndDO, w.bufM)}, {x, DIbuf(p0), ring_step(p0, w.nDI, w.bufM)}};
         if (dw_in_gemm) {
-            MOE_TRY(dispatch_rows(d, p0, np, m, redispatch ? 2 : 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
+            MOE_TRY(dispatch_rows(d, p0, np, m, redispatch ? 2 : 1, slot, y ? DObuf(p0) : nullptr, y ? ring_step(p0, w.nDO, w.bufM) : 0,
+                                  nullptr, topk_w, y, s));
         } else {
             MOE_TRY(dispatch_rows(d, p0, np, m, 1, slot, DObuf(p0), ring_step(p0, w.nDO, w.bufM), (float*)(ws + w.dw), topk_w, y, s));
             if (d.fuse) MOE_TRY(dispatch_rows(d, p0, np, m + 1, 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
         }
+        // (two partitions' dL at once need two of its transposed buffers)
+        float* second = np == 2 ? gate_sums_space(d, w, ws, p0 + 1, dw_in_gemm) : nullptr;
+        const int together = second ? 2 : 1;
+        GateDlArgs dl = gate_dl_of(d, w, ws, p0, together, logits, topk_idx, slot, dw_in_gemm);
+        bool dl_done = false;
         for (int p = p0; p < p0 + np; p += batch) {
             // the last partitions' input gradients share the launch of their group's weight gradients
             const int last = p + batch - 1;
@@ -291,13 +300,14 @@ static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Wor
             if (group_ends) {
                 const int g0 = p / G * G;
                 MOE_TRY(ffn_wgrad(d, g0, last - g0 + 1, d.overwrite && g0 == 0, DIbuf(g0), Zbuf(g0), dDObuf(g0), dZbuf(g0),
-                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s, W1, dDIbuf(p), step));
+                                  (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s, W1, dDIbuf(p), step,
+                                  last == p0 + np - 1 && together == np ? &dl : nullptr, &dl_done));
             }
         }
-        float* second = np == 2 ? gate_sums_space(d, w, ws, p0 + 1, dw_in_gemm) : nullptr;
-        const int together = second ? 2 : 1;
-        for (int p = p0; p < p0 + np; p += together)
-            MOE_TRY(back_to_tokens(cfg, d, w, ws, p, together, x, logits, topk_idx, slot, Wg, dw_in_gemm, dx, dWg, second, s));
+        for (int p = p0; p < p0 + np; p += together) {
+            if (p > p0) dl = gate_dl_of(d, w, ws, p, 1, logits, topk_idx, slot, dw_in_gemm);
+            MOE_TRY(back_to_tokens(d, w, ws, together, dl, dl_done, x, slot, Wg, dx, dWg, second, s));
+        }
         p0 += np;
     }
     return MOE_OK;
@@ -460,7 +470,8 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
             // S'_{p-1}: gate backward and rows of dDI back to token order
             const int q = p - 1;
             HIP_TRY(hipStreamWaitEvent(s0, evC[q], 0));
-            MOE_TRY(back_to_tokens(cfg, d, w, ws, q, 1, x, logits, topk_idx, slot, Wg, dw_in_gemm, dx, dWg, nullptr, s0));
+            MOE_TRY(back_to_tokens(d, w, ws, 1, gate_dl_of(d, w, ws, q, 1, logits, topk_idx, slot, dw_in_gemm), false, x, slot, Wg, dx,
+                                   dWg, nullptr, s0));
             HIP_TRY(hipEventRecord(evD[q], s0));
         }
     }
@@ -562,8 +573,9 @@ extern "C" moe_status moe_layer_step(const moe_config* cfg, const void* x, const
         !topk_w || !slot || !counts) return MOE_ERR_NULL;
     MOE_TRY(gate(cfg, d, w, (char*)workspace, x, Wg, gate_bias, y, logits, topk_idx, topk_w, slot, counts, s0));
     if (s0 == s1) {
-        // with every T_DO kept, the combine and the dispatch of dy with its row dots read the same rows: one kernel
-        const bool later = d.reuse == MOE_REUSE_NONE && !d.fcomb;
+        // where every partition has a T_DO buffer, the combine shares a kernel with the dispatch of dy, which takes its row
+        // dots from the same rows or takes their place
+        const bool later = w.nDO == d.n;
         MOE_TRY(chain_forward(d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, later, s0));
         return chain_backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
                               slot, counts, later ? y : nullptr, s0);

@@ -8,6 +8,7 @@
 // (a launch takes 4.6 us of the GPU however little it does): partition buffers then
 // lie a constant number of bytes apart.
 #include "common.h"
+#include "gate_bwd.h"
 
 namespace moe {
 
@@ -80,7 +81,8 @@ struct RowArgs {
 
 // dst[slot[t,j]] = src[t]; optionally on the way dw[t,j] = <src[t], rows[slot[t,j]]> (backward's dispatch of dy where
 // T_DO was kept) and y[t] = sum_j w[t,j] rows[slot[t,j]] (forward's combine, which reads the same rows, in a step that
-// has not run it yet).  One wavefront per token.  KM: choices per token at most.  All reads of a piece of the row - the
+// has not run it yet).  dst may be the very buffer of these rows (dT_DO in T_DO's place): a row belongs to one token's
+// wavefront, which has read a piece of it before it overwrites that piece.  One wavefront per token.  KM: choices per token at most.  All reads of a piece of the row - the
 // token's and its experts' - are in flight before the first is used: 32768 tokens x 2048, two choices, with dw, 62 us a
 // partition of 16384 and 72 with the experts' rows read one after another.
 // (float accumulation, ascending j; a lane's part of a dot in ascending column order)
@@ -90,9 +92,10 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
     const int tl = blockIdx.x * PERM_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (tl >= a.Tp) return;
     const int z = blockIdx.z, which = blockIdx.y, k = a.k, M = a.M;
+    const bool comb = COMB && which == 0;          // (the rows of the other source have nothing to do with T_DO)
     const size_t t = (size_t)(a.p0 + z) * a.Tp + tl;
     constexpr int N = Unit<T>::N;
-    constexpr int UN = DW && KM > 4 ? 1 : DW && KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
+    constexpr int UN = !DW && !COMB ? 4 : KM > 4 ? 1 : KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
     const int U = M / N;
     T* dst = reinterpret_cast<T*>(a.dst[which] + z * a.dst_stride[which]);
     const T* rows = DW || COMB ? reinterpret_cast<const T*>(a.rows + z * a.rows_stride) : nullptr;
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
 #pragma unroll
     for (int j = 0; j < KM; ++j) {
         s[j] = j < k ? a.slot[t * k + j] : -1;
-        ws[j] = COMB && s[j] >= 0 ? a.w[t * k + j] : 0.0f;
+        ws[j] = comb && s[j] >= 0 ? a.w[t * k + j] : 0.0f;
         dot[j] = 0.0f;
     }
     const uint4* in = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.src[which]) + t * M);
@@ -121,7 +124,7 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
                 for (int u = 0; u < UN; ++u) {
                     const int c = c0 + u * 64 + lane;
                     r[j][u] = zero;
-                    if (c < U && s[j] >= 0) r[j][u] = ld_row<true>(row + c);
+                    if (c < U && s[j] >= 0 && (DW || comb)) r[j][u] = ld_row<true>(row + c);
                 }
             }
         }
@@ -154,7 +157,7 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
                     }
                 }
                 if constexpr (COMB) {
-                    if (c < U) st_row<false>(reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * M) + c, Unit<T>::from_float(acc));
+                    if (c < U && comb) st_row<false>(reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * M) + c, Unit<T>::from_float(acc));
                 }
             }
         }
@@ -550,168 +553,11 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(Dispa
 
 // ---- gate backward ------------------------------------------------------------
 //
-// dL[t,e] = p[t,e] * (dp[t,e] - sum_e' dp[t,e'] p[t,e']) with dp nonzero only at the chosen
-// experts (the softmax Jacobian applied to the combine-weight gradients), then
-// dWg += x^T dL.  A workgroup of 256 threads prepares dL for a block of DWG_TOK tokens, four
-// lanes per token.
-constexpr int DWG_TOK = 64;
-constexpr int DWG_EMAX = 64;
-constexpr int DWG_LD = DWG_EMAX + 4;     // floats per row of the block's LDS tile
-
-// Combine-weight gradients of the block's (token, choice) pairs into sdw[ti*k + j]: either given,
-// or the fixed-order sum of the GEMM epilogue's column-block partial sums (four lanes per pair).
-// A thread has at most DWG_TOK*8*4/256 = 8 pairs; their slots are all requested before the first
-// row of partial sums is read.
-__device__ __forceinline__ void gate_block_dw(
-    float* sdw, const int* __restrict__ slot, const float* __restrict__ dw, const float* __restrict__ dw_part,
-    int parts, int t_first, int nt, int k) {
-    constexpr int NI = DWG_TOK * 8 * 4 / PERM_THREADS;
-    const int total = nt * k * 4;
-    const int sub = threadIdx.x & 3;
-    int sl[NI];
-    float given[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int q = threadIdx.x + i * PERM_THREADS;
-        const size_t at = (size_t)t_first * k + (q >> 2);          // pairs of the block are consecutive
-        sl[i] = (q < total && dw_part) ? slot[at] : -1;
-        given[i] = (q < total && !dw_part && sub == 0) ? dw[at] : 0.0f;
-    }
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int q = threadIdx.x + i * PERM_THREADS;
-        if (q >= total) break;                                     // uniform over the four lanes of a pair
-        float v = given[i];
-        if (sl[i] >= 0) {
-            const float* row = dw_part + (size_t)sl[i] * parts;
-            if ((parts & 3) == 0) {
-                // lane `sub` of the pair takes every fourth group of four partial sums, all
-                // requested before the first is added (fixed order: groups ascending, then the lanes)
-                const int ngrp = parts >> 2;
-                for (int g0 = sub; g0 < ngrp; g0 += 32) {
-                    float4 q4[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        q4[u] = (g0 + 4 * u < ngrp) ? *reinterpret_cast<const float4*>(row + 4 * (g0 + 4 * u))
-                                                    : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v += (q4[u].x + q4[u].y) + (q4[u].z + q4[u].w);
-                }
-            } else {
-                const int per = (parts + 3) >> 2;
-                const int c1 = min(parts, (sub + 1) * per);
-                for (int c = sub * per; c < c1; ++c) v += row[c];
-            }
-        }
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 2, 64);
-        if (sub == 0) sdw[q >> 2] = v;
-    }
-}
-
-// The block's logits (nt rows of E floats, contiguous in memory) into the LDS tile; a thread's
-// loads (at most DWG_TOK*DWG_EMAX/256 = 16 floats) are all requested before the first is written.
-__device__ __forceinline__ void gate_block_logits(float (*tile)[DWG_LD], const float* __restrict__ logits,
-                                                  int t_first, int nt, int E) {
-    const float* src = logits + (size_t)t_first * E;
-    if ((E & 3) == 0 && (((size_t)t_first * E) & 3) == 0) {
-        constexpr int NI = DWG_TOK * DWG_EMAX / 4 / PERM_THREADS;
-        const int E4 = E >> 2, total = nt * E4;
-        float4 v[NI];
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int q = threadIdx.x + i * PERM_THREADS;
-            v[i] = q < total ? reinterpret_cast<const float4*>(src)[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-            const int q = threadIdx.x + i * PERM_THREADS;
-            if (q < total) *reinterpret_cast<float4*>(&tile[q / E4][4 * (q % E4)]) = v[i];
-        }
-    } else {
-        for (int q = threadIdx.x; q < nt * E; q += PERM_THREADS) tile[q / E][q % E] = src[q];
-    }
-}
-
-// The experts chosen by the token of this thread (thread / 4 within the block), -1 beyond k or past the
-// last token; requested first so that the read is over by the time gate_block_dl needs it.
-__device__ __forceinline__ void gate_block_ids(int (&ids)[8], const int* __restrict__ topk_idx, int t_first, int nt, int k) {
-    const int ti = threadIdx.x >> 2;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) ids[j] = (ti < nt && j < k) ? topk_idx[(size_t)(t_first + ti) * k + j] : -1;
-}
-
-// dL of the block's tokens, four lanes per token (lane `sub` takes experts sub, sub+4, ...; maxima and
-// sums are folded over the four lanes).  The LDS tile holds the logits on entry and dL on return, with
-// zeros in the rows of missing tokens and in columns E .. E16-1 (E16 = E rounded up to 16).  dL also
-// goes to global memory, and, if dLt is given, as two bfloat16 terms (hi + lo, 16 bits of mantissa)
-// to dLt[(e/16)*32 + e%16][token] and dLt[(e/16)*32 + 16 + e%16][token], rows of tp_pad tokens.
-__device__ __forceinline__ void gate_block_dl(
-    float (*tile)[DWG_LD], const float* sdw, const int (&ids)[8], float* __restrict__ dL,
-    bf16_t* __restrict__ dLt, int tp_pad, int t_first, int tl0, int nt, int E, int k, int renorm) {
-    const int ti = threadIdx.x >> 2, sub = threadIdx.x & 3;
-    const int E16 = (E + 15) & ~15;
-    const bool live = ti < nt;
-    const int t = t_first + ti;
-    float* row = tile[ti];
-    float mx = -INFINITY;
-    if (live)
-        for (int e = sub; e < E; e += 4) mx = fmaxf(mx, row[e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 1, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 2, 64));
-    float g[8], pc[8];                  // gradient and exp(logit - max) of the chosen experts
-    float den = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        g[j] = 0.0f; pc[j] = 0.0f;
-        if (live && j < k) {
-            g[j] = sdw[ti * k + j];
-            pc[j] = expf(row[ids[j]] - mx);
-            den += pc[j];
-        }
-    }
-    if (!renorm) {
-        float sum = 0.0f;
-        if (live)
-            for (int e = sub; e < E; e += 4) sum += expf(row[e] - mx);
-        sum += __shfl_xor(sum, 1, 64);
-        sum += __shfl_xor(sum, 2, 64);
-        den = sum;
-    }
-    // (renormalised weights are a softmax over the chosen logits only: dL_e = w_j (dw_j - sum_j' dw_j' w_j')
-    // for a chosen e, zero otherwise)
-    const float inv = 1.0f / den;
-    float inner = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) inner = fmaf(g[j], pc[j] * inv, inner);
-    for (int e = sub; e < E16; e += 4) {
-        float v = 0.0f;
-        if (live && e < E) {
-            float dp = 0.0f;
-            bool chosen = false;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (ids[j] == e) { dp = g[j]; chosen = true; }
-            if (!renorm) v = expf(row[e] - mx) * inv * (dp - inner);
-            else if (chosen) v = expf(row[e] - mx) * inv * (dp - inner);
-            dL[(size_t)t * E + e] = v;
-        }
-        row[e] = v;
-        if (dLt) {
-            const bf16_t hi = f32_to_bf16(v);
-            const bf16_t lo = f32_to_bf16(v - bf16_to_f32(hi));
-            bf16_t* col = dLt + ((size_t)((e >> 4) * 32 + (e & 15)) * tp_pad + tl0 + ti);
-            col[0] = hi;
-            col[(size_t)16 * tp_pad] = lo;
-        }
-    }
-}
-
 // part[s][d][e] = sum over the tokens of chunk s of x[t,d] * dL[t,e] for float32 storage, on
 // v_mfma_f32_32x32x2_f32 (float operands, float accumulation): the tokens are the reduction dimension, lane l
 // holds column l%32 of x (or expert l%32 of dL) at token l/32 of two, so both operands come straight from memory,
 // 128 bytes of a token row per half-wavefront.  A wavefront owns 32 columns, all experts and a chunk of tokens;
-// sixteen tokens are requested while the sixteen before are multiplied.  Bound by latency at small sizes, by HIP
+// thirty-two tokens (sixteen beyond 32 experts) are requested while as many before are multiplied.  Bound by latency at small sizes, by HIP
 // events with dL and reduction: 256 tokens x 64 columns x 4 experts 16.5 us, 30.6 as float FMAs with eight columns
 // per thread (eight threads of 256 had columns); 1024 x 512 x 8: 25 against 28.
 typedef float gate_f32x16 __attribute__((ext_vector_type(16)));
@@ -721,7 +567,7 @@ __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_f32_kernel(
     long long part_stride, int p0, int t_count, int M, int E, int S, int TC) {
     const int t_begin = (p0 + (int)blockIdx.z) * t_count;
     part += blockIdx.z * part_stride;
-    constexpr int U = 8;                          // matrix instructions of two tokens requested together
+    constexpr int U = EB == 1 ? 16 : 8;           // matrix instructions of two tokens requested together
     const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
     const int ncb = (M + 31) / 32;
     const int w = blockIdx.x * PERM_WAVES + (threadIdx.x >> 6);
@@ -793,26 +639,9 @@ __global__ __launch_bounds__(PERM_THREADS) void gate_dwg_f32_kernel(
         }
 }
 
-// dL of one block of tokens per workgroup, to global memory in float and, for bfloat16 storage, transposed as
-// hi + lo bfloat16 terms (for the matrix-core kernel below).
-__global__ __launch_bounds__(PERM_THREADS) void gate_dl_kernel(
-    const float* __restrict__ logits, const int* __restrict__ topk_idx, const int* __restrict__ slot,
-    const float* __restrict__ dw, const float* __restrict__ dw_part, long long dw_part_stride, int parts,
-    float* __restrict__ dL, bf16_t* __restrict__ dLt, long long dLt_stride, int tp_pad, int p0, int t_count, int E, int k,
-    int renorm) {
-    const int t_begin = (p0 + (int)blockIdx.z) * t_count;
-    if (dw_part) dw_part += blockIdx.z * dw_part_stride;
-    if (dLt) dLt += blockIdx.z * dLt_stride;
-    __shared__ __attribute__((aligned(16))) float sdl[DWG_TOK][DWG_LD];
-    __shared__ float sdw[DWG_TOK * 8];
-    const int tl0 = blockIdx.x * DWG_TOK;
-    const int nt = max(0, min(DWG_TOK, t_count - tl0));
-    int ids[8];
-    gate_block_ids(ids, topk_idx, t_begin + tl0, nt, k);
-    gate_block_logits(sdl, logits, t_begin + tl0, nt, E);
-    gate_block_dw(sdw, slot, dw, dw_part, parts, t_begin + tl0, nt, k);
-    __syncthreads();
-    gate_block_dl(sdl, sdw, ids, dL, dLt, tp_pad, t_begin + tl0, tl0, nt, E, k, renorm);
+__global__ __launch_bounds__(PERM_THREADS) void gate_dl_kernel(GateDlArgs a) {
+    __shared__ __attribute__((aligned(16))) char smem[GATE_DL_LDS];
+    gate_dl(a, blockIdx.x, smem);
 }
 
 // part[s][d][e] = sum over the tokens of chunk s of x[t,d] * dL[t,e] on the matrix cores
@@ -948,7 +777,8 @@ static moe_status launch_dispatch(const RowArgs& a, int sources, int np, hipStre
 }
 template <typename T>
 static moe_status dispatch_t(const RowArgs& a, int sources, int np, hipStream_t s) {
-    if (a.y) return launch_dispatch<T, true, true>(a, sources, np, s);
+    if (a.y && a.dw) return launch_dispatch<T, true, true>(a, sources, np, s);
+    if (a.y) return launch_dispatch<T, false, true>(a, sources, np, s);
     if (a.dw) return launch_dispatch<T, true, false>(a, sources, np, s);
     return launch_dispatch<T, false, false>(a, sources, np, s);
 }
@@ -1070,23 +900,39 @@ size_t gate_dlt_bytes(const Dims& d) {
 }
 size_t gate_dlt_offset(const Dims& d) { return d.dtype == MOE_BF16 ? gate_mfma_plan(d).dlt_off : 0; }
 
-moe_status gate_bwd_rows(const Dims& d, int p0, int np, const void* x, const float* logits, const int* idx, const int* slot,
-                         const float* dw, const float* dw_part, long long dw_part_stride, int parts, float* dL, float* dWg,
-                         float* part, long long part_stride, void* dLt, hipStream_t s, GateSums* sums) {
+GateDlArgs gate_dl_args(const Dims& d, int p0, int np, const float* logits, const int* idx, const int* slot, const float* dw,
+                        const float* dw_part, long long dw_part_stride, int parts, float* dL, void* dLt) {
+    GateDlArgs a = {};
+    a.logits = logits; a.topk_idx = idx; a.slot = slot; a.dw = dw;
+    a.dw_part = dw_part; a.dw_part_stride = dw_part_stride; a.parts = parts;
+    a.dL = dL;
+    if (d.dtype == MOE_BF16) {
+        a.dLt = (bf16_t*)dLt;
+        a.dLt_stride = (long long)(gate_dlt_bytes(d) / sizeof(bf16_t));
+        a.tp_pad = gate_mfma_plan(d).tp_pad;
+    }
+    a.p0 = p0; a.Tp = d.Tp; a.E = d.E; a.k = d.k; a.renorm = d.renorm;
+    a.per_part = (d.Tp + DWG_TOK - 1) / DWG_TOK;
+    a.blocks = a.per_part * np;
+    return a;
+}
+
+moe_status gate_bwd_rows(const Dims& d, int np, const void* x, const GateDlArgs& dl, bool dl_done, float* dWg,
+                         float* part, long long part_stride, hipStream_t s, GateSums* sums) {
+    const int p0 = dl.p0;
     ProfScope ps(PK_GATE_BWD, s, np);
-    const int blocks = (d.Tp + DWG_TOK - 1) / DWG_TOK;
     GateSums t = {};
     t.part = part; t.part_stride = part_stride; t.dWg = dWg;
     t.ME = d.M * d.E; t.np = np; t.store = d.overwrite && p0 == 0;
+    if (!dl_done) {
+        hipLaunchKernelGGL(gate_dl_kernel, dim3(dl.blocks), dim3(PERM_THREADS), 0, s, dl);
+        MOE_CHECK_LAUNCH();
+    }
     if (d.dtype == MOE_BF16) {
         const GateMfmaPlan g = gate_mfma_plan(d);
-        const long long dlt_stride = (long long)(gate_dlt_bytes(d) / sizeof(bf16_t));
-        hipLaunchKernelGGL(gate_dl_kernel, dim3(blocks, 1, np), dim3(PERM_THREADS), 0, s, logits, idx, slot, dw,
-                           dw_part, dw_part_stride, parts, dL, (bf16_t*)dLt, dlt_stride, g.tp_pad, p0, d.Tp, d.E, d.k, d.renorm);
-        MOE_CHECK_LAUNCH();
         const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES, 1, np);
 #define LAUNCH_DWG(EB) hipLaunchKernelGGL((gate_dwg_mfma_kernel<EB, DWG_CPL>), grid, dim3(PERM_THREADS), 0, s, (const bf16_t*)x, \
-                           (const bf16_t*)dLt, dlt_stride, part, part_stride, p0, d.Tp, g.tp_pad, d.M, d.E, g.S, g.TC)
+                           (const bf16_t*)dl.dLt, dl.dLt_stride, part, part_stride, p0, d.Tp, g.tp_pad, d.M, d.E, g.S, g.TC)
         if (g.EB == 1) LAUNCH_DWG(1);
         else if (g.EB == 2) LAUNCH_DWG(2);
         else LAUNCH_DWG(4);
@@ -1094,16 +940,13 @@ moe_status gate_bwd_rows(const Dims& d, int p0, int np, const void* x, const flo
         t.nblk = g.S;
     } else {
         const GateF32Plan g = gate_f32_plan(d);
-        hipLaunchKernelGGL(gate_dl_kernel, dim3(blocks, 1, np), dim3(PERM_THREADS), 0, s, logits, idx, slot, dw, dw_part,
-                           dw_part_stride, parts, dL, (bf16_t*)nullptr, 0ll, 0, p0, d.Tp, d.E, d.k, d.renorm);
-        MOE_CHECK_LAUNCH();
         const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES, 1, np);
         if (d.E <= 32)
-            hipLaunchKernelGGL((gate_dwg_f32_kernel<1>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL, part, part_stride,
-                               p0, d.Tp, d.M, d.E, g.S, g.TC);
+            hipLaunchKernelGGL((gate_dwg_f32_kernel<1>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, (const float*)dl.dL, part,
+                               part_stride, p0, d.Tp, d.M, d.E, g.S, g.TC);
         else
-            hipLaunchKernelGGL((gate_dwg_f32_kernel<2>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, dL, part, part_stride,
-                               p0, d.Tp, d.M, d.E, g.S, g.TC);
+            hipLaunchKernelGGL((gate_dwg_f32_kernel<2>), grid, dim3(PERM_THREADS), 0, s, (const float*)x, (const float*)dl.dL, part,
+                               part_stride, p0, d.Tp, d.M, d.E, g.S, g.TC);
         t.nblk = g.S;
     }
     MOE_CHECK_LAUNCH();
@@ -1167,6 +1010,6 @@ extern "C" moe_status moe_gate_bwd(const moe_config* cfg, int32_t part, const vo
     if (!dw && !dw_part) return MOE_ERR_NULL;
     int parts = 0;
     MOE_TRY(moe_dw_parts(cfg, &parts));
-    return gate_bwd_rows(d, part, 1, x, logits, topk_idx, slot, dw, dw_part, 0, parts, dL, dWg, (float*)scratch, 0,
-                         (char*)scratch + gate_dlt_offset(d), (hipStream_t)stream, nullptr);
+    const GateDlArgs dl = gate_dl_args(d, part, 1, logits, topk_idx, slot, dw, dw_part, 0, parts, dL, (char*)scratch + gate_dlt_offset(d));
+    return gate_bwd_rows(d, 1, x, dl, false, dWg, (float*)scratch, 0, (hipStream_t)stream, nullptr);
 }

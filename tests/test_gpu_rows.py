@@ -94,14 +94,17 @@ def test_dispatch_with_row_dots(dtype, k, M):
         assert bool((err <= prod.abs().sum(2) * M * 2.0 ** -24).all())
 
 
-@pytest.mark.parametrize("T,M,H,E,k,n,dtype", [
-    (120, 72, 136, 5, 3, 5, "bf16"), (96, 520, 264, 9, 8, 1, "bf16"), (90, 264, 136, 3, 1, 3, "f32"), (128, 2056, 72, 4, 2, 2, "bf16"),
+@pytest.mark.parametrize("T,M,H,E,k,n,dtype,mode,fuse", [
+    (120, 72, 136, 5, 3, 5, "bf16", 0, 0), (96, 520, 264, 9, 8, 1, "bf16", 0, 1), (90, 264, 136, 3, 1, 3, "f32", 0, 0),
+    (128, 2056, 72, 4, 2, 2, "bf16", 0, 0), (128, 2056, 72, 4, 2, 2, "bf16", 2, 0), (96, 520, 264, 9, 8, 1, "bf16", 1, 1),
+    (90, 264, 136, 3, 3, 2, "f32", 2, 1), (90, 264, 136, 7, 5, 1, "f32", 1, 0), (120, 72, 136, 5, 3, 5, "bf16", 2, 0),
 ])
-def test_step_equals_its_two_halves(T, M, H, E, k, n, dtype):
-    """In a whole step that keeps T_DO the combine shares backward's dispatch of dy: the same bits as by itself."""
+def test_step_equals_its_two_halves(T, M, H, E, k, n, dtype, mode, fuse):
+    """In a whole step with a T_DO buffer for every partition the combine shares backward's dispatch of dy, which may take
+    the rows' place: the same bits as by itself."""
     from paper_2506_22175_amd import runner, synth
     s = synth.custom_shape(T, M, H, E, k, 0.75, dtype=dtype, x_std=1.0, w_std=0.05, name="halves")
-    st = runner.LayerState(T, M, H, E, k, 0.75, n, dtype, 0, grad_overwrite=1)
+    st = runner.LayerState(T, M, H, E, k, 0.75, n, dtype, mode, grad_overwrite=1, fuse_gather=fuse)
     assert B.moe_layer_streams(st.cfg) == 1
     st.upload(synth.make_inputs(s, seed=5))
     out = []
