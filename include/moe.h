@@ -203,8 +203,10 @@ moe_status moe_dw_parts(const moe_config* cfg, int32_t* parts);
 
 /* Host only.  Rows and columns of the output tiles in which a GEMM of partition `part` is
  * computed when moe_layer_step runs it under cfg (the moe_expert_ffn_* calls: as with
- * wgrad_group = 0 and fuse_combine = 0).  Which shape a launch uses depends on cfg alone;
- * a product's terms are added in the same order in all of them. */
+ * wgrad_group = 0 and fuse_combine = 0).  Which shape a launch uses depends on cfg alone, and
+ * where one launch covers several partitions (the schedule on one stream) on their number: the
+ * answer is for a launch that covers one.  A product's terms are added in the same order in all
+ * shapes. */
 typedef enum { MOE_GEMM_FIRST = 0 /* T_DI W1, GeLU */, MOE_GEMM_SECOND = 1 /* A W2 */,
                MOE_GEMM_RECOMPUTE = 2 /* T_DI W1 again */, MOE_GEMM_DGELU = 3 /* dDO W2^T, GeLU backward */,
                MOE_GEMM_DGRAD = 4 /* dZ W1^T */, MOE_GEMM_DW2 = 5, MOE_GEMM_DW1 = 6 } moe_gemm;

@@ -127,8 +127,10 @@ def test_step_equals_its_two_halves(T, M, H, E, k, n, dtype, mode, fuse):
     (1056, 72, 264, 33, 2, 4, "bf16", 1, dict(wgrad_group=2)),                # one at a time
     (512, 136, 72, 5, 1, 8, "bf16", 2, dict(fuse_gather=1, fuse_combine=1, wgrad_group=4)),
     (512, 136, 72, 5, 1, 8, "f32", 0, dict(fuse_gather=1, fuse_combine=1, wgrad_group=2)),
+    (2048, 512, 1024, 4, 2, 2, "bf16", 0, {}),                                # 128 x 128 instead of one partition's 64 x 128
+    (1600, 1032, 2056, 4, 2, 2, "bf16", 1, {}),
     (600, 72, 1032, 3, 2, 3, "f32", 0, {}),                                   # no room for a second activation buffer
-], ids=["two", "three", "one", "gathered_combined", "gathered_combined_f32", "no_room"])
+], ids=["two", "three", "one", "gathered_combined", "gathered_combined_f32", "other_tiles", "other_tiles_shared", "no_room"])
 def test_gemms_of_several_partitions_in_one_launch(T, M, H, E, k, n, dtype, mode, opts):
     """One stream runs the GEMMs of several partitions at once where their buffers allow it, two streams one by one: the
     same bits."""
@@ -142,14 +144,17 @@ def test_gemms_of_several_partitions_in_one_launch(T, M, H, E, k, n, dtype, mode
         assert np.isfinite(one[name]).all() and np.array_equal(one[name], two[name]), name
 
 
-@pytest.mark.parametrize("T,M,H,E,n", [(404, 136, 1288, 4, 2), (130, 72, 2056, 3, 1)])
-def test_scattered_rows_in_the_smallest_tiles(T, M, H, E, n):
-    """The fused combine from 64 x 64 tiles: what the combine kernel gives up to one rounding, zeros for dropped tokens."""
+@pytest.mark.parametrize("T,M,H,E,n,tile", [
+    (404, 136, 1288, 4, 2, (64, 64)), (130, 72, 2056, 3, 1, (64, 64)), (3000, 1544, 1544, 2, 1, (256, 128)),
+])
+def test_scattered_rows_in_other_tiles(T, M, H, E, n, tile):
+    """The fused combine from 64 x 64 and 256 x 128 tiles: what the combine kernel gives up to one rounding, zeros for
+    dropped tokens."""
     from paper_2506_22175_amd import runner, synth
     s = synth.custom_shape(T, M, H, E, 1, 0.9, dtype="bf16", x_std=1.0, w_std=0.05, zipf_s=1.2, zipf_tau=0.5, name="k1")
     d = synth.make_inputs(s, seed=17)
     cfg = B.make_config(T, M, H, E, 1, 0.9, n, B.MOE_BF16, 0, 1, fuse_combine=1)
-    assert B.moe_gemm_tile(cfg, 0, "second") == (64, 64)
+    assert B.moe_gemm_tile(cfg, 0, "second") == tile
     plain = runner.run_layer_step(s, d, n, 0, grad_overwrite=1)
     fused = runner.run_layer_step(s, d, n, 0, grad_overwrite=1, fuse_combine=1)
     dropped = (fused["slot"] < 0).all(axis=1)
