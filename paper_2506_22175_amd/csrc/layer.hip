@@ -32,7 +32,7 @@ struct Workspace {
     size_t slot_w, dw, dw_part, dL, gate_scratch, slot_scratch, rows;
     size_t bufM, bufH, dw_part_bytes;
     int parts;                        // row dots of the GeLU-backward GEMM per row
-    bool gate_pairs;                  // gate backward may take two partitions in one launch (one stream)
+    size_t gate_second;               // partial sums of a second partition, from gate_scratch
     size_t total, saved, temp, routing;
 };
 
@@ -93,9 +93,9 @@ static moe_status plan(const moe_config* cfg, const Dims& d, Workspace* w) {
     w->dw_part_bytes = align_up((size_t)d.Rp * w->parts * sizeof(float));
     w->dw_part = take(w->dw_part_bytes * 2);
     w->dL = take((size_t)d.T * d.E * sizeof(float));
-    // (two partitions at a time: two transposed dL; where their second partial sums go, see gate_sums_space)
-    w->gate_pairs = d.n > 1 && streams_used(d) == 1;
-    w->gate_scratch = take(gs + (w->gate_pairs ? gate_dlt_bytes(d) : 0));
+    // (two partitions at a time: two transposed dL, one behind the other, then the second's partial sums)
+    w->gate_second = align_up(gs + gate_dlt_bytes(d));
+    w->gate_scratch = take(d.n > 1 ? w->gate_second + gate_part_bytes(d) : gs);
     w->slot_scratch = take(ss);
     w->rows = take((d.fuse || d.fcomb) ? (size_t)d.n * d.Rp * sizeof(int) : 0);
     w->routing = off - r0;
@@ -157,11 +157,10 @@ static GateDlArgs gate_dl_of(const Dims& d, const Workspace& w, char* ws, int p0
 }
 static moe_status back_to_tokens(const Dims& d, const Workspace& w, char* ws, int np, const GateDlArgs& dl, bool dl_done,
                                  const void* x, const int* slot, const void* Wg, void* dx, float* dWg,
-                                 const float* second_part, hipStream_t s0) {
+                                 hipStream_t s0) {
     const int p0 = dl.p0, turn = p0 % 2 == 0 ? 1 : -1;
-    float* part = (float*)(ws + w.gate_scratch);
     GateSums sums;
-    MOE_TRY(gate_bwd_rows(d, np, x, dl, dl_done, dWg, part, second_part ? second_part - part : 0, s0, &sums));
+    MOE_TRY(gate_bwd_rows(d, np, x, dl, dl_done, dWg, (float*)(ws + w.gate_scratch), (long long)(w.gate_second / sizeof(float)), s0, &sums));
     return dispatch_bwd_rows(d, p0, np, ws + w.dDI + w.bufM * (p0 % 2), turn * (long long)w.bufM, slot,
                              (const float*)(ws + w.dL), Wg, dx, &sums, s0);
 }
@@ -241,16 +240,6 @@ static moe_status chain_forward(const Dims& d, const Workspace& w, char* ws, con
     return MOE_OK;
 }
 
-// Where the second of two partitions' partial sums of the gate-weight gradient can go: the first has the scratch buffer;
-// the second the partition's T_DO buffer, which nobody reads after its dispatch of dy (where T_DO is kept), or the row
-// dots of the GeLU-backward GEMM, which gate backward's first kernel has consumed by then.  NULL: too small.
-static float* gate_sums_space(const Dims& d, const Workspace& w, char* ws, int p, bool dw_in_gemm) {
-    const size_t need = gate_part_bytes(d);
-    if (!w.gate_pairs) return nullptr;
-    if (dw_in_gemm) return need <= 2 * w.dw_part_bytes ? (float*)(ws + w.dw_part) : nullptr;
-    return need <= w.bufM ? (float*)(ws + w.DO + w.bufM * (p % w.nDO)) : nullptr;
-}
-
 // y != NULL: forward's combine is still to be done, in the dispatch of dy.
 static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws,
                                  const void* x, const void* dy, const void* Wg, const void* W1, const void* W2,
@@ -278,10 +267,7 @@ static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Wor
             MOE_TRY(dispatch_rows(d, p0, np, m, 1, slot, DObuf(p0), ring_step(p0, w.nDO, w.bufM), (float*)(ws + w.dw), topk_w, y, s));
             if (d.fuse) MOE_TRY(dispatch_rows(d, p0, np, m + 1, 1, slot, nullptr, 0, nullptr, nullptr, nullptr, s));
         }
-        // (two partitions' dL at once need two of its transposed buffers)
-        float* second = np == 2 ? gate_sums_space(d, w, ws, p0 + 1, dw_in_gemm) : nullptr;
-        const int together = second ? 2 : 1;
-        GateDlArgs dl = gate_dl_of(d, w, ws, p0, together, logits, topk_idx, slot, dw_in_gemm);
+        const GateDlArgs dl = gate_dl_of(d, w, ws, p0, np, logits, topk_idx, slot, dw_in_gemm);
         bool dl_done = false;
         for (int p = p0; p < p0 + np; p += batch) {
             // the last partitions' input gradients share the launch of their group's weight gradients
@@ -301,13 +287,10 @@ static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Wor
                 const int g0 = p / G * G;
                 MOE_TRY(ffn_wgrad(d, g0, last - g0 + 1, d.overwrite && g0 == 0, DIbuf(g0), Zbuf(g0), dDObuf(g0), dZbuf(g0),
                                   (long long)(w.bufM / d.es), (long long)(w.bufH / d.es), counts, dW1, dW2, s, W1, dDIbuf(p), step,
-                                  last == p0 + np - 1 && together == np ? &dl : nullptr, &dl_done));
+                                  last == p0 + np - 1 ? &dl : nullptr, &dl_done));
             }
         }
-        for (int p = p0; p < p0 + np; p += together) {
-            if (p > p0) dl = gate_dl_of(d, w, ws, p, 1, logits, topk_idx, slot, dw_in_gemm);
-            MOE_TRY(back_to_tokens(d, w, ws, together, dl, dl_done, x, slot, Wg, dx, dWg, second, s));
-        }
+        MOE_TRY(back_to_tokens(d, w, ws, np, dl, dl_done, x, slot, Wg, dx, dWg, s));
         p0 += np;
     }
     return MOE_OK;
@@ -470,8 +453,7 @@ static moe_status backward(const moe_config* cfg, const Dims& d, const Workspace
             // S'_{p-1}: gate backward and rows of dDI back to token order
             const int q = p - 1;
             HIP_TRY(hipStreamWaitEvent(s0, evC[q], 0));
-            MOE_TRY(back_to_tokens(d, w, ws, 1, gate_dl_of(d, w, ws, q, 1, logits, topk_idx, slot, dw_in_gemm), false, x, slot, Wg, dx,
-                                   dWg, nullptr, s0));
+            MOE_TRY(back_to_tokens(d, w, ws, 1, gate_dl_of(d, w, ws, q, 1, logits, topk_idx, slot, dw_in_gemm), false, x, slot, Wg, dx, dWg, s0));
             HIP_TRY(hipEventRecord(evD[q], s0));
         }
     }
