@@ -1239,13 +1239,14 @@ void gemm_bf16_kernel(GemmArgs g, int tiles_m, int tiles_n) {
 // What follows GeLU-backward - the input gradient dZ W1^T (NT) and the two weight gradients (TN), which do not depend
 // on each other - in one launch, a tile per workgroup: whichever CU is free takes the next one.  Alone, each
 // of the three ends in a round of tiles that leaves most of the chip idle (a launch of 128 or 144 tiles of 256 x 256 all
-// the way through), and a tile's time varies with the rows of its expert.  The tiles with the longest reduction, those
-// of the input gradient, come first.  A workgroup's first operand loads are not covered by another tile's epilogue as in
+// the way through), and a tile's time varies with the rows of its expert.  The tiles that take longest,
+// by the estimate that the tile shapes are chosen with, come first.  A workgroup's first operand loads are not covered by another tile's epilogue as in
 // the persistent launches (2 to 3 us of a tile), so this is for launches of a few rounds.
 struct BackwardArgs {
     GemmArgs d;                          // input gradient; not there if tiles_d == 0
     GemmArgs w[2];                       // weight gradients
     int tiles_dm, tiles_dn, tiles_wm[2], tiles_wn[2];
+    int w_first;                         // the weight gradients' tiles come first
     GateDlArgs gate;                     // in the blocks after the last tile (blocks = 0: not there)
 };
 template <int EPI, typename CN, typename CT>
@@ -1255,27 +1256,38 @@ void gemm_bf16_backward_kernel(BackwardArgs a) {
                   "tiles of one launch share its shape");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63;
-    int b = blockIdx.x;
-    if (a.tiles_dm > 0) {
-        const TileNumbers t = number_tiles<GEMM_NT, EPI_STORE, CN>(a.d, a.tiles_dm, a.tiles_dn, lane);
-        const int n = (t.nblocks + 7) & ~7;                // (a number keeps its place modulo the eight XCDs)
-        if (b < n) {
-            gemm_tiles<GEMM_NT, EPI_STORE, CN, true>(a.d, a.tiles_dm, a.tiles_dn, t, b, 1 << 30);
-            return;
+    auto space = [](const TileNumbers& t) { return (t.nblocks + 7) & ~7; };     // (a number keeps its place modulo the eight XCDs)
+    int b = blockIdx.x, q = 0;                             // q: weight gradient, or 2: input gradient, 3: beyond both
+    TileNumbers t = {};
+    if (a.tiles_dm > 0 && !a.w_first) {
+        t = number_tiles<GEMM_NT, EPI_STORE, CN>(a.d, a.tiles_dm, a.tiles_dn, lane);
+        if (b < space(t)) q = 2;
+        else b -= space(t);
+    }
+    if (q == 0) {
+        t = number_tiles<GEMM_TN, EPI, CT>(a.w[0], a.tiles_wm[0], a.tiles_wn[0], lane);
+        if (b >= space(t)) {
+            b -= space(t);
+            q = 1;
+            t = number_tiles<GEMM_TN, EPI, CT>(a.w[1], a.tiles_wm[1], a.tiles_wn[1], lane);
+            if (b >= space(t)) {
+                b -= space(t);
+                q = 3;
+                if (a.w_first) {
+                    t = number_tiles<GEMM_NT, EPI_STORE, CN>(a.d, a.tiles_dm, a.tiles_dn, lane);
+                    if (b < space(t)) q = 2;
+                    else b -= space(t);
+                }
+            }
         }
-        b -= n;
     }
-    TileNumbers t = number_tiles<GEMM_TN, EPI, CT>(a.w[0], a.tiles_wm[0], a.tiles_wn[0], lane);
-    int q = 0;
-    const int n = (t.nblocks + 7) & ~7;
-    if (b >= n) {
-        b -= n;
-        q = 1;
-        t = number_tiles<GEMM_TN, EPI, CT>(a.w[1], a.tiles_wm[1], a.tiles_wn[1], lane);
+    if (q == 2) {
+        gemm_tiles<GEMM_NT, EPI_STORE, CN, true>(a.d, a.tiles_dm, a.tiles_dn, t, b, 1 << 30);
+        return;
     }
-    if (q == 1 && b >= t.nblocks) {
+    if (q == 3) {
         // the gate's dL, which only needs the row dots of the GeLU-backward GEMM: a launch of its own takes 4 to 6 us
-        if (b - t.nblocks < a.gate.blocks) gate_dl(a.gate, b - t.nblocks, smem);
+        if (b < a.gate.blocks) gate_dl(a.gate, b, smem);
         return;
     }
     gemm_tiles<GEMM_TN, EPI, CT, true>(a.w[q], a.tiles_wm[q], a.tiles_wn[q], t, b, 1 << 30);
@@ -1381,7 +1393,8 @@ static constexpr TileCost TILE_COSTS[5] = {
     {64, 128, 1, {0.44, 0.42, 0.0}, 0.92, {1.5, 2.5, 5.0, 0.0, 0.0}},            // CfgT (not for TN)
     {64, 64, 1, {0.24, 0.0, 0.0}, 0.24, {1.2, 0.0, 0.0, 0.0, 0.0}},              // CfgU (NN stores)
 };
-static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, int cus) {
+// (one: a single tile's, not the launch's)
+static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, int cus, bool one = false) {
     const int which = epi == EPI_GELU ? 1 : epi == EPI_DGELU ? 2 : epi == EPI_STORE_F32 ? 3 : epi == EPI_ACCUM_F32 ? 4 : 0;
     const int E = lay == GEMM_TN ? a.E : launch_experts(a);
     const long long tn = (a.N + c.bn - 1) / c.bn;
@@ -1399,6 +1412,7 @@ static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, 
         share = rest ? (rest + c.bm / 4 - 1) / (c.bm / 4) * 0.25 : 0.25;
     }
     const double tile = kt * c.step[lay] + c.epi[which], launch = 1.7;
+    if (one) return tile;
     if (c.per_cu == 2) {
         const long long n = whole + tail, rounds = n / (2 * cus), rest = n - rounds * 2 * cus;
         return launch + rounds * tile + (rest == 0 ? 0.0 : rest <= cus ? 0.53 * tile : tile);
@@ -1473,9 +1487,10 @@ static moe_status check_args(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a
 constexpr int BACKWARD_ROUNDS = 24;
 
 template <int EPI, typename CN, typename CT>
-static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, const GateDlArgs* gate,
-                                  hipStream_t s, bool* done) {
+static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, bool w_first,
+                                  const GateDlArgs* gate, hipStream_t s, bool* done) {
     BackwardArgs b = {};
+    b.w_first = w_first;
     b.w[0] = w2;
     b.w[1] = w1;
     int blocks = 0;
@@ -1515,15 +1530,17 @@ static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const 
     // (the shapes are those of the launches by themselves; shapes with one workgroup per CU and with two do not mix)
     const int cw = tile_choice(GEMM_TN, EPI, w2), cd = dgrad ? tile_choice(GEMM_NT, EPI_STORE, *dgrad) : cw;
     if (cw == 1 || tile_choice(GEMM_TN, EPI, w1) != cw || w2.free_cus > 0) return MOE_OK;
+    const bool w_first = dgrad && tile_time(TILE_COSTS[cw], GEMM_TN, EPI, w2, persistent_grid(), true) >
+                                      tile_time(TILE_COSTS[cd], GEMM_NT, EPI_STORE, *dgrad, persistent_grid(), true);
     if (cw == 2) {
         if (cd < 2) return MOE_OK;
-        if (cd == 3) return launch_backward<EPI, CfgT2, CfgS>(dgrad, w2, w1, gate, s, done);
-        return launch_backward<EPI, CfgS, CfgS>(dgrad, w2, w1, gate, s, done);
+        if (cd == 3) return launch_backward<EPI, CfgT2, CfgS>(dgrad, w2, w1, w_first, gate, s, done);
+        return launch_backward<EPI, CfgS, CfgS>(dgrad, w2, w1, w_first, gate, s, done);
     }
     if (cd == 2) return MOE_OK;
-    if (cd == 1) return launch_backward<EPI, CfgM, Cfg4>(dgrad, w2, w1, gate, s, done);
-    if (cd == 3) return launch_backward<EPI, CfgT, Cfg4>(dgrad, w2, w1, gate, s, done);
-    return launch_backward<EPI, CfgN, Cfg4>(dgrad, w2, w1, gate, s, done);
+    if (cd == 1) return launch_backward<EPI, CfgM, Cfg4>(dgrad, w2, w1, w_first, gate, s, done);
+    if (cd == 3) return launch_backward<EPI, CfgT, Cfg4>(dgrad, w2, w1, w_first, gate, s, done);
+    return launch_backward<EPI, CfgN, Cfg4>(dgrad, w2, w1, w_first, gate, s, done);
 }
 
 moe_status gemm_bf16_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, GemmEpilogue epi,
