@@ -233,6 +233,7 @@ __device__ __forceinline__ void gate_dwg_reduce(const GateSums& g, int block, fl
         const float* part = g.part + q * g.part_stride;
         float s = 0.0f;
         if (i < g.ME)
+#pragma unroll 4
             for (int b = sl; b < g.nblk; b += 8) s += part[(size_t)b * g.ME + i];
         if (q) __syncthreads();
         red[sl * COLS + col] = s;
@@ -273,8 +274,8 @@ struct DispatchBwdArgs {
 template <int THREADS>
 __device__ __forceinline__ bool dispatch_bwd_sums(const DispatchBwdArgs& a, char* smem) {
     if ((int)blockIdx.y < a.token_rows) return false;
-    if (blockIdx.z == 0)
-        gate_dwg_reduce<THREADS>(a.sums, ((int)blockIdx.y - a.token_rows) * gridDim.x + blockIdx.x, reinterpret_cast<float*>(smem));
+    const int block = (((int)blockIdx.y - a.token_rows) * gridDim.x + blockIdx.x) * gridDim.z + blockIdx.z;
+    gate_dwg_reduce<THREADS>(a.sums, block, reinterpret_cast<float*>(smem));
     return true;
 }
 
@@ -372,8 +373,10 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(Dispat
 // slots of float FMAs.  dL is split into two bfloat16 terms (hi + lo), which keeps 16 bits of
 // its mantissa; Wg is bfloat16 already.  With more than sixteen experts the products are float ones, all of
 // dL's bits and its infinities included: v_mfma_f32_4x4x1_16B_f32, the same blocks with one expert per
-// instruction and the weights widened when they are read (4096 tokens x 768 columns x 64 experts, launches back to
-// back: 16.5 us, 11.5 with the two terms; 16384 x 2048 x 64: 97 and 68).  Up to 64 experts: a slice of the gate
+// instruction and the weights widened when they are read.  There dL comes through LDS, in one request per round, and
+// 128 registers leave room for a second workgroup on the CU (launches back to back: 8192 tokens x 768 columns x 64
+// experts 23 us, 29 with dL in four requests one after the other and 156 registers; 8192 x 768 x 32: 15 and 20;
+// 16384 x 2048 x 64: 82 and 101).  Up to 64 experts: a slice of the gate
 // weights is at most 65 KB, so that two workgroups still fit a CU (the former: 1065 us with the weights read from
 // memory again for every token; 776 columns x 6 experts x 1001 tokens: 22.4 -> 11.0
 // by the number of tokens per group).  The kernel is bound by the latency of its row reads,
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(Dispat
 typedef short bf16x4_hw __attribute__((ext_vector_type(4)));
 typedef float f32x4_hw __attribute__((ext_vector_type(4)));
 template <int EG>                    // expert groups of four: E <= 4*EG
-__global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(DispatchBwdArgs a) {
+__global__ __launch_bounds__(DXB_THREADS, EG > 4 ? 4 : 2) void dispatch_bwd_mfma_kernel(DispatchBwdArgs a) {
     extern __shared__ __attribute__((aligned(16))) char dxm_smem[];
     if (dispatch_bwd_sums<DXB_THREADS>(a, dxm_smem)) return;
     const bf16_t* __restrict__ dDI = reinterpret_cast<const bf16_t*>(a.dDI + blockIdx.z * a.dDI_stride);
@@ -419,28 +422,47 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(Dispa
                 raw[u][jj] = sj >= 0 ? v : make_uint4(0, 0, 0, 0);
             }
     };
-    // gate gradients of this lane's token (tb + lane%4) for the A operand, expert groups g0 .. g0 + GC - 1:
-    // with more than sixteen experts they come in pieces, so that they never hold more than sixteen registers
-    constexpr int GC = EG < 4 ? EG : 4;
     constexpr bool SPLIT = EG <= 4;                // dL as two bfloat16 terms (else float products)
-    auto request_dl = [&](int tb, int g0, float4 (&dl)[GC]) __attribute__((always_inline)) {
+    // gate gradients of this lane's token (tb + lane%4) for the A operand
+    auto request_dl = [&](int tb, float4 (&dl)[SPLIT ? EG : 1]) __attribute__((always_inline)) {
         const int ta = tb + (lane & 3);
 #pragma unroll
-        for (int gi = 0; gi < GC; ++gi) {
-            dl[gi] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int g = 0; g < EG; ++g) {
+            dl[g] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (ta < tl1) {
-                const int e0 = 4 * (g0 + gi);
-                const float* row = dL + (size_t)(t_begin + ta) * E + e0;
+                const float* row = dL + (size_t)(t_begin + ta) * E + 4 * g;
                 if (E == 4 * EG) {
-                    dl[gi] = *reinterpret_cast<const float4*>(row);
+                    dl[g] = *reinterpret_cast<const float4*>(row);
                 } else {
-                    if (e0 + 0 < E) dl[gi].x = row[0];
-                    if (e0 + 1 < E) dl[gi].y = row[1];
-                    if (e0 + 2 < E) dl[gi].z = row[2];
-                    if (e0 + 3 < E) dl[gi].w = row[3];
+                    if (4 * g + 0 < E) dl[g].x = row[0];
+                    if (4 * g + 1 < E) dl[g].y = row[1];
+                    if (4 * g + 2 < E) dl[g].z = row[2];
+                    if (4 * g + 3 < E) dl[g].w = row[3];
                 }
             }
         }
+    };
+    // With more than sixteen experts they would take too many registers, and piece by piece too many round trips to
+    // memory: the four tokens' go through a row each of LDS, which the wavefront has to itself.  They are 4*E
+    // consecutive floats, of which lane l requests l, l + 64, ...
+    constexpr int DLN = EG > 4 ? EG / 4 : 1;
+    constexpr int DLP = 4 * EG + 4;                // floats per row: the four tokens' reads fall into different banks
+    float* dl_rows = reinterpret_cast<float*>(dxm_smem + DXB_CT * (64 * EG + 16)) + tg * 4 * DLP;
+    auto request_dl_rows = [&](int tb, float (&v)[DLN]) __attribute__((always_inline)) {
+        const int n = max(tl1 - tb, 0) * E;        // (fewer than 4*E at the end)
+#pragma unroll
+        for (int i = 0; i < DLN; ++i) {
+            const int q = lane + 64 * i;
+            v[i] = q < min(n, 4 * E) ? dL[(size_t)(t_begin + tb) * E + q] : 0.0f;
+        }
+    };
+    auto put_dl_rows = [&](const float (&v)[DLN]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < DLN; ++i) {
+            const int q = lane + 64 * i, u = q / E;
+            if (u < 4) dl_rows[u * DLP + q - u * E] = v[i];
+        }
+        __builtin_amdgcn_wave_barrier();
     };
     // Gate weights of this workgroup's columns into LDS with coalesced 16-byte reads.  A lane's
     // piece (64*EG bytes: 8 columns x 4*EG experts) is padded by 16 bytes so that the reads of a
@@ -472,55 +494,66 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_mfma_kernel(Dispa
         }
     }
     uint4 raw[4][2];
-    float4 dl[GC];
-    request_dl(tl0, 0, dl);
-    request(tl0, 0, raw);
+    float4 dl[SPLIT ? EG : 1];
+    float dlv[DLN];
+    auto request_all = [&](int tb) __attribute__((always_inline)) {
+        if constexpr (SPLIT) request_dl(tb, dl);
+        else request_dl_rows(tb, dlv);
+        request(tb, 0, raw);
+    };
+    if constexpr (!SPLIT)                          // experts that do not exist: zeros, as in the weights
+        if (lane < 4)
+            for (int e = E; e < 4 * EG; ++e) dl_rows[lane * DLP + e] = 0.0f;
+    request_all(tl0);
     __syncthreads();
     for (int tb = tl0; tb < tl1; tb += 4) {
-        if (tb > tl0) {
-            request_dl(tb, 0, dl);
-            request(tb, 0, raw);
-        }
+        if (tb > tl0) request_all(tb);
         f32x4_hw gate[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) gate[i] = f32x4_hw{0.0f, 0.0f, 0.0f, 0.0f};
         int my_off = ct * PITCH;                   // opaque: the compiler must not keep the weights in registers
         asm volatile("" : "+v"(my_off));
-#pragma unroll 1
-        for (int g0 = 0; g0 < EG; g0 += GC) {
-            float v[GC][4];
-            bf16x4_hw a_hi[GC], a_lo[GC];
+        auto weights = [&](int g, bf16x4_hw (&w)[8]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int gi = 0; gi < GC; ++gi) {
-                v[gi][0] = dl[gi].x; v[gi][1] = dl[gi].y; v[gi][2] = dl[gi].z; v[gi][3] = dl[gi].w;
+            for (int i = 0; i < 8; ++i) w[i] = *reinterpret_cast<const bf16x4_hw*>(dxm_smem + my_off + (i * EG + g) * 8);
+        };
+        if constexpr (SPLIT) {
+            bf16x4_hw hi[EG], lo[EG];
+#pragma unroll
+            for (int g = 0; g < EG; ++g) {
+                const float v[4] = {dl[g].x, dl[g].y, dl[g].z, dl[g].w};
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const bf16_t h = f32_to_bf16(v[gi][r]);
-                    a_hi[gi][r] = (short)h;
-                    a_lo[gi][r] = (short)f32_to_bf16(v[gi][r] - bf16_to_f32(h));
+                    const bf16_t h = f32_to_bf16(v[r]);
+                    hi[g][r] = (short)h;
+                    lo[g][r] = (short)f32_to_bf16(v[r] - bf16_to_f32(h));
                 }
             }
-            if (g0 + GC < EG) request_dl(tb, g0 + GC, dl);     // on its way while this piece is multiplied
 #pragma unroll
-            for (int gi = 0; gi < GC; ++gi) {
+            for (int g = 0; g < EG; ++g) {
                 bf16x4_hw w[8];
+                weights(g, w);
 #pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    w[i] = *reinterpret_cast<const bf16x4_hw*>(dxm_smem + my_off + (i * EG + g0 + gi) * 8);
-                if constexpr (SPLIT) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_hi[gi], w[i], gate[i], 0, 0, 0);
-                        gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a_lo[gi], w[i], gate[i], 0, 0, 0);
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-#pragma unroll
-                        for (int i = 0; i < 8; ++i)
-                            gate[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(v[gi][r], bf16_to_f32((bf16_t)w[i][r]), gate[i], 0, 0, 0);
+                for (int i = 0; i < 8; ++i) {
+                    gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(hi[g], w[i], gate[i], 0, 0, 0);
+                    gate[i] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(lo[g], w[i], gate[i], 0, 0, 0);
                 }
             }
+        } else {
+            put_dl_rows(dlv);
+#pragma unroll 2
+            for (int g = 0; g < EG; ++g) {
+                const float4 d4 = *reinterpret_cast<const float4*>(dl_rows + (lane & 3) * DLP + 4 * g);
+                const float v[4] = {d4.x, d4.y, d4.z, d4.w};
+                bf16x4_hw w[8];
+                weights(g, w);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        gate[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(v[r], bf16_to_f32((bf16_t)w[i][r]), gate[i], 0, 0, 0);
+            }
+            __builtin_amdgcn_wave_barrier();
         }
         float acc[4][8];
 #pragma unroll
@@ -832,7 +865,7 @@ moe_status dispatch_bwd_rows(const Dims& d, int p0, int np, const void* dDI, lon
     if (sums) {
         a.sums = *sums;
         const int blocks = (sums->ME + DXB_THREADS / 8 - 1) / (DXB_THREADS / 8);
-        sum_rows = (blocks + slices - 1) / slices;
+        sum_rows = (blocks + slices * np - 1) / (slices * np);
     }
     const dim3 grid(slices, a.token_rows + sum_rows, np);
     ProfScope ps(PK_DISPATCH_BWD, s, np);
@@ -849,8 +882,8 @@ moe_status dispatch_bwd_rows(const Dims& d, int p0, int np, const void* dDI, lon
     else if (d.E <= 4) LAUNCH_DXB((dispatch_bwd_mfma_kernel<1>), DXB_CT * (64 * 1 + 16));
     else if (d.E <= 8) LAUNCH_DXB((dispatch_bwd_mfma_kernel<2>), DXB_CT * (64 * 2 + 16));
     else if (d.E <= 16) LAUNCH_DXB((dispatch_bwd_mfma_kernel<4>), DXB_CT * (64 * 4 + 16));
-    else if (d.E <= 32) LAUNCH_DXB((dispatch_bwd_mfma_kernel<8>), DXB_CT * (64 * 8 + 16));
-    else LAUNCH_DXB((dispatch_bwd_mfma_kernel<16>), DXB_CT * (64 * 16 + 16));
+    else if (d.E <= 32) LAUNCH_DXB((dispatch_bwd_mfma_kernel<8>), DXB_CT * (64 * 8 + 16) + DXB_TG * 64 * (8 + 1));
+    else LAUNCH_DXB((dispatch_bwd_mfma_kernel<16>), DXB_CT * (64 * 16 + 16) + DXB_TG * 64 * (16 + 1));
 #undef LAUNCH_DXB
     count_launch(LC_PERMUTE, np);
     MOE_CHECK_LAUNCH();
