@@ -82,9 +82,10 @@ struct RowArgs {
 // dst[slot[t,j]] = src[t]; optionally on the way dw[t,j] = <src[t], rows[slot[t,j]]> (backward's dispatch of dy where
 // T_DO was kept) and y[t] = sum_j w[t,j] rows[slot[t,j]] (forward's combine, which reads the same rows, in a step that
 // has not run it yet).  dst may be the very buffer of these rows (dT_DO in T_DO's place): a row belongs to one token's
-// wavefront, which has read a piece of it before it overwrites that piece.  One wavefront per token.  KM: choices per token at most.  All reads of a piece of the row - the
-// token's and its experts' - are in flight before the first is used: 32768 tokens x 2048, two choices, with dw, 62 us a
-// partition of 16384 and 72 with the experts' rows read one after another.
+// wavefront, which has read a piece of it before it overwrites that piece.  One wavefront per token.  KM: choices per
+// token at most.  All reads of a piece of the row - the token's and its experts' - are in flight before the first is
+// used: 32768 tokens x 2048, two choices, with dw, 52 us a partition of 16384 under rocprofv3, 67 to 72 with the
+// experts' rows read one after another (39 us is the time of a copy of as many bytes).
 // (float accumulation, ascending j; a lane's part of a dot in ascending column order)
 template <typename T, int KM, bool DW, bool COMB>
 __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
