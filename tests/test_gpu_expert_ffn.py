@@ -125,6 +125,14 @@ def test_last_gradients_in_one_launch(M, H, E, Cp, dgrad, dw, recompute, overwri
     _run("bf16", M, H, counts, Cp, 17, recompute, overwrite, tiles=dict(dgrad=dgrad, dW2=dw, dW1=dw))
 
 
+# more rows than the hidden dimension: the weight gradients' tiles come first in that launch
+@pytest.mark.parametrize("recompute,overwrite", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("M,H,counts,Cp", [(24, 40, (300, 0, 257, 64, 1), 300), (136, 72, (700, 65, 0), 700)], ids=["thin", "wide"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_last_gradients_with_more_rows_than_columns(dtype, M, H, counts, Cp, recompute, overwrite):
+    _run(dtype, M, H, counts, Cp, 23, recompute, overwrite)
+
+
 # 64 x 64 tiles of the second layer: few rows against a long reduction that ends inside a step, columns inside a tile
 @pytest.mark.parametrize("M,H,counts,Cp", [
     (296, 1592, (1, 0, 18, 17, 64, 65, 33, 128), 128), (8, 1024, (1, 3), 3), (72, 4104, (129,), 129), (136, 1288, (64, 63, 31, 32), 64),

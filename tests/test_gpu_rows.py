@@ -129,8 +129,10 @@ def test_step_equals_its_two_halves(T, M, H, E, k, n, dtype, mode, fuse):
     (512, 136, 72, 5, 1, 8, "f32", 0, dict(fuse_gather=1, fuse_combine=1, wgrad_group=2)),
     (2048, 512, 1024, 4, 2, 2, "bf16", 0, {}),                                # 128 x 128 instead of one partition's 64 x 128
     (1600, 1032, 2056, 4, 2, 2, "bf16", 1, {}),
+    (4096, 24, 40, 3, 2, 2, "bf16", 2, {}),                                   # the weight gradients' tiles before the input gradient's
+    (4096, 24, 40, 3, 2, 2, "f32", 1, {}),
     (600, 72, 1032, 3, 2, 3, "f32", 0, {}),                                   # no room for a second activation buffer
-], ids=["two", "three", "one", "gathered_combined", "gathered_combined_f32", "other_tiles", "other_tiles_shared", "no_room"])
+], ids=["two", "three", "one", "gathered_combined", "gathered_combined_f32", "other_tiles", "other_tiles_shared", "long_rows", "long_rows_f32", "no_room"])
 def test_gemms_of_several_partitions_in_one_launch(T, M, H, E, k, n, dtype, mode, opts):
     """One stream runs the GEMMs of several partitions at once where their buffers allow it, two streams one by one: the
     same bits."""
