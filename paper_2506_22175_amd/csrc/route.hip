@@ -465,11 +465,21 @@ __global__ __launch_bounds__(ROUTE_THREADS, sizeof(T) == 4 && TB == 4 ? 2 : 4) v
     }
 #pragma unroll
     for (int off = 1; off < 8; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    if (!renorm) {
+        // Expert by expert in ascending order, as softmax_topk adds them, so that a weight's bits do not depend on the kernel:
+        // in step s lane `sub` = s continues from what lane s - 1 had in the step before (what the other lanes have is not used).
+        float q[EPL];
 #pragma unroll
-    for (int i = 0; i < EPL; ++i)
-        if (sub * EPL + i < E) sum += expf(v[i] - mx);
+        for (int i = 0; i < EPL; ++i) q[i] = expf(v[i] - mx);
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) sum += __shfl_xor(sum, off, 64);
+        for (int s = 0; s < 8; ++s) {
+            if (s > 0) sum = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sum), 0x111 /* row_shr:1 */, 0xf, 0xf, false));
+#pragma unroll
+            for (int i = 0; i < EPL; ++i)
+                if (sub * EPL + i < E) sum += q[i];
+        }
+        sum = __shfl(sum, lane | 7, 64);
+    }
     // the k largest logits in descending order, ties to the lower index, NaN as -inf
     int best_e[8];
     float raw[8];

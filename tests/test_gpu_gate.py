@@ -50,3 +50,32 @@ def test_gate(T, M, E, k, dtype, renorm):
         assert fine.any()
         # expf within 2 units, logit - max rounded once (half a unit of a difference of up to 60), a sum of 64, a quotient
         assert np.abs(tw.cpu().numpy() / w - 1.0)[fine].max() <= 2.0 ** -23 * (60 + 64 + 6)
+
+
+@pytest.mark.parametrize("T,E,k,dtype", [
+    (300, 17, 2, "bf16"), (300, 32, 8, "f32"), (5000, 24, 1, "bf16"), (300, 33, 3, "f32"), (300, 64, 2, "bf16"), (3000, 64, 8, "f32"),
+])
+@pytest.mark.parametrize("odd", [None, float("inf"), float("nan")], ids=["finite", "infinite", "nan"])
+def test_weights_are_the_same_bits_for_few_and_for_many_experts(T, E, k, dtype, odd):
+    """Sixteen experts by themselves, where one lane adds up a token's exponentials in ascending order, and the same sixteen
+    in the same order among experts whose logits are -infinity: those add zeros to the sum, so the weights are the same
+    bits, for infinite and NaN logits too."""
+    few, M = 16, 72
+    dt, mt = (torch.bfloat16, B.MOE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_F32)
+    g = torch.Generator().manual_seed(T + E)
+    x, Wg = torch.randn((T, M), generator=g).to(dt).to(D), (torch.randn((M, few), generator=g) * 0.2).to(dt)
+    if odd is not None:
+        Wg[3, 5] = odd
+    place = torch.sort(torch.randperm(E, generator=g)[:few])[0]
+    many, bias = torch.zeros((M, E), dtype=dt), torch.full((E,), -float("inf"))
+    many[:, place], bias[place] = Wg, torch.randn((few,), generator=g)
+    got = []
+    for n, W, b in ((few, Wg, bias[place]), (E, many, bias)):
+        cfg = B.make_config(T, M, 8, n, k, 1.0, 1, mt, 0)
+        lo, ti, tw = torch.empty((T, n), device=D), torch.empty((T, k), dtype=torch.int32, device=D), torch.empty((T, k), device=D)
+        B.moe_route(cfg, x, W.contiguous().to(D), b.contiguous().to(D), lo, ti, tw)
+        got.append((lo.cpu(), ti.cpu().long(), tw.cpu()))
+    (lo, ti, tw), (lo_many, ti_many, tw_many) = got
+    assert np.array_equal(lo.numpy(), lo_many[:, place].numpy(), equal_nan=True)
+    assert torch.equal(place[ti], ti_many)
+    assert np.array_equal(tw.numpy(), tw_many.numpy(), equal_nan=True)
