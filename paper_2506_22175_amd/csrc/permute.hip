@@ -967,9 +967,14 @@ moe_status gate_bwd_rows(const Dims& d, int np, const void* x, const GateDlArgs&
         const dim3 grid((g.ncb * g.S + PERM_WAVES - 1) / PERM_WAVES, 1, np);
 #define LAUNCH_DWG(EB) hipLaunchKernelGGL((gate_dwg_mfma_kernel<EB, DWG_CPL>), grid, dim3(PERM_THREADS), 0, s, (const bf16_t*)x, \
                            (const bf16_t*)dl.dLt, dl.dLt_stride, part, part_stride, p0, d.Tp, g.tp_pad, d.M, d.E, g.S, g.TC)
-        if (g.EB == 1) LAUNCH_DWG(1);
-        else if (g.EB == 2) LAUNCH_DWG(2);
-        else LAUNCH_DWG(4);
+        // (a kernel for every number of blocks: it reads all of its own of dL^T, which the plan has room for exactly so many of)
+        switch (g.EB) {
+            case 1: LAUNCH_DWG(1); break;
+            case 2: LAUNCH_DWG(2); break;
+            case 3: LAUNCH_DWG(3); break;
+            case 4: LAUNCH_DWG(4); break;
+            default: return MOE_ERR_UNSUPPORTED;
+        }
 #undef LAUNCH_DWG
         t.nblk = g.S;
     } else {

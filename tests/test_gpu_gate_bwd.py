@@ -1,16 +1,16 @@
-"""Gate backward alone (moe_gate_bwd, float32) at the edges of its token blocks, column blocks and expert blocks."""
+"""Gate backward alone (moe_gate_bwd) at the edges of its token blocks, column blocks and expert blocks."""
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
 
-def _run(T, M, E, k, seed, x_change=None):
+def _run(T, M, E, k, seed, x_change=None, dtype=torch.float32):
     """dL and dWg of one partition, the same in float64, and the magnitudes that their roundings follow."""
     from paper_2506_22175_amd import binding as B
-    cfg = B.make_config(T, M, 64, E, k, 1.0, 1, B.MOE_F32, grad_overwrite=1)
+    cfg = B.make_config(T, M, 64, E, k, 1.0, 1, B.MOE_F32 if dtype == torch.float32 else B.MOE_BF16, grad_overwrite=1)
     g = torch.Generator().manual_seed(seed)
-    x = torch.randn((T, M), generator=g)
+    x = torch.randn((T, M), generator=g).to(dtype)
     if x_change:
         x_change(x)
     logits, dw = torch.randn((T, E), generator=g), torch.randn((T, k), generator=g)
@@ -42,6 +42,18 @@ def test_gate_backward_matches_float64(T, M, E, k):
     assert bool(((dL - ref).abs() <= mag * (E + 16) * 2.0 ** -24).all())
     # and T products of them, added in any order
     bound = x.abs().t() @ mag * (E + 16 + T) * 2.0 ** -24
+    assert bool(((dWg - x.t() @ ref).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("T,M,E,k", [
+    (1, 8, 16, 1), (64, 72, 17, 2), (65, 64, 32, 3), (129, 136, 33, 2), (200, 72, 40, 4), (1000, 264, 48, 8), (65, 72, 49, 2), (130, 72, 64, 8),
+])
+def test_bfloat16_gate_backward_matches_float64(T, M, E, k):
+    """One expert into each further block of sixteen, and whole blocks."""
+    x, dL, dWg, ref, mag = _run(T, M, E, k, T + E, dtype=torch.bfloat16)
+    assert bool(((dL - ref).abs() <= mag * (E + 16) * 2.0 ** -24).all())
+    # as above, with dL as two bfloat16 numbers, the second of which rounds what the first leaves to 2^-9 * 2^-9 of dL
+    bound = x.abs().t() @ (mag * (E + 16 + T) * 2.0 ** -24 + dL.abs() * 2.0 ** -17)
     assert bool(((dWg - x.t() @ ref).abs() <= bound).all())
 
 

@@ -32,3 +32,15 @@ def test_buffer_accesses_have_no_scalar_offset():
                 assert args[soffset] == "0", (f, args)
                 seen += 1
     assert seen >= 15
+
+
+def test_gate_weight_gradient_reads_the_expert_blocks_that_its_plan_has_room_for():
+    """The plan sizes dL^T for EB blocks of sixteen experts and the kernel reads all blocks of its template argument, also
+    those whose results it does not store: for each of the 64 numbers of experts the two have to be the same."""
+    text = re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, "permute.hip")).read())
+    assert re.search(r"g\.EB = \(d\.E \+ 15\) / 16;", text) and "g.EB * 32 * g.tp_pad" in text
+    launched = {int(blocks): int(kernel) for blocks, kernel in
+                re.findall(r"(?:g\.EB == |case )(\d+)(?:\)|:) LAUNCH_DWG\((\d+)\);", text)}
+    for E in range(1, 65):
+        blocks = (E + 15) // 16
+        assert launched.get(blocks) == blocks, E
