@@ -324,8 +324,11 @@ moe_status moe_launch_counts(int64_t out[3], int32_t reset);
  * stream each kernel is launched on.  moe_profile_enable(1) clears earlier
  * records and starts recording; moe_profile_enable(0) stops.  moe_profile_read
  * waits for the recorded events and returns, per kernel kind, the number of
- * launches and the summed duration in milliseconds (of one launch for several
- * GEMMs, which are of the same size: one each, and equal shares).  Kinds: 0 first FFN GEMM
+ * launches and the summed duration in milliseconds.  Of one launch for several GEMMs or
+ * permutations each counts as one, and the duration is shared out by their work at even loads
+ * (GEMMs: operations, so that a weight gradient of a group of partitions has as many shares as
+ * partitions); what runs beside them for another kind is in their time: the gate's dL beside the last
+ * GEMMs, the last sums of the gate-weight gradient beside a dispatch backward.  Kinds: 0 first FFN GEMM
  * (GeLU epilogue), 1 second FFN GEMM and recomputation, 2 GEMM with the
  * GeLU-backward epilogue, 3 input-gradient GEMM, 4 weight-gradient GEMMs,
  * 5 dispatch, 6 combine, 7 dispatch backward, 8 gate, 9 slot assignment,

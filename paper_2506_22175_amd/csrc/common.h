@@ -157,8 +157,8 @@ enum ProfKind {
 };
 struct ProfScope {
     int idx; hipStream_t s;
-    // one launch may do the work of several: `units` of `kind`, and `also_units` of `also`
-    ProfScope(int kind, hipStream_t stream, int units = 1, int also = -1, int also_units = 1);
+    // one launch may do the work of several: `units` of `kind`, each `unit_work` times the work of one of `also_units` of `also`
+    ProfScope(int kind, hipStream_t stream, int units = 1, int also = -1, int also_units = 1, double unit_work = 1.0);
     ~ProfScope();
 };
 

@@ -55,7 +55,7 @@ static std::atomic<long long> g_launches[3];
 void count_launch(LaunchClass c, int n) { g_launches[c].fetch_add(n, std::memory_order_relaxed); }
 
 // ---- optional kernel timing ---------------------------------------------------------
-struct ProfRec { int kind, units, also, also_units; hipEvent_t a, b; };
+struct ProfRec { int kind, units, also, also_units; double unit_work; hipEvent_t a, b; };
 static bool g_prof_on = false;
 static std::vector<ProfRec> g_prof_recs;      // records of the current session
 static std::vector<hipEvent_t> g_prof_pool;   // timing events, reused across sessions
@@ -72,13 +72,14 @@ static bool prof_event(hipEvent_t* e) {
     return true;
 }
 
-ProfScope::ProfScope(int kind, hipStream_t stream, int units, int also, int also_units) : idx(-1), s(stream) {
+ProfScope::ProfScope(int kind, hipStream_t stream, int units, int also, int also_units, double unit_work) : idx(-1), s(stream) {
     if (!g_prof_on || g_prof_recs.size() >= PROF_MAX_RECS) return;
     ProfRec r;
     r.kind = kind;
     r.units = units;
     r.also = also;
     r.also_units = also >= 0 ? also_units : 0;
+    r.unit_work = unit_work;
     if (!prof_event(&r.a) || !prof_event(&r.b)) return;
     if (hipEventRecord(r.a, s) != hipSuccess) return;
     idx = (int)g_prof_recs.size();
@@ -104,13 +105,13 @@ extern "C" moe_status moe_profile_read(int32_t kinds, int64_t* launches, double*
         HIP_TRY(hipEventSynchronize(r.b));
         float ms = 0.0f;
         HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
-        // (the GEMMs of one launch are of the same number of operations, its permutations about of the same bytes)
-        const int all = r.units + r.also_units;
+        // (by operations for GEMMs; the permutations of a launch move about the same number of bytes each)
+        const double all = r.units * r.unit_work + r.also_units;
         launches[r.kind] += r.units;
-        total_ms[r.kind] += ms * r.units / all;
+        total_ms[r.kind] += ms * (r.units * r.unit_work / all);
         if (r.also >= 0 && r.also < kinds) {
             launches[r.also] += r.also_units;
-            total_ms[r.also] += ms * r.also_units / all;
+            total_ms[r.also] += ms * (r.also_units / all);
         }
     }
     return MOE_OK;

@@ -1516,7 +1516,9 @@ static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, con
         attr_done = true;
     }
     {
-        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1, dgrad && dgrad->np > 1 ? dgrad->np : 1);
+        // (a weight gradient reduces the rows of all partitions of its group, an input gradient has those of one)
+        ProfScope ps(PK_GEMM_WGRAD, s, 2, dgrad ? PK_GEMM_DGRAD : -1, dgrad && dgrad->np > 1 ? dgrad->np : 1,
+                     w2.k_segs > 1 ? w2.k_segs : 1);
         hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, s, b);
     }
     count_launch(LC_GEMM, 2 + (!dgrad ? 0 : dgrad->np > 1 ? dgrad->np : 1));

@@ -797,6 +797,26 @@ def test_kernel_timing_hooks_see_every_gemm(runner):
     assert all(ms > 0 for cnt, ms in prof.values() if cnt)
 
 
+@pytest.mark.parametrize("dtype,group", [("bf16", 1), ("bf16", 2), ("f32", 1)])
+def test_kernel_timing_shares_a_joint_launch_by_the_work(runner, dtype, group):
+    """One launch for backward's last GEMMs: its two weight gradients over `group` partitions are 2 * group times as many
+    operations as one partition's input gradient, of which there are `group`."""
+    from paper_2506_22175_amd import binding as B
+    s = synth.custom_shape(1024, 256, 512, 4, 2, 1.0, dtype=dtype)
+    st = runner.LayerState(s.T, s.M, s.H, s.E, s.k, s.capacity_factor, group, s.dtype, 0, wgrad_group=group)
+    assert B.moe_layer_streams(st.cfg) == 1
+    st.upload(synth.make_inputs(s, seed=0))
+    st.zero_grads()
+    st.step()
+    B.moe_profile_enable(True)
+    st.step()
+    torch.cuda.synchronize()
+    B.moe_profile_enable(False)
+    prof = B.moe_profile_read()
+    assert prof["gemm_wgrad"][0] == 2 and prof["gemm_dgrad"][0] == group       # all in the one launch
+    assert prof["gemm_wgrad"][1] == pytest.approx(2 * prof["gemm_dgrad"][1], rel=1e-5)
+
+
 @pytest.mark.parametrize("free_cus", [0, 8], ids=["one_stream", "two_streams"])
 def test_graph_replay_equals_eager_every_time(runner, free_cus):
     """A captured step replayed several times, with eager steps and synchronisations
