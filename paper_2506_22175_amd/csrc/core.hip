@@ -101,15 +101,18 @@ extern "C" moe_status moe_profile_read(int32_t kinds, int64_t* launches, double*
     if (!launches || !total_ms) return MOE_ERR_NULL;
     for (int i = 0; i < kinds; ++i) { launches[i] = 0; total_ms[i] = 0.0; }
     for (const moe::ProfRec& r : moe::g_prof_recs) {
-        if (r.kind >= kinds) continue;
+        const bool own = r.kind < kinds, also = r.also >= 0 && r.also < kinds;
+        if (!own && !also) continue;
         HIP_TRY(hipEventSynchronize(r.b));
         float ms = 0.0f;
         HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
         // (by operations for GEMMs; the permutations of a launch move about the same number of bytes each)
         const double all = r.units * r.unit_work + r.also_units;
-        launches[r.kind] += r.units;
-        total_ms[r.kind] += ms * (r.units * r.unit_work / all);
-        if (r.also >= 0 && r.also < kinds) {
+        if (own) {
+            launches[r.kind] += r.units;
+            total_ms[r.kind] += ms * (r.units * r.unit_work / all);
+        }
+        if (also) {
             launches[r.also] += r.also_units;
             total_ms[r.also] += ms * (r.also_units / all);
         }

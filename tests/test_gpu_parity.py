@@ -800,7 +800,8 @@ def test_kernel_timing_hooks_see_every_gemm(runner):
 @pytest.mark.parametrize("dtype,group", [("bf16", 1), ("bf16", 2), ("f32", 1)])
 def test_kernel_timing_shares_a_joint_launch_by_the_work(runner, dtype, group):
     """One launch for backward's last GEMMs: its two weight gradients over `group` partitions are 2 * group times as many
-    operations as one partition's input gradient, of which there are `group`."""
+    operations as one partition's input gradient, of which there are `group`.  Reading fewer kinds loses nothing of those that are read."""
+    import ctypes
     from paper_2506_22175_amd import binding as B
     s = synth.custom_shape(1024, 256, 512, 4, 2, 1.0, dtype=dtype)
     st = runner.LayerState(s.T, s.M, s.H, s.E, s.k, s.capacity_factor, group, s.dtype, 0, wgrad_group=group)
@@ -815,6 +816,9 @@ def test_kernel_timing_shares_a_joint_launch_by_the_work(runner, dtype, group):
     prof = B.moe_profile_read()
     assert prof["gemm_wgrad"][0] == 2 and prof["gemm_dgrad"][0] == group       # all in the one launch
     assert prof["gemm_wgrad"][1] == pytest.approx(2 * prof["gemm_dgrad"][1], rel=1e-5)
+    few, ms = (ctypes.c_int64 * 4)(), (ctypes.c_double * 4)()
+    assert B.lib().moe_profile_read(ctypes.c_int32(4), few, ms) == 0
+    assert few[3] == group and ms[3] == pytest.approx(prof["gemm_dgrad"][1], rel=1e-6)
 
 
 @pytest.mark.parametrize("free_cus", [0, 8], ids=["one_stream", "two_streams"])
