@@ -10,6 +10,7 @@
 // multiply-add each, starting from +0; the 64 lane sums are folded pairwise
 // with offsets 32, 16, 8, 4, 2, 1; the bias is added last.
 #include "common.h"
+#include <climits>
 
 namespace moe {
 
@@ -106,8 +107,9 @@ template <> struct RowLoad<float> {
     }
 };
 
-// tokens whose logits a wavefront keeps in LDS before it ranks them (1 KB of LDS per padded expert for the workgroup)
-constexpr int ROUTE_HELD = 32;
+// tokens whose logits a wavefront keeps in LDS before it ranks them (1 KB of LDS per padded expert
+// for the workgroup; with 64 experts half as many, so that 512 gate-weight rows still fit beside them)
+template <int EP> struct RouteHeld { static constexpr int N = EP >= 64 ? 16 : 32; };
 
 // Where the gate weights of element i (of a lane's eight), experts 4*e4 .. 4*e4 + 3 and lane l lie in LDS, in 16-byte
 // pieces from the span's first: a wavefront reads one (i, e4) at a time, any rotation of its 64 pieces without a
@@ -119,11 +121,11 @@ __device__ __forceinline__ int weight_piece(int i, int e4, int l) {
     return (i * E4 + e4) * 64 + (ROT ? (l + i * 8 + (e4 >> 1)) & 63 : l);
 }
 
-// Few experts.  EP = E rounded up to a power of two (>= 4); TB tokens per wavefront, TB*EP <= 64.
+// All experts in a wavefront.  EP = E rounded up to a power of two (>= 4); TB tokens per wavefront, TB*EP <= 64.
 // MC = gate-weight rows held in LDS at a time (multiple of 512, or >= M).
 //
 // A wavefront multiplies TB tokens at a time (a group) and parks their logits in LDS; once
-// ROUTE_HELD tokens are parked, or its groups are done, one lane per token does softmax and
+// RouteHeld tokens are parked, or its groups are done, one lane per token does softmax and
 // top-k, so that the serial part runs once for many tokens instead of once per group.
 template <typename T, int EP, int TB>
 __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(
@@ -139,7 +141,7 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(
     const int nchunks = (M + MC - 1) / MC;
     constexpr int E4 = EP / 4;
     constexpr unsigned ES = sizeof(T);
-    constexpr int HELD = ROUTE_HELD;
+    constexpr int HELD = RouteHeld<EP>::N;
     constexpr bool ROT = TB == 2 && EP <= 16;       // few tokens per workgroup
     float* mylg = lg + (size_t)wid * HELD * EP;
     int held = 0, held_g0 = 0;                      // parked tokens, and the group of the first of them
@@ -372,7 +374,7 @@ __global__ __launch_bounds__(ROUTE_THREADS, sizeof(T) == 4 && TB == 4 ? 2 : 4) v
     float acc[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) acc[i] = 0.0f;
-    const bool whole = E == EP && (reinterpret_cast<unsigned long long>(Wg) & 15ull) == 0;
+    const bool eights = (E & 7) == 0 && (reinterpret_cast<unsigned long long>(Wg) & 15ull) == 0;
     constexpr int G = EP / 8, NP = 64 * ES * G / ROUTE_THREADS;  // eight experts of a row per load, loads per thread
     constexpr int NPB = sizeof(T) == 2 ? NP : 2;                 // of which in flight together
     Raw8<T> xr[TB];
@@ -383,14 +385,14 @@ __global__ __launch_bounds__(ROUTE_THREADS, sizeof(T) == 4 && TB == 4 ? 2 : 4) v
         for (int i0 = 0; i0 < 8; i0 += ES) {
             if (c0 + i0 > 0) __syncthreads();       // the weights before these have been used
             // row r of a piece: lane r/ES, element i0 + r%ES
-            if (whole) {
+            if (eights) {
 #pragma unroll
                 for (int b = 0; b < NP; b += NPB) {
                     Raw8<T> wr[NPB];
 #pragma unroll
                     for (int i = 0; i < NPB; ++i) {
                         const int q = tid + (b + i) * ROUTE_THREADS, r = q / G, d = c0 + (r / ES) * 8 + i0 + r % ES;
-                        if (d < M) wr[i].load(Wg + (size_t)d * E + (q % G) * 8);
+                        if (d < M && (q % G) * 8 < E) wr[i].load(Wg + (size_t)d * E + (q % G) * 8);
                         else wr[i].zero();
                     }
 #pragma unroll
@@ -470,13 +472,12 @@ __global__ __launch_bounds__(ROUTE_THREADS, sizeof(T) == 4 && TB == 4 ? 2 : 4) v
         // in step s lane `sub` = s continues from what lane s - 1 had in the step before (what the other lanes have is not used).
         float q[EPL];
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) q[i] = expf(v[i] - mx);
+        for (int i = 0; i < EPL; ++i) q[i] = sub * EPL + i < E ? expf(v[i] - mx) : 0.0f;      // (adding zero changes no bit of the sum)
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             if (s > 0) sum = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sum), 0x111 /* row_shr:1 */, 0xf, 0xf, false));
 #pragma unroll
-            for (int i = 0; i < EPL; ++i)
-                if (sub * EPL + i < E) sum += q[i];
+            for (int i = 0; i < EPL; ++i) sum += q[i];
         }
         sum = __shfl(sum, lane | 7, 64);
     }
@@ -537,11 +538,13 @@ static moe_status launch_route_wide(const Dims& d, const void* x, const void* Wg
     return MOE_OK;
 }
 
+static bool route_fits(int M, int EP) { return (M + 511) / 512 * 512 <= 32768 / EP; }
+
 template <typename T, int EP, int TB>
 static moe_status launch_route(const Dims& d, const void* x, const void* Wg, const float* bias,
                                float* logits, int* idx, float* w, hipStream_t s) {
     // Gate-weight rows held in LDS at a time.  If the whole matrix fits in 128 KB of
-    // floats it is loaded once per workgroup, which then walks over many token groups;
+    // floats (route_fits) it is loaded once per workgroup, which then walks over many token groups;
     // otherwise it is streamed through LDS in 64 KB pieces for every token group.
     const int Mpad = ((d.M + 511) / 512) * 512;
     int MC = (32768 / EP) / 512 * 512;
@@ -550,7 +553,7 @@ static moe_status launch_route(const Dims& d, const void* x, const void* Wg, con
         MC = (16384 / EP) / 512 * 512;
         if (MC < 512) MC = 512;
     }
-    size_t lds = ((size_t)MC * EP + (size_t)ROUTE_WAVES * ROUTE_HELD * EP) * sizeof(float);
+    size_t lds = ((size_t)MC * EP + (size_t)ROUTE_WAVES * RouteHeld<EP>::N * EP) * sizeof(float);
     auto kern = route_kernel<T, EP, TB>;
     static size_t attr_bytes = 0;                     // largest size asked for so far (per instantiation)
     if (lds > attr_bytes) {
@@ -584,11 +587,31 @@ static moe_status route_dispatch(const Dims& d, const void* x, const void* Wg, c
         return few ? launch_route<T, 8, 2>(d, x, Wg, bias, logits, idx, w, s) : launch_route<T, 8, 8>(d, x, Wg, bias, logits, idx, w, s);
     if (d.E <= 16)
         return few ? launch_route<T, 16, 2>(d, x, Wg, bias, logits, idx, w, s) : launch_route<T, 16, 4>(d, x, Wg, bias, logits, idx, w, s);
+    // Beyond sixteen experts: sixteen of them per wavefront, with the weights through LDS for every round of tokens (two
+    // workgroups per CU), or all in a wavefront, with weights that stay in LDS where all fit.  The latter win from so many
+    // rounds on; how many follows from the way of the weights to LDS, eight of a row per load or one by one.  us of the
+    // former / the latter, columns 64 and 1024 (32 padded experts) or 512 (64):
+    //   bfloat16, one by one   28 experts, 2 rounds: 24 / 28 and 46 / 53, 3: 34 / 34 and 67 / 62; 44, 2: 33 / 42 and 42 / 50, 3: 47 / 51 and 60 / 58
+    //   bfloat16, by eights    32, 3: 29 / 32 and 47 / 47, 4: 37 / 39 and 60 / 57; 24 and 40 to 64: never (64, 12: 118 / 148)
+    //   float32, one by one    28, 1: 18 / 21 and 36 / 40, 1.5: 25 / 24 and 66 / 47; 44, 1: 23 / 32 and 29 / 35, 1.5: 32 / 37 and 41 / 40
+    //   float32, by eights     24, 3: 34 / 33 and 57 / 61, 4: 44 / 41 and 74 / 72; 32, 2: 24 / 27 and 41 / 39, 3: 34 / 33 and 58 / 48;
+    //                          48, 6: 76 / 73 and 81 / 89, 8: 99 / 91 and 106 / 106; 64, 5: 64 / 63 and 69 / 68, 6: 76 / 72 and 81 / 78
+    constexpr bool f32 = sizeof(T) == 4;
+    const int EP = d.E <= 32 ? 32 : 64, round = 2 * cus * (ROUTE_WAVES * 16 / EP) * 4;
+    const bool eights = (d.E & 7) == 0 && ((uintptr_t)Wg & 15) == 0;
+    const int rounds = !eights ? (f32 ? 1 : 2) : f32 ? (EP == 32 ? (d.E == 32 ? 2 : 3) : (d.E == 64 ? 5 : 6)) : d.E == 32 ? 3 : INT_MAX;
+    long long most = (long long)rounds * round;      // tokens up to which sixteen experts per wavefront it is
+    if (!eights && EP == 64 && d.M <= 384) most += most / 2;          // (60 experts, 1.5 rounds in float32: columns 64 32 / 37, 344 38 / 39, 504 42 / 41)
+    const bool stay = route_fits(d.M, EP) && d.T > most;
     if (d.E <= 32) {
-        // float32 rows of many tokens: the weights that stay in LDS win (27 362 x 344 x 32: 33 us against 42; 13 681: 24 and 23)
-        if constexpr (sizeof(T) == 4) { if (d.T > 16384) return launch_route<T, 32, 2>(d, x, Wg, bias, logits, idx, w, s); }
-        return few ? launch_route_wide<T, 32, 2>(d, x, Wg, bias, logits, idx, w, s) : launch_route_wide<T, 32, 4>(d, x, Wg, bias, logits, idx, w, s);
+        if (stay) return launch_route<T, 32, 2>(d, x, Wg, bias, logits, idx, w, s);
+        // (float32, one by one: two tokens per wavefront up to a whole round, 8192 x 1024 x 28 36 us against 42; but not for about
+        // a thousand rows of a multiple of 16 KB: 1000 x 4096 x 20 51 us with four, 62 with two, 58 with all experts in a wavefront)
+        const bool same_lines = !eights && d.T >= 700 && d.T < 2000 && (size_t)d.M * sizeof(T) % 16384 == 0;
+        const bool two = same_lines ? false : f32 && !eights ? d.T <= round : few;
+        return two ? launch_route_wide<T, 32, 2>(d, x, Wg, bias, logits, idx, w, s) : launch_route_wide<T, 32, 4>(d, x, Wg, bias, logits, idx, w, s);
     }
+    if (stay) return launch_route<T, 64, 1>(d, x, Wg, bias, logits, idx, w, s);
     return few ? launch_route_wide<T, 64, 2>(d, x, Wg, bias, logits, idx, w, s) : launch_route_wide<T, 64, 4>(d, x, Wg, bias, logits, idx, w, s);
 }
 

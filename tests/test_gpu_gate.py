@@ -79,3 +79,27 @@ def test_weights_are_the_same_bits_for_few_and_for_many_experts(T, E, k, dtype, 
     assert np.array_equal(lo.numpy(), lo_many[:, place].numpy(), equal_nan=True)
     assert torch.equal(place[ti], ti_many)
     assert np.array_equal(tw.numpy(), tw_many.numpy(), equal_nan=True)
+
+
+@pytest.mark.parametrize("T,M,E,dtype", [
+    (16385, 40, 28, "bf16"), (24577, 72, 32, "bf16"), (8193, 504, 44, "bf16"), (12289, 72, 35, "bf16"), (8193, 72, 17, "f32"), (24577, 40, 24, "f32"),
+    (4097, 504, 33, "f32"), (6145, 384, 60, "f32"), (24577, 40, 48, "f32"), (20481, 504, 64, "f32"), (1000, 4096, 20, "f32"), (701, 8192, 28, "bf16"),
+])
+def test_gate_of_many_tokens_is_that_of_its_pieces(T, M, E, dtype):
+    """Around the numbers of tokens from which the gate weights stay in LDS, with gate weights read by eights and one by one:
+    the same bits as for 600 tokens at a time."""
+    dt, mt = (torch.bfloat16, B.MOE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_F32)
+    g, k, piece = torch.Generator(D).manual_seed(T + E), 3, 600
+    x, Wg = torch.randn((T, M), generator=g, device=D).to(dt), (torch.randn((M, E), generator=g, device=D) * 0.2).to(dt)
+    bias = torch.randn((E,), generator=g, device=D)
+
+    def gate(rows):
+        n = rows.shape[0]
+        cfg = B.make_config(n, M, 8, E, k, 1.0, 1, mt, 0)
+        out = torch.empty((n, E), device=D), torch.full((n, k), -9, dtype=torch.int32, device=D), torch.empty((n, k), device=D)
+        B.moe_route(cfg, rows, Wg, bias, *out)
+        return out
+    whole = gate(x)
+    for t in range(0, T, piece):
+        for a, b in zip(whole, gate(x[t:t + piece].contiguous())):
+            assert torch.equal(a[t:t + piece], b)
