@@ -33,9 +33,11 @@ def test_scattered_and_gathered_rows(T, M, H, E, n, second, first):
     d = synth.make_inputs(s, seed=17)
     cfg = B.make_config(T, M, H, E, 1, cf, n, B.MOE_BF16, 0, 1, fuse_combine=1)
     assert B.moe_gemm_tile(cfg, 0, "second") == second and B.moe_gemm_tile(cfg, 0, "first") == first
-    plain = runner.run_layer_step(s, d, n, 0, grad_overwrite=1)
-    fused = runner.run_layer_step(s, d, n, 0, grad_overwrite=1, fuse_combine=1)
-    gathered = runner.run_layer_step(s, d, n, 0, grad_overwrite=1, fuse_combine=1, fuse_gather=1)
+    # (two streams: one partition per launch, whose tiles the above are)
+    two = dict(grad_overwrite=1, gemm_free_cus=8 if n > 1 else 0)
+    plain = runner.run_layer_step(s, d, n, 0, **two)
+    fused = runner.run_layer_step(s, d, n, 0, fuse_combine=1, **two)
+    gathered = runner.run_layer_step(s, d, n, 0, fuse_combine=1, fuse_gather=1, **two)
     for k_ in ("y", "dx", "dWg", "dW1", "dW2", "slot", "counts"):
         assert np.array_equal(gathered[k_], fused[k_]), k_
     dropped = (fused["slot"] < 0).all(axis=1)
