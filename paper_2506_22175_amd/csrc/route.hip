@@ -577,9 +577,12 @@ static moe_status route_dispatch(const Dims& d, const void* x, const void* Wg, c
                                  float* logits, int* idx, float* w, hipStream_t s) {
     // Tokens per wavefront: as many as the registers hold; two where that would leave half of the CUs without a workgroup
     // (64 tokens x 1024 x 8 experts 6.8 us against 9.7, 4096 x 512 x 8 5.9 / 8.4, 1024 x 1024 x 16 9.7 / 13.9) or, beyond
-    // sixteen experts, fewer than two workgroups per CU.
+    // sixteen experts, fewer than two workgroups per CU.  Of five to eight experts in float32 only one such workgroup fits a CU,
+    // so no more than one per CU (4300 x 64, 512, 1024 x 8 experts: two tokens 11.3, 11.3, 13.5 us, eight 10.0, 10.1, 11.5; 4096: 6.8, 7.2, 7.9 and
+    // 9.9, 10.0, 11.4).
     constexpr int cus = 256;
-    const bool few = d.T < (d.E <= 8 ? cus / 2 * ROUTE_WAVES * 8 : d.E <= 16 ? cus / 2 * ROUTE_WAVES * 4
+    constexpr bool f32 = sizeof(T) == 4;
+    const bool few = d.T < (d.E > 4 && d.E <= 8 && f32 ? cus * ROUTE_WAVES * 2 + 1 : d.E <= 8 ? cus / 2 * ROUTE_WAVES * 8 : d.E <= 16 ? cus / 2 * ROUTE_WAVES * 4
                                                                     : 2 * cus * (ROUTE_WAVES * 16 / (d.E <= 32 ? 32 : 64)) * 2);
     if (d.E <= 4)
         return few ? launch_route<T, 4, 2>(d, x, Wg, bias, logits, idx, w, s) : launch_route<T, 4, 8>(d, x, Wg, bias, logits, idx, w, s);
@@ -596,7 +599,6 @@ static moe_status route_dispatch(const Dims& d, const void* x, const void* Wg, c
     //   float32, one by one    28, 1: 18 / 21 and 36 / 40, 1.5: 25 / 24 and 66 / 47; 44, 1: 23 / 32 and 29 / 35, 1.5: 32 / 37 and 41 / 40
     //   float32, by eights     24, 3: 34 / 33 and 57 / 61, 4: 44 / 41 and 74 / 72; 32, 2: 24 / 27 and 41 / 39, 3: 34 / 33 and 58 / 48;
     //                          48, 6: 76 / 73 and 81 / 89, 8: 99 / 91 and 106 / 106; 64, 5: 64 / 63 and 69 / 68, 6: 76 / 72 and 81 / 78
-    constexpr bool f32 = sizeof(T) == 4;
     const int EP = d.E <= 32 ? 32 : 64, round = 2 * cus * (ROUTE_WAVES * 16 / EP) * 4;
     const bool eights = (d.E & 7) == 0 && ((uintptr_t)Wg & 15) == 0;
     const int rounds = !eights ? (f32 ? 1 : 2) : f32 ? (EP == 32 ? (d.E == 32 ? 2 : 3) : (d.E == 64 ? 5 : 6)) : d.E == 32 ? 3 : INT_MAX;

@@ -82,12 +82,12 @@ def test_weights_are_the_same_bits_for_few_and_for_many_experts(T, E, k, dtype, 
 
 
 @pytest.mark.parametrize("T,M,E,dtype", [
-    (16385, 40, 28, "bf16"), (24577, 72, 32, "bf16"), (8193, 504, 44, "bf16"), (12289, 72, 35, "bf16"), (8193, 72, 17, "f32"), (24577, 40, 24, "f32"),
+    (4097, 1000, 7, "f32"), (16385, 40, 28, "bf16"), (24577, 72, 32, "bf16"), (8193, 504, 44, "bf16"), (12289, 72, 35, "bf16"), (8193, 72, 17, "f32"), (24577, 40, 24, "f32"),
     (4097, 504, 33, "f32"), (6145, 384, 60, "f32"), (24577, 40, 48, "f32"), (20481, 504, 64, "f32"), (1000, 4096, 20, "f32"), (701, 8192, 28, "bf16"),
 ])
 def test_gate_of_many_tokens_is_that_of_its_pieces(T, M, E, dtype):
-    """Around the numbers of tokens from which the gate weights stay in LDS, with gate weights read by eights and one by one:
-    the same bits as for 600 tokens at a time."""
+    """Around the numbers of tokens from which a wavefront takes more of them and the gate weights stay in LDS, with gate
+    weights read by eights and one by one: the same bits as for 600 tokens at a time."""
     dt, mt = (torch.bfloat16, B.MOE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_F32)
     g, k, piece = torch.Generator(D).manual_seed(T + E), 3, 600
     x, Wg = torch.randn((T, M), generator=g, device=D).to(dt), (torch.randn((M, E), generator=g, device=D) * 0.2).to(dt)
