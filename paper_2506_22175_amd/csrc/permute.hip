@@ -87,7 +87,10 @@ struct RowArgs {
 // used: 32768 tokens x 2048, two choices, with dw, 52 us a partition of 16384 under rocprofv3, 67 to 72 with the
 // experts' rows read one after another (39 us is the time of a copy of as many bytes).
 // (float accumulation, ascending j; a lane's part of a dot in ascending column order)
-template <typename T, int KM, bool DW, bool COMB>
+// STRAIGHT: rows through descriptors of their own, where lanes past the end and rows that are not there read zeros and write
+// nothing.  Else under execution masks, where the compiler puts a wait for all that is in flight in front of every store: a
+// wavefront has one store on its way.  See dispatch_straight.
+template <typename T, int KM, bool DW, bool COMB, bool STRAIGHT>
 __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
     const int lane = threadIdx.x & 63;
     const int tl = blockIdx.x * PERM_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
     const bool comb = COMB && which == 0;          // (the rows of the other source have nothing to do with T_DO)
     const size_t t = (size_t)(a.p0 + z) * a.Tp + tl;
     constexpr int N = Unit<T>::N;
-    constexpr int UN = !DW && !COMB ? 4 : KM > 4 ? 1 : KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
+    constexpr int UN = !DW && !COMB ? 4 : KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
     const int U = M / N;
     T* dst = reinterpret_cast<T*>(a.dst[which] + z * a.dst_stride[which]);
     const T* rows = DW || COMB ? reinterpret_cast<const T*>(a.rows + z * a.rows_stride) : nullptr;
@@ -104,10 +107,27 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
     float ws[KM], dot[KM];
 #pragma unroll
     for (int j = 0; j < KM; ++j) {
-        s[j] = j < k ? a.slot[t * k + j] : -1;
+        // (in straight-line code all on their way together; many wavefronts that write one store at a time are slower so, 8192 x 512
+        // bfloat16, two choices 7.9 us instead of 6.7)
+        if constexpr (STRAIGHT) s[j] = a.slot[t * k + min(j, k - 1)];
+        else s[j] = j < k ? a.slot[t * k + j] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < KM; ++j) {
+        if (STRAIGHT && j >= k) s[j] = -1;
         ws[j] = comb && s[j] >= 0 ? a.w[t * k + j] : 0.0f;
         dot[j] = 0.0f;
     }
+    const int row_bytes = M * (int)sizeof(T);
+    auto descriptor = [&](const void* row, bool there) __attribute__((always_inline)) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, there ? row_bytes : 0, 0x00020000);
+    };
+    auto load = [&](__amdgpu_buffer_rsrc_t row, int c) __attribute__((always_inline)) {
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(row, c * 16, 0, 2 /* non-temporal */));
+    };
+    auto store = [&](__amdgpu_buffer_rsrc_t row, int c, const uint4& u) __attribute__((always_inline)) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_hw, u), row, c * 16, 0, 0);
+    };
     const uint4* in = reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.src[which]) + t * M);
     const uint4 zero = make_uint4(0, 0, 0, 0);
     for (int c0 = 0; c0 < U; c0 += 64 * UN) {
@@ -115,28 +135,36 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int c = c0 + u * 64 + lane;
-            if (c < U) v[u] = ld_row<true>(in + c);
+            if constexpr (STRAIGHT) v[u] = load(descriptor(in, true), c);
+            else if (c < U) v[u] = ld_row<true>(in + c);
         }
         if constexpr (DW || COMB) {
 #pragma unroll
             for (int j = 0; j < KM; ++j) {
                 const uint4* row = reinterpret_cast<const uint4*>(rows + (size_t)max(s[j], 0) * M);
+                const bool there = s[j] >= 0 && (DW || comb);
 #pragma unroll
                 for (int u = 0; u < UN; ++u) {
                     const int c = c0 + u * 64 + lane;
-                    r[j][u] = zero;
-                    if (c < U && s[j] >= 0 && (DW || comb)) r[j][u] = ld_row<true>(row + c);
+                    if constexpr (STRAIGHT) {
+                        r[j][u] = load(descriptor(row, there), c);
+                    } else {
+                        r[j][u] = zero;
+                        if (c < U && there) r[j][u] = ld_row<true>(row + c);
+                    }
                 }
             }
         }
 #pragma unroll
         for (int j = 0; j < KM; ++j) {
-            if (s[j] < 0) continue;
-            uint4* out = reinterpret_cast<uint4*>(dst + (size_t)s[j] * M);
+            if (STRAIGHT && j >= k) break;
+            if (!STRAIGHT && s[j] < 0) continue;
+            uint4* out = reinterpret_cast<uint4*>(dst + (size_t)(STRAIGHT ? max(s[j], 0) : s[j]) * M);
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int c = c0 + u * 64 + lane;
-                if (c < U) st_row<false>(out + c, v[u]);
+                if constexpr (STRAIGHT) store(descriptor(out, s[j] >= 0), c, v[u]);
+                else if (c < U) st_row<false>(out + c, v[u]);
             }
         }
         if constexpr (DW || COMB) {
@@ -144,7 +172,7 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
             for (int u = 0; u < UN; ++u) {
                 const int c = c0 + u * 64 + lane;
                 float x[N], acc[N];
-                Unit<T>::to_float(c < U ? v[u] : zero, x);
+                Unit<T>::to_float(STRAIGHT || c < U ? v[u] : zero, x);
 #pragma unroll
                 for (int i = 0; i < N; ++i) acc[i] = 0.0f;
 #pragma unroll
@@ -158,7 +186,9 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
                     }
                 }
                 if constexpr (COMB) {
-                    if (c < U && comb) st_row<false>(reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * M) + c, Unit<T>::from_float(acc));
+                    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * M);
+                    if constexpr (STRAIGHT) store(descriptor(out, comb), c, Unit<T>::from_float(acc));
+                    else if (c < U && comb) st_row<false>(out + c, Unit<T>::from_float(acc));
                 }
             }
         }
@@ -188,7 +218,11 @@ __global__ __launch_bounds__(PERM_THREADS) void combine_kernel(RowArgs a) {
     const int U = a.M / N;
     int s[8];
     float ws[8];
-    for (int j = 0; j < k; ++j) { s[j] = a.slot[t * k + j]; ws[j] = a.w[t * k + j]; }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {                  // (all on their way together)
+        s[j] = a.slot[t * k + min(j, k - 1)];
+        ws[j] = a.w[t * k + min(j, k - 1)];
+    }
     uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * a.M);
     for (int c0 = 0; c0 < U; c0 += 256) {
         float acc[4][N];
@@ -792,13 +826,33 @@ __global__ __launch_bounds__(256) void gate_dwg_reduce_kernel(GateSums g) {
     gate_dwg_reduce<256>(g, blockIdx.x, red);
 }
 
+// Whether a plain dispatch runs in straight-line code.  One store on its way per wavefront is the faster one where many
+// wavefronts write: their reads and writes come in longer runs.  It is slower where few wavefronts have to hide it, and
+// for rows of several pieces (of 4 KB) with few choices.  us, masks / straight: 16 384 tokens x 512 bfloat16, two choices 11.2 / 12.4,
+// 8192 x 2048 16.7 / 19.7, three 21.3 / 25.2, 2000 x 1024 4.3 / 4.2, 1000 x 776, eight 6.6 / 5.4; float32, 1000 x 776, six 8.3 / 6.5,
+// 16 384 x 2048, two 88 / 81, 4096 x 2048, six 40 / 52.  (With more than four choices also rows of about 1 KB: 16 384 x 512 bfloat16,
+// eight 35 / 30.)
+static bool dispatch_straight(int row_bytes, int waves, int k) {
+    const int units = row_bytes / 16;
+    return (units > 64 && waves <= 2048) || (units > 256 && k <= 2) || (units >= 64 && units <= 96 && k > 4);
+}
+template <typename T, int KM, bool DW, bool COMB>
+static void launch_dispatch_k(const RowArgs& a, dim3 grid, hipStream_t s) {
+    // (with the rows of T_DO: straight-line code for more than two choices, 8192 x 2048 float32, eight 277 / 246)
+    constexpr bool plain = !DW && !COMB;
+    if (plain ? dispatch_straight(a.M * (int)sizeof(T), a.Tp * (int)(grid.y * grid.z), a.k) : KM > 2) {
+        if constexpr (plain || KM > 2) hipLaunchKernelGGL((dispatch_kernel<T, KM, DW, COMB, true>), grid, dim3(PERM_THREADS), 0, s, a);
+    } else {
+        if constexpr (plain || KM <= 2) hipLaunchKernelGGL((dispatch_kernel<T, KM, DW, COMB, false>), grid, dim3(PERM_THREADS), 0, s, a);
+    }
+}
 template <typename T, bool DW, bool COMB>
 static moe_status launch_dispatch(const RowArgs& a, int sources, int np, hipStream_t s) {
     const dim3 grid((a.Tp + PERM_WAVES - 1) / PERM_WAVES, sources, np);
-    if (a.k == 1) hipLaunchKernelGGL((dispatch_kernel<T, 1, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
-    else if (a.k == 2) hipLaunchKernelGGL((dispatch_kernel<T, 2, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
-    else if (a.k <= 4) hipLaunchKernelGGL((dispatch_kernel<T, 4, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
-    else hipLaunchKernelGGL((dispatch_kernel<T, 8, DW, COMB>), grid, dim3(PERM_THREADS), 0, s, a);
+    if (a.k == 1) launch_dispatch_k<T, 1, DW, COMB>(a, grid, s);
+    else if (a.k == 2) launch_dispatch_k<T, 2, DW, COMB>(a, grid, s);
+    else if (a.k <= 4) launch_dispatch_k<T, 4, DW, COMB>(a, grid, s);
+    else launch_dispatch_k<T, 8, DW, COMB>(a, grid, s);
     MOE_CHECK_LAUNCH();
     return MOE_OK;
 }

@@ -94,6 +94,28 @@ def test_dispatch_with_row_dots(dtype, k, M):
         assert bool((err <= prod.abs().sum(2) * M * 2.0 ** -24).all())
 
 
+@pytest.mark.parametrize("T,M,k,dtype", [
+    (2047, 8, 3, "bf16"), (2049, 520, 1, "bf16"), (2049, 2040, 2, "bf16"), (2048, 1032, 4, "f32"), (2049, 1016, 4, "f32"),
+    (2049, 1032, 2, "f32"), (2049, 1032, 3, "f32"), (2100, 512, 5, "bf16"), (2100, 504, 8, "bf16"), (2100, 776, 7, "bf16"), (2100, 392, 6, "f32"),
+])
+def test_dispatch_of_many_tokens(T, M, k, dtype):
+    """Around the numbers of tokens, row lengths and choices by which dispatch changes the form of its stores: rows land bit
+    for bit and nowhere else."""
+    E, dt, mt = 9, *((torch.bfloat16, B.MOE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_F32))
+    cfg = B.make_config(T, M, 8, E, k, 0.7, 1, mt, 0)
+    Cp = B.moe_capacity(cfg)
+    ref, _ = _slots(_choices(T, E, k, k), 1, E, Cp)
+    assert (ref < 0).any()
+    src = torch.randn((T, M), generator=torch.Generator(D).manual_seed(M), device=D).to(dt)
+    slot = torch.from_numpy(ref).to(D)
+    out = torch.full((E * Cp + 8, M), float("nan"), device=D).to(dt)
+    B.moe_dispatch(cfg, 0, src, slot, out[:E * Cp])
+    want = torch.full_like(out, float("nan"))
+    t, j = torch.nonzero(slot >= 0, as_tuple=True)
+    want[slot[t, j].long()] = src[t]
+    assert torch.equal(out.isnan(), want.isnan()) and torch.equal(out.nan_to_num(), want.nan_to_num())
+
+
 @pytest.mark.parametrize("T,M,H,E,k,n,dtype,mode,fuse", [
     (120, 72, 136, 5, 3, 5, "bf16", 0, 0), (96, 520, 264, 9, 8, 1, "bf16", 0, 1), (90, 264, 136, 3, 1, 3, "f32", 0, 0),
     (128, 2056, 72, 4, 2, 2, "bf16", 0, 0), (128, 2056, 72, 4, 2, 2, "bf16", 2, 0), (96, 520, 264, 9, 8, 1, "bf16", 1, 1),
