@@ -99,7 +99,7 @@ __global__ __launch_bounds__(PERM_THREADS) void dispatch_kernel(RowArgs a) {
     const bool comb = COMB && which == 0;          // (the rows of the other source have nothing to do with T_DO)
     const size_t t = (size_t)(a.p0 + z) * a.Tp + tl;
     constexpr int N = Unit<T>::N;
-    constexpr int UN = !DW && !COMB ? 4 : KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
+    constexpr int UN = !DW && !COMB ? 4 : KM > 4 && !STRAIGHT ? 1 : KM > 2 ? 2 : 4;      // 16-byte units per row and lane in flight
     const int U = M / N;
     T* dst = reinterpret_cast<T*>(a.dst[which] + z * a.dst_stride[which]);
     const T* rows = DW || COMB ? reinterpret_cast<const T*>(a.rows + z * a.rows_stride) : nullptr;
@@ -218,11 +218,15 @@ __global__ __launch_bounds__(PERM_THREADS) void combine_kernel(RowArgs a) {
     const int U = a.M / N;
     int s[8];
     float ws[8];
+    auto choices = [&](int j0, int j1) __attribute__((always_inline)) {      // (all on their way together)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {                  // (all on their way together)
-        s[j] = a.slot[t * k + min(j, k - 1)];
-        ws[j] = a.w[t * k + min(j, k - 1)];
-    }
+        for (int j = j0; j < j1; ++j) {
+            s[j] = a.slot[t * k + min(j, k - 1)];
+            ws[j] = a.w[t * k + min(j, k - 1)];
+        }
+    };
+    choices(0, 2);
+    if (k > 2) choices(2, 8);
     uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<T*>(a.y) + t * a.M);
     for (int c0 = 0; c0 < U; c0 += 256) {
         float acc[4][N];
@@ -297,9 +301,15 @@ constexpr int DXB_THREADS = DXB_CT * DXB_TG;
 // Partitions p0 .. p0 + gridDim.z - 1.  Blocks from token_rows on (in y) do not belong to dispatch backward: they add up
 // the gate-weight gradient's partial sums, which saves that its own launch.  (The kernels' pointers are parameters of their own:
 // what is read through a structure counts as something that the stores to dx may change, and is read by every lane instead
-// of once per wavefront.  float32, 1001 tokens x 776 x 6 experts, five choices 9.8 us so, 6.6 now; 8192 x 2048 x 64, eight: 166 and 139.)
+// of once per wavefront.  float32, 1001 tokens x 776 x 6 experts, five choices 9.8 us so, 6.6 now; 8192 x 2048 x 64, eight: 166 and 139.
+// Nine to sixteen experts in bfloat16 take them from the structure all the same: 4096 x 2048 x 16 12.1 us so, 12.7 with parameters.)
 struct DispatchBwdArgs {
+    const void* dDI;
     long long dDI_stride;                // bytes
+    const int* slot;
+    const float* dL;
+    const void* Wg;
+    void* dx;
     int p0, Tp, tok, M, E, k, token_rows;
     GateSums sums;
 };
@@ -420,6 +430,9 @@ __global__ __launch_bounds__(DXB_THREADS, EG > 4 ? 4 : 2) void dispatch_bwd_mfma
     const bf16_t* __restrict__ Wg, bf16_t* __restrict__ dx, DispatchBwdArgs a) {
     extern __shared__ __attribute__((aligned(16))) char dxm_smem[];
     if (dispatch_bwd_sums<DXB_THREADS>(a, dxm_smem)) return;
+    if constexpr (EG == 4) {
+        dDI = (const bf16_t*)a.dDI; slot = a.slot; dL = a.dL; Wg = (const bf16_t*)a.Wg; dx = (bf16_t*)a.dx;
+    }
     dDI = reinterpret_cast<const bf16_t*>(reinterpret_cast<const char*>(dDI) + blockIdx.z * a.dDI_stride);
     const int t_begin = (a.p0 + (int)blockIdx.z) * a.Tp, t_count = a.Tp, tok = a.tok, M = a.M, E = a.E, k = a.k;
     const int ct = threadIdx.x % DXB_CT;                       // column thread
@@ -838,12 +851,14 @@ static bool dispatch_straight(int row_bytes, int waves, int k) {
 }
 template <typename T, int KM, bool DW, bool COMB>
 static void launch_dispatch_k(const RowArgs& a, dim3 grid, hipStream_t s) {
-    // (with the rows of T_DO: straight-line code for more than two choices, 8192 x 2048 float32, eight 277 / 246)
+    // (with the rows of T_DO: straight-line code for more than two choices and rows of more than 1 KB; dots, masks / straight, 8192 x 2048
+    // float32, eight 277 / 224, 1000 x 776, five 12.7 / 10.2, 16 384 x 256 bfloat16, five 21.6 / 27.5)
     constexpr bool plain = !DW && !COMB;
-    if (plain ? dispatch_straight(a.M * (int)sizeof(T), a.Tp * (int)(grid.y * grid.z), a.k) : KM > 2) {
+    const int row_bytes = a.M * (int)sizeof(T);
+    if (plain ? dispatch_straight(row_bytes, a.Tp * (int)(grid.y * grid.z), a.k) : KM > 2 && row_bytes > 1024) {
         if constexpr (plain || KM > 2) hipLaunchKernelGGL((dispatch_kernel<T, KM, DW, COMB, true>), grid, dim3(PERM_THREADS), 0, s, a);
     } else {
-        if constexpr (plain || KM <= 2) hipLaunchKernelGGL((dispatch_kernel<T, KM, DW, COMB, false>), grid, dim3(PERM_THREADS), 0, s, a);
+        hipLaunchKernelGGL((dispatch_kernel<T, KM, DW, COMB, false>), grid, dim3(PERM_THREADS), 0, s, a);
     }
 }
 template <typename T, bool DW, bool COMB>
@@ -905,7 +920,8 @@ moe_status dispatch_bwd_rows(const Dims& d, int p0, int np, const void* dDI, lon
     const int fit = (int)((long long)d.Tp * np * slices / (512 * DXB_TG)) / 4 * 4;
     const int tok = fit < 4 ? 4 : fit > DXB_TOK ? DXB_TOK : fit;
     DispatchBwdArgs a = {};
-    a.dDI_stride = dDI_stride;
+    a.dDI = dDI; a.dDI_stride = dDI_stride;
+    a.slot = slot; a.dL = dL; a.Wg = Wg; a.dx = dx;
     a.p0 = p0; a.Tp = d.Tp; a.tok = tok; a.M = d.M; a.E = d.E; a.k = d.k;
     a.token_rows = (d.Tp + tok * DXB_TG - 1) / (tok * DXB_TG);
     int sum_rows = 0;
