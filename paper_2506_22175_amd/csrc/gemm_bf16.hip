@@ -1325,11 +1325,10 @@ typedef TileCfg<128, 128, 32, 5, 2, 2, 2, LOOP_PIPE32> CfgS;
 typedef TileCfg<64, 128, 64, 6, 2, 2, 1, LOOP_R64> CfgT;
 //   CfgT2  CfgT with three stages, two workgroups per CU: beside CfgS in one launch.
 typedef TileCfg<64, 128, 64, 3, 2, 2, 2, LOOP_R64> CfgT2;
-//   CfgU   64 x 64, waves of 32 x 32, ten 64-k stages, for plain stores over a long K: where CfgT has tiles for half of
-//          the CUs at most, its steps wait for loads that were requested five steps before.  8 rows of 16, N = 1024,
-//          K = 4096: 22 us in 64 tiles of CfgT, 13 in 128; 8 x 128 rows: 38.9 and 29.3; K = 2048: the same either way.
+//   CfgU   64 x 64, waves of 32 x 32, ten 64-k stages, for plain stores over a long K of few tiles (few_tiles): their
+//          steps in CfgT wait for loads that were requested five steps before.  8 rows of 16, N = 1024, K = 4096: 22 us in 64
+//          tiles of CfgT, 13 in 128; 8 x 128 rows: 38.9 and 29.3.
 typedef TileCfg<64, 64, 64, 10, 2, 2, 1, LOOP_R64> CfgU;
-constexpr int CFG_U_MIN_K = 1024;
 
 int gemm_bf16_dw_parts(int H) { return (H + 2 * DW_COLS - 1) / (2 * DW_COLS) * 2; }
 
@@ -1393,22 +1392,40 @@ static constexpr TileCost TILE_COSTS[5] = {
     {64, 128, 1, {0.44, 0.42, 0.0}, 0.92, {1.5, 2.5, 5.0, 0.0, 0.0}},            // CfgT (not for TN)
     {64, 64, 1, {0.24, 0.0, 0.0}, 0.24, {1.2, 0.0, 0.0, 0.0, 0.0}},              // CfgU (NN stores)
 };
+// Tiles of a launch with rows of all experts alike; the last ones have fewer rows.
+static void count_tiles(const TileCost& c, const GemmArgs& a, long long* whole, long long* tail) {
+    const long long per_row = (long long)((a.N + c.bn - 1) / c.bn) * launch_experts(a);
+    const int full = a.mean_rows / c.bm, rest = a.mean_rows - full * c.bm;
+    *whole = full * per_row;
+    // an even multiple on average: about half the experts have a few rows more, where the capacity allows it
+    *tail = rest ? per_row : a.mean_rows < a.Cp ? per_row / 2 : 0;
+}
+// Whether a store over K has so few 64 x 64 tiles that CfgU may take it.  Its gain is per step of 64 k, and many tiles lose it to
+// reading their operands twice as often as CfgT.  us, of both expert GEMMs, the first the same, second in CfgT / CfgU, 64 tiles: K = 1024
+// 17.2 / 16.7 (4 x 64 rows, N = 512), 17.6 / 17.9 (16 x 64, 256), K = 4096 35.4 / 33.1; 128 tiles: 18.0 / 18.7 (16 x 32, 512), 41.0 / 39.7; 192 (16 x 192, 256):
+// 22.1 / 24.0, 52.4 / 59.8; 256: 23.6 / 24.4 (16 x 100, 512), 52.0 / 53.5, and of experts with one row of tiles 22.9 / 23.4 (16 x 32, 1024),
+// 63.7 / 61.0, with 48 rows 34.3 / 32.2 at K = 2048.
+static bool few_tiles(const GemmArgs& a, int cus) {
+    long long whole, tail;
+    count_tiles(TILE_COSTS[4], a, &whole, &tail);
+    const int E = launch_experts(a);
+    if (a.mean_rows % 64 == 0 && (E <= 4 || (E <= 8 && a.K >= 4096))) tail = 0;      // (a row more costs few experts little)
+    const long long n = whole + tail;
+    if (a.K >= 1024 && n <= cus / 2 && n * 1024 <= (long long)a.K * (cus / 4)) return true;
+    return n <= cus && a.mean_rows < 56 && a.K >= (a.mean_rows > 32 ? 2048 : 4096);
+}
 // (one: a single tile's, not the launch's)
 static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, int cus, bool one = false) {
     const int which = epi == EPI_GELU ? 1 : epi == EPI_DGELU ? 2 : epi == EPI_STORE_F32 ? 3 : epi == EPI_ACCUM_F32 ? 4 : 0;
-    const int E = lay == GEMM_TN ? a.E : launch_experts(a);
-    const long long tn = (a.N + c.bn - 1) / c.bn;
     const int segs = a.k_segs > 1 ? a.k_segs : 1;
     const double kt = lay == GEMM_TN ? (double)((a.mean_rows + 63) / 64) * segs : (double)((a.K + 63) / 64);
     long long whole, tail = 0;                       // tiles; those of the experts' last, partly filled tile rows
     double share = 1.0;                              // how full a tail tile is, in quarters
     if (lay == GEMM_TN) {
-        whole = (long long)((a.Mo + c.bm - 1) / c.bm) * tn * a.E;
+        whole = (long long)((a.Mo + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn) * a.E;
     } else {
-        const int full = a.mean_rows / c.bm, rest = a.mean_rows - full * c.bm;
-        whole = full * tn * E;
-        // an even multiple on average: about half the experts have a few rows more, where the capacity allows it
-        tail = rest ? tn * E : a.mean_rows < a.Cp ? tn * E / 2 : 0;
+        const int rest = a.mean_rows % c.bm;
+        count_tiles(c, a, &whole, &tail);
         share = rest ? (rest + c.bm / 4 - 1) / (c.bm / 4) * 0.25 : 0.25;
     }
     const double tile = kt * c.step[lay] + c.epi[which], launch = 1.7;
@@ -1427,7 +1444,7 @@ static int tile_choice(int lay, int epi, const GemmArgs& a) {
     const int cus = persistent_grid();               // (units left free change the time of a launch, not its results)
     int best = 0;
     double least = 0.0;
-    const bool u = lay == GEMM_NN && (epi == EPI_STORE || epi == EPI_SCATTER) && a.K >= CFG_U_MIN_K;
+    const bool u = lay == GEMM_NN && (epi == EPI_STORE || epi == EPI_SCATTER) && few_tiles(a, cus);
     for (int c = 0; c < (lay == GEMM_TN ? 3 : u ? 5 : 4); ++c) {
         const double t = tile_time(TILE_COSTS[c], lay, epi, a, cus);
         // (a smaller tile has to be clearly better: skewed loads drop rows and make more cheap last tile rows)

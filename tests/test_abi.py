@@ -158,3 +158,14 @@ def test_workspace_with_grouped_weight_gradients_and_fused_combine(oracle):
             f = B.moe_workspace_bytes(B.make_config(T, M, H, E, k, cf, n, B.MOE_BF16, mode, fuse_combine=1))
             n_do = n if (mode == 0 or n <= 2) else 2
             assert a[1] - f[1] == n_do * bufM                       # no T_DO among what forward keeps
+
+
+@pytest.mark.parametrize("E,rows,M,H,small", [
+    (16, 16, 256, 1024, True), (16, 100, 256, 1024, False), (16, 100, 256, 2048, True),      # 64 and 128 tiles of 64 x 64
+    (8, 192, 512, 2048, False), (8, 192, 512, 4096, False), (16, 100, 512, 4096, False),     # 224 and 256
+    (16, 32, 1024, 2048, False), (16, 32, 1024, 4096, True), (16, 48, 1024, 2048, True),     # 256, one row of tiles per expert
+    (4, 32, 256, 1016, False),
+])
+def test_second_gemm_in_64_x_64_tiles_only_where_there_are_few(E, rows, M, H, small):
+    cfg = B.make_config(E * rows, M, H, E, 1, 1.25, 1, B.MOE_BF16, 0)
+    assert (B.moe_gemm_tile(cfg, 0, "second") == (64, 64)) == small
