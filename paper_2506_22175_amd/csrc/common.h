@@ -144,6 +144,9 @@ void note_hip_error(hipError_t e, const char* file, int line);
 enum LaunchClass { LC_GEMM = 0, LC_PERMUTE = 1, LC_OTHER = 2 };
 void count_launch(LaunchClass c, int n = 1);
 
+// Compute units of the device, rounded down to a multiple of 8 so that tile numbers keep their XCD; 256 where there is none to ask.
+int compute_units();
+
 // Optional per-kernel timing with HIP events on the launching stream (off by
 // default; moe_profile_enable).  Kinds index the table in moe_profile_read.
 enum ProfKind {

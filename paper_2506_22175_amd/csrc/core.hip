@@ -51,6 +51,17 @@ void note_hip_error(hipError_t e, const char* file, int line) {
     snprintf(g_last_error, sizeof(g_last_error), "%s (%d) at %s:%d", hipGetErrorString(e), (int)e, file, line);
 }
 
+int compute_units() {
+    static const int units = [] {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
+            cus = 256;
+        return cus / 8 * 8;
+    }();
+    return units;
+}
+
 static std::atomic<long long> g_launches[3];
 void count_launch(LaunchClass c, int n) { g_launches[c].fetch_add(n, std::memory_order_relaxed); }
 

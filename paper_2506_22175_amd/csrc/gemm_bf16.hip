@@ -1332,27 +1332,14 @@ typedef TileCfg<64, 64, 64, 10, 2, 2, 1, LOOP_R64> CfgU;
 
 int gemm_bf16_dw_parts(int H) { return (H + 2 * DW_COLS - 1) / (2 * DW_COLS) * 2; }
 
-// Workgroups of a full grid: one per CU (times TileCfg::OCC; together they fill a CU's LDS), rounded down to a
-// multiple of 8 so that tile numbers keep their XCD.
-static int persistent_grid() {
-    static int grid = 0;
-    if (grid == 0) {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-            cus = 256;
-        grid = cus / 8 * 8;
-    }
-    return grid;
-}
-
 template <int LAY, int EPI, typename C>
 static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
     const int Mmax = (LAY == GEMM_TN) ? a.Mo : a.Cp;
     const int tiles_m = (Mmax + C::BM - 1) / C::BM, tiles_n = (a.N + C::BN - 1) / C::BN;
     int nblocks = launch_experts(a) * tiles_m * tiles_n;
     nblocks = (nblocks + 7) / 8 * 8;
-    int full = persistent_grid() - (a.free_cus + 7) / 8 * 8;
+    // a full grid: one workgroup per CU (times TileCfg::OCC; together they fill a CU's LDS)
+    int full = compute_units() - (a.free_cus + 7) / 8 * 8;
     if (full < 8) full = 8;
     full *= C::OCC;
     const int grid = nblocks < full ? nblocks : full;
@@ -1441,7 +1428,7 @@ static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, 
            extra * (kt * (c.tail_step + (c.step[lay] - c.tail_step) * share) + c.epi[which] * (0.4 + 0.6 * share));
 }
 static int tile_choice(int lay, int epi, const GemmArgs& a) {
-    const int cus = persistent_grid();               // (units left free change the time of a launch, not its results)
+    const int cus = compute_units();                  // (units left free change the time of a launch, not its results)
     int best = 0;
     double least = 0.0;
     const bool u = lay == GEMM_NN && (epi == EPI_STORE || epi == EPI_SCATTER) && few_tiles(a, cus);
@@ -1522,7 +1509,7 @@ static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, con
         b.tiles_wn[q] = (b.w[q].N + CT::BN - 1) / CT::BN;
         blocks += (b.w[q].E * b.tiles_wm[q] * b.tiles_wn[q] + 7) / 8 * 8;
     }
-    *done = blocks <= BACKWARD_ROUNDS * CT::OCC * persistent_grid();
+    *done = blocks <= BACKWARD_ROUNDS * CT::OCC * compute_units();
     if (!*done) return MOE_OK;
     if (gate) { b.gate = *gate; blocks += gate->blocks; }
     constexpr int lds = CN::LDS_BYTES > CT::LDS_BYTES ? CN::LDS_BYTES : CT::LDS_BYTES;
@@ -1549,8 +1536,8 @@ static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const 
     // (the shapes are those of the launches by themselves; shapes with one workgroup per CU and with two do not mix)
     const int cw = tile_choice(GEMM_TN, EPI, w2), cd = dgrad ? tile_choice(GEMM_NT, EPI_STORE, *dgrad) : cw;
     if (cw == 1 || tile_choice(GEMM_TN, EPI, w1) != cw || w2.free_cus > 0) return MOE_OK;
-    const bool w_first = dgrad && tile_time(TILE_COSTS[cw], GEMM_TN, EPI, w2, persistent_grid(), true) >
-                                      tile_time(TILE_COSTS[cd], GEMM_NT, EPI_STORE, *dgrad, persistent_grid(), true);
+    const bool w_first = dgrad && tile_time(TILE_COSTS[cw], GEMM_TN, EPI, w2, compute_units(), true) >
+                                      tile_time(TILE_COSTS[cd], GEMM_NT, EPI_STORE, *dgrad, compute_units(), true);
     if (cw == 2) {
         if (cd < 2) return MOE_OK;
         if (cd == 3) return launch_backward<EPI, CfgT2, CfgS>(dgrad, w2, w1, w_first, gate, s, done);

@@ -348,7 +348,8 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(
 // are registers for one or two, and the kernel reads LDS at twice the rate there is).  The gate weights pass through LDS
 // once per workgroup, 64 KB at a time (ES of the eight elements of every lane of a span of 512), and two workgroups share
 // a CU: one multiplies while the other waits for its weights, folds or ranks (eight lanes per token); four float32
-// rows take too many registers for that.  us, bfloat16, against TB = 1 or 2 tokens with all experts in a wavefront:
+// rows take too many registers for that.  us, bfloat16, launches back to back on the same inputs, against TB = 1 or 2
+// tokens with all experts in a wavefront (in a step, x not in the caches: the first is 45):
 // 8192 tokens x 768 x 64 experts 32 and 77, 1000 x 768 x 64 9.5 and 31, 4000 x 768 x 32 10.7 and 19, 3000 x 2048 x 48 60 and
 // 138; the multiply-adds of the first take 11.  What is left is the way of the weights through LDS for every 8 tokens.
 template <typename T, int EP, int TB>
@@ -439,14 +440,12 @@ __global__ __launch_bounds__(ROUTE_THREADS, sizeof(T) == 4 && TB == 4 ? 2 : 4) v
         }
     }
     fold_lanes<NV, 32>(acc, lane);
-    // value index vi = tb*16 + expert: two in a lane (2*lane, 2*lane + 1) of 128, one of 64, one in two lanes of 32
-    constexpr int PER = NV > 64 ? NV / 64 : 1, SHARE = NV < 64 ? 64 / NV : 1;
+    // value index vi = tb*16 + expert: one in a lane of 64 values, one in two lanes of 32
+    static_assert(NV == 64 || NV == 32, "two or four tokens of sixteen experts");
+    constexpr int SHARE = 64 / NV;
     if (lane % SHARE == 0) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int vi = lane / SHARE * PER + u, e = eb * 16 + vi % 16;
-            if (e < E) lg[(set * TB + vi / 16) * LGP + e] = bias ? acc[u] + bias[e] : acc[u];
-        }
+        const int vi = lane / SHARE, e = eb * 16 + vi % 16;
+        if (e < E) lg[(set * TB + vi / 16) * LGP + e] = bias ? acc[0] + bias[e] : acc[0];
     }
     __syncthreads();
     const int ntok = min(TOK, Ttot - tw);
@@ -562,7 +561,7 @@ static moe_status launch_route(const Dims& d, const void* x, const void* Wg, con
         attr_bytes = lds;
     }
     int ngroups = (d.T + ROUTE_WAVES * TB - 1) / (ROUTE_WAVES * TB);
-    const int cap = lds > 80 * 1024 ? 256 : 512;      // one or two workgroups per CU fit
+    const int cap = (lds > 80 * 1024 ? 1 : 2) * compute_units();      // one or two workgroups per CU fit
     int grid = ngroups < cap ? ngroups : cap;
     ProfScope ps(PK_ROUTE, s);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(ROUTE_THREADS), lds, s,
@@ -580,7 +579,7 @@ static moe_status route_dispatch(const Dims& d, const void* x, const void* Wg, c
     // sixteen experts, fewer than two workgroups per CU.  Of five to eight experts in float32 only one such workgroup fits a CU,
     // so no more than one per CU (4300 x 64, 512, 1024 x 8 experts: two tokens 11.3, 11.3, 13.5 us, eight 10.0, 10.1, 11.5; 4096: 6.8, 7.2, 7.9 and
     // 9.9, 10.0, 11.4).
-    constexpr int cus = 256;
+    const int cus = compute_units();
     constexpr bool f32 = sizeof(T) == 4;
     const bool few = d.T < (d.E > 4 && d.E <= 8 && f32 ? cus * ROUTE_WAVES * 2 + 1 : d.E <= 8 ? cus / 2 * ROUTE_WAVES * 8 : d.E <= 16 ? cus / 2 * ROUTE_WAVES * 4
                                                                     : 2 * cus * (ROUTE_WAVES * 16 / (d.E <= 32 ? 32 : 64)) * 2);
