@@ -314,10 +314,13 @@ moe_status moe_layer_backward(const moe_config* cfg, const void* x, const void* 
                               void* workspace, size_t workspace_bytes,
                               void* const* streams, int32_t n_streams);
 
-/* Counters of kernels launched by this process since the last reset, by class:
+/* Counters of this process's work on the device since the last reset, by class:
  * out[0] GEMMs, out[1] permutations (dispatch, combine, dispatch-backward),
- * out[2] everything else.  A launch that does the work of several counts as
- * all of them.  Host only. */
+ * out[2] everything else (a gate 1, a slot assignment 2, a partition's gate
+ * backward 3).  Units of work and not kernels launched: a launch that does the
+ * work of several counts as all of them, and a unit counts the same whether it
+ * took a launch of its own, a part of one, or (slot assignment) one or two.
+ * Host only. */
 moe_status moe_launch_counts(int64_t out[3], int32_t reset);
 
 /* Optional timing of the library's kernels with HIP events recorded on the

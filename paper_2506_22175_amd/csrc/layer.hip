@@ -10,9 +10,11 @@
 // recomputing T_M from T_DI (Table II, strategy S4: 5 GEMMs and 3 exchanges in
 // backward instead of 4 and 2).
 //
-// Stream 0 carries the gate, S, R and their backward counterparts; stream 1
-// carries the GEMMs.  Cross-stream order is kept with events; a buffer shared by
-// partitions p and p+2 is rewritten only after its reader of partition p is done.
+// On two streams (forward, backward) stream 0 carries the gate, S, R and their
+// backward counterparts and stream 1 the GEMMs.  Cross-stream order is kept with
+// events; a buffer shared by partitions p and p+2 is rewritten only after its reader
+// of partition p is done.  Small work, and two streams that are the same, run as one
+// chain (chain_forward, chain_backward), several partitions to a launch.
 #include "common.h"
 #include <vector>
 
@@ -26,7 +28,7 @@ struct Workspace {
     int nDI, nDO, ndDO;
     bool dDO_aliases_DO;
     // H-wide
-    size_t Z, HT;                     // Z: nZ buffers; HT: G temporaries (forward A in the first, backward dZ)
+    size_t Z, HT;                     // Z: nZ buffers; HT: G temporaries (backward's dZ).  Forward's activated rows: see forward_activations
     int nZ;
     // routing-class data
     size_t slot_w, dw, dw_part, dL, gate_scratch, slot_scratch, rows;
@@ -73,6 +75,8 @@ static moe_status plan(const moe_config* cfg, const Dims& d, Workspace* w) {
     w->nZ = mode_recomputes(d.reuse) ? d.G : mode_offloads_z(d.reuse) ? (d.n < 2 ? d.n : 2) : d.n;
     w->dDO_aliases_DO = reuse && !d.fcomb;
     w->ndDO = w->dDO_aliases_DO ? w->nDO : (d.n > alive ? alive : d.n);
+    // (Z, HT, dDO where it is not DO, and dDI follow one another without a gap: forward on one stream takes them, from Z or HT on,
+    // as one buffer for the activated rows of several partitions)
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += align_up(bytes); return o; };
     w->DI = take(w->bufM * w->nDI);
@@ -93,7 +97,8 @@ static moe_status plan(const moe_config* cfg, const Dims& d, Workspace* w) {
     w->dw_part_bytes = align_up((size_t)d.Rp * w->parts * sizeof(float));
     w->dw_part = take(w->dw_part_bytes * 2);
     w->dL = take((size_t)d.T * d.E * sizeof(float));
-    // (two partitions at a time: two transposed dL, one behind the other, then the second's partial sums)
+    // (two partitions at a time on one stream, which any n > 1 may run on - the caller may hand over the same stream twice: two
+    // transposed dL, one behind the other, then the second's partial sums)
     w->gate_second = align_up(gs + gate_dlt_bytes(d));
     w->gate_scratch = take(d.n > 1 ? w->gate_second + gate_part_bytes(d) : gs);
     w->slot_scratch = take(ss);
@@ -172,9 +177,9 @@ static moe_status back_to_tokens(const Dims& d, const Workspace& w, char* ws, in
 // of a small partition little more, so the permutations run for as many partitions at once as there are buffers:
 // forward sends the rows of a whole ring of T_DI buffers, then runs their GEMMs, then combines; backward takes
 // partitions two by two (dT_DI has two buffers).  What a partition's kernels compute does not
-// depend on it.  4096 tokens, 512/2048, two partitions with recomputation: 27 launches and 367 us one by one, 16 and 344
-// so; 3003 tokens, 776/2600, three partitions: 39 and 695, 22 and 644 (with the GEMMs of several partitions and the
-// gate's dL in joint launches as well: 15 launches and 309 us; 596).
+// depend on it.  4096 tokens, 512/2048, two partitions with recomputation: 27 launches and 430 us one by one, 15 and 330
+// so; 3003 tokens, 776/2600, three partitions: 39 and 789, 19 and 609 (the GEMMs of several partitions and the
+// gate's dL in joint launches included).
 
 // buffers of consecutive partitions in a ring: bytes from p's to the next one's
 static long long ring_step(int p, int ring, size_t bytes) {
@@ -242,7 +247,7 @@ static moe_status chain_forward(const Dims& d, const Workspace& w, char* ws, con
 }
 
 // y != NULL: forward's combine is still to be done, in the dispatch of dy.
-static moe_status chain_backward(const moe_config* cfg, const Dims& d, const Workspace& w, char* ws,
+static moe_status chain_backward(const Dims& d, const Workspace& w, char* ws,
                                  const void* x, const void* dy, const void* Wg, const void* W1, const void* W2,
                                  void* dx, float* dWg, float* dW1, float* dW2,
                                  const float* logits, const int* topk_idx, const float* topk_w, const int* slot,
@@ -538,7 +543,7 @@ extern "C" moe_status moe_layer_backward(const moe_config* cfg, const void* x, c
     if (!x || !dy || !Wg || !W1 || !W2 || !dx || !dWg || !dW1 || !dW2 || !logits || !topk_idx || !topk_w ||
         !slot || !counts) return MOE_ERR_NULL;
     if (s0 == s1)
-        return chain_backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
+        return chain_backward(d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
                               slot, counts, nullptr, s0);
     return backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, slot,
                     counts, s0, s1);
@@ -560,7 +565,7 @@ extern "C" moe_status moe_layer_step(const moe_config* cfg, const void* x, const
         // dots from the same rows or takes their place
         const bool later = w.nDO == d.n;
         MOE_TRY(chain_forward(d, w, (char*)workspace, x, W1, W2, y, topk_w, slot, counts, later, s0));
-        return chain_backward(cfg, d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
+        return chain_backward(d, w, (char*)workspace, x, dy, Wg, W1, W2, dx, dWg, dW1, dW2, logits, topk_idx, topk_w,
                               slot, counts, later ? y : nullptr, s0);
     }
     const bool early = first_backward_dispatch_can_go_early(d, w, false);

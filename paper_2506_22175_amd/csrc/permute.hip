@@ -416,7 +416,7 @@ __global__ __launch_bounds__(DXB_THREADS, 2) void dispatch_bwd_f32_kernel(
 // instruction and the weights widened when they are read.  There dL comes through LDS, in one request per round, and
 // 128 registers leave room for a second workgroup on the CU (launches back to back: 8192 tokens x 768 columns x 64
 // experts 23 us, 29 with dL in four requests one after the other and 156 registers; 8192 x 768 x 32: 15 and 20;
-// 16384 x 2048 x 64: 82 and 101).  Up to 64 experts: a slice of the gate
+// 16384 x 2048 x 64: 82 and 101; in a step, its inputs not in the caches, the first is 34).  Up to 64 experts: a slice of the gate
 // weights is at most 65 KB, so that two workgroups still fit a CU (the former: 1065 us with the weights read from
 // memory again for every token; 776 columns x 6 experts x 1001 tokens: 22.4 -> 11.0
 // by the number of tokens per group).  The kernel is bound by the latency of its row reads,
