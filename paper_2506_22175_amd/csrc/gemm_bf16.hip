@@ -1387,19 +1387,20 @@ static void count_tiles(const TileCost& c, const GemmArgs& a, long long* whole, 
     // an even multiple on average: about half the experts have a few rows more, where the capacity allows it
     *tail = rest ? per_row : a.mean_rows < a.Cp ? per_row / 2 : 0;
 }
-// Whether a store over K has so few 64 x 64 tiles that CfgU may take it.  Its gain is per step of 64 k, and many tiles lose it to
-// reading their operands twice as often as CfgT.  us, of both expert GEMMs, the first the same, second in CfgT / CfgU, 64 tiles: K = 1024
-// 17.2 / 16.7 (4 x 64 rows, N = 512), 17.6 / 17.9 (16 x 64, 256), K = 4096 35.4 / 33.1; 128 tiles: 18.0 / 18.7 (16 x 32, 512), 41.0 / 39.7; 192 (16 x 192, 256):
-// 22.1 / 24.0, 52.4 / 59.8; 256: 23.6 / 24.4 (16 x 100, 512), 52.0 / 53.5, and of experts with one row of tiles 22.9 / 23.4 (16 x 32, 1024),
-// 63.7 / 61.0, with 48 rows 34.3 / 32.2 at K = 2048.
+// Whether a store over K has so few 64 x 64 tiles that CfgU may take it: not more than three quarters of the CUs, so that uneven loads find room
+// beside them, and no second round of them with loads one deviation above the mean either.  More CUs read the weights at once, which is worth most
+// where they come from memory; many tiles lose it to reading their operands twice as often.  us, of both expert GEMMs, the first the same,
+// second in CfgT / CfgU, mean of 2021 launches, weights in the caches (and not): 0-63 tiles, K 1024-1999 0.6 less (0.9), 2000-3499 1.2 (2.4),
+// 5000+ 3.8 (8.7); 128-191 tiles 0.3 (1.5), 1.0 (3.3), 3.8 (10.0); 192-255 0.3 more (1.5 less, up to 4.3 more), 0.2 less (3.0, up to 6.9 more);
+// 256-319 2.9 more (1.8 more), 2.9 more (0.3 more); below K = 1024 0.2 (0.3).
 static bool few_tiles(const GemmArgs& a, int cus) {
+    const TileCost& c = TILE_COSTS[4];
     long long whole, tail;
-    count_tiles(TILE_COSTS[4], a, &whole, &tail);
-    const int E = launch_experts(a);
-    if (a.mean_rows % 64 == 0 && (E <= 4 || (E <= 8 && a.K >= 4096))) tail = 0;      // (a row more costs few experts little)
-    const long long n = whole + tail;
-    if (a.K >= 1024 && n <= cus / 2 && n * 1024 <= (long long)a.K * (cus / 4)) return true;
-    return n <= cus && a.mean_rows < 56 && a.K >= (a.mean_rows > 32 ? 2048 : 4096);
+    count_tiles(c, a, &whole, &tail);
+    const double above = a.mean_rows + sqrt((double)a.mean_rows);
+    const int rows = above < a.Cp ? (int)above : a.Cp;
+    const long long most = (long long)((rows + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn) * launch_experts(a);
+    return a.K >= 1024 && whole + tail <= cus * 3 / 4 && most <= cus;
 }
 // (one: a single tile's, not the launch's)
 static double tile_time(const TileCost& c, int lay, int epi, const GemmArgs& a, int cus, bool one = false) {

@@ -161,10 +161,11 @@ def test_workspace_with_grouped_weight_gradients_and_fused_combine(oracle):
 
 
 @pytest.mark.parametrize("E,rows,M,H,small", [
-    (16, 16, 256, 1024, True), (16, 100, 256, 1024, False), (16, 100, 256, 2048, True),      # 64 and 128 tiles of 64 x 64
-    (8, 192, 512, 2048, False), (8, 192, 512, 4096, False), (16, 100, 512, 4096, False),     # 224 and 256
-    (16, 32, 1024, 2048, False), (16, 32, 1024, 4096, True), (16, 48, 1024, 2048, True),     # 256, one row of tiles per expert
-    (4, 32, 256, 1016, False),
+    (16, 16, 256, 1024, True), (16, 100, 256, 1024, True), (4, 32, 256, 1016, False),          # 64, 128 and 16 tiles of 64 x 64
+    (4, 99, 1472, 2208, True), (8, 178, 512, 2048, True), (3, 100, 2048, 2048, True),         # 184, 192, 192
+    (8, 192, 512, 2048, False), (16, 100, 512, 4096, False), (16, 32, 1024, 2048, False),     # 224, 256, 256
+    (3, 64, 4096, 1024, False), (12, 252, 192, 1024, True), (20, 250, 128, 1024, True),       # 288, 144, 160 (200 with more rows)
+    (15, 253, 192, 1024, True), (60, 60, 192, 1024, False),                                   # 180 (225), 180 (360)
 ])
 def test_second_gemm_in_64_x_64_tiles_only_where_there_are_few(E, rows, M, H, small):
     cfg = B.make_config(E * rows, M, H, E, 1, 1.25, 1, B.MOE_BF16, 0)
