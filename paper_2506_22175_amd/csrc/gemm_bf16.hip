@@ -1489,7 +1489,36 @@ static moe_status check_args(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a
 // together; 8192 tokens, 768/3072, 64 experts (18 rounds of weight gradients, 3 of the input gradient) 1.35 and 1.33 ms.
 // Below: 16 384 tokens, 1024/4096, 8 experts, four partitions (0.6 + 4 rounds; 108 + 97 + 94 us one by one) 3.03 and 2.85
 // ms, 16 unevenly loaded experts 2.94 and 2.72, 4096 tokens, 512/2048 435 and 397 us.
+// (Tiles of full experts, since the host does not know the loads and a launch has to have room for them: what the capacity adds
+// are workgroups without a tile at the launch's end.  Ten shapes at capacity factors of 1.25 to 8: what a launch below the line takes varies by 1 %.)
 constexpr int BACKWARD_ROUNDS = 24;
+
+// Whether they are the faster ones below that: apart, each ends in a round that leaves CUs idle and together only the last one does, but
+// a workgroup of the launch for all has one tile and begins it with nothing requested yet, where a persistent one fetches its next
+// tile under the last one's epilogue: 1.5 us a tile of 256 x 256 rows and columns (those of 128 x 128 have a second workgroup
+// beside them).  Fitted to 1326 backwards, even and uneven loads: 11 are more than 2 % slower together than apart (5 %), without this 93 (9 %).
+// us, apart / together: 64 experts x 64 rows, 768/3072 (9 + 9 rounds of weight gradients, 1.5) 430 / 442, 24 x 457, 2048/4096
+// (12 + 12, 3) 1216 / 1279, 8 x 1024, 1024/4096 (2 + 2, 0.6) 417 / 368; both weight gradients alone, 16 x 500, 2048/5120 (10 + 10) 977 / 1001.
+static bool together_pays(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, const GateDlArgs* gate, int epi, int cw, int cd) {
+    if (cw == 2) return true;
+    const int cus = compute_units();
+    const TileCost& c = TILE_COSTS[cw];
+    // (apart, the gate's dL has a launch of its own: 8192 tokens, 64 experts 12 us and the gap before the next one, as a step measures it 18)
+    double busy = 0.0, apart = gate ? 6.0 + 0.2 * w2.E : 0.0;
+    for (const GemmArgs* w : {&w2, &w1}) {
+        const long long n = (long long)((w->Mo + c.bm - 1) / c.bm) * ((w->N + c.bn - 1) / c.bn) * w->E;
+        busy += n * (tile_time(c, GEMM_TN, epi, *w, cus, true) + 1.5);
+        apart += tile_time(c, GEMM_TN, epi, *w, cus);
+    }
+    if (dgrad) {
+        long long whole, tail;
+        count_tiles(TILE_COSTS[cd], *dgrad, &whole, &tail);
+        busy += (whole + tail) * (tile_time(TILE_COSTS[cd], GEMM_NT, EPI_STORE, *dgrad, cus, true) + 1.5);
+        apart += tile_time(TILE_COSTS[cd], GEMM_NT, EPI_STORE, *dgrad, cus);
+    }
+    // (the two alone, without an input gradient to fill their rounds, have to promise more)
+    return busy / cus < (dgrad ? 1.04 : 0.85) * apart;
+}
 
 template <int EPI, typename CN, typename CT>
 static moe_status launch_backward(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, bool w_first,
@@ -1537,6 +1566,7 @@ static moe_status backward_cfg(const GemmArgs* dgrad, const GemmArgs& w2, const 
     // (the shapes are those of the launches by themselves; shapes with one workgroup per CU and with two do not mix)
     const int cw = tile_choice(GEMM_TN, EPI, w2), cd = dgrad ? tile_choice(GEMM_NT, EPI_STORE, *dgrad) : cw;
     if (cw == 1 || tile_choice(GEMM_TN, EPI, w1) != cw || w2.free_cus > 0) return MOE_OK;
+    if (!together_pays(dgrad, w2, w1, gate, EPI, cw, cd)) return MOE_OK;
     const bool w_first = dgrad && tile_time(TILE_COSTS[cw], GEMM_TN, EPI, w2, compute_units(), true) >
                                       tile_time(TILE_COSTS[cd], GEMM_NT, EPI_STORE, *dgrad, compute_units(), true);
     if (cw == 2) {
