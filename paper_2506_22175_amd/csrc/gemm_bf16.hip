@@ -1,10 +1,13 @@
 // bf16 grouped GEMM on the CDNA4 matrix cores for the expert FFN: the two linear
 // layers of every local expert (Section II-B2) and their four backward GEMMs
 // (Table II counts 2 forward and 4 backward GEMM units per partition, 5 with
-// recomputation).  Float accumulation in v_mfma_f32_32x32x16_bf16.
+// recomputation).  Float accumulation in v_mfma_f32_16x16x32_bf16: the main loops run
+// at the chip's power limit, and of the two shapes of the instruction this one takes less
+// power (all CUs, operands from registers, normally distributed: 1.95 PFLOP/s at 1.95 GHz,
+// 32x32x16 1.67 at 1.67 GHz).
 //
 // One workgroup computes a BM x BN tile of one expert with WAVES_M x WAVES_N
-// wavefronts, each owning (BM/WAVES_M) x (BN/WAVES_N) as 32x32 MFMA tiles.
+// wavefronts, each owning (BM/WAVES_M) x (BN/WAVES_N) as 16x16 MFMA tiles.
 //
 // Operand tiles (64 K-elements deep) travel global -> LDS with
 // buffer_load_dwordx4 ... lds: no staging registers, no LDS-write instructions,
@@ -16,13 +19,13 @@
 //     NT) is kept as [row][64 k] with a 16-byte-chunk XOR swizzle and read with
 //     ds_read_b128 - conflict-free both ways;
 //   * an operand stored [k][n] with n contiguous ("NC": B of NN, both of TN) is
-//     kept as it is, rows rotated by 64 bytes per k mod 4, and read with
+//     kept as it is, with a 16-byte-unit XOR that depends on k, and read with
 //     ds_read_b64_tr_b16, which hands each lane four consecutive k of one n.
 // LDS is a ring of NS stages of BK K-elements each; the loads of the next NS-1
 // tiles are in flight while one tile is multiplied (a CU draws about 64 KB per
 // microsecond at speed and a miss in L2 takes longer than one tile's arithmetic,
 // so the depth of the ring, not the hit rate, decides whether the matrix pipe
-// waits).  One s_barrier per tile.
+// waits).  One or two s_barriers per 64 k.
 #include "common.h"
 #include "epilogue.h"
 #include "gate_bwd.h"
@@ -31,9 +34,11 @@
 namespace moe {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4s lds_v4s;
+typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
 
 constexpr unsigned OOB_OFFSET = 0x80000000u;
 constexpr int DW_COLS = 128;         // columns per partial sum of GeLU-backward's row dots (an even number of blocks per row)
@@ -61,6 +66,19 @@ __device__ __forceinline__ void load_to_lds(v4i rsrc, unsigned lds_off, unsigned
                  "buffer_load_dwordx4 %1, %2, 0 offen lds"
                  : : "s"(lds_off), "v"(voff), "s"(rsrc) : "memory");
 }
+// The same in two parts for the main loops, with a matrix instruction between them (m0 has to be written one wait state
+// before the load), and with the step along K as the load's scalar offset, which is no part of its bounds check.
+template <int ADD>
+__device__ __forceinline__ void lds_destination(unsigned lds_off) {
+    asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_off), "n"(ADD) : "memory", "scc");
+}
+__device__ __forceinline__ void lds_next_destination() { asm volatile("s_add_u32 m0, m0, 0x400" : : : "memory", "scc"); }
+__device__ __forceinline__ void load_to_destination(v4i rsrc, unsigned voff, unsigned soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" : : "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+// an address in a vector register moved by a wave-uniform step, here and now
+__device__ __forceinline__ void move_address(unsigned& at, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(by)); }
+__device__ __forceinline__ void flip_address(unsigned& at, unsigned bits) { asm volatile("v_xor_b32 %0, %1, %0" : "+v"(at) : "s"(bits)); }
 __device__ __forceinline__ unsigned lds_address(const char* p) {
     return (unsigned)(unsigned long long)(__attribute__((address_space(3))) const char*)p;
 }
@@ -68,8 +86,8 @@ __device__ __forceinline__ unsigned lds_address(const char* p) {
 // ---- tile shape ------------------------------------------------------------------
 // Four main loops, all hand-scheduled:
 //   LOOP_PIPE32 ring of 32-k stages for both operands;
-//   LOOP_W64    64-k steps with one ring per operand: a K-contiguous operand travels as whole
-//               128-byte lines (units of 64 k), the other one in tiles of 32 k.
+//   LOOP_W64    NN: 64-k steps with one ring per operand: the rows travel as whole 128-byte lines (units of
+//               64 k), the weights in tiles of 32 k.
 //   LOOP_R64    64-k steps with one ring for both operands (tiles small enough for three or more stages of 64 k);
 //   LOOP_N64    256 x 256 of two K-contiguous operands: both travel as whole lines in units of 64 k, of which five fit;
 //               the weights of a whole step are held in registers, so that their unit is free half a step early.
@@ -78,10 +96,16 @@ template <int BM_, int BN_, int BK_, int NS_, int WAVES_M_, int WAVES_N_, int OC
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
     static constexpr int OCC = OCC_, LOOP = LOOP_;
+    // Matrix instruction 32 x 32 x 16 (256 x 256: 16 x 16 x 32; two of the former add up the same products in the same order as
+    // one of the latter, bit for bit in every case measured).  Smaller tiles keep it: their launches do not run at the power
+    // limit, and half as many matrix instructions each hide twice as many others.  (With 16 x 16: 128 x 128 weight gradients
+    // 1040 cycles a step of 32 k against 880, 64 x 128 with GeLU 1000 against 940; 9096 tokens, 160/480, n = 4: 168 us against 156.)
+    static constexpr bool S32 = BM_ * BN_ < 256 * 256;
     static constexpr int WAVES = WAVES_M * WAVES_N;
     static constexpr int THREADS = 64 * WAVES;
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    static constexpr int TM = WM / 32, TN = WN / 32;
+    static constexpr int TM = WM / 32;                   // blocks of 32 rows of a wave: of epilogue passes, and of `active` rows
+    static constexpr int RB = WM / 16, NB = WN / 16;     // its blocks of 16 rows and of 16 columns
     static constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
     static constexpr int LDS_BYTES = LOOP == LOOP_W64 || LOOP == LOOP_N64 ? 160 * 1024 : NS * STAGE_BYTES;
     static constexpr bool PIPE = LOOP == LOOP_PIPE32;
@@ -100,11 +124,14 @@ struct TileCfg {
 
 // ---- K-contiguous operand tile: R rows x BK k ---------------------------------------
 // A row is CPR = BK/8 chunks of 16 bytes.  LDS byte of (row, chunk c) =
-// row*ROWB + ((c ^ sw(row)) << 4), with sw chosen so that the 16 rows one
-// ds_read_b128 quarter-wave touches fall into 16 different 16-byte bank groups
-// (64 banks of 4 bytes).  One wave instruction fills 1024 bytes = RPI rows:
-// lane l -> row RPI*q + l/CPR, physical chunk l%CPR.
-template <int R, int WAVES, int BK>
+// row*ROWB + ((c ^ sw(row)) << 4).  A ds_read_b128 serves the lanes 0-3, 12-15, 20-27 of a half
+// wave together, then the other sixteen; of a fragment (16 rows, two chunks per half wave) those are
+// the rows 0-3 and 12-15 of one chunk and 4-11 of the next one, and sw puts them into 16 different
+// 16-byte bank groups (64 banks of 4 bytes).  (With a swizzle that does so for 16 lanes in
+// succession only, 40 % of the LDS cycles of an NT launch were conflicts; S32: a fragment is 32 rows of one chunk per half wave, and
+// sixteen lanes in succession it is.)  One wave instruction
+// fills 1024 bytes = RPI rows: lane l -> row RPI*q + l/CPR, physical chunk l%CPR.
+template <int R, int WAVES, int BK, bool S32>
 struct KCTile {
     static constexpr int ROWB = BK * 2;
     static constexpr int CPR = BK / 8;
@@ -113,15 +140,16 @@ struct KCTile {
     static constexpr int BYTES = R * ROWB;
     static_assert(R % (RPI * WAVES) == 0 && NI >= 1, "rows must divide over the wavefronts");
     static __device__ __forceinline__ int sw(int row) {
-        return CPR == 8 ? ((row ^ (row >> 3)) & 7) : ((row >> 2) & 3);
+        if (S32) return CPR == 8 ? (row ^ (row >> 3)) & 7 : (row >> 2) & 3;
+        return CPR == 8 ? (row >> 1) & 7 : ((row >> 2) & 3) ^ ((row >> 1) & 2);
     }
     v4i rsrc;
     unsigned voff[NI];       // byte offset of this lane's chunk at k0 = 0
-    // First k of this lane's chunk in load j: kc0 ^ 8*j for rows of eight chunks (loads of consecutive j lie eight
-    // rows apart, which the swizzle turns into the chunk number), the same for every j for rows of four.
+    // First k of this lane's chunk in load j (loads of consecutive j lie eight rows of eight chunks apart, which the swizzle turns
+    // into one bit of the chunk number; S32: into the number).
     int kc0;
     static_assert((NI & (NI - 1)) == 0, "wid*NI + j is wid*NI ^ j");
-    __device__ __forceinline__ int first_k(int j) const { return CPR == 8 ? kc0 ^ (8 * j) : kc0; }
+    __device__ __forceinline__ int first_k(int j) const { return CPR == 8 ? kc0 ^ (S32 ? 8 * j : 32 * (j & 1)) : kc0; }
     __device__ __forceinline__ void init_kc(int lane, int wid) {
         kc0 = ((lane % CPR) ^ sw(wid * NI * RPI + lane / CPR)) * 8;
     }
@@ -157,19 +185,26 @@ struct KCTile {
             voff[j] = src >= 0 ? (unsigned)(src * ld + c * 8) * 2u : OOB_OFFSET;
         }
     }
+    // Loads of the tile at k0: voff[j] + koff(k0) to dst(tile) + 1024 * j.  Before the first of them end_at switches off the
+    // lanes that lie beyond K, for this tile and all later ones (tiles are requested in ascending order).
+    __device__ __forceinline__ unsigned koff(int k0) const { return (unsigned)k0 * 2u; }
+    __device__ __forceinline__ void end_at(int k0) {
+        if (k0 + BK > K) {                               // wave-uniform, and true of the last tiles only
+            asm volatile("" ::: "memory");               // (a branch, not eight selections)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) voff[j] = (k0 + first_k(j) < K) ? voff[j] : OOB_OFFSET;
+        }
+    }
+    static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
+    // S32: a load at once, its lanes switched off as it goes
     __device__ __forceinline__ void load_one(char* tile, int k0, int wid, int j) const {
-        const int q = wid * NI + j;
         unsigned off = voff[j] + (unsigned)k0 * 2u;
         // only a tile that reaches beyond K (a wave-uniform condition) has lanes to switch off
         if (k0 + BK > K) off = (k0 + first_k(j) < K) ? off : OOB_OFFSET;
-        load_to_lds(rsrc, lds_address(tile) + q * 1024, off);
+        load_to_lds(rsrc, lds_address(tile) + (wid * NI + j) * 1024, off);
     }
-    __device__ __forceinline__ void load(char* tile, int k0, int wid) const {
-#pragma unroll
-        for (int j = 0; j < NI; ++j) load_one(tile, k0, wid, j);
-    }
-    // fragment of the 32 rows starting at rb: lane reads row rb + lane%32, k = 16*kk + 8*(lane/32) .. +7
-    struct Frag {
+    // S32: fragment of the 32 rows starting at rb: lane reads row rb + lane%32, k = 16*kk + 8*(lane/32) .. +7
+    struct Frag32 {
         int addr;    // byte address inside the tile for kk = 0
         __device__ __forceinline__ void init(int rb, int lane) {
             const int row = rb + (lane & 31);
@@ -179,13 +214,34 @@ struct KCTile {
             return *reinterpret_cast<const bf16x8*>(tile + (addr ^ (kk << 5)));
         }
     };
+    // fragments of 16 rows x 32 k: of the rows rb + d .. rb + d + 15 a lane reads row lane%16, k = 32*kk + 8*(lane/16) .. +7.
+    // rb and d are multiples of 16, which the swizzle does not see.
+    // at: LDS addresses, one for each kk; fragments are constant offsets from them.
+    template <int BLOCKS> struct Frag {
+        static constexpr int READS = 1;                  // LDS reads per fragment; `part` is the number of one of them
+        unsigned at[CPR / 4];
+        template <typename D> __device__ __forceinline__ void init(unsigned tile, int rb, int lane, D&&) {
+            const int row = rb + (lane & 15);
+#pragma unroll
+            for (int kk = 0; kk < CPR / 4; ++kk) at[kk] = tile + row * ROWB + (((4 * kk + (lane >> 4)) ^ sw(row)) << 4);
+        }
+        struct Value {
+            bf16x8 v;
+            __device__ __forceinline__ bf16x8 all() const { return v; }
+        };
+        // fragment i, of the rows from rb + d on, in the tile `off` bytes behind the one that init was told
+        __device__ __forceinline__ void read(Value& f, int, int d, int kk, int, unsigned off) const {
+            f.v = *(lds_bf16x8*)(uintptr_t)(at[kk] + off + d * ROWB);
+        }
+    };
 };
 
 // ---- N-contiguous operand tile: BK k rows x R n --------------------------------------
-// LDS byte of (k, 16-byte unit u) = k*PITCH + (((u + 4*(k&3)) % UPR) << 4): the four k rows
-// that one transposing read touches fall into different banks (64 banks of 4 bytes).
-// One wave instruction fills 1024 bytes = RPI rows: lane l -> row RPI*q + l/UPR, unit l%UPR.
-template <int R, int WAVES, int BK>
+// LDS byte of (k, 16-byte unit u) = k*PITCH + ((u ^ turn(k)) << 4): the eight k rows (k, k+1, k+2, k+3 and those
+// eight further on) of which half a wave's transposing read takes two units each fall into different banks (64 banks
+// of 4 bytes).  (S32: four k rows and four units each, ((u + 4*(k&3)) % UPR) << 4.)  One wave instruction fills 1024 bytes = RPI
+// rows: lane l -> row RPI*q + l/UPR, unit l%UPR.
+template <int R, int WAVES, int BK, bool S32>
 struct NCTile {
     static constexpr int PITCH = R * 2;                // bytes per k row
     static constexpr int UPR = R / 8;                  // 16-byte units per row
@@ -193,10 +249,14 @@ struct NCTile {
     static constexpr int NI = BK / RPI / WAVES;
     static constexpr int BYTES = BK * PITCH;
     static_assert(BK % (RPI * WAVES) == 0 && NI >= 1, "rows must divide over the wavefronts");
-    static_assert(UPR >= 16 || UPR == 8, "four k rows rotated by four units each must fit a row of units (or two rows)");
+    static_assert(UPR >= 16 || UPR == 8, "the turns of eight k rows must fit a row of units (or two rows)");
+    static __device__ __forceinline__ int turn(int k) {
+        return (UPR >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1)) + 2 * ((k >> 3) & 1);
+    }
     v4i rsrc;
     unsigned voff[NI];
     unsigned kstep;          // bytes per k row in memory
+    int K, row0;             // k rows; this lane's row in load 0
     // descriptor of rows [0, K) x columns [0, n_valid) of the matrix at P
     static __device__ __forceinline__ v4i rsrc_of(const bf16_t* P, int ld, int n_valid, int K) {
         return make_rsrc(P, K > 0 ? (unsigned)(((size_t)(K - 1) * ld + n_valid) * 2) : 0u);
@@ -205,27 +265,33 @@ struct NCTile {
     __device__ __forceinline__ void init(const bf16_t* P, int ld, int n0, int n_limit, int K, int lane, int wid) {
         const int n_valid = n_limit - n0;
         kstep = (unsigned)ld * 2u;
+        this->K = K;
+        row0 = wid * NI * RPI + lane / UPR;
         rsrc = rsrc_of(P + n0, ld, n_valid, K);
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int q = wid * NI + j;
             const int row = q * RPI + lane / UPR;
-            const int u = ((lane % UPR) - 4 * (row & 3) + 4 * UPR) % UPR;
+            const int u = S32 ? ((lane % UPR) - 4 * (row & 3) + 4 * UPR) % UPR : (lane % UPR) ^ turn(row);
             voff[j] = (u * 8 < n_valid) ? (unsigned)(row * ld + u * 8) * 2u : OOB_OFFSET;
         }
     }
-    __device__ __forceinline__ void load_one(char* tile, int k0, int wid, int j) const {
-        const int q = wid * NI + j;
-        load_to_lds(rsrc, lds_address(tile) + q * 1024, voff[j] + (unsigned)k0 * kstep);
-    }
-    __device__ __forceinline__ void load(char* tile, int k0, int wid) const {
+    __device__ __forceinline__ unsigned koff(int k0) const { return (unsigned)k0 * kstep; }
+    __device__ __forceinline__ void end_at(int k0) {
+        if (k0 + BK > K) {
+            asm volatile("" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < NI; ++j) load_one(tile, k0, wid, j);
+            for (int j = 0; j < NI; ++j) voff[j] = (k0 + row0 + j * RPI < K) ? voff[j] : OOB_OFFSET;
+        }
     }
-    // fragment of the 32 columns starting at nb: two transposing reads give the lane
-    // n = nb + lane%32, k = 16*kk + 8*(lane/32) .. +7.  In a 16-lane group lane a points at
-    // row a/4, columns 4*(a%4)..+3; the hardware returns to lane i four k of column i.
-    struct Frag {
+    static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
+    // S32: a load at once (the descriptor ends at the last row)
+    __device__ __forceinline__ void load_one(char* tile, int k0, int wid, int j) const {
+        load_to_lds(rsrc, lds_address(tile) + (wid * NI + j) * 1024, voff[j] + (unsigned)k0 * kstep);
+    }
+    // S32: fragment of the 32 columns starting at nb: two transposing reads give the lane n = nb + lane%32, k = 16*kk +
+    // 8*(lane/32) .. +7, as below.
+    struct Frag32 {
         int addr;
         __device__ __forceinline__ void init(int nb, int lane) {
             const int g = lane >> 4, a = lane & 15;
@@ -235,19 +301,46 @@ struct NCTile {
         }
         __device__ __forceinline__ bf16x8 read(const char* tile, int kk) const {
             const char* p = tile + addr + kk * 16 * PITCH;
-            v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
-            v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * PITCH));
+            const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+            const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * PITCH));
             typedef short v8s __attribute__((ext_vector_type(8)));
-            v8s both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            const v8s both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             return __builtin_bit_cast(bf16x8, both);
+        }
+    };
+    // fragments of 16 columns x 32 k: two transposing reads give the lane column nb + d + lane%16, k = 32*kk +
+    // 8*(lane/16) .. +7.  In a 16-lane group lane a points at row a/4, columns 4*(a%4)..+3; the hardware returns to
+    // lane i four k of column i.  nb and d have no bits in common, so that d turns into an exclusive or: an address each.
+    template <int BLOCKS> struct Frag {
+        static constexpr int READS = 2;
+        unsigned at[BLOCKS];
+        template <typename D> __device__ __forceinline__ void init(unsigned tile, int nb, int lane, D&& d) {
+            const int g = lane >> 4, a = lane & 15;
+            const int k_in = 8 * g + (a >> 2);
+            const int n = nb + 4 * (a & 3);
+#pragma unroll
+            for (int i = 0; i < BLOCKS; ++i) at[i] = tile + ((k_in * PITCH + (((n >> 3) ^ turn(k_in)) << 4) + ((n & 7) << 1)) ^ (d(i) << 1));
+        }
+        struct Value {
+            v4s lo, hi;
+            __device__ __forceinline__ bf16x8 all() const {
+                typedef short v8s __attribute__((ext_vector_type(8)));
+                const v8s both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                return __builtin_bit_cast(bf16x8, both);
+            }
+        };
+        __device__ __forceinline__ void read(Value& f, int i, int, int kk, int part, unsigned off) const {
+            const unsigned p = at[i] + off + kk * 32 * PITCH;
+            if (part == 0) f.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)p);
+            else f.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)(p + 4 * PITCH));
         }
     };
 };
 
-template <int LAY, int R, int W, int BK> struct ATile { typedef KCTile<R, W, BK> type; };
-template <int R, int W, int BK> struct ATile<GEMM_TN, R, W, BK> { typedef NCTile<R, W, BK> type; };
-template <int LAY, int R, int W, int BK> struct BTile { typedef NCTile<R, W, BK> type; };
-template <int R, int W, int BK> struct BTile<GEMM_NT, R, W, BK> { typedef KCTile<R, W, BK> type; };
+template <int LAY, int R, int W, int BK, bool S> struct ATile { typedef KCTile<R, W, BK, S> type; };
+template <int R, int W, int BK, bool S> struct ATile<GEMM_TN, R, W, BK, S> { typedef NCTile<R, W, BK, S> type; };
+template <int LAY, int R, int W, int BK, bool S> struct BTile { typedef NCTile<R, W, BK, S> type; };
+template <int R, int W, int BK, bool S> struct BTile<GEMM_NT, R, W, BK, S> { typedef KCTile<R, W, BK, S> type; };
 
 struct Unit8 {
     static __device__ __forceinline__ void to_float(const uint4& u, float* o) {
@@ -268,26 +361,68 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("" ::: "memory");
 }
 
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() { asm volatile("s_waitcnt lgkmcnt(%0)" : : "i"(N) : "memory"); }
+
+// What goes behind which of the MB matrix instructions of a block.  A matrix instruction takes sixteen cycles; one other instruction
+// of its wave behind it is free, or a vector and a scalar one, each further one costs eight cycles (one wave per SIMD; measured
+// for independent vector, scalar and LDS instructions alike).  Hence: no address arithmetic in the loops but what moves from slot to
+// slot, and everything in a gap of its own.  LDS reads, of which the four waves' together take 32 cycles (16 for the transposing
+// ones), come behind the first eight, early enough for the next block, then two loads, in two parts, and moves of addresses between.
+template <int MB>
+struct Gaps {
+    static constexpr int SPAN = MB >= 12 ? 8 : MB;
+    template <typename F>
+    static __device__ __forceinline__ void reads(int m, int n, F&& read) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (r < n && r * SPAN / n == m) read(r);
+    }
+    // two loads: prepare(l) is followed by go(l) one gap later, or in the same one where there are few
+    template <typename P, typename G>
+    static __device__ __forceinline__ void loads(int m, P&& prepare, G&& go) {
+#pragma unroll
+        for (int l = 0; l < 2; ++l) {
+            const int at = MB >= 8 ? MB * (9 + 4 * l) / 16 : MB - 2 + l;
+            if (m == at) prepare(l);
+            if constexpr (MB < 8) { if (m == at) { asm volatile("s_nop 0" ::: "memory"); go(l); } }
+            else if (m == at + 1) go(l);
+        }
+    }
+    // four moves: between the reads where those leave room (`odd`), else around the loads
+    template <typename F>
+    static __device__ __forceinline__ void moves(int m, bool odd, F&& move) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int at = MB < 12 ? e * MB / 4 : odd ? 2 * e + 1 : (e == 0 ? 8 : e == 1 ? 11 : e == 2 ? 12 : 15) * MB / 16;
+            if (m == at) move(e);
+        }
+    }
+};
+
 // The matrix instruction as volatile assembly with a memory clobber: the compiler keeps
 // such statements, the LDS reads and the loads into LDS in the order they are written,
 // which is what the hand-scheduled loop below relies on (it still allocates registers
 // and inserts the s_waitcnt lgkmcnt for LDS reads it issued itself).
+// Accumulators live in the AGPR half of the register file when a wave owns 512 registers, in ordinary VGPRs when two waves
+// share a SIMD.
+__device__ __forceinline__ void mfma_pinned(floatx4& acc, const bf16x8& a, const bf16x8& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b) : "memory");
+}
 template <bool ACC_IN_AGPR>
-__device__ __forceinline__ void mfma_pinned(floatx16& acc, const bf16x8& a, const bf16x8& b) {
-    // accumulators live in the AGPR half of the register file when a wave owns 512 registers,
-    // in ordinary VGPRs when two waves share a SIMD
+__device__ __forceinline__ void mfma32_pinned(floatx16& acc, const bf16x8& a, const bf16x8& b) {
     if constexpr (ACC_IN_AGPR)
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b) : "memory");
     else
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b) : "memory");
 }
 
-// TN only: the reduction dimension may run over the rows of several partitions (up to MAX_KSEGS row
-// ranges, one per partition buffer); tiles of 32 k never straddle two ranges.  KCursor says which range
-// the tile that is being requested lies in and where.
+// Which tile of both operands is being requested: its first k, among the K of its row range, and its byte offsets in the
+// operands.  TN only: the reduction dimension may run over the rows of several partitions (up to MAX_KSEGS row ranges, one per
+// partition buffer); tiles of 32 k never straddle two ranges, and seg says which range it is.
 constexpr int MAX_KSEGS = 8;
 struct TileCoord { int e, q, er, tn, m0, n0, Mdim, Kdim, KT; };      // expert, partition of the launch, their place in row arrays
-struct KCursor { int seg, jl, tiles; };
+struct KCursor { int seg, k0, K; unsigned ka, kb; };       // (S32: k0 and K in tiles, the offsets unused)
 
 // Numbers of the tiles of a launch.  Only tiles that exist are numbered: an expert with fewer rows than the capacity
 // has fewer tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups, which take
@@ -344,17 +479,18 @@ __device__ __forceinline__ TileNumbers number_tiles(const GemmArgs& g, int tiles
 template <int LAY, int EPI, typename C, bool ONE>
 __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int tiles_n, const TileNumbers& tiles, int b0, int step) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, TNN = C::TN;
+    constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, RB = C::RB, NB = C::NB;
     constexpr int STAGE = C::STAGE_BYTES, BK = C::BK, NS = C::NS;
+    constexpr bool S32 = C::S32;
+    constexpr int TNN = WN / 32;
     constexpr bool W64 = C::LOOP == LOOP_W64, R64 = C::LOOP == LOOP_R64, N64 = C::LOOP == LOOP_N64;
     static_assert(!N64 || LAY == GEMM_NT, "units of 64 k of both operands");
     constexpr bool ALT = C::LOOP != LOOP_PIPE32;     // waves' row blocks alternate (see block_row)
-    // Depth of one load unit of each operand.  In the two-ring loop a K-contiguous row operand (A of
-    // NN) or the K-contiguous weights (B of NT) travel 64 k at a time, so that every request is a whole
-    // 128-byte line; the other operand keeps tiles of 32 k.
-    constexpr bool A_WIDE = W64 && LAY == GEMM_NN;
-    constexpr int AK = W64 ? (A_WIDE ? 64 : 32) : BK, BKB = W64 ? (A_WIDE ? 32 : 64) : BK;
-    static_assert(!W64 || LAY != GEMM_TN, "both operands of the weight-gradient GEMM are N-contiguous: five stages of 32 k serve them");
+    constexpr bool QUAD = C::LOOP == LOOP_PIPE32 && C::OCC == 1;
+    // Depth of one load unit of each operand.  In the two-ring loop the rows travel 64 k at a time, so that every request
+    // is a whole 128-byte line; the weights, whose rows are whole lines anyway, keep tiles of 32 k.
+    constexpr int AK = BK, BKB = W64 ? 32 : BK;
+    static_assert(!W64 || LAY == GEMM_NN, "one K-contiguous operand");
     constexpr int A_BYTES = BM * BK * 2;
     // The epilogue stages accumulators in the first SB stages of the ring; a tile's ring
     // starts at stage SB, so that its first operand tiles can arrive during the epilogue
@@ -369,23 +505,60 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wid / C::WAVES_N, wn = wid % C::WAVES_N;
-    typedef typename ATile<LAY, BM, C::WAVES, AK>::type AT;
-    typedef typename BTile<LAY, BN, C::WAVES, BKB>::type BT;
+    typedef typename ATile<LAY, BM, C::WAVES, AK, C::S32>::type AT;
+    typedef typename BTile<LAY, BN, C::WAVES, BKB, C::S32>::type BT;
     constexpr int LPW = AT::NI + BT::NI;         // loads per wave per tile
     // Where two workgroups share a CU the operands' offsets and descriptors are formed again at the top of a
     // tile (the other workgroup covers that) instead of being carried from the one before: with 128 registers
     // for accumulators and fragments the compiler otherwise moves descriptors into vector registers, which the
     // load cannot take.
     constexpr bool REBIND = C::OCC == 2 && !ONE;
-    typename AT::Frag fa[TM];
-    typename BT::Frag fb[TNN];
     // First row of the wave's block i of 32 rows.  In the 64-k loops the waves' blocks alternate, so that a tile
     // with few rows left needs only the first blocks of every wave (see `active` below).
-    auto block_row = [&](int i) __attribute__((always_inline)) { return ALT ? (i * C::WAVES_M + wm) * 32 : wm * WM + i * 32; };
+    constexpr int ROW_STEP = ALT ? 32 * C::WAVES_M : 32;
+    auto block_row = [&](int i) __attribute__((always_inline)) { return ALT ? i * ROW_STEP + wm * 32 : wm * WM + i * 32; };
+    typename AT::template Frag<RB> fa;
+    typename BT::template Frag<NB> fb;
+    auto dist_a = [](int i) __attribute__((always_inline)) { return (i >> 1) * ROW_STEP + (i & 1) * 16; };     // of a block of 16 rows from the first
+    auto dist_b = [](int j) __attribute__((always_inline)) { return j * 16; };
+    const unsigned lds0 = lds_address(smem);
+    // addresses in the operands' tiles that begin at these LDS addresses
+    auto frags_at = [&](unsigned a, unsigned b) __attribute__((always_inline)) {
+        int l = lane;                                    // (formed for every tile: there are no registers to keep them in through an epilogue)
+        if constexpr (QUAD || W64 || N64) asm volatile("" : "+v"(l));
+        fa.init(a, block_row(0), l, dist_a);
+        fb.init(b, wn * WN, l, dist_b);
+        if constexpr (QUAD || W64) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[i].init(block_row(i), lane);
+            for (unsigned& at : fa.at) asm volatile("" : "+v"(at));
 #pragma unroll
-    for (int j = 0; j < TNN; ++j) fb[j].init(wn * WN + j * 32, lane);
+            for (unsigned& at : fb.at) asm volatile("" : "+v"(at));
+        }
+    };
+    typename AT::Frag32 fa32[TM];
+    typename BT::Frag32 fb32[TNN];
+    if constexpr (S32) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa32[i].init(block_row(i), lane);
+#pragma unroll
+        for (int j = 0; j < TNN; ++j) fb32[j].init(wn * WN + j * 32, lane);
+    } else if constexpr (!QUAD && !W64 && !N64) frags_at(lds0, lds0 + A_BYTES);     // (the 256 x 256 loops move theirs along)
+    // fragment of the wave's block i of 16 rows / j of 16 columns, read in one part or two
+    typedef decltype(fa) TA;
+    typedef decltype(fb) TB;
+    typedef typename TA::Value FA;
+    typedef typename TB::Value FB;
+    constexpr int AR = TA::READS, BR = TB::READS;
+    auto frag_a = [&](FA& f, unsigned off, int i, int kk, int part) __attribute__((always_inline)) { fa.read(f, i, dist_a(i), kk, part, off); };
+    auto frag_b = [&](FB& f, unsigned off, int j, int kk, int part) __attribute__((always_inline)) { fb.read(f, j, dist_b(j), kk, part, off); };
+    auto whole_a = [&](FA& f, unsigned off, int i, int kk) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < AR; ++q) frag_a(f, off, i, kk, q);
+    };
+    auto whole_b = [&](FB& f, unsigned off, int j, int kk) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < BR; ++q) frag_b(f, off, j, kk, q);
+    };
 
     // ---- tile number -> (expert, tile) -----------------------------------------------
     const int lane_tm = tiles.lane_tm, lane_end = tiles.lane_end, tail_end = tiles.tail_end;
@@ -461,115 +634,154 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         if (!gathered) ta_.init(A, g.lda, t.m0, t.Mdim, t.Kdim, lane, wid);
         tb_.init(B, g.ldb, t.n0, g.N, t.Kdim, lane, wid);
     };
-    // load l of the tile that starts at k0.  Over several row ranges (TN) the tiles are requested in
-    // ascending order, each starting with its load 0: that is where the cursor moves on, into the next
-    // range with rows where the last one is used up (its operands then get new descriptors), and past
-    // the last range, where everything reads as zeros.
+    // Tiles are requested in ascending order, over several row ranges (TN) with new descriptors where one is used up, and past
+    // the last range everything reads as zeros.
     // operand descriptors of row range seg (TN), its rows
     auto bind_range = [&](const TileCoord& tc, int seg, AT& ta_, BT& tb_) -> int {
         int rows = 0;
         if constexpr (LAY == GEMM_TN) {
             rows = seg < g.k_segs ? g.counts[seg * g.E + tc.e] : 0;
-            const bf16_t* A = (const bf16_t*)g.A + (size_t)tc.e * g.a_estride + seg * g.a_sstride + tc.m0;
-            const bf16_t* B = (const bf16_t*)g.B + (size_t)tc.e * g.b_estride + seg * g.b_sstride + tc.n0;
-            ta_.rsrc = AT::rsrc_of(A, g.lda, tc.Mdim - tc.m0, rows);
-            tb_.rsrc = BT::rsrc_of(B, g.ldb, g.N - tc.n0, rows);
+            const bf16_t* A = (const bf16_t*)g.A + (size_t)tc.e * g.a_estride + seg * g.a_sstride;
+            const bf16_t* B = (const bf16_t*)g.B + (size_t)tc.e * g.b_estride + seg * g.b_sstride;
+            if constexpr (S32) {
+                ta_.rsrc = AT::rsrc_of(A + tc.m0, g.lda, tc.Mdim - tc.m0, rows);
+                tb_.rsrc = BT::rsrc_of(B + tc.n0, g.ldb, g.N - tc.n0, rows);
+            } else {                             // (and the lanes that the end of the range before switched off)
+                ta_.init(A, g.lda, tc.m0, tc.Mdim, rows, lane, wid);
+                tb_.init(B, g.ldb, tc.n0, g.N, rows, lane, wid);
+            }
         }
         return rows;
     };
-    auto request = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
+    // The tile the cursor is at reaches beyond its K: into the next range with rows, or the lanes beyond K switched off.
+    auto enter = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        if constexpr (LAY == GEMM_TN) {
+            if (g.k_segs > 1) {
+                while (kc_.k0 >= kc_.K && kc_.seg < g.k_segs) {
+                    ++kc_.seg;
+                    kc_.k0 = 0;
+                    kc_.ka = kc_.kb = 0;
+                    kc_.K = bind_range(tc, kc_.seg, ta_, tb_);
+                }
+            }
+        }
+        if (kc_.k0 + BK > kc_.K) {
+            ta_.end_at(kc_.k0);
+            tb_.end_at(kc_.k0);
+        }
+    };
+    auto start = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        kc_ = {-1, 0, LAY == GEMM_TN && g.k_segs > 1 ? 0 : ta_.K, 0, 0};
+        if (BK > kc_.K) enter(tc, kc_, ta_, tb_);
+    };
+    // on to the next tile (before its first load; a handful of scalar instructions, in the shadow of a matrix instruction)
+    auto advance = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        kc_.k0 += BK;
+        kc_.ka += ta_.koff(BK);
+        kc_.kb += tb_.koff(BK);
+        if (kc_.k0 + BK > kc_.K) enter(tc, kc_, ta_, tb_);
+    };
+    // The byte offsets into scalar registers, where the compiler does not keep them: a load may follow five wait states later.
+    auto settle = [&](KCursor& kc_) __attribute__((always_inline)) {
+        kc_.ka = __builtin_amdgcn_readfirstlane(kc_.ka);
+        kc_.kb = __builtin_amdgcn_readfirstlane(kc_.kb);
+        asm volatile("" : "+s"(kc_.ka), "+s"(kc_.kb) : : "memory");
+    };
+    // its load l, to the LDS address in m0
+    auto go = [&](const KCursor& kc_, const AT& ta_, const BT& tb_, int l) __attribute__((always_inline)) {
+        if (l < AT::NI) load_to_destination(ta_.rsrc, ta_.voff[l], kc_.ka);
+        else load_to_destination(tb_.rsrc, tb_.voff[l - AT::NI], kc_.kb);
+    };
+    // S32: load l of the tile that starts at k0; the cursor moves on with load 0
+    auto request32 = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
         if constexpr (LAY == GEMM_TN) {
             if (g.k_segs > 1) {
                 if (l == 0) {
-                    if (k0 == 0) { kc_.seg = -1; kc_.jl = 0; kc_.tiles = 0; } else ++kc_.jl;
-                    while (kc_.jl >= kc_.tiles) {
+                    if (k0 == 0) { kc_.seg = -1; kc_.k0 = 0; kc_.K = 0; } else ++kc_.k0;
+                    while (kc_.k0 >= kc_.K) {
                         ++kc_.seg;
-                        kc_.jl = 0;
+                        kc_.k0 = 0;
                         const int rows = bind_range(tc, kc_.seg, ta_, tb_);
-                        kc_.tiles = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
+                        kc_.K = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
                     }
                 }
-                k0 = kc_.jl * BK;
+                k0 = kc_.k0 * BK;
             }
         }
         if (l < AT::NI) ta_.load_one(st, k0, wid, l);
         else tb_.load_one(st + A_BYTES, k0, wid, l - AT::NI);
     };
-    // two-ring loop: load l of wide unit u / of narrow tile j (k0 follows from the unit number)
-    auto load_wide = [&](const AT& ta_, const BT& tb_, int slot3, int u, int l) {
-        char* dst = smem + slot3 * WIDE_UNIT;
-        if constexpr (A_WIDE) ta_.load_one(dst, u * 64, wid, l); else tb_.load_one(dst, u * 64, wid, l);
+    // loads l0 to l1 - 1 at once, of the tile that starts at k0 (tiles in ascending order, each begun with load 0)
+    auto request = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l0, int l1) __attribute__((always_inline)) {
+        if constexpr (S32) {
+#pragma unroll
+            for (int l = l0; l < l1; ++l) request32(tc, kc_, ta_, tb_, st, k0, l);
+            return;
+        }
+        if (l0 == 0) { if (k0 == 0) start(tc, kc_, ta_, tb_); else advance(tc, kc_, ta_, tb_); }
+#pragma unroll
+        for (int l = l0; l < l1; ++l) {
+            if (l < AT::NI) load_to_lds(ta_.rsrc, AT::dst(st, wid) + l * 1024, ta_.voff[l] + kc_.ka);
+            else load_to_lds(tb_.rsrc, BT::dst(st + A_BYTES, wid) + (l - AT::NI) * 1024, tb_.voff[l - AT::NI] + kc_.kb);
+        }
     };
-    auto load_narrow = [&](const AT& ta_, const BT& tb_, int slot4, int j, int l) {
-        char* dst = smem + NARROW_OFF + slot4 * NARROW_TILE;
-        if constexpr (A_WIDE) tb_.load_one(dst, j * 32, wid, l); else ta_.load_one(dst, j * 32, wid, l);
+    // unit of one operand (rings and units of their own): loads l0 to l1 - 1 of the unit that starts at k0
+    auto load_unit = [&](auto& t_, const char* dst, int k0, int l0, int l1) __attribute__((always_inline)) {
+        typedef std::remove_reference_t<decltype(t_)> OT;
+        if (l0 == 0) t_.end_at(k0);
+#pragma unroll
+        for (int l = l0; l < l1; ++l) load_to_lds(t_.rsrc, OT::dst(dst, wid) + l * 1024, t_.voff[l] + t_.koff(k0));
     };
-    constexpr int WL = W64 ? (A_WIDE ? AT::NI : BT::NI) : 0;       // loads per wave: one wide unit (8)
-    constexpr int NL = W64 ? (A_WIDE ? BT::NI : AT::NI) : 0;       //                 one narrow tile (4)
+    auto wide_slot = [&](int slot3) __attribute__((always_inline)) { return smem + slot3 * WIDE_UNIT; };
+    auto narrow_slot = [&](int slot4) __attribute__((always_inline)) { return smem + NARROW_OFF + slot4 * NARROW_TILE; };
+    constexpr int WL = W64 ? AT::NI : 0;       // loads per wave: one wide unit (8)
+    constexpr int NL = W64 ? BT::NI : 0;       //                 one narrow tile (4)
     static_assert(!W64 || (WL == 8 && NL == 4), "the two-ring schedule issues two wide and two narrow loads per block");
-    // half-size tiles: a wave's loads of a stage that go out in block 3 of a step, the rest follow in blocks 0, 1, 2
-    constexpr int R64_G3 = (LPW + 2) / 3, R64_G0 = (LPW + 1) / 3, R64_G1 = LPW / 3, R64_G2 = 0;
-    static_assert(!R64 || R64_G3 + R64_G0 + R64_G1 + R64_G2 == LPW, "loads of a stage over the blocks");
+    // ring of 64-k stages: a wave's loads of a stage that go out in block 3 of a step, the rest follow in blocks 0 and 1
+    constexpr int R64_G3 = (LPW + 2) / 3, R64_G0 = (LPW + 1) / 3, R64_G1 = LPW / 3;
+    static_assert(!R64 || R64_G3 + R64_G0 + R64_G1 == LPW, "loads of a stage over the blocks");
+    // ring of 32 k: loads of tile NS-1 that are on their way when the loop begins
+    constexpr int PIPE_EARLY = LPW / 2;
     // five-unit loop: load l of the weights' / the rows' unit of step t into a unit slot
     constexpr int UL = N64 ? 8 : 0;
     static_assert(!N64 || (AT::NI == 8 && BT::NI == 8), "eight loads per wave and unit");
-    auto load_b = [&](const BT& tb_, int slot, int t, int l) { tb_.load_one(smem + slot * WIDE_UNIT, t * 64, wid, l); };
-    auto load_a = [&](const AT& ta_, int slot, int t, int l) { ta_.load_one(smem + slot * WIDE_UNIT, t * 64, wid, l); };
     // the part of a tile's first loads that does not touch the staging region, and the rest
     auto issue_early = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
             // what the loop expects to be on its way when it starts: wide units 0 and 1 and the first
             // quarter of unit 2 (late: its slot is the staging region), narrow tiles 0..2 and half of tile 3
-#pragma unroll
-            for (int l = 0; l < WL; ++l) load_wide(ta_, tb_, 0, 0, l);
-#pragma unroll
-            for (int l = 0; l < NL; ++l) load_narrow(ta_, tb_, 0, 0, l);
-#pragma unroll
-            for (int l = 0; l < NL; ++l) load_narrow(ta_, tb_, 1, 1, l);
-#pragma unroll
-            for (int l = 0; l < WL; ++l) load_wide(ta_, tb_, 1, 1, l);
-#pragma unroll
-            for (int l = 0; l < NL; ++l) load_narrow(ta_, tb_, 2, 2, l);
-#pragma unroll
-            for (int l = 0; l < NL / 2; ++l) load_narrow(ta_, tb_, 3, 3, l);
+            load_unit(ta_, wide_slot(0), 0, 0, WL);
+            load_unit(tb_, narrow_slot(0), 0, 0, NL);
+            load_unit(tb_, narrow_slot(1), 32, 0, NL);
+            load_unit(ta_, wide_slot(1), 64, 0, WL);
+            load_unit(tb_, narrow_slot(2), 64, 0, NL);
+            load_unit(tb_, narrow_slot(3), 96, 0, NL / 2);
         } else if constexpr (N64) {
             // units 0 to 3: weights and rows of steps 0 and 1
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-#pragma unroll
-                for (int l = 0; l < UL; ++l) load_b(tb_, 2 * t, t, l);
-#pragma unroll
-                for (int l = 0; l < UL; ++l) load_a(ta_, 2 * t + 1, t, l);
+                load_unit(tb_, wide_slot(2 * t), t * 64, 0, UL);
+                load_unit(ta_, wide_slot(2 * t + 1), t * 64, 0, UL);
             }
         } else {
             constexpr int FIRST = R64 ? 0 : SB, STAGES = R64 ? NS - C::SBR : NS - SB;
 #pragma unroll
-            for (int s = 0; s < STAGES; ++s)
-#pragma unroll
-                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (FIRST + s) * STAGE, s * BK, l);
+            for (int s = 0; s < STAGES; ++s) request(tc, kc_, ta_, tb_, smem + (FIRST + s) * STAGE, s * BK, 0, LPW);
         }
     };
     auto issue_late = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
-#pragma unroll
-            for (int l = 0; l < WL / 4; ++l) load_wide(ta_, tb_, 2, 2, l);
+            load_unit(ta_, wide_slot(2), 128, 0, WL / 4);
         } else if constexpr (N64) {
-#pragma unroll
-            for (int l = 0; l < UL / 4; ++l) load_b(tb_, 4, 2, l);
+            load_unit(tb_, wide_slot(4), 128, 0, UL / 4);
         } else if constexpr (R64) {
 #pragma unroll
-            for (int s = NS - C::SBR; s < NS - 1; ++s)
-#pragma unroll
-                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + s * STAGE, s * BK, l);
-#pragma unroll
-            for (int l = 0; l < R64_G3; ++l) request(tc, kc_, ta_, tb_, smem + (NS - 1) * STAGE, (NS - 1) * BK, l);
+            for (int s = NS - C::SBR; s < NS - 1; ++s) request(tc, kc_, ta_, tb_, smem + s * STAGE, s * BK, 0, LPW);
+            request(tc, kc_, ta_, tb_, smem + (NS - 1) * STAGE, (NS - 1) * BK, 0, R64_G3);
         } else {
 #pragma unroll
-            for (int s = NS - SB; s < NS - 1; ++s)
-#pragma unroll
-                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (SB + s - NS) * STAGE, s * BK, l);
-#pragma unroll
-            for (int l = 0; l < LPW / 2; ++l) request(tc, kc_, ta_, tb_, smem + (SB - 1) * STAGE, (NS - 1) * BK, l);
+            for (int s = NS - SB; s < NS - 1; ++s) request(tc, kc_, ta_, tb_, smem + (SB + s - NS) * STAGE, s * BK, 0, LPW);
+            request(tc, kc_, ta_, tb_, smem + (SB - 1) * STAGE, (NS - 1) * BK, 0, PIPE_EARLY);
         }
     };
 
@@ -579,7 +791,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     AT ta;
     BT tb;
     bind(cur, ta, tb, lane);
-    KCursor kc = {0, 0, 0};
+    KCursor kc = {};
     issue_early(cur, kc, ta, tb);
     issue_late(cur, kc, ta, tb);
     bool first = true;
@@ -589,203 +801,285 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             bind(cur, ta, tb, lane);
             if constexpr (LAY == GEMM_TN) { if (g.k_segs > 1) bind_range(cur, kc.seg, ta, tb); }
         }
-        const int m0 = cur.m0, n0 = cur.n0, e = cur.e, q = cur.q, er = cur.er, tn = cur.tn, Mdim = cur.Mdim, KT = cur.KT;
+        const int m0 = cur.m0, n0 = cur.n0, e = cur.e, q = cur.q, er = cur.er, tn = cur.tn, Mdim = cur.Mdim;
+        // (256 x 256: an empty reduction is one tile of zeros, since a loop that may not run at all costs a copy of all accumulators behind it)
+        const int KT = S32 ? cur.KT : max(cur.KT, 1);
+        if constexpr (!S32) __builtin_assume(KT > 0);
         // blocks of 32 rows per wave that hold rows of this tile
         const int active = ALT && LAY != GEMM_TN ? min(TM, (Mdim - m0 + 32 * C::WAVES_M - 1) / (32 * C::WAVES_M)) : TM;
-        floatx16 acc[TM][TNN];
+        floatx4 acc[S32 ? 1 : RB][S32 ? 1 : NB];
+        floatx16 acc32[S32 ? TM : 1][S32 ? TNN : 1];
+        if constexpr (S32) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TNN; ++j)
+                for (int j = 0; j < TNN; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+                    for (int r = 0; r < 16; ++r) acc32[i][j][r] = 0.0f;
+        } else {
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0f;
+        }
+        if constexpr (QUAD) {
+            // (here, while the first loads are on their way: left to itself the compiler writes all 256 right before the loop.  With
+            // a loop for each number of active blocks it would then have to move them between those, and spills.)
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) asm volatile("" : "+a"(acc[i][j]));
+        }
+        // The compiler does not see the matrix instructions, which need two wait states behind a vector instruction that
+        // writes an operand and up to eighteen before another one reads the result.  So every main loop begins with a pause, and
+        // behind it the accumulators pass through a longer one before anything, a copy of the compiler's too, reads them.
+        auto pause = [&]() __attribute__((always_inline)) { asm volatile("s_nop 1" ::: "memory"); };
+        auto retire = [&]() __attribute__((always_inline)) {
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+            if constexpr (!S32) {
+                static_assert(S32 || C::OCC == 1, "accumulators in the AGPR half");
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j) asm volatile("" : "+a"(acc[i][j]) : : "memory");
+            }
+        };
+        // Product of the wave's 16 rows i and 16 columns j.
+        auto mul = [&](int i, int j, const FA& rows, const FB& cols) __attribute__((always_inline)) {
+            mfma_pinned(acc[i][j], cols.all(), rows.all());
+        };
+        // With 256 x 256 the accumulators leave registers for the fragments of one chunk of 32 k and no more.  A chunk is
+        // therefore multiplied in four blocks - the lower half of the fragments X times the lower and the upper half of Y,
+        // then the upper half of X times the upper and the lower half of Y - in each of which one half dies, whose registers
+        // receive what the block after it needs: Y's upper half, X's upper half, X's lower half of the next chunk, and
+        // Y's lower half of it in the place of the upper one (so the places of Y's halves change from chunk to chunk).  Of the
+        // half that came last one fragment after the other is used, so that the last ones read have as long as the first.
 
         if constexpr (W64) {
-            // Hand-scheduled loop over steps of 64 k = four blocks of TM x TN matrix instructions (16 k each).
-            // While block b is multiplied, the fragments of block b+1 are read and four loads are issued, one
-            // LDS read or load per matrix instruction.  Step t reads wide unit t (slot t mod 3) and narrow
+            // Hand-scheduled loop over steps of 64 k = two chunks = eight blocks 0 to 7 (see above), with the rows as X and
+            // the weights as Y.  While a block is multiplied the half it frees is filled and two loads are issued,
+            // at most one LDS read or load per matrix instruction.  Step t reads wide unit t (slot t mod 3) and narrow
             // tiles 2t, 2t+1 (slots mod 4).  Two barriers per step:
-            //   after block 0: every wave has read narrow tile 2t for the last time (its slot then receives
+            //   after block 1: every wave has read narrow tile 2t for the last time (its slot then receives
             //           tile 2t+4), and tile 2t+1 has landed;
-            //   after block 2: every wave has read wide unit t and narrow tile 2t+1 for the last time (their
+            //   after block 5: every wave has read wide unit t and narrow tile 2t+1 for the last time (their
             //           slots receive unit t+3 and tile 2t+5), and unit t+1 and tile 2t+2 have landed.
-            // Each wave issues, per step, in this order: block 0 - wide unit t+2 loads 2,3, narrow tile 2t+3
-            // loads 2,3; block 1 - unit t+2 loads 4,5, tile 2t+4 loads 0,1; block 2 - unit t+2 loads 6,7, tile
-            // 2t+4 loads 2,3; block 3 - unit t+3 loads 0,1, tile 2t+5 loads 0,1.  At either barrier the sixteen
+            // Each wave issues, per step, in this order, two loads per block: 0 - wide unit t+2 loads 2,3, 1 - narrow tile
+            // 2t+3 loads 2,3; 2 - unit t+2 loads 4,5, 3 - tile 2t+4 loads 0,1; 4 - unit t+2 loads 6,7, 5 - tile
+            // 2t+4 loads 2,3; 6 - unit t+3 loads 0,1, 7 - tile 2t+5 loads 0,1.  At either barrier the sixteen
             // youngest loads of the wave may still be in flight; everything older is what the step needs next.
+            frags_at(lds0, lds0 + NARROW_OFF);
             if (first) wait_vmcnt<0>();
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             // TMA: blocks of 32 rows per wave that hold something; loads, waits and barriers are the same for all
             auto loop = [&](auto tma) __attribute__((always_inline)) {
             constexpr int TMA = decltype(tma)::value;
-            constexpr int MB = TMA * TNN, FR = TMA + TNN;
-            // what follows matrix instruction m of a block: FR LDS reads, then four loads; one after every other
-            // matrix instruction where there is room, else spread evenly
-            auto follow = [&](int m, auto&& read, auto&& load) __attribute__((always_inline)) {
-                if constexpr (FR + 7 <= MB) {
-                    if (m < FR) read(m);
-                    else if (m - FR < 8 && (m - FR) % 2 == 0) load((m - FR) / 2);
-                } else {
-                    constexpr int items = FR + 4;
+            constexpr int HX = TMA, HY = NB / 2, MB = HX * HY;
+            static_assert(AR == 1 && BR == 2, "rows read by ds_read_b128, weights by pairs of transposing reads");
+            FA X[2][HX];
+            FB Y[2][HY];
+            // LDS read r of half h, of unit t or of the narrow tile `off` bytes behind tile 2t, by the addresses as they stand
+            auto read_x = [&](FA (&to)[HX], int h, int r, int kk) __attribute__((always_inline)) { frag_a(to[r], 0, h * HX + r, kk, 0); };
+            auto read_y = [&](FB (&to)[HY], int h, int r, unsigned off) __attribute__((always_inline)) { frag_b(to[r / 2], off, h * HY + r / 2, 0, r % 2); };
+            // X's half xh times Y's half yh, which lies in Y[ys]; new_x: X's came last.  Beside it `reads` LDS reads, loads L0 and
+            // L0 + 1 of a wide unit or narrow tile (byte offset k) to LDS address d, and moves of addresses.
+            auto block = [&](int xh, int yh, int ys, bool new_x, int reads, auto&& read, bool wide, unsigned d, unsigned k, auto first_load, auto&& move)
+                             __attribute__((always_inline)) {
+                constexpr int L0 = decltype(first_load)::value;
 #pragma unroll
-                    for (int it = 0; it < items; ++it)
-                        if (it * MB / items == m) { if (it < FR) read(it); else load(it - FR); }
+                for (int m = 0; m < MB; ++m) {
+                    const int x = new_x ? m / HY : m % HX, y = new_x ? m % HY : m / HX;
+                    mul(xh * HX + x, yh * HY + y, X[xh][x], Y[ys][y]);
+                    Gaps<MB>::reads(m, reads, read);
+                    Gaps<MB>::loads(m, [&](int l) __attribute__((always_inline)) { if (l == 0) lds_destination<L0 * 1024>(d); else lds_next_destination(); },
+                                    [&](int l) __attribute__((always_inline)) {
+                                        if (wide) load_to_destination(ta.rsrc, ta.voff[L0 + l], k); else load_to_destination(tb.rsrc, tb.voff[L0 + l], k);
+                                    });
+                    Gaps<MB>::moves(m, reads == HX, move);
                 }
             };
-            bf16x8 F0[FR], F1[FR];
-            // fragment f of 16-k block kk of a step: from the wide unit at wb or from the narrow tile pair at nb0, nb1
-            auto frag = [&](int f, int kk, const char* wb, const char* nb0, const char* nb1) __attribute__((always_inline)) -> bf16x8 {
-                const char* nb = kk < 2 ? nb0 : nb1;
-                if constexpr (A_WIDE) return f < TMA ? fa[f].read(wb, kk) : fb[f - TMA].read(nb, kk & 1);
-                else return f < TMA ? fa[f].read(nb, kk & 1) : fb[f - TMA].read(wb, kk);
-            };
 #pragma unroll
-            for (int f = 0; f < FR; ++f) F0[f] = frag(f, 0, smem, smem + NARROW_OFF, smem + NARROW_OFF);
-            int w3 = 0, n4 = 0;                       // slot of wide unit t, slot of narrow tile 2t
+            for (int r = 0; r < HX; ++r) read_x(X[0], 0, r, 0);
+#pragma unroll
+            for (int r = 0; r < 2 * HY; ++r) read_y(Y[0], 0, r, 0);
+            constexpr unsigned TURN = NARROW_OFF ^ (NARROW_OFF + 2 * NARROW_TILE);       // between narrow slots 0, 1 and 2, 3
+            static_assert(((NARROW_OFF | (2 * NARROW_TILE + NARROW_OFF)) & (NARROW_TILE - 1)) == 0, "slots differ in the bits above a tile's");
+            const unsigned kn = tb.koff(32);            // bytes from one narrow tile to the next
+            const unsigned w_end = AT::dst(wide_slot(3), wid);
+            unsigned d_w = AT::dst(wide_slot(2), wid);       // where unit t+2 goes
+            unsigned d_n = BT::dst(narrow_slot(0), wid), d_n3 = BT::dst(narrow_slot(2), wid);    // slots of tiles 2t and 2t+2
+            unsigned kw = 256, k3 = 3 * kn;              // byte offsets of unit t+2 and of tile 2t+3
+            int w3 = 0;                                  // slot of wide unit t
+#define READ(what) [&](int r) __attribute__((always_inline)) { what; }
+#define MOVE(what) [&](int e) __attribute__((always_inline)) { what; }
+#define L(n) std::integral_constant<int, n>{}
 #pragma unroll 1
             for (int t = 0; t < KT; ++t) {
-                const int w3a = w3 == 2 ? 0 : w3 + 1, w3b = w3a == 2 ? 0 : w3a + 1;   // slots of units t+1, t+2
-                const int n4b = n4 ^ 2;                                               // slot of tile 2t+2
-                const char* wb = smem + w3 * WIDE_UNIT;
-                const char* nb0 = smem + NARROW_OFF + n4 * NARROW_TILE;
-                const char* nb1 = nb0 + NARROW_TILE;
-                const char* wb_next = smem + w3a * WIDE_UNIT;
-                const char* nb_next = smem + NARROW_OFF + n4b * NARROW_TILE;
-                // block 0
-#pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
-                    follow(m, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 1, wb, nb0, nb1); },
-                           [&](int l) __attribute__((always_inline)) {
-                               if (l < 2) load_wide(ta, tb, w3b, t + 2, 2 + l); else load_narrow(ta, tb, n4b + 1, 2 * t + 3, l); });
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                const int dx = w3 == 2 ? -2 * WIDE_UNIT : WIDE_UNIT;
+                pause();
+                block(0, 0, 0, false, 2 * HY, READ(read_y(Y[1], 1, r, 0)), true, d_w, kw, L(2), MOVE());
+                block(0, 1, 1, false, HX, READ(read_x(X[1], 1, r, 0)), false, d_n3 + NARROW_TILE, k3, L(2), MOVE());
+                wait_lgkmcnt<HX>();
                 wait_vmcnt<16>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                // block 1
-#pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
-                    follow(m, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 2, wb, nb0, nb1); },
-                           [&](int l) __attribute__((always_inline)) {
-                               if (l < 2) load_wide(ta, tb, w3b, t + 2, 4 + l); else load_narrow(ta, tb, n4, 2 * t + 4, l - 2); });
-                }
-                // block 2
-#pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
-                    follow(m, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, wb, nb0, nb1); },
-                           [&](int l) __attribute__((always_inline)) {
-                               if (l < 2) load_wide(ta, tb, w3b, t + 2, 6 + l); else load_narrow(ta, tb, n4, 2 * t + 4, l); });
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                if (t * 64 + 160 > g.K) tb.end_at(t * 64 + 128);
+                k3 += kn;
+                block(1, 1, 1, true, HX, READ(read_x(X[0], 0, r, 1)), true, d_w, kw, L(4), MOVE(if (e == 1) move_address(fa.at[0], dx)));
+                block(1, 0, 0, true, 2 * HY, READ(read_y(Y[1], 0, r, NARROW_TILE)), false, d_n, k3, L(0), MOVE());
+                block(0, 0, 1, false, 2 * HY, READ(read_y(Y[0], 1, r, NARROW_TILE)), true, d_w, kw, L(6), MOVE());
+                // (the lower half's addresses of Y, which its reads in the last block need)
+                block(0, 1, 0, false, HX, READ(read_x(X[1], 1, r, 1)), false, d_n, k3, L(2),
+                      MOVE(flip_address(fb.at[e], TURN)));
+                wait_lgkmcnt<0>();
                 wait_vmcnt<16>();
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
-                // block 3
-#pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<true>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
-                    follow(m, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 0, wb_next, nb_next, nb_next); },
-                           [&](int l) __attribute__((always_inline)) {
-                               if (l < 2) load_wide(ta, tb, w3, t + 3, l); else load_narrow(ta, tb, n4 + 1, 2 * t + 5, l - 2); });
+                if (t * 64 + 256 > g.K) {
+                    ta.end_at(t * 64 + 192);
+                    tb.end_at(t * 64 + 160);
                 }
-                w3 = w3a;
-                n4 = n4b;
+                kw += 128;
+                k3 += kn;
+                d_w += WIDE_UNIT;
+                if (d_w == w_end) d_w -= 3 * WIDE_UNIT;
+                block(1, 1, 0, true, HX, READ(read_x(X[0], 0, r, 0)), true, d_w, kw, L(0),
+                      MOVE(flip_address(fb.at[4 + e], TURN)));
+                block(1, 0, 1, true, 2 * HY, READ(read_y(Y[0], 0, r, 0)), false, d_n + NARROW_TILE, k3, L(0), MOVE(if (e == 1) move_address(fa.at[1], dx)));
+                w3 = w3 == 2 ? 0 : w3 + 1;
+                d_n ^= TURN;
+                d_n3 ^= TURN;
             }
+#undef L
+#undef MOVE
+#undef READ
+            retire();
             };
-            if (active == 4) loop(std::integral_constant<int, 4>{});
+            if (__builtin_expect(active == 4, 1)) loop(std::integral_constant<int, 4>{});
             else if (active == 3) loop(std::integral_constant<int, 3>{});
             else if (active == 2) loop(std::integral_constant<int, 2>{});
             else loop(std::integral_constant<int, 1>{});
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         } else if constexpr (N64) {
-            // Hand-scheduled loop over steps of 64 k = eight blocks of 2 x TN matrix instructions: blocks 0 to 3 the wave's
-            // first two blocks of rows over the four 16 k, blocks 4 to 7 the other two.  Unit 2t holds the weights of
-            // step t, unit 2t+1 its rows, unit u lies in slot u mod 5.  All weights of a step are in registers when it
-            // begins; in blocks 4 to 7 those of the next step take their places, each behind the last matrix instruction
-            // that needs the old ones.  Rows are read one block ahead.  Two barriers per step:
+            // Hand-scheduled loop over steps of 64 k = eight blocks: the lower half of the wave's rows over the two chunks of
+            // 32 k (blocks 0, 1 and 2, 3), then the upper half (4, 5 and 6, 7), each time against the lower and the upper half
+            // of the columns.  Unit 2t holds the weights of step t, unit 2t+1 its rows, unit u lies in slot u mod 5.  All
+            // weights of a step are in registers when it begins; in blocks 4 to 7 those of the next step take their places,
+            // each behind the last matrix instruction that needs the old ones.  Rows are read two blocks ahead.  Two barriers
+            // per step:
             //   after block 3: every wave has read the weights of step t for the last time (block 7 of step t-1), their
             //           slot receives the rows of step t+2 (blocks 4 to 6); and the weights of step t+1 have landed;
-            //   after block 6: every wave has read the rows of step t for the last time, their slot receives the weights
+            //   after block 5: every wave has read the rows of step t for the last time, their slot receives the weights
             //           of step t+3 (block 7 and blocks 0 to 2 of the next step); and the rows of step t+1 have landed.
-            // So a unit is requested 1.4 (rows) or 1.6 steps (weights) before it has to be there, and at either barrier
-            // the sixteen youngest loads of a wave may still be in flight.  (LOOP_W64 has this layout's rows in tiles of
+            // So a unit is requested 1.3 (rows) or 1.6 steps (weights) before it has to be there, and at the barriers
+            // the sixteen or fourteen youngest loads of a wave may still be in flight.  (LOOP_W64 has this layout's rows in tiles of
             // 32 k, that is in half lines.  Input gradient in launches by itself, 12 x 1400 rows x 640, K = 2560: 79.6 us with
             // LOOP_W64, 73.3 so; 16 x 2048 x 2048, K = 8192: 998 and 976; 8 x 4096 x 1024, K = 4096, with the weight gradients:
-            // 242 and 235 per GEMM.)
+            // 242 and 235 per GEMM; all with the 32 x 32 instruction.)
+            frags_at(lds0 + WIDE_UNIT, lds0);
             if (first) wait_vmcnt<16 + UL / 4>();
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             auto loop = [&](auto tma) __attribute__((always_inline)) {
             constexpr int TMA = decltype(tma)::value;
-            bf16x8 W[4][TNN], R[2][2];               // weights per 16 k; rows of this block and of the next one
-            const auto row_frag = [&](int b, int i, const char* unit) __attribute__((always_inline)) -> bf16x8 {
-                return fa[(b < 4 ? 0 : 2) + i].read(unit, b & 3);
-            };
+            FB W[2][NB];
+            FA R[2][4];                              // weights per chunk; rows of this pair of blocks and of the next one
+            constexpr int HN = NB / 2;
+            static_assert(HN == 4, "blocks of up to 4 x 4");
+            // rows of a pair of blocks: half g / 2 of the wave's rows, chunk g % 2
+            const auto row_frag = [&](int g, int i) __attribute__((always_inline)) { whole_a(R[g & 1][i], 0, (g >> 1) * 4 + i, g & 1); };
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
+            for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-                for (int j = 0; j < TNN; ++j) W[kk][j] = fb[j].read(smem, kk);
+                for (int j = 0; j < NB; ++j) whole_b(W[kk][j], 0, j, kk);
 #pragma unroll
-            for (int i = 0; i < (TMA < 2 ? TMA : 2); ++i) R[0][i] = row_frag(0, i, smem + WIDE_UNIT);
+            for (int i = 0; i < (TMA < 2 ? 2 : 4); ++i) row_frag(0, i);
+            fb.at[0] += 2 * WIDE_UNIT;                  // the weights of step 1
+            fb.at[1] += 2 * WIDE_UNIT;
             int s5 = 0;                              // slot of the weights of step t
             const auto slot = [&](int add) __attribute__((always_inline)) { const int v = s5 + add; return v >= 5 ? v - 5 : v; };
 #pragma unroll 1
             for (int t = 0; t < KT; ++t) {
-                const char* rows = smem + slot(1) * WIDE_UNIT;
-                const char* w_next = smem + slot(2) * WIDE_UNIT;
-                const char* rows_next = smem + slot(3) * WIDE_UNIT;
-                const int to_a = s5, to_b2 = slot(4), to_b3 = slot(1);
-#pragma unroll
-                for (int b = 0; b < 8; ++b) {
-                    const int i0 = b < 4 ? 0 : 2, nr = TMA - i0 < 0 ? 0 : TMA - i0 > 2 ? 2 : TMA - i0;      // rows' blocks of this block
-                    const int bn = (b + 1) & 7, n0r = bn < 4 ? 0 : 2;
-                    const int nn = TMA - n0r < 0 ? 0 : TMA - n0r > 2 ? 2 : TMA - n0r;                       // and of the next one
-                    const char* rn = b == 7 ? rows_next : rows;
-                    // what follows matrix instruction m of the block (all of it where the block has none)
-                    auto rows_ahead = [&](int i) __attribute__((always_inline)) { if (i < nn) R[bn & 1][i] = row_frag(bn, i, rn); };
-                    auto weights_ahead = [&](int j) __attribute__((always_inline)) { if (b >= 4) W[b - 4][j] = fb[j].read(w_next, b - 4); };
-                    auto load = [&](int l) __attribute__((always_inline)) {
-                        if (b < 3) { if (l < 2) load_b(tb, to_b2, t + 2, 2 * (b + 1) + l); }
-                        else if (b == 7) { if (l < 2) load_b(tb, to_b3, t + 3, l); }
-                        else if (b >= 4) { if (l < (b == 6 ? 2 : 3)) load_a(ta, to_a, t + 2, 3 * (b - 4) + l); }
+                // the rows' and the weights' addresses move two units on, of five
+                const int da = s5 + 1 >= 3 && s5 + 1 < 5 ? -3 * WIDE_UNIT : 2 * WIDE_UNIT;
+                const int db = s5 == 1 || s5 == 2 ? -3 * WIDE_UNIT : 2 * WIDE_UNIT;
+                const unsigned to_a = AT::dst(wide_slot(s5), wid), to_b2 = BT::dst(wide_slot(slot(4)), wid), to_b3 = BT::dst(wide_slot(slot(1)), wid);
+                const unsigned k2 = (t + 2) * 128, k3 = k2 + 128;
+                pause();
+                auto block = [&](auto number) __attribute__((always_inline)) {
+                    constexpr int b = decltype(number)::value, g = b >> 1, gn = (g + 1) & 3, j0 = (b & 1) * HN;
+                    // rows' blocks of this block and of the next pair
+                    constexpr int LOW = TMA < 2 ? 2 : 4, HIGH = TMA < 3 ? 0 : 2 * TMA - 4;
+                    constexpr int nr = g < 2 ? LOW : HIGH, nn = gn < 2 ? LOW : HIGH, MB = nr * HN;      // 16, 8 or none
+                    auto rows_ahead = [&](int i) __attribute__((always_inline)) { const int f = 2 * (b & 1) + i; if (f < nn) row_frag(gn, f); };
+                    auto weights_ahead = [&](int j) __attribute__((always_inline)) { if constexpr (b >= 4) whole_b(W[g & 1][j0 + j], 0, j0 + j, g & 1); };
+                    // behind their last reads: rows of chunk 0 are read in blocks 2, 3 and 6, 7, of chunk 1 in 0, 1 and 4, 5,
+                    // weights of chunk 0 in 4, 5, of chunk 1 in 6, 7
+                    auto move = [&]() __attribute__((always_inline)) {
+                        if constexpr (b == 4) move_address(fa.at[0], da);
+                        if constexpr (b == 6) { move_address(fa.at[1], da); move_address(fb.at[0], db); }
+                        if constexpr (b == 7) move_address(fb.at[1], db);
                     };
-                    if (nr == 0) {
+                    constexpr bool OF_B = b < 3 || b == 7;
+                    constexpr int nl = b == 3 ? 0 : b == 4 || b == 5 ? 3 : 2, l0 = b < 3 ? 2 * (b + 1) : b == 7 ? 0 : 3 * (b - 4);
+                    auto pre = [&](int l) __attribute__((always_inline)) {
+                        if (l == 0) lds_destination<l0 * 1024>(b < 3 ? to_b2 : b == 7 ? to_b3 : to_a);
+                        else lds_next_destination();
+                    };
+                    auto go = [&](int l) __attribute__((always_inline)) {
+                        if constexpr (OF_B) load_to_destination(tb.rsrc, tb.voff[l0 + l], b == 7 ? k3 : k2);
+                        else load_to_destination(ta.rsrc, ta.voff[l0 + l], k2);
+                    };
+                    if constexpr (b == 4) ta.end_at(t * 64 + 128);
+                    if constexpr (b == 7) tb.end_at(t * 64 + 192);
+                    if constexpr (MB > 0) {
+#pragma unroll
+                        for (int m = 0; m < MB; ++m) {
+                            mul((g >> 1) * 4 + m / HN, j0 + m % HN, R[g & 1][m / HN], W[g & 1][j0 + m % HN]);
+                            if (m == 0 || m == 2) rows_ahead(m / 2);
+#pragma unroll
+                            for (int l = 0; l < nl; ++l) {
+                                const int at = MB == 16 ? 4 + 3 * l : 1 + 2 * l;
+                                if (m == at) pre(l);
+                                if (m == at + 1) go(l);
+                            }
+                            if (m / HN == nr - 1) weights_ahead(m % HN);
+                        }
+                        move();
+                    } else {
 #pragma unroll
                         for (int i = 0; i < 2; ++i) rows_ahead(i);
 #pragma unroll
-                        for (int j = 0; j < TNN; ++j) weights_ahead(j);
+                        for (int j = 0; j < HN; ++j) weights_ahead(j);
+                        move();
 #pragma unroll
-                        for (int l = 0; l < 3; ++l) load(l);
+                        for (int l = 0; l < nl; ++l) { pre(l); asm volatile("s_nop 0" ::: "memory"); go(l); }
                     }
-#pragma unroll
-                    for (int m = 0; m < 2 * TNN; ++m) {
-                        if (m >= nr * TNN) continue;
-                        const int i = m / TNN, j = m % TNN;
-                        mfma_pinned<true>(acc[i0 + i][j], W[b & 3][j], R[b & 1][i]);
-                        if (m < 2) rows_ahead(m);
-                        else if (m < 4) load(m - 2);
-                        if (m == nr * TNN - 1) load(2);
-                        if (i == nr - 1) weights_ahead(j);
-                    }
-                    if (b == 3 || b == 6) {
-                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                        wait_vmcnt<16>();
+                    if constexpr (b == 3 || b == 5) {
+                        // (of block 5 the reads of rows, which come before those of four fragments of weights)
+                        if constexpr (b == 3) wait_vmcnt<16>(); else { wait_lgkmcnt<HN * BR>(); wait_vmcnt<14>(); }
                         __builtin_amdgcn_s_barrier();
                         asm volatile("" ::: "memory");
                     }
-                }
+                };
+                block(std::integral_constant<int, 0>{});
+                block(std::integral_constant<int, 1>{});
+                block(std::integral_constant<int, 2>{});
+                block(std::integral_constant<int, 3>{});
+                block(std::integral_constant<int, 4>{});
+                block(std::integral_constant<int, 5>{});
+                block(std::integral_constant<int, 6>{});
+                block(std::integral_constant<int, 7>{});
                 s5 = slot(2);
             }
+            retire();
             };
-            if (active == 4) loop(std::integral_constant<int, 4>{});
+            if (__builtin_expect(active == 4, 1)) loop(std::integral_constant<int, 4>{});
             else if (active == 3) loop(std::integral_constant<int, 3>{});
             else if (active == 2) loop(std::integral_constant<int, 2>{});
             else loop(std::integral_constant<int, 1>{});
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         } else if constexpr (R64) {
             // Hand-scheduled loop over steps of 64 k = four blocks of TM x TN matrix instructions (16 k each).  A
             // ring of NS stages; while block b is multiplied the fragments of block b+1 are read.  One barrier per
@@ -808,7 +1102,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             };
             bf16x8 F0[FR], F1[FR];
             auto frag = [&](int f, int kk, const char* st) __attribute__((always_inline)) -> bf16x8 {
-                return f < TMA ? fa[f].read(st, kk) : fb[f - TMA].read(st + A_BYTES, kk);
+                return f < TMA ? fa32[f].read(st, kk) : fb32[f - TMA].read(st + A_BYTES, kk);
             };
 #pragma unroll
             for (int f = 0; f < FR; ++f) F0[f] = frag(f, 0, smem);
@@ -821,21 +1115,21 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 char* st2 = smem + (s3 == 0 ? NS - 1 : s3 - 1) * STAGE;      // of stage t + NS-1
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
                     follow(m, R64_G0, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 1, st); },
-                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + l); });
+                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + l); });
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
                     follow(m, R64_G1, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 2, st); },
-                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + l); });
+                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + l); });
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
-                    follow(m, R64_G2, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, st); },
-                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + R64_G1 + l); });
+                    mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
+                    follow(m, 0, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, st); },
+                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st2, (t + NS - 1) * BK, 0); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 wait_vmcnt<(NS - 2) * LPW>();
@@ -843,53 +1137,113 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
+                    mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
                     follow(m, R64_G3, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 0, st1); },
-                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st, (t + NS) * BK, l); });
+                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st, (t + NS) * BK, l); });
                 }
                 s3 = s3a;
             }
+            retire();
             };
             if (TM == 1 || active == 1) loop(std::integral_constant<int, 1>{});
             else if (TM == 2 || active == 2) loop(std::integral_constant<int, TM < 2 ? 1 : 2>{});
             else if (active == 3) loop(std::integral_constant<int, TM < 3 ? 1 : 3>{});
             else loop(std::integral_constant<int, TM < 4 ? 1 : 4>{});
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
         } else {
-            // Hand-scheduled loop (with one wave per SIMD nothing else hides a stall): every
-            // LDS read and every load into LDS sits between two matrix instructions, one per
-            // instruction, and the data a block of TM x TN matrix instructions needs was
-            // requested during the block before.
-            // A tile is 32 k = two such blocks; the ring holds NS tiles.  In iteration t
-            //   block 0 multiplies k 0..15 of tile t, reads k 16..31 of it into the second
-            //           fragment set and requests the second half of tile t+NS-1;
-            //   then the wave waits for its part of tile t+1 and meets the others (their
-            //           parts have landed too, and nobody reads stage t any more);
-            //   block 1 multiplies k 16..31, reads k 0..15 of tile t+1 into the first
-            //           fragment set and requests the first half of tile t+NS into stage t.
-            // Up to NS - 1 tiles are in flight towards a workgroup.
+            // Hand-scheduled loop over tiles of 32 k = one chunk; the ring holds NS tiles, of which up to NS - 1 are in flight
+            // towards a workgroup.  Every LDS read and every load into LDS sits between two matrix instructions (with one
+            // wave per SIMD nothing else hides a stall).
+            int st = SB;
+            if constexpr (QUAD) {
+                // 256 x 256: four blocks (see above), the rows as X, the columns as Y.  In iteration t blocks 0 and 1 read the
+                // upper halves of tile t and request the second half of tile t+NS-1; then the wave waits for its part of
+                // tile t+1 and meets the others (their parts have landed too, and nobody reads stage t any more); blocks 2
+                // and 3 read the lower halves of tile t+1 and request the first half of tile t+NS into stage t.
+                static_assert(RB == 8 && NB == 8 && LPW == 8, "four blocks of 4 x 4 with two loads each");
+                frags_at(lds0 + SB * STAGE, lds0 + SB * STAGE + A_BYTES);
+                if (first) wait_vmcnt<(NS - 2) * LPW + PIPE_EARLY>();         // tile 0 is in (later tiles: waited for at the handover)
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                FA X[2][4];
+                FB Y[2][4];
+                // (an odd number of tiles begins with the second half of an iteration)
+                bool skip = KT & 1;
+#pragma unroll
+                for (int f = 0; f < 4; ++f) whole_a(X[0][f], 0, f, 0);
+                if (skip) {
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) whole_b(Y[1][f], 0, f, 0);
+                } else {
+#pragma unroll
+                    for (int f = 0; f < 4; ++f) whole_b(Y[0][f], 0, f, 0);
+                }
+                int kt = 0;
+                // y: the place of the lower half of Y
+                auto tile = [&](auto y) __attribute__((always_inline)) {
+                    constexpr int LO = decltype(y)::value, UP = LO ^ 1;
+                    char* cs = smem + st * STAGE;
+                    char* prv = smem + ((st == 0) ? NS - 1 : st - 1) * STAGE;
+                    const int next = st == NS - 1 ? (1 - NS) * STAGE : STAGE;
+                    auto block = [&](int xh, int yh, int ys, bool new_x, int reads, auto&& read, const char* to, auto first_load, auto&& move) __attribute__((always_inline)) {
+                        constexpr int L0 = decltype(first_load)::value;
+#pragma unroll
+                        for (int m = 0; m < 16; ++m) {
+                            const int x = new_x ? m / 4 : m % 4, y = new_x ? m % 4 : m / 4;
+                            mul(xh * 4 + x, yh * 4 + y, X[xh][x], Y[ys][y]);
+                            if (L0 == 0 && m == 7) { advance(cur, kc, ta, tb); settle(kc); }
+                            Gaps<16>::reads(m, reads, read);
+                            Gaps<16>::loads(m, [&](int l) __attribute__((always_inline)) {
+                                                if (l) lds_next_destination();
+                                                else if constexpr (L0 < AT::NI) lds_destination<L0 * 1024>(AT::dst(to, wid));
+                                                else lds_destination<A_BYTES + (L0 - AT::NI) * 1024>(BT::dst(to, wid));
+                                            },
+                                            [&](int l) __attribute__((always_inline)) { go(kc, ta, tb, L0 + l); });
+                            Gaps<16>::moves(m, false, move);
+                        }
+                    };
+#define READ(what) [&](int r) __attribute__((always_inline)) { what; }
+#define MOVE(what) [&](int e) __attribute__((always_inline)) { what; }
+#define L(n) std::integral_constant<int, n>{}
+                    settle(kc);
+                    pause();
+                    block(0, 0, LO, false, 4 * BR, READ(frag_b(Y[UP][r / BR], 0, 4 + r / BR, 0, r % BR)), prv, L(4), MOVE(move_address(fa.at[e], next)));
+                    block(0, 1, UP, false, 4 * AR, READ(frag_a(X[1][r / AR], 0, 4 + r / AR, 0, r % AR)), prv, L(6), MOVE(move_address(fb.at[4 + e], next)));
+                    wait_lgkmcnt<0>();                                     // this wave no longer reads stage t
+                    wait_vmcnt<(NS - 2) * LPW>();                          // its part of tile t+1 is in
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                    block(1, 1, UP, true, 4 * AR, READ(frag_a(X[0][r / AR], 0, r / AR, 0, r % AR)), cs, L(0), MOVE(move_address(fb.at[e], next)));
+                    block(1, 0, LO, true, 4 * BR, READ(frag_b(Y[UP][r / BR], 0, r / BR, 0, r % BR)), cs, L(2), MOVE(move_address(fa.at[4 + e], next)));
+#undef L
+#undef MOVE
+#undef READ
+                    st = (st + 1 == NS) ? 0 : st + 1;
+                    ++kt;
+                };
+#pragma unroll 1
+                while (kt < KT) {
+                    if (!skip) tile(std::integral_constant<int, 0>{});
+                    skip = false;
+                    tile(std::integral_constant<int, 1>{});
+                }
+            } else {
+            // Smaller tiles: two blocks of TM x TN matrix instructions.  In iteration t block 0 multiplies k 0..15 of tile t, reads
+            // k 16..31 of it and requests the second half of tile t+NS-1; then the wave waits for its part of tile t+1 and meets
+            // the others (their parts have landed too, and nobody reads stage t any more); block 1 multiplies k 16..31, reads
+            // k 0..15 of tile t+1 and requests the first half of tile t+NS into stage t.
+            static_assert(QUAD || S32, "waves of 64 x 64");
             constexpr int MB = TM * TNN;                 // matrix instructions per block
             constexpr int FR = TM + TNN;                 // fragments per block: A rows first, then B columns
             constexpr int LH = LPW / 2;                  // loads of a tile requested one block earlier than the rest
-            // What follows matrix instruction m of a block: LDS reads first, then loads.  A load costs the wave
-            // more issue time than one matrix instruction hides: where there is room, only every other matrix
-            // instruction is followed by one; where there is not even a matrix instruction for each item (tiles
-            // of 64 x 64 per wave), the items are spread evenly.
+            // What follows matrix instruction m of a block, spread evenly: LDS reads first, then loads.
             constexpr int LMAX = LPW - LH;
-            constexpr int LS = (FR + 2 * LMAX - 1 <= MB) ? 2 : 1;
-            constexpr bool ROOMY = FR + LMAX <= MB;
             auto follow = [&](int m, int nload, auto&& read, auto&& load) __attribute__((always_inline)) {
-                if constexpr (ROOMY) {
-                    if (m < FR) read(m);
-                    else if (m - FR < LS * nload && (m - FR) % LS == 0) load((m - FR) / LS);
-                } else {
-                    const int items = FR + nload;
+                const int items = FR + nload;
 #pragma unroll
-                    for (int it = 0; it < FR + LMAX; ++it) {
-                        if (it < items && it * MB / items == m) {
-                            if (it < FR) read(it);
-                            else load(it - FR);
-                        }
+                for (int it = 0; it < FR + LMAX; ++it) {
+                    if (it < items && it * MB / items == m) {
+                        if (it < FR) read(it);
+                        else load(it - FR);
                     }
                 }
             };
@@ -899,8 +1253,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             bf16x8 F0[FR], F1[FR];
 #pragma unroll
             for (int f = 0; f < FR; ++f)
-                F0[f] = f < TM ? fa[f].read(smem + SB * STAGE, 0) : fb[f - TM].read(smem + SB * STAGE + A_BYTES, 0);
-            int st = SB;
+                F0[f] = f < TM ? fa32[f].read(smem + SB * STAGE, 0) : fb32[f - TM].read(smem + SB * STAGE + A_BYTES, 0);
 #pragma unroll 1
             for (int kt = 0; kt < KT; ++kt) {
                 char* cs = smem + st * STAGE;
@@ -910,10 +1263,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 char* prv = smem + stp * STAGE;
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F0[TM + m % TNN], F0[m / TNN]);
+                    mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F0[TM + m % TNN], F0[m / TNN]);
                     follow(m, LPW - LH,
-                           [&](int f) __attribute__((always_inline)) { F1[f] = f < TM ? fa[f].read(cs, 1) : fb[f - TM].read(cs + A_BYTES, 1); },
-                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, prv, (kt + NS - 1) * BK, LH + l); });
+                           [&](int f) __attribute__((always_inline)) { F1[f] = f < TM ? fa32[f].read(cs, 1) : fb32[f - TM].read(cs + A_BYTES, 1); },
+                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, prv, (kt + NS - 1) * BK, LH + l); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave no longer reads stage t
                 wait_vmcnt<(NS - 2) * LPW>();                          // its part of tile t+1 is in
@@ -921,16 +1274,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
-                    mfma_pinned<C::OCC == 1>(acc[m / TNN][m % TNN], F1[TM + m % TNN], F1[m / TNN]);
+                    mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F1[TM + m % TNN], F1[m / TNN]);
                     follow(m, LH,
-                           [&](int f) __attribute__((always_inline)) { F0[f] = f < TM ? fa[f].read(nxt, 0) : fb[f - TM].read(nxt + A_BYTES, 0); },
-                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, cs, (kt + NS) * BK, l); });
+                           [&](int f) __attribute__((always_inline)) { F0[f] = f < TM ? fa32[f].read(nxt, 0) : fb32[f - TM].read(nxt + A_BYTES, 0); },
+                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, cs, (kt + NS) * BK, l); });
                 }
                 st = stn;
             }
-            // the assembler-level matrix instructions are invisible to the compiler's hazard
-            // checks: let the last of them retire before anything reads the accumulators
-            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+            }
+            retire();
         }
         wait_vmcnt<0>();                             // nothing of this workgroup is in flight into LDS any more
         __builtin_amdgcn_s_barrier();                // and every wave is done reading the ring
@@ -938,9 +1290,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
 
         // ---- the tile after this one ------------------------------------------------------
         TileCoord nx;
-        // (GeLU-backward has no registers to carry the next tile's offsets through its passes: it forms them where
-        // they are used, from a lane number that the compiler cannot tell from another)
-        constexpr bool LATE_BIND = EPI == EPI_DGELU && C::OCC == 1;
+        // (beside the five-unit loop there are no registers to carry the next tile's offsets through the epilogue: it forms
+        // them where they are used, from a lane number that the compiler cannot tell from another)
+        constexpr bool LATE_BIND = N64;
         AT ta2;
         BT tb2;
         auto bind_again = [&]() __attribute__((always_inline)) {
@@ -948,7 +1300,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             asm volatile("" : "+v"(l));
             bind(nx, ta2, tb2, l);
         };
-        KCursor kc2 = {0, 0, 0};
+        KCursor kc2 = {};
         int vn = -1;
         if constexpr (!ONE) {
             vn = next_tile(vb + step, nx);
@@ -957,9 +1309,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         }
 
         // ---- epilogue -----------------------------------------------------------------------
-        // An MFMA accumulator holds one row per lane (row = lane & 31, four consecutive
-        // columns per register group), which would make every global access a 8- or 16-byte
-        // piece of 32 different rows.  Each wave therefore passes its 32 x WN blocks through a
+        // An MFMA accumulator holds four consecutive columns of one row per lane (row = lane & 15,
+        // columns 4 * (lane / 16) ..; S32: row = lane & 31, four such groups), which would make every global access a 8- or 16-byte
+        // piece of 16 different rows.  Each wave therefore passes its 32 x WN blocks through a
         // private LDS region (float, 16-byte chunks XOR-swizzled by row) and picks them up
         // with eight consecutive columns per lane, so that eight lanes cover a whole line of
         // a row: all global reads and writes of the epilogue are 16 or 32 bytes per lane,
@@ -971,7 +1323,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         constexpr int CPRW = CW / 8;                 // 8-column pieces per row of a pass
         constexpr int SW = CW >= 64 ? 15 : CW / 4 - 1;       // the row bits that the 16-byte chunks of a staged row are swizzled by
         constexpr int NPIECE = 32 * CPRW / 64;       // pieces per lane
-        constexpr int NCH = WN / CW, TJ = CW / 32;   // passes per 32 rows; 32-column accumulator blocks per pass
+        constexpr int NCH = WN / CW, TJ = CW / 16;   // passes per 32 rows; 16-column accumulator blocks per pass
         constexpr int NPASS = TM * NCH;
         float* stage = reinterpret_cast<float*>(smem + C::STAGING_OFF + wid * (32 * CW * 4));
         constexpr int CES = (EPI == EPI_ACCUM_F32 || EPI == EPI_STORE_F32) ? 4 : 2;   // bytes per output element
@@ -989,7 +1341,6 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         const __amdgpu_buffer_rsrc_t rZ = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<bf16_t*>(Zbase), 0, Zbase ? (unsigned)(((size_t)(trows - 1) * g.ldz + g.N) * 2) : 0u, 0x00020000);
         const float* wbase = g.slot_w ? g.slot_w + (size_t)er * g.Cp : nullptr;
-        const int erow = lane & 31, ehalf = lane >> 5;
         // What a pass reads from memory (the pre-activation and row weight for GeLU-backward, the old
         // sums for float accumulation) is requested one pass ahead.
         constexpr bool READS = (EPI == EPI_DGELU || EPI == EPI_ACCUM_F32 || EPI == EPI_SCATTER);
@@ -1063,16 +1414,25 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             // no rows in the second half (wave-uniform; tested once, so that the scheduler sees long stretches)
             if (ALT && TM > 1 && ps == NPASS / 2 && active <= TM / 2) break;
             if constexpr (READS && PB == 1) request_pass(ps, pin[0]);
+            if constexpr (S32) {
 #pragma unroll
-            for (int jj = 0; jj < TJ; ++jj) {
-                const int j = ch * TJ + jj;
+                for (int jj = 0; jj < CW / 32; ++jj)
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    const int cch = (jj * 32 + g4 * 8 + ehalf * 4) >> 2;
-                    float4 v = make_float4(acc[i][j][g4 * 4 + 0], acc[i][j][g4 * 4 + 1], acc[i][j][g4 * 4 + 2], acc[i][j][g4 * 4 + 3]);
-                    *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & SW)) << 2)) = v;
+                    for (int g4 = 0; g4 < 4; ++g4) {
+                        const floatx16& a = acc32[i][ch * (CW / 32) + jj];
+                        const int erow = lane & 31, cch = (jj * 32 + g4 * 8 + (lane >> 5) * 4) >> 2;
+                        *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & SW)) << 2)) =
+                            make_float4(a[g4 * 4], a[g4 * 4 + 1], a[g4 * 4 + 2], a[g4 * 4 + 3]);
+                    }
+            } else
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int jj = 0; jj < TJ; ++jj) {
+                    const floatx4 a = acc[2 * i + h][ch * TJ + jj];
+                    const int erow = h * 16 + (lane & 15), cch = jj * 4 + (lane >> 4);
+                    *reinterpret_cast<float4*>(stage + erow * CW + ((cch ^ (erow & SW)) << 2)) = make_float4(a[0], a[1], a[2], a[3]);
                 }
-            }
             if constexpr (READS && PB == 2) {
                 if (ps + 1 < NPASS) request_pass(ps + 1, pin[(ps + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);   // (the scheduler would sink them to their uses)
@@ -1294,12 +1654,10 @@ void gemm_bf16_backward_kernel(BackwardArgs a) {
 }
 
 // Tile shapes in use.  The first three cover 256 x 256 per workgroup with four waves of 128 x 128, one per SIMD.
-//   CfgW   two-ring loop: NN, and NT with the GeLU-backward epilogue.  A request for half a
-//          128-byte line costs the L1 as much as one for a whole line, and the loop's speed follows
-//          the number of requests; here every request but those of NT's row operand is a whole line.
-//   CfgN   five-unit loop: NT with a plain store (the input gradient); every request is a whole line.  With the
-//          GeLU-backward epilogue it needs more registers than there are (11 spilled) and is 1 % faster on the large layer
-//          (1283 -> 1269 us), 3 % slower on mid-size ones (8 x 4096 x 4096, K = 1024: 411 -> 424).
+//   CfgW   two-ring loop: NN.  A request for half a 128-byte line costs the L1 as much as one for a whole line, and the
+//          loops' speed follows the number of requests; here every request is a whole line.
+//   CfgN   five-unit loop: NT, both epilogues; every request is a whole line.  (GeLU-backward in the two-ring loop, its rows
+//          in half lines: 1.58 us a step against 1.39, 32 768 rows x 8192, K = 2048.)
 //   Cfg4   ring of 5 x 32 k: the weight-gradient GEMMs (TN), whose two operands are N-contiguous
 //          and come in whole lines anyway.
 // (Shapes with two waves of 128 x 64 per SIMD - TileCfg<256, 256, 32, 5, 2, 4, 2, LOOP_PIPE32> - ran the GeLU
@@ -1309,7 +1667,7 @@ typedef TileCfg<256, 256, 32, 5, 2, 2, 1, LOOP_PIPE32> Cfg4;
 typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_W64> CfgW;
 typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_N64> CfgN;
 template <int LAY, int EPI> struct CfgFor { typedef CfgW type; };
-template <> struct CfgFor<GEMM_NT, EPI_STORE> { typedef CfgN type; };
+template <int EPI> struct CfgFor<GEMM_NT, EPI> { typedef CfgN type; };
 template <int EPI> struct CfgFor<GEMM_TN, EPI> { typedef Cfg4 type; };
 // Smaller tiles for launches that 256 x 256 leaves too few of, all layouts (the flat one: NN, NT):
 //   CfgM   256 x 128, waves of 128 x 64, three 64-k stages of both operands, so that every request is a whole line.
