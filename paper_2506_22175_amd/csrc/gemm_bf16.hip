@@ -108,7 +108,6 @@ struct TileCfg {
     static constexpr int RB = WM / 16, NB = WN / 16;     // its blocks of 16 rows and of 16 columns
     static constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
     static constexpr int LDS_BYTES = LOOP == LOOP_W64 || LOOP == LOOP_N64 ? 160 * 1024 : NS * STAGE_BYTES;
-    static constexpr bool PIPE = LOOP == LOOP_PIPE32;
     // columns of a wave's block that pass through the staging region at a time, and where that region starts
     static constexpr int CW = WN < 64 || (LOOP == LOOP_PIPE32 && OCC == 1) ? WN : LOOP == LOOP_R64 && OCC == 2 ? 32 : 64;
     static constexpr int SBR = (WAVES * 32 * CW * 4 + STAGE_BYTES - 1) / STAGE_BYTES;      // stages that region takes
@@ -124,36 +123,37 @@ struct TileCfg {
 
 // ---- K-contiguous operand tile: R rows x BK k ---------------------------------------
 // A row is CPR = BK/8 chunks of 16 bytes.  LDS byte of (row, chunk c) =
-// row*ROWB + ((c ^ sw(row)) << 4).  A ds_read_b128 serves the lanes 0-3, 12-15, 20-27 of a half
-// wave together, then the other sixteen; of a fragment (16 rows, two chunks per half wave) those are
-// the rows 0-3 and 12-15 of one chunk and 4-11 of the next one, and sw puts them into 16 different
-// 16-byte bank groups (64 banks of 4 bytes).  (With a swizzle that does so for 16 lanes in
-// succession only, 40 % of the LDS cycles of an NT launch were conflicts; S32: a fragment is 32 rows of one chunk per half wave, and
-// sixteen lanes in succession it is.)  One wave instruction
-// fills 1024 bytes = RPI rows: lane l -> row RPI*q + l/CPR, physical chunk l%CPR.
+// row*ROWB + ((c ^ sw(row)) << 4), with sw by the rows that a ds_read_b128 serves together, so that they fall into 16
+// different 16-byte bank groups (64 banks of 4 bytes).  A fragment of the 32 x 32 instruction (S32) is 32 rows of one chunk per half wave,
+// and sixteen rows in succession are served together.  One of the 16 x 16 instruction is 16 rows, two chunks per half wave, of which the
+// lanes 0-3, 12-15, 20-27 are served together, then the other sixteen: the rows 0-3 and 12-15 of one chunk and 4-11 of the next one.
+// (With the former's swizzle 40 % of the LDS cycles of an NT launch in 256 x 256 were conflicts.)  One wave instruction fills 1024
+// bytes = RPI rows: lane l -> row RPI*q + l/CPR, physical chunk l%CPR.
 template <int R, int WAVES, int BK, bool S32>
-struct KCTile {
+struct KCRows {
     static constexpr int ROWB = BK * 2;
     static constexpr int CPR = BK / 8;
     static constexpr int RPI = 1024 / ROWB;
     static constexpr int NI = R / RPI / WAVES;         // load instructions per wave per tile
     static constexpr int BYTES = R * ROWB;
+    static constexpr int READS = 1;                    // LDS reads per fragment
     static_assert(R % (RPI * WAVES) == 0 && NI >= 1, "rows must divide over the wavefronts");
+    static_assert((NI & (NI - 1)) == 0, "wid*NI + j is wid*NI ^ j");
+    static_assert(S32 || CPR == 8, "the 16 x 16 instruction's units are 64 k deep");
     static __device__ __forceinline__ int sw(int row) {
         if (S32) return CPR == 8 ? (row ^ (row >> 3)) & 7 : (row >> 2) & 3;
-        return CPR == 8 ? (row >> 1) & 7 : ((row >> 2) & 3) ^ ((row >> 1) & 2);
+        return (row >> 1) & 7;
     }
     v4i rsrc;
     unsigned voff[NI];       // byte offset of this lane's chunk at k0 = 0
-    // First k of this lane's chunk in load j (loads of consecutive j lie eight rows of eight chunks apart, which the swizzle turns
-    // into one bit of the chunk number; S32: into the number).
-    int kc0;
-    static_assert((NI & (NI - 1)) == 0, "wid*NI + j is wid*NI ^ j");
+    int kc0;                 // first k of this lane's chunk in load 0
+    int K;
+    // ... in load j: loads of consecutive j lie eight rows of eight chunks apart, which the swizzle turns into the chunk number (S32) or
+    // into one bit of it, or sixteen rows of four, which it does not see.
     __device__ __forceinline__ int first_k(int j) const { return CPR == 8 ? kc0 ^ (S32 ? 8 * j : 32 * (j & 1)) : kc0; }
     __device__ __forceinline__ void init_kc(int lane, int wid) {
         kc0 = ((lane % CPR) ^ sw(wid * NI * RPI + lane / CPR)) * 8;
     }
-    int K;
     // P: operand base of this expert; rows [row0, row_limit) x [0, K) are valid
     __device__ __forceinline__ void init(const bf16_t* P, int ld, int row0, int row_limit, int K_, int lane, int wid) {
         const int valid = min(R, row_limit - row0);
@@ -185,50 +185,67 @@ struct KCTile {
             voff[j] = src >= 0 ? (unsigned)(src * ld + c * 8) * 2u : OOB_OFFSET;
         }
     }
-    // Loads of the tile at k0: voff[j] + koff(k0) to dst(tile) + 1024 * j.  Before the first of them end_at switches off the
-    // lanes that lie beyond K, for this tile and all later ones (tiles are requested in ascending order).
-    __device__ __forceinline__ unsigned koff(int k0) const { return (unsigned)k0 * 2u; }
-    __device__ __forceinline__ void end_at(int k0) {
-        if (k0 + BK > K) {                               // wave-uniform, and true of the last tiles only
-            asm volatile("" ::: "memory");               // (a branch, not eight selections)
-#pragma unroll
-            for (int j = 0; j < NI; ++j) voff[j] = (k0 + first_k(j) < K) ? voff[j] : OOB_OFFSET;
-        }
-    }
-    static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
-    // S32: a load at once, its lanes switched off as it goes
+};
+
+// for the 32 x 32 instruction
+template <int R, int WAVES, int BK>
+struct KCTile : KCRows<R, WAVES, BK, true> {
+    typedef KCRows<R, WAVES, BK, true> Rows;
+    using Rows::ROWB;
+    using Rows::NI;
     __device__ __forceinline__ void load_one(char* tile, int k0, int wid, int j) const {
-        unsigned off = voff[j] + (unsigned)k0 * 2u;
+        unsigned off = this->voff[j] + (unsigned)k0 * 2u;
         // only a tile that reaches beyond K (a wave-uniform condition) has lanes to switch off
-        if (k0 + BK > K) off = (k0 + first_k(j) < K) ? off : OOB_OFFSET;
-        load_to_lds(rsrc, lds_address(tile) + (wid * NI + j) * 1024, off);
+        if (k0 + BK > this->K) off = (k0 + this->first_k(j) < this->K) ? off : OOB_OFFSET;
+        load_to_lds(this->rsrc, lds_address(tile) + (wid * NI + j) * 1024, off);
     }
-    // S32: fragment of the 32 rows starting at rb: lane reads row rb + lane%32, k = 16*kk + 8*(lane/32) .. +7
-    struct Frag32 {
+    // fragment of the 32 rows starting at rb: lane reads row rb + lane%32, k = 16*kk + 8*(lane/32) .. +7
+    typedef bf16x8 Value;
+    struct Frag {
         int addr;    // byte address inside the tile for kk = 0
         __device__ __forceinline__ void init(int rb, int lane) {
             const int row = rb + (lane & 31);
-            addr = row * ROWB + (((lane >> 5) ^ sw(row)) << 4);
+            addr = row * ROWB + (((lane >> 5) ^ Rows::sw(row)) << 4);
         }
         __device__ __forceinline__ bf16x8 read(const char* tile, int kk) const {
             return *reinterpret_cast<const bf16x8*>(tile + (addr ^ (kk << 5)));
         }
     };
+    template <int BLOCKS16> using Frags = Frag[BLOCKS16 / 2];
+};
+
+// for the 16 x 16 instruction
+template <int R, int WAVES, int BK>
+struct KCTile16 : KCRows<R, WAVES, BK, false> {
+    typedef KCRows<R, WAVES, BK, false> Rows;
+    using Rows::ROWB;
+    using Rows::CPR;
+    using Rows::NI;
+    // Loads of the tile at k0: voff[j] + koff(k0) to dst(tile) + 1024 * j.  Before the first of them end_at switches off the
+    // lanes that lie beyond K, for this tile and all later ones (tiles are requested in ascending order).
+    __device__ __forceinline__ unsigned koff(int k0) const { return (unsigned)k0 * 2u; }
+    __device__ __forceinline__ void end_at(int k0) {
+        if (k0 + BK > this->K) {                         // wave-uniform, and true of the last tiles only
+            asm volatile("" ::: "memory");               // (a branch, not eight selections)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) this->voff[j] = (k0 + this->first_k(j) < this->K) ? this->voff[j] : OOB_OFFSET;
+        }
+    }
+    static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
     // fragments of 16 rows x 32 k: of the rows rb + d .. rb + d + 15 a lane reads row lane%16, k = 32*kk + 8*(lane/16) .. +7.
     // rb and d are multiples of 16, which the swizzle does not see.
     // at: LDS addresses, one for each kk; fragments are constant offsets from them.
-    template <int BLOCKS> struct Frag {
-        static constexpr int READS = 1;                  // LDS reads per fragment; `part` is the number of one of them
+    struct Value {
+        bf16x8 v;
+        __device__ __forceinline__ bf16x8 all() const { return v; }
+    };
+    template <int BLOCKS> struct Frags {
         unsigned at[CPR / 4];
         template <typename D> __device__ __forceinline__ void init(unsigned tile, int rb, int lane, D&&) {
             const int row = rb + (lane & 15);
 #pragma unroll
-            for (int kk = 0; kk < CPR / 4; ++kk) at[kk] = tile + row * ROWB + (((4 * kk + (lane >> 4)) ^ sw(row)) << 4);
+            for (int kk = 0; kk < CPR / 4; ++kk) at[kk] = tile + row * ROWB + (((4 * kk + (lane >> 4)) ^ Rows::sw(row)) << 4);
         }
-        struct Value {
-            bf16x8 v;
-            __device__ __forceinline__ bf16x8 all() const { return v; }
-        };
         // fragment i, of the rows from rb + d on, in the tile `off` bytes behind the one that init was told
         __device__ __forceinline__ void read(Value& f, int, int d, int kk, int, unsigned off) const {
             f.v = *(lds_bf16x8*)(uintptr_t)(at[kk] + off + d * ROWB);
@@ -237,26 +254,24 @@ struct KCTile {
 };
 
 // ---- N-contiguous operand tile: BK k rows x R n --------------------------------------
-// LDS byte of (k, 16-byte unit u) = k*PITCH + ((u ^ turn(k)) << 4): the eight k rows (k, k+1, k+2, k+3 and those
-// eight further on) of which half a wave's transposing read takes two units each fall into different banks (64 banks
-// of 4 bytes).  (S32: four k rows and four units each, ((u + 4*(k&3)) % UPR) << 4.)  One wave instruction fills 1024 bytes = RPI
-// rows: lane l -> row RPI*q + l/UPR, unit l%UPR.
+// LDS byte of (k, 16-byte unit u) = k*PITCH + (place of u in row k << 4), so that the k rows that half a wave's transposing read
+// touches fall into different banks (64 banks of 4 bytes).  32 x 32 instruction (S32): four k rows, four units each, rotated by
+// four units: (u + 4*(k&3)) % UPR.  16 x 16: eight (k, k+1, k+2, k+3 and those eight further on), two units each: u ^ turn(k).
+// One wave instruction fills 1024 bytes = RPI rows: lane l -> row RPI*q + l/UPR, place l%UPR.
 template <int R, int WAVES, int BK, bool S32>
-struct NCTile {
+struct NCRows {
     static constexpr int PITCH = R * 2;                // bytes per k row
     static constexpr int UPR = R / 8;                  // 16-byte units per row
     static constexpr int RPI = 1024 / PITCH;           // rows per wave instruction
     static constexpr int NI = BK / RPI / WAVES;
     static constexpr int BYTES = BK * PITCH;
+    static constexpr int READS = 2;                    // LDS reads per fragment
     static_assert(BK % (RPI * WAVES) == 0 && NI >= 1, "rows must divide over the wavefronts");
-    static_assert(UPR >= 16 || UPR == 8, "the turns of eight k rows must fit a row of units (or two rows)");
-    static __device__ __forceinline__ int turn(int k) {
-        return (UPR >= 16 ? 4 * (k & 3) : 4 * ((k >> 1) & 1)) + 2 * ((k >> 3) & 1);
-    }
+    static_assert(UPR >= 16 || (S32 && UPR == 8), "the turns of the k rows must fit a row of units (S32: or two)");
+    static __device__ __forceinline__ int turn(int k) { return 4 * (k & 3) + 2 * ((k >> 3) & 1); }
     v4i rsrc;
     unsigned voff[NI];
     unsigned kstep;          // bytes per k row in memory
-    int K, row0;             // k rows; this lane's row in load 0
     // descriptor of rows [0, K) x columns [0, n_valid) of the matrix at P
     static __device__ __forceinline__ v4i rsrc_of(const bf16_t* P, int ld, int n_valid, int K) {
         return make_rsrc(P, K > 0 ? (unsigned)(((size_t)(K - 1) * ld + n_valid) * 2) : 0u);
@@ -265,8 +280,6 @@ struct NCTile {
     __device__ __forceinline__ void init(const bf16_t* P, int ld, int n0, int n_limit, int K, int lane, int wid) {
         const int n_valid = n_limit - n0;
         kstep = (unsigned)ld * 2u;
-        this->K = K;
-        row0 = wid * NI * RPI + lane / UPR;
         rsrc = rsrc_of(P + n0, ld, n_valid, K);
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
@@ -276,22 +289,24 @@ struct NCTile {
             voff[j] = (u * 8 < n_valid) ? (unsigned)(row * ld + u * 8) * 2u : OOB_OFFSET;
         }
     }
-    __device__ __forceinline__ unsigned koff(int k0) const { return (unsigned)k0 * kstep; }
-    __device__ __forceinline__ void end_at(int k0) {
-        if (k0 + BK > K) {
-            asm volatile("" ::: "memory");
-#pragma unroll
-            for (int j = 0; j < NI; ++j) voff[j] = (k0 + row0 + j * RPI < K) ? voff[j] : OOB_OFFSET;
-        }
-    }
-    static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
-    // S32: a load at once (the descriptor ends at the last row)
+};
+
+// for the 32 x 32 instruction
+template <int R, int WAVES, int BK>
+struct NCTile : NCRows<R, WAVES, BK, true> {
+    typedef NCRows<R, WAVES, BK, true> Rows;
+    using Rows::PITCH;
+    using Rows::UPR;
+    using Rows::NI;
+    // (the descriptor ends at the last row)
     __device__ __forceinline__ void load_one(char* tile, int k0, int wid, int j) const {
-        load_to_lds(rsrc, lds_address(tile) + (wid * NI + j) * 1024, voff[j] + (unsigned)k0 * kstep);
+        load_to_lds(this->rsrc, lds_address(tile) + (wid * NI + j) * 1024, this->voff[j] + (unsigned)k0 * this->kstep);
     }
-    // S32: fragment of the 32 columns starting at nb: two transposing reads give the lane n = nb + lane%32, k = 16*kk +
-    // 8*(lane/32) .. +7, as below.
-    struct Frag32 {
+    // fragment of the 32 columns starting at nb: two transposing reads give the lane n = nb + lane%32, k = 16*kk +
+    // 8*(lane/32) .. +7.  In a 16-lane group lane a points at row a/4, columns 4*(a%4)..+3; the hardware returns to lane i
+    // four k of column i.
+    typedef bf16x8 Value;
+    struct Frag {
         int addr;
         __device__ __forceinline__ void init(int nb, int lane) {
             const int g = lane >> 4, a = lane & 15;
@@ -301,34 +316,60 @@ struct NCTile {
         }
         __device__ __forceinline__ bf16x8 read(const char* tile, int kk) const {
             const char* p = tile + addr + kk * 16 * PITCH;
-            const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
-            const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * PITCH));
+            v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)p);
+            v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(p + 4 * PITCH));
+            typedef short v8s __attribute__((ext_vector_type(8)));
+            v8s both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            return __builtin_bit_cast(bf16x8, both);
+        }
+    };
+    template <int BLOCKS16> using Frags = Frag[BLOCKS16 / 2];
+};
+
+// for the 16 x 16 instruction
+template <int R, int WAVES, int BK>
+struct NCTile16 : NCRows<R, WAVES, BK, false> {
+    typedef NCRows<R, WAVES, BK, false> Rows;
+    using Rows::PITCH;
+    using Rows::UPR;
+    using Rows::RPI;
+    using Rows::NI;
+    int K, row0;             // k rows; this lane's row in load 0
+    __device__ __forceinline__ void init(const bf16_t* P, int ld, int n0, int n_limit, int K, int lane, int wid) {
+        Rows::init(P, ld, n0, n_limit, K, lane, wid);
+        this->K = K;
+        row0 = wid * NI * RPI + lane / UPR;
+    }
+    // as for K-contiguous operands
+    __device__ __forceinline__ unsigned koff(int k0) const { return (unsigned)k0 * this->kstep; }
+    __device__ __forceinline__ void end_at(int k0) {
+        if (k0 + BK > K) {
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int j = 0; j < NI; ++j) this->voff[j] = (k0 + row0 + j * RPI < K) ? this->voff[j] : OOB_OFFSET;
+        }
+    }
+    static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
+    // fragments of 16 columns x 32 k: two transposing reads give the lane column nb + d + lane%16, k = 32*kk +
+    // 8*(lane/16) .. +7.  nb and d have no bits in common, so that d turns into an exclusive or: an address each.
+    struct Value {
+        v4s lo, hi;
+        __device__ __forceinline__ bf16x8 all() const {
             typedef short v8s __attribute__((ext_vector_type(8)));
             const v8s both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             return __builtin_bit_cast(bf16x8, both);
         }
     };
-    // fragments of 16 columns x 32 k: two transposing reads give the lane column nb + d + lane%16, k = 32*kk +
-    // 8*(lane/16) .. +7.  In a 16-lane group lane a points at row a/4, columns 4*(a%4)..+3; the hardware returns to
-    // lane i four k of column i.  nb and d have no bits in common, so that d turns into an exclusive or: an address each.
-    template <int BLOCKS> struct Frag {
-        static constexpr int READS = 2;
+    template <int BLOCKS> struct Frags {
         unsigned at[BLOCKS];
         template <typename D> __device__ __forceinline__ void init(unsigned tile, int nb, int lane, D&& d) {
             const int g = lane >> 4, a = lane & 15;
             const int k_in = 8 * g + (a >> 2);
             const int n = nb + 4 * (a & 3);
 #pragma unroll
-            for (int i = 0; i < BLOCKS; ++i) at[i] = tile + ((k_in * PITCH + (((n >> 3) ^ turn(k_in)) << 4) + ((n & 7) << 1)) ^ (d(i) << 1));
+            for (int i = 0; i < BLOCKS; ++i) at[i] = tile + ((k_in * PITCH + (((n >> 3) ^ Rows::turn(k_in)) << 4) + ((n & 7) << 1)) ^ (d(i) << 1));
         }
-        struct Value {
-            v4s lo, hi;
-            __device__ __forceinline__ bf16x8 all() const {
-                typedef short v8s __attribute__((ext_vector_type(8)));
-                const v8s both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                return __builtin_bit_cast(bf16x8, both);
-            }
-        };
+        // part (0 or 1) of fragment i
         __device__ __forceinline__ void read(Value& f, int i, int, int kk, int part, unsigned off) const {
             const unsigned p = at[i] + off + kk * 32 * PITCH;
             if (part == 0) f.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)p);
@@ -337,10 +378,10 @@ struct NCTile {
     };
 };
 
-template <int LAY, int R, int W, int BK, bool S> struct ATile { typedef KCTile<R, W, BK, S> type; };
-template <int R, int W, int BK, bool S> struct ATile<GEMM_TN, R, W, BK, S> { typedef NCTile<R, W, BK, S> type; };
-template <int LAY, int R, int W, int BK, bool S> struct BTile { typedef NCTile<R, W, BK, S> type; };
-template <int R, int W, int BK, bool S> struct BTile<GEMM_NT, R, W, BK, S> { typedef KCTile<R, W, BK, S> type; };
+// the operands' tiles of a layout, for either instruction
+template <bool KC, bool S32, int R, int W, int BK>
+using OperandTile = std::conditional_t<KC, std::conditional_t<S32, KCTile<R, W, BK>, KCTile16<R, W, BK>>,
+                                       std::conditional_t<S32, NCTile<R, W, BK>, NCTile16<R, W, BK>>>;
 
 struct Unit8 {
     static __device__ __forceinline__ void to_float(const uint4& u, float* o) {
@@ -417,12 +458,13 @@ __device__ __forceinline__ void mfma32_pinned(floatx16& acc, const bf16x8& a, co
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b) : "memory");
 }
 
-// Which tile of both operands is being requested: its first k, among the K of its row range, and its byte offsets in the
-// operands.  TN only: the reduction dimension may run over the rows of several partitions (up to MAX_KSEGS row ranges, one per
-// partition buffer); tiles of 32 k never straddle two ranges, and seg says which range it is.
+// Which tile of both operands is being requested.  TN only: the reduction dimension may run over the rows of several
+// partitions (up to MAX_KSEGS row ranges, one per partition buffer); tiles never straddle two ranges, and seg says
+// which range it is.
 constexpr int MAX_KSEGS = 8;
 struct TileCoord { int e, q, er, tn, m0, n0, Mdim, Kdim, KT; };      // expert, partition of the launch, their place in row arrays
-struct KCursor { int seg, k0, K; unsigned ka, kb; };       // (S32: k0 and K in tiles, the offsets unused)
+struct KCursor { int seg, k0, K; unsigned ka, kb; };       // its first k, among the K of its range; its byte offsets in the operands
+struct KCursor32 { int seg, jl, tiles; };                  // S32, several ranges: its number, among the tiles of its range
 
 // Numbers of the tiles of a launch.  Only tiles that exist are numbered: an expert with fewer rows than the capacity
 // has fewer tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups, which take
@@ -505,9 +547,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     const int tid = threadIdx.x, lane = tid & 63;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wid / C::WAVES_N, wn = wid % C::WAVES_N;
-    typedef typename ATile<LAY, BM, C::WAVES, AK, C::S32>::type AT;
-    typedef typename BTile<LAY, BN, C::WAVES, BKB, C::S32>::type BT;
+    typedef OperandTile<LAY != GEMM_TN, S32, BM, C::WAVES, AK> AT;
+    typedef OperandTile<LAY == GEMM_NT, S32, BN, C::WAVES, BKB> BT;
     constexpr int LPW = AT::NI + BT::NI;         // loads per wave per tile
+    typedef std::conditional_t<S32, KCursor32, KCursor> Cursor;
     // Where two workgroups share a CU the operands' offsets and descriptors are formed again at the top of a
     // tile (the other workgroup covers that) instead of being carried from the one before: with 128 registers
     // for accumulators and fragments the compiler otherwise moves descriptors into vector registers, which the
@@ -517,40 +560,38 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     // with few rows left needs only the first blocks of every wave (see `active` below).
     constexpr int ROW_STEP = ALT ? 32 * C::WAVES_M : 32;
     auto block_row = [&](int i) __attribute__((always_inline)) { return ALT ? i * ROW_STEP + wm * 32 : wm * WM + i * 32; };
-    typename AT::template Frag<RB> fa;
-    typename BT::template Frag<NB> fb;
+    typename AT::template Frags<RB> fa;
+    typename BT::template Frags<NB> fb;
+    typedef typename AT::Value FA;
+    typedef typename BT::Value FB;
+    constexpr int AR = AT::READS, BR = BT::READS;
     auto dist_a = [](int i) __attribute__((always_inline)) { return (i >> 1) * ROW_STEP + (i & 1) * 16; };     // of a block of 16 rows from the first
     auto dist_b = [](int j) __attribute__((always_inline)) { return j * 16; };
     const unsigned lds0 = lds_address(smem);
-    // addresses in the operands' tiles that begin at these LDS addresses
-    auto frags_at = [&](unsigned a, unsigned b) __attribute__((always_inline)) {
-        int l = lane;                                    // (formed for every tile: there are no registers to keep them in through an epilogue)
-        if constexpr (QUAD || W64 || N64) asm volatile("" : "+v"(l));
-        fa.init(a, block_row(0), l, dist_a);
-        fb.init(b, wn * WN, l, dist_b);
-        if constexpr (QUAD || W64) {
-#pragma unroll
-            for (unsigned& at : fa.at) asm volatile("" : "+v"(at));
-#pragma unroll
-            for (unsigned& at : fb.at) asm volatile("" : "+v"(at));
-        }
-    };
-    typename AT::Frag32 fa32[TM];
-    typename BT::Frag32 fb32[TNN];
     if constexpr (S32) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa32[i].init(block_row(i), lane);
+        for (int i = 0; i < TM; ++i) fa[i].init(block_row(i), lane);
 #pragma unroll
-        for (int j = 0; j < TNN; ++j) fb32[j].init(wn * WN + j * 32, lane);
-    } else if constexpr (!QUAD && !W64 && !N64) frags_at(lds0, lds0 + A_BYTES);     // (the 256 x 256 loops move theirs along)
+        for (int j = 0; j < TNN; ++j) fb[j].init(wn * WN + j * 32, lane);
+    }
+    // 256 x 256: addresses in the operands' tiles that begin at these LDS addresses (the loops move them along)
+    auto frags_at = [&](unsigned a, unsigned b) __attribute__((always_inline)) {
+        if constexpr (!S32) {
+            int l = lane;                                // (formed for every tile: there are no registers to keep them in through an epilogue)
+            asm volatile("" : "+v"(l));
+            fa.init(a, block_row(0), l, dist_a);
+            fb.init(b, wn * WN, l, dist_b);
+            if constexpr (!N64) {
+#pragma unroll
+                for (unsigned& at : fa.at) asm volatile("" : "+v"(at));
+#pragma unroll
+                for (unsigned& at : fb.at) asm volatile("" : "+v"(at));
+            }
+        }
+    };
     // fragment of the wave's block i of 16 rows / j of 16 columns, read in one part or two
-    typedef decltype(fa) TA;
-    typedef decltype(fb) TB;
-    typedef typename TA::Value FA;
-    typedef typename TB::Value FB;
-    constexpr int AR = TA::READS, BR = TB::READS;
-    auto frag_a = [&](FA& f, unsigned off, int i, int kk, int part) __attribute__((always_inline)) { fa.read(f, i, dist_a(i), kk, part, off); };
-    auto frag_b = [&](FB& f, unsigned off, int j, int kk, int part) __attribute__((always_inline)) { fb.read(f, j, dist_b(j), kk, part, off); };
+    auto frag_a = [&](FA& f, unsigned off, int i, int kk, int part) __attribute__((always_inline)) { if constexpr (!S32) fa.read(f, i, dist_a(i), kk, part, off); };
+    auto frag_b = [&](FB& f, unsigned off, int j, int kk, int part) __attribute__((always_inline)) { if constexpr (!S32) fb.read(f, j, dist_b(j), kk, part, off); };
     auto whole_a = [&](FA& f, unsigned off, int i, int kk) __attribute__((always_inline)) {
 #pragma unroll
         for (int q = 0; q < AR; ++q) frag_a(f, off, i, kk, q);
@@ -654,73 +695,76 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         return rows;
     };
     // The tile the cursor is at reaches beyond its K: into the next range with rows, or the lanes beyond K switched off.
-    auto enter = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
-        if constexpr (LAY == GEMM_TN) {
-            if (g.k_segs > 1) {
-                while (kc_.k0 >= kc_.K && kc_.seg < g.k_segs) {
-                    ++kc_.seg;
-                    kc_.k0 = 0;
-                    kc_.ka = kc_.kb = 0;
-                    kc_.K = bind_range(tc, kc_.seg, ta_, tb_);
-                }
-            }
-        }
-        if (kc_.k0 + BK > kc_.K) {
-            ta_.end_at(kc_.k0);
-            tb_.end_at(kc_.k0);
-        }
-    };
-    auto start = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
-        kc_ = {-1, 0, LAY == GEMM_TN && g.k_segs > 1 ? 0 : ta_.K, 0, 0};
-        if (BK > kc_.K) enter(tc, kc_, ta_, tb_);
-    };
-    // on to the next tile (before its first load; a handful of scalar instructions, in the shadow of a matrix instruction)
-    auto advance = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
-        kc_.k0 += BK;
-        kc_.ka += ta_.koff(BK);
-        kc_.kb += tb_.koff(BK);
-        if (kc_.k0 + BK > kc_.K) enter(tc, kc_, ta_, tb_);
-    };
-    // The byte offsets into scalar registers, where the compiler does not keep them: a load may follow five wait states later.
-    auto settle = [&](KCursor& kc_) __attribute__((always_inline)) {
-        kc_.ka = __builtin_amdgcn_readfirstlane(kc_.ka);
-        kc_.kb = __builtin_amdgcn_readfirstlane(kc_.kb);
-        asm volatile("" : "+s"(kc_.ka), "+s"(kc_.kb) : : "memory");
-    };
-    // its load l, to the LDS address in m0
-    auto go = [&](const KCursor& kc_, const AT& ta_, const BT& tb_, int l) __attribute__((always_inline)) {
-        if (l < AT::NI) load_to_destination(ta_.rsrc, ta_.voff[l], kc_.ka);
-        else load_to_destination(tb_.rsrc, tb_.voff[l - AT::NI], kc_.kb);
-    };
-    // S32: load l of the tile that starts at k0; the cursor moves on with load 0
-    auto request32 = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
-        if constexpr (LAY == GEMM_TN) {
-            if (g.k_segs > 1) {
-                if (l == 0) {
-                    if (k0 == 0) { kc_.seg = -1; kc_.k0 = 0; kc_.K = 0; } else ++kc_.k0;
-                    while (kc_.k0 >= kc_.K) {
+    auto enter = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        if constexpr (!S32) {
+            if constexpr (LAY == GEMM_TN) {
+                if (g.k_segs > 1) {
+                    while (kc_.k0 >= kc_.K && kc_.seg < g.k_segs) {
                         ++kc_.seg;
                         kc_.k0 = 0;
-                        const int rows = bind_range(tc, kc_.seg, ta_, tb_);
-                        kc_.K = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
+                        kc_.ka = kc_.kb = 0;
+                        kc_.K = bind_range(tc, kc_.seg, ta_, tb_);
                     }
                 }
-                k0 = kc_.k0 * BK;
+            }
+            if (kc_.k0 + BK > kc_.K) {
+                ta_.end_at(kc_.k0);
+                tb_.end_at(kc_.k0);
             }
         }
-        if (l < AT::NI) ta_.load_one(st, k0, wid, l);
-        else tb_.load_one(st + A_BYTES, k0, wid, l - AT::NI);
     };
-    // loads l0 to l1 - 1 at once, of the tile that starts at k0 (tiles in ascending order, each begun with load 0)
-    auto request = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l0, int l1) __attribute__((always_inline)) {
-        if constexpr (S32) {
-#pragma unroll
-            for (int l = l0; l < l1; ++l) request32(tc, kc_, ta_, tb_, st, k0, l);
-            return;
+    auto start = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        if constexpr (!S32) {
+            kc_ = {-1, 0, LAY == GEMM_TN && g.k_segs > 1 ? 0 : ta_.K, 0, 0};
+            if (BK > kc_.K) enter(tc, kc_, ta_, tb_);
         }
-        if (l0 == 0) { if (k0 == 0) start(tc, kc_, ta_, tb_); else advance(tc, kc_, ta_, tb_); }
-#pragma unroll
-        for (int l = l0; l < l1; ++l) {
+    };
+    // on to the next tile (before its first load; a handful of scalar instructions, in the shadow of a matrix instruction)
+    auto advance = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        if constexpr (!S32) {
+            kc_.k0 += BK;
+            kc_.ka += ta_.koff(BK);
+            kc_.kb += tb_.koff(BK);
+            if (kc_.k0 + BK > kc_.K) enter(tc, kc_, ta_, tb_);
+        }
+    };
+    // The byte offsets into scalar registers, where the compiler does not keep them: a load may follow five wait states later.
+    auto settle = [&](Cursor& kc_) __attribute__((always_inline)) {
+        if constexpr (!S32) {
+            kc_.ka = __builtin_amdgcn_readfirstlane(kc_.ka);
+            kc_.kb = __builtin_amdgcn_readfirstlane(kc_.kb);
+            asm volatile("" : "+s"(kc_.ka), "+s"(kc_.kb) : : "memory");
+        }
+    };
+    // its load l, to the LDS address in m0
+    auto go = [&](const Cursor& kc_, const AT& ta_, const BT& tb_, int l) __attribute__((always_inline)) {
+        if constexpr (!S32) {
+            if (l < AT::NI) load_to_destination(ta_.rsrc, ta_.voff[l], kc_.ka);
+            else load_to_destination(tb_.rsrc, tb_.voff[l - AT::NI], kc_.kb);
+        }
+    };
+    // load l of the tile that starts at k0 (tiles in ascending order, each begun with load 0).  S32: the cursor moves on with
+    // load 0, into the next range with rows where the last one is used up, and past the last range, where everything reads as zeros
+    auto request = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
+        if constexpr (S32) {
+            if constexpr (LAY == GEMM_TN) {
+                if (g.k_segs > 1) {
+                    if (l == 0) {
+                        if (k0 == 0) { kc_.seg = -1; kc_.jl = 0; kc_.tiles = 0; } else ++kc_.jl;
+                        while (kc_.jl >= kc_.tiles) {
+                            ++kc_.seg;
+                            kc_.jl = 0;
+                            const int rows = bind_range(tc, kc_.seg, ta_, tb_);
+                            kc_.tiles = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
+                        }
+                    }
+                    k0 = kc_.jl * BK;
+                }
+            }
+            if (l < AT::NI) ta_.load_one(st, k0, wid, l);
+            else tb_.load_one(st + A_BYTES, k0, wid, l - AT::NI);
+        } else {
+            if (l == 0) { if (k0 == 0) start(tc, kc_, ta_, tb_); else advance(tc, kc_, ta_, tb_); }
             if (l < AT::NI) load_to_lds(ta_.rsrc, AT::dst(st, wid) + l * 1024, ta_.voff[l] + kc_.ka);
             else load_to_lds(tb_.rsrc, BT::dst(st + A_BYTES, wid) + (l - AT::NI) * 1024, tb_.voff[l - AT::NI] + kc_.kb);
         }
@@ -746,7 +790,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     constexpr int UL = N64 ? 8 : 0;
     static_assert(!N64 || (AT::NI == 8 && BT::NI == 8), "eight loads per wave and unit");
     // the part of a tile's first loads that does not touch the staging region, and the rest
-    auto issue_early = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
+    auto issue_early = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
             // what the loop expects to be on its way when it starts: wide units 0 and 1 and the first
             // quarter of unit 2 (late: its slot is the staging region), narrow tiles 0..2 and half of tile 3
@@ -766,22 +810,30 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         } else {
             constexpr int FIRST = R64 ? 0 : SB, STAGES = R64 ? NS - C::SBR : NS - SB;
 #pragma unroll
-            for (int s = 0; s < STAGES; ++s) request(tc, kc_, ta_, tb_, smem + (FIRST + s) * STAGE, s * BK, 0, LPW);
+            for (int s = 0; s < STAGES; ++s)
+#pragma unroll
+                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (FIRST + s) * STAGE, s * BK, l);
         }
     };
-    auto issue_late = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
+    auto issue_late = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
             load_unit(ta_, wide_slot(2), 128, 0, WL / 4);
         } else if constexpr (N64) {
             load_unit(tb_, wide_slot(4), 128, 0, UL / 4);
         } else if constexpr (R64) {
 #pragma unroll
-            for (int s = NS - C::SBR; s < NS - 1; ++s) request(tc, kc_, ta_, tb_, smem + s * STAGE, s * BK, 0, LPW);
-            request(tc, kc_, ta_, tb_, smem + (NS - 1) * STAGE, (NS - 1) * BK, 0, R64_G3);
+            for (int s = NS - C::SBR; s < NS - 1; ++s)
+#pragma unroll
+                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + s * STAGE, s * BK, l);
+#pragma unroll
+            for (int l = 0; l < R64_G3; ++l) request(tc, kc_, ta_, tb_, smem + (NS - 1) * STAGE, (NS - 1) * BK, l);
         } else {
 #pragma unroll
-            for (int s = NS - SB; s < NS - 1; ++s) request(tc, kc_, ta_, tb_, smem + (SB + s - NS) * STAGE, s * BK, 0, LPW);
-            request(tc, kc_, ta_, tb_, smem + (SB - 1) * STAGE, (NS - 1) * BK, 0, PIPE_EARLY);
+            for (int s = NS - SB; s < NS - 1; ++s)
+#pragma unroll
+                for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (SB + s - NS) * STAGE, s * BK, l);
+#pragma unroll
+            for (int l = 0; l < PIPE_EARLY; ++l) request(tc, kc_, ta_, tb_, smem + (SB - 1) * STAGE, (NS - 1) * BK, l);
         }
     };
 
@@ -791,7 +843,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     AT ta;
     BT tb;
     bind(cur, ta, tb, lane);
-    KCursor kc = {};
+    Cursor kc = {};
     issue_early(cur, kc, ta, tb);
     issue_late(cur, kc, ta, tb);
     bool first = true;
@@ -848,7 +900,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
         };
         // Product of the wave's 16 rows i and 16 columns j.
         auto mul = [&](int i, int j, const FA& rows, const FB& cols) __attribute__((always_inline)) {
-            mfma_pinned(acc[i][j], cols.all(), rows.all());
+            if constexpr (!S32) mfma_pinned(acc[i][j], cols.all(), rows.all());
         };
         // With 256 x 256 the accumulators leave registers for the fragments of one chunk of 32 k and no more.  A chunk is
         // therefore multiplied in four blocks - the lower half of the fragments X times the lower and the upper half of Y,
@@ -1102,7 +1154,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             };
             bf16x8 F0[FR], F1[FR];
             auto frag = [&](int f, int kk, const char* st) __attribute__((always_inline)) -> bf16x8 {
-                return f < TMA ? fa32[f].read(st, kk) : fb32[f - TMA].read(st + A_BYTES, kk);
+                return f < TMA ? fa[f].read(st, kk) : fb[f - TMA].read(st + A_BYTES, kk);
             };
 #pragma unroll
             for (int f = 0; f < FR; ++f) F0[f] = frag(f, 0, smem);
@@ -1117,19 +1169,19 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 for (int m = 0; m < MB; ++m) {
                     mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
                     follow(m, R64_G0, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 1, st); },
-                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + l); });
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + l); });
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
                     mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
                     follow(m, R64_G1, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 2, st); },
-                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + l); });
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, R64_G3 + R64_G0 + l); });
                 }
 #pragma unroll
                 for (int m = 0; m < MB; ++m) {
                     mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F0[TMA + m % TNN], F0[m / TNN]);
                     follow(m, 0, [&](int f) __attribute__((always_inline)) { F1[f] = frag(f, 3, st); },
-                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st2, (t + NS - 1) * BK, 0); });
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st2, (t + NS - 1) * BK, 0); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 wait_vmcnt<(NS - 2) * LPW>();
@@ -1139,16 +1191,16 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 for (int m = 0; m < MB; ++m) {
                     mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F1[TMA + m % TNN], F1[m / TNN]);
                     follow(m, R64_G3, [&](int f) __attribute__((always_inline)) { F0[f] = frag(f, 0, st1); },
-                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, st, (t + NS) * BK, l); });
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, st, (t + NS) * BK, l); });
                 }
                 s3 = s3a;
             }
-            retire();
             };
             if (TM == 1 || active == 1) loop(std::integral_constant<int, 1>{});
             else if (TM == 2 || active == 2) loop(std::integral_constant<int, TM < 2 ? 1 : 2>{});
             else if (active == 3) loop(std::integral_constant<int, TM < 3 ? 1 : 3>{});
             else loop(std::integral_constant<int, TM < 4 ? 1 : 4>{});
+            retire();
         } else {
             // Hand-scheduled loop over tiles of 32 k = one chunk; the ring holds NS tiles, of which up to NS - 1 are in flight
             // towards a workgroup.  Every LDS read and every load into LDS sits between two matrix instructions (with one
@@ -1231,7 +1283,6 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             // k 16..31 of it and requests the second half of tile t+NS-1; then the wave waits for its part of tile t+1 and meets
             // the others (their parts have landed too, and nobody reads stage t any more); block 1 multiplies k 16..31, reads
             // k 0..15 of tile t+1 and requests the first half of tile t+NS into stage t.
-            static_assert(QUAD || S32, "waves of 64 x 64");
             constexpr int MB = TM * TNN;                 // matrix instructions per block
             constexpr int FR = TM + TNN;                 // fragments per block: A rows first, then B columns
             constexpr int LH = LPW / 2;                  // loads of a tile requested one block earlier than the rest
@@ -1253,7 +1304,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             bf16x8 F0[FR], F1[FR];
 #pragma unroll
             for (int f = 0; f < FR; ++f)
-                F0[f] = f < TM ? fa32[f].read(smem + SB * STAGE, 0) : fb32[f - TM].read(smem + SB * STAGE + A_BYTES, 0);
+                F0[f] = f < TM ? fa[f].read(smem + SB * STAGE, 0) : fb[f - TM].read(smem + SB * STAGE + A_BYTES, 0);
 #pragma unroll 1
             for (int kt = 0; kt < KT; ++kt) {
                 char* cs = smem + st * STAGE;
@@ -1265,8 +1316,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 for (int m = 0; m < MB; ++m) {
                     mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F0[TM + m % TNN], F0[m / TNN]);
                     follow(m, LPW - LH,
-                           [&](int f) __attribute__((always_inline)) { F1[f] = f < TM ? fa32[f].read(cs, 1) : fb32[f - TM].read(cs + A_BYTES, 1); },
-                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, prv, (kt + NS - 1) * BK, LH + l); });
+                           [&](int f) __attribute__((always_inline)) { F1[f] = f < TM ? fa[f].read(cs, 1) : fb[f - TM].read(cs + A_BYTES, 1); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, prv, (kt + NS - 1) * BK, LH + l); });
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave no longer reads stage t
                 wait_vmcnt<(NS - 2) * LPW>();                          // its part of tile t+1 is in
@@ -1276,8 +1327,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 for (int m = 0; m < MB; ++m) {
                     mfma32_pinned<C::OCC == 1>(acc32[m / TNN][m % TNN], F1[TM + m % TNN], F1[m / TNN]);
                     follow(m, LH,
-                           [&](int f) __attribute__((always_inline)) { F0[f] = f < TM ? fa32[f].read(nxt, 0) : fb32[f - TM].read(nxt + A_BYTES, 0); },
-                           [&](int l) __attribute__((always_inline)) { request32(cur, kc, ta, tb, cs, (kt + NS) * BK, l); });
+                           [&](int f) __attribute__((always_inline)) { F0[f] = f < TM ? fa[f].read(nxt, 0) : fb[f - TM].read(nxt + A_BYTES, 0); },
+                           [&](int l) __attribute__((always_inline)) { request(cur, kc, ta, tb, cs, (kt + NS) * BK, l); });
                 }
                 st = stn;
             }
@@ -1290,9 +1341,9 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
 
         // ---- the tile after this one ------------------------------------------------------
         TileCoord nx;
-        // (beside the five-unit loop there are no registers to carry the next tile's offsets through the epilogue: it forms
-        // them where they are used, from a lane number that the compiler cannot tell from another)
-        constexpr bool LATE_BIND = N64;
+        // (beside the five-unit loop, and in GeLU-backward's passes, there are no registers to carry the next tile's offsets through
+        // the epilogue: it forms them where they are used, from a lane number that the compiler cannot tell from another)
+        constexpr bool LATE_BIND = N64 || (EPI == EPI_DGELU && C::OCC == 1);
         AT ta2;
         BT tb2;
         auto bind_again = [&]() __attribute__((always_inline)) {
@@ -1300,7 +1351,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             asm volatile("" : "+v"(l));
             bind(nx, ta2, tb2, l);
         };
-        KCursor kc2 = {};
+        Cursor kc2 = {};
         int vn = -1;
         if constexpr (!ONE) {
             vn = next_tile(vb + step, nx);

@@ -1,0 +1,78 @@
+"""What the compiler made of the bfloat16 GEMM's kernels, from the metadata in the built library: the main loops rest on
+register budgets that nothing else checks."""
+import os
+import re
+import struct
+
+import msgpack
+import pytest
+
+from paper_2506_22175_amd import build
+
+NT_AMDGPU_METADATA, SHT_NOTE = 32, 7
+
+
+def _code_objects(data):
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        (n,) = struct.unpack_from("<Q", data, at + 24)
+        p = at + 32
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + length]:
+                yield data[at + offset:at + offset + size]
+            p += 24 + length
+        at = data.find(magic, at + 24)
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """(operand layout, epilogue, rows, columns) of the GEMMs' kernels -> metadata"""
+    if not os.path.exists(build.OUT):
+        build.build()
+    found = {}
+    for obj in _code_objects(open(build.OUT, "rb").read()):
+        (table,) = struct.unpack_from("<Q", obj, 0x28)
+        size, count = struct.unpack_from("<HH", obj, 0x3a)
+        for s in range(count):
+            if struct.unpack_from("<I", obj, table + s * size + 4)[0] != SHT_NOTE:
+                continue
+            (at,) = struct.unpack_from("<Q", obj, table + s * size + 0x18)
+            name, desc, kind = struct.unpack_from("<III", obj, at)
+            if kind == NT_AMDGPU_METADATA:
+                start = at + 12 + (name + 3) // 4 * 4
+                for k in msgpack.unpackb(obj[start:start + desc])["amdhsa.kernels"]:
+                    found[k[".name"]] = k
+    return found
+
+
+def test_no_vector_register_is_spilled(kernels):
+    gemms = [k for name, k in kernels.items() if "gemm_" in name]
+    assert len(gemms) >= 38
+    for k in gemms:
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, k[".name"]
+
+
+# (layout NN/NT/TN, epilogue: store, GeLU, GeLU-backward, float store, float sums, scattered; rows, columns): vector
+# registers, spilled scalars.  A spilled scalar is a lane write and a lane read in a tile's prologue, which a launch of a
+# tile or two per CU does not cover.
+SMALLER_TILES = {
+    (0, 0, 64, 64): (104, 33), (0, 0, 64, 128): (124, 26), (0, 0, 128, 128): (142, 9), (0, 0, 256, 128): (272, 63),
+    (0, 1, 64, 128): (128, 37), (0, 1, 128, 128): (144, 28), (0, 1, 256, 128): (272, 91),
+    (0, 5, 64, 64): (104, 39), (0, 5, 64, 128): (132, 34), (0, 5, 128, 128): (143, 22), (0, 5, 256, 128): (276, 74),
+    (1, 0, 64, 128): (172, 29), (1, 0, 128, 128): (148, 10), (1, 0, 256, 128): (304, 65),
+    (1, 2, 64, 128): (172, 92), (1, 2, 128, 128): (181, 69), (1, 2, 256, 128): (320, 177),
+    (2, 3, 128, 128): (139, 28), (2, 3, 256, 128): (280, 61), (2, 4, 128, 128): (139, 23), (2, 4, 256, 128): (248, 53),
+}
+
+
+def test_smaller_tiles_keep_within_their_registers(kernels):
+    """What the 256 x 256 tiles' loops need (offsets and a cursor to carry along) must not end up in these."""
+    seen = {}
+    for name, k in kernels.items():
+        m = re.search(r"gemm_bf16_kernelILi(\d)ELi(\d)ENS_7TileCfgILi(\d+)ELi(\d+)E", name)
+        if m:
+            seen[tuple(int(v) for v in m.groups())] = (k[".vgpr_count"], k[".sgpr_spill_count"])
+    for kernel, (registers, spilled) in SMALLER_TILES.items():
+        assert seen[kernel][0] <= registers and seen[kernel][1] <= spilled, (kernel, seen[kernel])
