@@ -53,6 +53,13 @@ __device__ __forceinline__ v4i make_rsrc(const void* p, unsigned bytes) {
              __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
     return d;
 }
+// The descriptor of the same columns without the first rows, of `bytes` bytes together; none may be left.
+__device__ __forceinline__ void drop_rows(v4i& rsrc, unsigned bytes) {
+    const unsigned long long at = ((unsigned long long)(unsigned)rsrc[1] << 32 | (unsigned)rsrc[0]) + bytes;
+    rsrc[0] = (int)(unsigned)at;
+    rsrc[1] = (int)(unsigned)(at >> 32);
+    rsrc[2] = max(rsrc[2] - (int)bytes, 0);
+}
 // 16 bytes per lane from the buffer straight into LDS at lds_off + 16*lane (lds_off is a
 // wave-uniform LDS byte address).  Written as assembly so that the compiler's
 // wait-count bookkeeping does not see an LDS store in flight: it would otherwise make
@@ -67,7 +74,7 @@ __device__ __forceinline__ void load_to_lds(v4i rsrc, unsigned lds_off, unsigned
                  : : "s"(lds_off), "v"(voff), "s"(rsrc) : "memory");
 }
 // The same in two parts for the main loops, with a matrix instruction between them (m0 has to be written one wait state
-// before the load), and with the step along K as the load's scalar offset, which is no part of its bounds check.
+// before the load); the step along K is the load's scalar offset, which is no part of its bounds check, or in the descriptor.
 template <int ADD>
 __device__ __forceinline__ void lds_destination(unsigned lds_off) {
     asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_off), "n"(ADD) : "memory", "scc");
@@ -75,6 +82,9 @@ __device__ __forceinline__ void lds_destination(unsigned lds_off) {
 __device__ __forceinline__ void lds_next_destination() { asm volatile("s_add_u32 m0, m0, 0x400" : : : "memory", "scc"); }
 __device__ __forceinline__ void load_to_destination(v4i rsrc, unsigned voff, unsigned soff) {
     asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" : : "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ void load_to_destination(v4i rsrc, unsigned voff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds" : : "v"(voff), "s"(rsrc) : "memory");
 }
 // an address in a vector register moved by a wave-uniform step, here and now
 __device__ __forceinline__ void move_address(unsigned& at, int by) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(at) : "s"(by)); }
@@ -351,7 +361,8 @@ struct NCTile16 : NCRows<R, WAVES, BK, false> {
     }
     static __device__ __forceinline__ unsigned dst(const char* tile, int wid) { return lds_address(tile) + wid * NI * 1024; }
     // fragments of 16 columns x 32 k: two transposing reads give the lane column nb + d + lane%16, k = 32*kk +
-    // 8*(lane/16) .. +7.  nb and d have no bits in common, so that d turns into an exclusive or: an address each.
+    // 8*(lane/16) .. +7.  nb and d have no bits in common (and tiles begin at multiples of
+    // PITCH), so that d turns into an exclusive or: an address each.
     struct Value {
         v4s lo, hi;
         __device__ __forceinline__ bf16x8 all() const {
@@ -367,7 +378,7 @@ struct NCTile16 : NCRows<R, WAVES, BK, false> {
             const int k_in = 8 * g + (a >> 2);
             const int n = nb + 4 * (a & 3);
 #pragma unroll
-            for (int i = 0; i < BLOCKS; ++i) at[i] = tile + ((k_in * PITCH + (((n >> 3) ^ Rows::turn(k_in)) << 4) + ((n & 7) << 1)) ^ (d(i) << 1));
+            for (int i = 0; i < BLOCKS; ++i) at[i] = (tile + k_in * PITCH + (((n >> 3) ^ Rows::turn(k_in)) << 4) + ((n & 7) << 1)) ^ (d(i) << 1);
         }
         // part (0 or 1) of fragment i
         __device__ __forceinline__ void read(Value& f, int i, int, int kk, int part, unsigned off) const {
@@ -458,13 +469,12 @@ __device__ __forceinline__ void mfma32_pinned(floatx16& acc, const bf16x8& a, co
         asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b) : "memory");
 }
 
-// Which tile of both operands is being requested.  TN only: the reduction dimension may run over the rows of several
-// partitions (up to MAX_KSEGS row ranges, one per partition buffer); tiles never straddle two ranges, and seg says
-// which range it is.
+// TN only: the reduction dimension may run over the rows of several
+// partitions (up to MAX_KSEGS row ranges, one per partition buffer); tiles never straddle two ranges.  KCursor says which range
+// the tile that is being requested lies in and where.
 constexpr int MAX_KSEGS = 8;
 struct TileCoord { int e, q, er, tn, m0, n0, Mdim, Kdim, KT; };      // expert, partition of the launch, their place in row arrays
-struct KCursor { int seg, k0, K; unsigned ka, kb; };       // its first k, among the K of its range; its byte offsets in the operands
-struct KCursor32 { int seg, jl, tiles; };                  // S32, several ranges: its number, among the tiles of its range
+struct KCursor { int seg, jl, tiles; };
 
 // Numbers of the tiles of a launch.  Only tiles that exist are numbered: an expert with fewer rows than the capacity
 // has fewer tile rows (NN, NT), an expert without rows has no tiles at all (TN), so that the workgroups, which take
@@ -550,7 +560,6 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     typedef OperandTile<LAY != GEMM_TN, S32, BM, C::WAVES, AK> AT;
     typedef OperandTile<LAY == GEMM_NT, S32, BN, C::WAVES, BKB> BT;
     constexpr int LPW = AT::NI + BT::NI;         // loads per wave per tile
-    typedef std::conditional_t<S32, KCursor32, KCursor> Cursor;
     // Where two workgroups share a CU the operands' offsets and descriptors are formed again at the top of a
     // tile (the other workgroup covers that) instead of being carried from the one before: with 128 registers
     // for accumulators and fragments the compiler otherwise moves descriptors into vector registers, which the
@@ -681,82 +690,59 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     auto bind_range = [&](const TileCoord& tc, int seg, AT& ta_, BT& tb_) -> int {
         int rows = 0;
         if constexpr (LAY == GEMM_TN) {
-            rows = seg < g.k_segs ? g.counts[seg * g.E + tc.e] : 0;
-            const bf16_t* A = (const bf16_t*)g.A + (size_t)tc.e * g.a_estride + seg * g.a_sstride;
-            const bf16_t* B = (const bf16_t*)g.B + (size_t)tc.e * g.b_estride + seg * g.b_sstride;
-            if constexpr (S32) {
-                ta_.rsrc = AT::rsrc_of(A + tc.m0, g.lda, tc.Mdim - tc.m0, rows);
-                tb_.rsrc = BT::rsrc_of(B + tc.n0, g.ldb, g.N - tc.n0, rows);
-            } else {                             // (and the lanes that the end of the range before switched off)
-                ta_.init(A, g.lda, tc.m0, tc.Mdim, rows, lane, wid);
-                tb_.init(B, g.ldb, tc.n0, g.N, rows, lane, wid);
-            }
+            int e = tc.e;
+            if constexpr (!S32) asm volatile("" : "+s"(e));      // (what follows belongs here, not before the loop)
+            rows = seg < g.k_segs ? g.counts[seg * g.E + e] : 0;
+            const bf16_t* A = (const bf16_t*)g.A + (size_t)e * g.a_estride + seg * g.a_sstride + tc.m0;
+            const bf16_t* B = (const bf16_t*)g.B + (size_t)e * g.b_estride + seg * g.b_sstride + tc.n0;
+            ta_.rsrc = AT::rsrc_of(A, g.lda, tc.Mdim - tc.m0, rows);
+            tb_.rsrc = BT::rsrc_of(B, g.ldb, g.N - tc.n0, rows);
         }
         return rows;
     };
-    // The tile the cursor is at reaches beyond its K: into the next range with rows, or the lanes beyond K switched off.
-    auto enter = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
-        if constexpr (!S32) {
-            if constexpr (LAY == GEMM_TN) {
-                if (g.k_segs > 1) {
-                    while (kc_.k0 >= kc_.K && kc_.seg < g.k_segs) {
-                        ++kc_.seg;
-                        kc_.k0 = 0;
-                        kc_.ka = kc_.kb = 0;
-                        kc_.K = bind_range(tc, kc_.seg, ta_, tb_);
-                    }
-                }
-            }
-            if (kc_.k0 + BK > kc_.K) {
-                ta_.end_at(kc_.k0);
-                tb_.end_at(kc_.k0);
-            }
+    // into the next range with rows, if this one is used up
+    auto next_range = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        while (kc_.jl >= kc_.tiles) {
+            ++kc_.seg;
+            kc_.jl = 0;
+            const int rows = bind_range(tc, kc_.seg, ta_, tb_);
+            kc_.tiles = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
         }
     };
-    auto start = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
-        if constexpr (!S32) {
-            kc_ = {-1, 0, LAY == GEMM_TN && g.k_segs > 1 ? 0 : ta_.K, 0, 0};
-            if (BK > kc_.K) enter(tc, kc_, ta_, tb_);
+    // 256 x 256 weight gradients: on to the next tile.  Its loads have no offset for K: the descriptors begin at the tile's first row
+    // and end at the range's last one.  (Eight scalar instructions a tile.  With K in the loads' scalar offset, which is no part of the bounds
+    // check, the lanes beyond the last row had to be switched off, and on again for the next range: half a microsecond more before
+    // a tile's first product, which tiles of few steps show: 16 experts x 6 rows, 1920/5760: 568 us against 561; 64 experts x 64 rows,
+    // 768/3072, two ranges: 1238 and 1231.)
+    auto advance = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        if constexpr (LAY == GEMM_TN && !S32) {
+            drop_rows(ta_.rsrc, ta_.kstep * BK);
+            drop_rows(tb_.rsrc, tb_.kstep * BK);
+            ++kc_.jl;
+            if (g.k_segs > 1) next_range(tc, kc_, ta_, tb_);
         }
     };
-    // on to the next tile (before its first load; a handful of scalar instructions, in the shadow of a matrix instruction)
-    auto advance = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) __attribute__((always_inline)) {
-        if constexpr (!S32) {
-            kc_.k0 += BK;
-            kc_.ka += ta_.koff(BK);
-            kc_.kb += tb_.koff(BK);
-            if (kc_.k0 + BK > kc_.K) enter(tc, kc_, ta_, tb_);
+    // The descriptors into scalar registers, where the compiler does not keep them: a load may follow five wait states later.
+    auto settle = [&](AT& ta_, BT& tb_) __attribute__((always_inline)) {
+        for (v4i* r : {&ta_.rsrc, &tb_.rsrc}) {
+            int w0 = __builtin_amdgcn_readfirstlane((*r)[0]), w1 = __builtin_amdgcn_readfirstlane((*r)[1]), w2 = __builtin_amdgcn_readfirstlane((*r)[2]);
+            asm volatile("" : "+s"(w0), "+s"(w1), "+s"(w2) : : "memory");
+            (*r)[0] = w0; (*r)[1] = w1; (*r)[2] = w2;
         }
     };
-    // The byte offsets into scalar registers, where the compiler does not keep them: a load may follow five wait states later.
-    auto settle = [&](Cursor& kc_) __attribute__((always_inline)) {
-        if constexpr (!S32) {
-            kc_.ka = __builtin_amdgcn_readfirstlane(kc_.ka);
-            kc_.kb = __builtin_amdgcn_readfirstlane(kc_.kb);
-            asm volatile("" : "+s"(kc_.ka), "+s"(kc_.kb) : : "memory");
-        }
+    // load l of the tile the descriptors begin with, to the LDS address in m0
+    auto go = [&](const AT& ta_, const BT& tb_, int l) __attribute__((always_inline)) {
+        if (l < AT::NI) load_to_destination(ta_.rsrc, ta_.voff[l]);
+        else load_to_destination(tb_.rsrc, tb_.voff[l - AT::NI]);
     };
-    // its load l, to the LDS address in m0
-    auto go = [&](const Cursor& kc_, const AT& ta_, const BT& tb_, int l) __attribute__((always_inline)) {
-        if constexpr (!S32) {
-            if (l < AT::NI) load_to_destination(ta_.rsrc, ta_.voff[l], kc_.ka);
-            else load_to_destination(tb_.rsrc, tb_.voff[l - AT::NI], kc_.kb);
-        }
-    };
-    // load l of the tile that starts at k0 (tiles in ascending order, each begun with load 0).  S32: the cursor moves on with
-    // load 0, into the next range with rows where the last one is used up, and past the last range, where everything reads as zeros
-    auto request = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
+    // load l of the tile that starts at k0 (tiles in ascending order, each begun with load 0: that is where the cursor moves on)
+    auto request = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_, char* st, int k0, int l) {
         if constexpr (S32) {
             if constexpr (LAY == GEMM_TN) {
                 if (g.k_segs > 1) {
                     if (l == 0) {
                         if (k0 == 0) { kc_.seg = -1; kc_.jl = 0; kc_.tiles = 0; } else ++kc_.jl;
-                        while (kc_.jl >= kc_.tiles) {
-                            ++kc_.seg;
-                            kc_.jl = 0;
-                            const int rows = bind_range(tc, kc_.seg, ta_, tb_);
-                            kc_.tiles = kc_.seg < g.k_segs ? (rows + BK - 1) / BK : 0x7fffffff;
-                        }
+                        next_range(tc, kc_, ta_, tb_);
                     }
                     k0 = kc_.jl * BK;
                 }
@@ -764,9 +750,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             if (l < AT::NI) ta_.load_one(st, k0, wid, l);
             else tb_.load_one(st + A_BYTES, k0, wid, l - AT::NI);
         } else {
-            if (l == 0) { if (k0 == 0) start(tc, kc_, ta_, tb_); else advance(tc, kc_, ta_, tb_); }
-            if (l < AT::NI) load_to_lds(ta_.rsrc, AT::dst(st, wid) + l * 1024, ta_.voff[l] + kc_.ka);
-            else load_to_lds(tb_.rsrc, BT::dst(st + A_BYTES, wid) + (l - AT::NI) * 1024, tb_.voff[l - AT::NI] + kc_.kb);
+            if (l == 0) {
+                if (k0 > 0) advance(tc, kc_, ta_, tb_);
+                else if (g.k_segs > 1) { kc_ = {-1, 0, 0}; next_range(tc, kc_, ta_, tb_); }
+            }
+            if (l < AT::NI) load_to_lds(ta_.rsrc, AT::dst(st, wid) + l * 1024, ta_.voff[l]);
+            else load_to_lds(tb_.rsrc, BT::dst(st + A_BYTES, wid) + (l - AT::NI) * 1024, tb_.voff[l - AT::NI]);
         }
     };
     // unit of one operand (rings and units of their own): loads l0 to l1 - 1 of the unit that starts at k0
@@ -790,7 +779,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     constexpr int UL = N64 ? 8 : 0;
     static_assert(!N64 || (AT::NI == 8 && BT::NI == 8), "eight loads per wave and unit");
     // the part of a tile's first loads that does not touch the staging region, and the rest
-    auto issue_early = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) {
+    auto issue_early = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
             // what the loop expects to be on its way when it starts: wide units 0 and 1 and the first
             // quarter of unit 2 (late: its slot is the staging region), narrow tiles 0..2 and half of tile 3
@@ -815,7 +804,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 for (int l = 0; l < LPW; ++l) request(tc, kc_, ta_, tb_, smem + (FIRST + s) * STAGE, s * BK, l);
         }
     };
-    auto issue_late = [&](const TileCoord& tc, Cursor& kc_, AT& ta_, BT& tb_) {
+    auto issue_late = [&](const TileCoord& tc, KCursor& kc_, AT& ta_, BT& tb_) {
         if constexpr (W64) {
             load_unit(ta_, wide_slot(2), 128, 0, WL / 4);
         } else if constexpr (N64) {
@@ -843,7 +832,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
     AT ta;
     BT tb;
     bind(cur, ta, tb, lane);
-    Cursor kc = {};
+    KCursor kc = {};
     issue_early(cur, kc, ta, tb);
     issue_late(cur, kc, ta, tb);
     bool first = true;
@@ -1218,17 +1207,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                 asm volatile("" ::: "memory");
                 FA X[2][4];
                 FB Y[2][4];
-                // (an odd number of tiles begins with the second half of an iteration)
+                // (an odd number of tiles begins with the second half of an iteration; Y's lower half is read into both places rather
+                // than into one of them, which would cost copies of it behind the branch)
                 bool skip = KT & 1;
 #pragma unroll
                 for (int f = 0; f < 4; ++f) whole_a(X[0][f], 0, f, 0);
-                if (skip) {
 #pragma unroll
-                    for (int f = 0; f < 4; ++f) whole_b(Y[1][f], 0, f, 0);
-                } else {
+                for (int f = 0; f < 4; ++f) whole_b(Y[0][f], 0, f, 0);
 #pragma unroll
-                    for (int f = 0; f < 4; ++f) whole_b(Y[0][f], 0, f, 0);
-                }
+                for (int f = 0; f < 4; ++f) whole_b(Y[1][f], 0, f, 0);
                 int kt = 0;
                 // y: the place of the lower half of Y
                 auto tile = [&](auto y) __attribute__((always_inline)) {
@@ -1242,21 +1229,20 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
                         for (int m = 0; m < 16; ++m) {
                             const int x = new_x ? m / 4 : m % 4, y = new_x ? m % 4 : m / 4;
                             mul(xh * 4 + x, yh * 4 + y, X[xh][x], Y[ys][y]);
-                            if (L0 == 0 && m == 7) { advance(cur, kc, ta, tb); settle(kc); }
+                            if (L0 == 0 && m == 7) { advance(cur, kc, ta, tb); settle(ta, tb); }
                             Gaps<16>::reads(m, reads, read);
                             Gaps<16>::loads(m, [&](int l) __attribute__((always_inline)) {
                                                 if (l) lds_next_destination();
                                                 else if constexpr (L0 < AT::NI) lds_destination<L0 * 1024>(AT::dst(to, wid));
                                                 else lds_destination<A_BYTES + (L0 - AT::NI) * 1024>(BT::dst(to, wid));
                                             },
-                                            [&](int l) __attribute__((always_inline)) { go(kc, ta, tb, L0 + l); });
+                                            [&](int l) __attribute__((always_inline)) { go(ta, tb, L0 + l); });
                             Gaps<16>::moves(m, false, move);
                         }
                     };
 #define READ(what) [&](int r) __attribute__((always_inline)) { what; }
 #define MOVE(what) [&](int e) __attribute__((always_inline)) { what; }
 #define L(n) std::integral_constant<int, n>{}
-                    settle(kc);
                     pause();
                     block(0, 0, LO, false, 4 * BR, READ(frag_b(Y[UP][r / BR], 0, 4 + r / BR, 0, r % BR)), prv, L(4), MOVE(move_address(fa.at[e], next)));
                     block(0, 1, UP, false, 4 * AR, READ(frag_a(X[1][r / AR], 0, 4 + r / AR, 0, r % AR)), prv, L(6), MOVE(move_address(fb.at[4 + e], next)));
@@ -1351,7 +1337,7 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs& g, int tiles_m, int t
             asm volatile("" : "+v"(l));
             bind(nx, ta2, tb2, l);
         };
-        Cursor kc2 = {};
+        KCursor kc2 = {};
         int vn = -1;
         if constexpr (!ONE) {
             vn = next_tile(vb + step, nx);

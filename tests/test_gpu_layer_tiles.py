@@ -56,7 +56,8 @@ def test_scattered_and_gathered_rows(T, M, H, E, n, second, first):
     (136, 3232, 5, 131, 1.25, 8, 1, HALF),          # ranges of a step of 64 and a few rows more
     (264, 1032, 4, 700, 1.0, 3, 0, SMALL),
     (768, 1032, 16, 700, 1.0, 3, 0, LARGE),
-], ids=["half_add", "half_store", "half_short_ranges", "small_add", "large_add"])
+    (768, 1032, 16, 700, 1.0, 3, 1, LARGE),         # experts without a row in any partition of a group, ranges of a few rows
+], ids=["half_add", "half_store", "half_short_ranges", "small_add", "large_add", "large_store"])
 def test_weight_gradients_over_several_partitions(M, H, E, mean, cf, G, overwrite, tile):
     """Skewed loads: ranges of every length between partitions without a row for the expert.  One reduction over a
     group's rows gives what adding partition by partition gives, up to the rounding of float sums."""
@@ -72,6 +73,9 @@ def test_weight_gradients_over_several_partitions(M, H, E, mean, cf, G, overwrit
     group = runner.run_layer_step(s, d, n, 0, grad_overwrite=overwrite, wgrad_group=G)
     c = one["counts"]
     assert (c == 0).any() and (c % 64 != 0).any()
+    if tile == LARGE:
+        tiles = (c + 31) // 32
+        assert (c[:G].sum(axis=0) == 0).any() and (c[c > 0] < 32).any() and (tiles % 2 == 1).any() and ((tiles > 0) & (tiles % 2 == 0)).any()
     for k_ in ("y", "dx", "counts", "slot"):
         assert np.array_equal(group[k_], one[k_]), k_
     # the terms of an element are alike in size and of either sign: r of them sum to about sqrt(r) of one and round
@@ -79,3 +83,29 @@ def test_weight_gradients_over_several_partitions(M, H, E, mean, cf, G, overwrit
     r = int(c.sum(axis=0).max())
     for k_ in ("dW1", "dW2"):
         assert _relerr(group[k_], one[k_]) <= max(1e-5, r ** 1.5 * 2.0 ** -24 / 8), k_
+
+
+@pytest.mark.parametrize("M,H", [(768, 1032), (1032, 1288)])
+@pytest.mark.parametrize("overwrite", [0, 1])
+def test_weight_gradients_do_not_depend_on_the_partitions(M, H, overwrite):
+    """Every partition's rows of an expert are whole tiles of 32 k, in odd and even numbers and none, so that one reduction over
+    eight partitions adds the same products in the same order as one over all rows at once.  The other GEMMs take different
+    tiles for the two."""
+    E, n = 16, 8
+    rows = np.array([0, 32, 64, 96, 128, 160, 192, 224, 0, 32, 320, 96, 128, 32, 416, 128])
+    T = n * int(rows.sum())
+    s = synth.custom_shape(T, M, H, E, 1, 416 / 128, dtype="bf16", x_std=1.0, w_std=0.05, name="blocks")
+    d = synth.make_inputs(s, seed=31)
+    rng = np.random.default_rng(31)
+    counts = np.stack([np.roll(rows, p) for p in range(n)])
+    chosen = np.concatenate([rng.permutation(np.repeat(np.arange(E), counts[p])) for p in range(n)])
+    d["x"][:, :E] = 8.0 * np.eye(E, dtype=np.float32)[chosen]
+    d["Wg"][:E] = 4.0 * np.eye(E, dtype=np.float32)
+    got = []
+    for parts, group in ((n, 8), (1, 0)):
+        cfg = B.make_config(T, M, H, E, 1, 416 / 128, parts, B.MOE_BF16, 0, overwrite, wgrad_group=group)
+        assert all(B.moe_gemm_tile(cfg, parts - 1, gemm) == LARGE for gemm in ("dW1", "dW2"))
+        got.append(runner.run_layer_step(s, d, parts, 0, grad_overwrite=overwrite, wgrad_group=group))
+    assert np.array_equal(got[0]["counts"], counts) and np.array_equal(got[1]["counts"][0], counts.sum(axis=0))
+    for k_ in ("y", "dx", "dW1", "dW2"):
+        assert np.isfinite(got[0][k_]).all() and np.array_equal(got[0][k_], got[1][k_]), k_

@@ -65,14 +65,17 @@ SMALLER_TILES = {
     (1, 2, 64, 128): (172, 92), (1, 2, 128, 128): (181, 69), (1, 2, 256, 128): (320, 177),
     (2, 3, 128, 128): (139, 28), (2, 3, 256, 128): (280, 61), (2, 4, 128, 128): (139, 23), (2, 4, 256, 128): (248, 53),
 }
+# 256 x 256 weight gradients: the descriptors carry K, so that neither offsets nor lanes are formed again for every tile and range
+LARGE_WEIGHT_GRADIENTS = {(2, 3, 256, 256): (468, 68), (2, 4, 256, 256): (400, 50)}
 
 
-def test_smaller_tiles_keep_within_their_registers(kernels):
-    """What the 256 x 256 tiles' loops need (offsets and a cursor to carry along) must not end up in these."""
+@pytest.mark.parametrize("bounds", [SMALLER_TILES, LARGE_WEIGHT_GRADIENTS], ids=["smaller_tiles", "large_weight_gradients"])
+def test_tiles_keep_within_their_registers(kernels, bounds):
+    """What the 256 x 256 tiles' loops need (offsets to carry along) must not end up in the smaller tiles."""
     seen = {}
     for name, k in kernels.items():
         m = re.search(r"gemm_bf16_kernelILi(\d)ELi(\d)ENS_7TileCfgILi(\d+)ELi(\d+)E", name)
         if m:
             seen[tuple(int(v) for v in m.groups())] = (k[".vgpr_count"], k[".sgpr_spill_count"])
-    for kernel, (registers, spilled) in SMALLER_TILES.items():
+    for kernel, (registers, spilled) in bounds.items():
         assert seen[kernel][0] <= registers and seen[kernel][1] <= spilled, (kernel, seen[kernel])
