@@ -75,6 +75,8 @@ __device__ __forceinline__ void load_to_lds(v4i rsrc, unsigned lds_off, unsigned
 }
 // The same in two parts for the main loops, with a matrix instruction between them (m0 has to be written one wait state
 // before the load); the step along K is the load's scalar offset, which is no part of its bounds check, or in the descriptor.
+// m0 is a reserved register, which a statement cannot name as written or read: that no instruction of the compiler's stands
+// between the two parts is checked in the built code (tests/test_kernel_registers.py).
 template <int ADD>
 __device__ __forceinline__ void lds_destination(unsigned lds_off) {
     asm volatile("s_add_u32 m0, %0, %1" : : "s"(lds_off), "n"(ADD) : "memory", "scc");

@@ -1,8 +1,10 @@
-"""What the compiler made of the bfloat16 GEMM's kernels, from the metadata in the built library: the main loops rest on
-register budgets that nothing else checks."""
+"""What the compiler made of the bfloat16 GEMM's kernels, from the metadata and the code in the built library: the main loops rest
+on register budgets, and their loads on a register that the compiler does not know to be in use, which nothing else checks."""
 import os
 import re
+import shutil
 import struct
+import subprocess
 
 import msgpack
 import pytest
@@ -27,12 +29,17 @@ def _code_objects(data):
 
 
 @pytest.fixture(scope="module")
-def kernels():
-    """(operand layout, epilogue, rows, columns) of the GEMMs' kernels -> metadata"""
+def objects():
     if not os.path.exists(build.OUT):
         build.build()
+    return list(_code_objects(open(build.OUT, "rb").read()))
+
+
+@pytest.fixture(scope="module")
+def kernels(objects):
+    """name -> metadata"""
     found = {}
-    for obj in _code_objects(open(build.OUT, "rb").read()):
+    for obj in objects:
         (table,) = struct.unpack_from("<Q", obj, 0x28)
         size, count = struct.unpack_from("<HH", obj, 0x3a)
         for s in range(count):
@@ -79,3 +86,40 @@ def test_tiles_keep_within_their_registers(kernels, bounds):
             seen[tuple(int(v) for v in m.groups())] = (k[".vgpr_count"], k[".sgpr_spill_count"])
     for kernel, (registers, spilled) in bounds.items():
         assert seen[kernel][0] <= registers and seen[kernel][1] <= spilled, (kernel, seen[kernel])
+
+
+def _objdump():
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    for root in (os.path.dirname(os.path.dirname(os.path.realpath(hipcc))), "/opt/rocm"):
+        tool = os.path.join(root, "llvm", "bin", "llvm-objdump")
+        if os.path.exists(tool):
+            return tool
+    pytest.skip("no disassembler for gfx950")
+
+
+def test_every_load_into_lds_has_the_address_that_was_set_for_it(objects, tmp_path):
+    """m0 holds the LDS address of a buffer load into LDS.  The kernels set it in assembly, some loads one or more instructions
+    later, and the compiler, for which m0 cannot be named as changed or read by such a statement, could write it in between."""
+    loads = 0
+    for i, obj in enumerate(objects):
+        path = tmp_path / f"{i}.co"
+        path.write_bytes(obj)
+        text = subprocess.run([_objdump(), "-d", "--no-show-raw-insn", str(path)], capture_output=True, text=True, check=True).stdout
+        for kernel in re.split(r"\n(?=[0-9a-f]{16} <)", text):
+            if "gemm_bf16" not in kernel.split("\n", 1)[0]:
+                continue
+            code = [re.sub(r"\s*//.*", "", line).strip() for line in kernel.splitlines()[1:]]
+            code = [line for line in code if line]
+            set_at = None                              # where m0 was written for a load to come
+            for at, line in enumerate(code):
+                if re.match(r"buffer_load_dwordx4 .*\blds$", line):
+                    assert set_at is not None and at - set_at >= 2, (line, code[max(0, at - 4):at])
+                    loads, set_at = loads + 1, None
+                elif re.search(r"\bm0\b", line):
+                    # either statement that sets it, and only once for a load
+                    assert re.match(r"s_add_u32 m0, (m0, 0x400|s\d+, )", line) or \
+                        (re.match(r"s_mov_b32 m0, ", line) and code[at + 1] == "s_nop 0" and code[at + 2].endswith(" lds")), line
+                    assert set_at is None, code[set_at:at + 1]
+                    set_at = at
+            assert set_at is None
+    assert loads > 1000
