@@ -170,12 +170,12 @@ def test_expert_ffn_at_tile_edges(dtype, M, H, counts, Cp, recompute, overwrite)
 
 # 256 x 256 tiles multiply with another shape of the matrix instruction than the smaller ones: the same products in the same
 # order, so that a result does not depend on the tiles that a schedule gives it.  Rows and tiles of 32 k in odd and even
-# numbers, dimensions that end inside a step.
-@pytest.mark.parametrize("M,H,counts,Cp,mean,gemms", [
-    (768, 1032, (700, 513, 640, 641, 1, 0, 257, 384, 385, 128, 129, 639, 577, 576, 512, 64), 700, 8, GEMMS[:5]),
-    (1024, 1032, (65, 33, 32, 225, 256, 700, 0, 449), 700, 100, GEMMS[5:]),
-], ids=["rows", "weight_gradients"])
-def test_expert_ffn_is_the_same_in_large_and_small_tiles(M, H, counts, Cp, mean, gemms):
+# numbers, dimensions that end inside a step, experts without rows.
+@pytest.mark.parametrize("M,H,counts,Cp,mean,overwrite,gemms", [
+    (768, 1032, (700, 513, 640, 641, 1, 0, 257, 384, 385, 128, 129, 639, 577, 576, 512, 64), 700, 8, 0, GEMMS),
+    (1024, 1032, (65, 33, 32, 225, 256, 700, 0, 449), 700, 100, 1, GEMMS[5:]),
+], ids=["all_add", "weight_gradients_store"])
+def test_expert_ffn_is_the_same_in_large_and_small_tiles(M, H, counts, Cp, mean, overwrite, gemms):
     from paper_2506_22175_amd import binding as B
     E, d, dt = len(counts), "cuda:0", torch.bfloat16
     g = torch.Generator(d).manual_seed(29)
@@ -183,19 +183,29 @@ def test_expert_ffn_is_the_same_in_large_and_small_tiles(M, H, counts, Cp, mean,
     W1 = (torch.randn((E, M, H), generator=g, device=d) * 0.05).to(dt)
     W2 = (torch.randn((E, H, M), generator=g, device=d) * 0.05).to(dt)
     w = torch.rand((E * Cp,), generator=g, device=d)
+    old1, old2 = torch.randn((E, M, H), generator=g, device=d), torch.randn((E, H, M), generator=g, device=d)
     c = torch.tensor([counts], dtype=torch.int32, device=d)
     kept = torch.cat([torch.arange(e * Cp, e * Cp + r, device=d) for e, r in enumerate(counts)])
+    padding = torch.ones((E * Cp,), dtype=torch.bool, device=d)
+    padding[kept] = False
+    for t in (x, dy, w):
+        t[padding] = float("nan")
     got = []
     for rows, large in ((Cp, True), (mean, False)):
-        cfg = B.make_config(E * rows, M, H, E, 1, Cp / rows, 1, B.MOE_BF16, 0, 1)
+        cfg = B.make_config(E * rows, M, H, E, 1, Cp / rows, 1, B.MOE_BF16, 0, overwrite)
         assert B.moe_capacity(cfg) == Cp
         assert all((B.moe_gemm_tile(cfg, 0, gemm) == LARGE) == large for gemm in gemms)
-        new = lambda *s, dtype=dt: torch.zeros(s, dtype=dtype, device=d)  # noqa: E731
-        Z, A, DO, dZ, dDI = new(E * Cp, H), new(E * Cp, H), new(E * Cp, M), new(E * Cp, H), new(E * Cp, M)
-        dW1, dW2 = new(E, M, H, dtype=torch.float32), new(E, H, M, dtype=torch.float32)
+        nan = lambda *s, dtype=dt: torch.full(s, float("nan"), dtype=dtype, device=d)  # noqa: E731
+        Z, A, DO, dZ, dDI = nan(E * Cp, H), nan(E * Cp, H), nan(E * Cp, M), nan(E * Cp, H), nan(E * Cp, M)
+        dW1, dW2 = (nan(E, M, H, dtype=torch.float32), nan(E, H, M, dtype=torch.float32)) if overwrite else (old1.clone(), old2.clone())
         B.moe_expert_ffn_fwd(cfg, 0, x, c, W1, W2, Z, A, DO)
         B.moe_expert_ffn_bwd(cfg, 0, 0, x, Z, dy, c, w, W1, W2, dZ, dDI, dW1, dW2, None)
         torch.cuda.synchronize()
         got.append({"DO": DO[kept], "dZ": dZ[kept], "dDI": dDI[kept], "dW1": dW1, "dW2": dW2})
     for name, value in got[0].items():
-        assert torch.equal(value, got[1][name]), name
+        assert bool(torch.isfinite(value).all()) and torch.equal(value, got[1][name]), name
+    empty = counts.index(0)
+    if overwrite:
+        assert not bool(got[0]["dW1"][empty].any()) and not bool(got[0]["dW2"][empty].any())
+    else:
+        assert torch.equal(got[0]["dW1"][empty], old1[empty]) and torch.equal(got[0]["dW2"][empty], old2[empty])
