@@ -1,18 +1,19 @@
 // bf16 grouped GEMM on the CDNA4 matrix cores for the expert FFN: the two linear
 // layers of every local expert (Section II-B2) and their four backward GEMMs
 // (Table II counts 2 forward and 4 backward GEMM units per partition, 5 with
-// recomputation).  Float accumulation in v_mfma_f32_16x16x32_bf16: the main loops run
-// at the chip's power limit, and of the two shapes of the instruction this one takes less
-// power (all CUs, operands from registers, normally distributed: 1.95 PFLOP/s at 1.95 GHz,
-// 32x32x16 1.67 at 1.67 GHz).
+// recomputation).  Float accumulation, in 256 x 256 tiles with v_mfma_f32_16x16x32_bf16:
+// their main loops run at the chip's power limit, and of the two shapes of the instruction
+// this one takes less power (all CUs, operands from registers, normally distributed: 1.95
+// PFLOP/s at 1.95 GHz, 32x32x16 1.67 at 1.67 GHz).  Smaller tiles use v_mfma_f32_32x32x16_bf16
+// (TileCfg::S32).
 //
 // One workgroup computes a BM x BN tile of one expert with WAVES_M x WAVES_N
-// wavefronts, each owning (BM/WAVES_M) x (BN/WAVES_N) as 16x16 MFMA tiles.
+// wavefronts, each owning (BM/WAVES_M) x (BN/WAVES_N) as 16x16 or 32x32 MFMA tiles.
 //
-// Operand tiles (64 K-elements deep) travel global -> LDS with
+// Operand tiles (32 or 64 K-elements deep) travel global -> LDS with
 // buffer_load_dwordx4 ... lds: no staging registers, no LDS-write instructions,
 // and rows beyond the valid range read as zeros in hardware (the buffer
-// descriptor ends after the last valid row), so the main loop has no branches.
+// descriptor ends after the last valid row): no row needs a branch.
 // Each lane of such a load lands at LDS base + 16*lane, so the LDS layout is
 // chosen by choosing which 16 global bytes each lane fetches:
 //   * an operand whose rows are K-contiguous in memory ("KC": A of NN/NT, B of
@@ -1701,7 +1702,7 @@ void gemm_bf16_backward_kernel(BackwardArgs a) {
 //          and come in whole lines anyway.
 // (Shapes with two waves of 128 x 64 per SIMD - TileCfg<256, 256, 32, 5, 2, 4, 2, LOOP_PIPE32> - ran the GeLU
 // epilogues faster and the main loops slower, reading half as much again from LDS; with the cheaper GeLU
-// arithmetic the four-wave shapes win everywhere.)
+// arithmetic the four-wave shapes won everywhere, measured with the 32 x 32 instruction.)
 typedef TileCfg<256, 256, 32, 5, 2, 2, 1, LOOP_PIPE32> Cfg4;
 typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_W64> CfgW;
 typedef TileCfg<256, 256, 64, 3, 2, 2, 1, LOOP_N64> CfgN;
@@ -1762,15 +1763,17 @@ static moe_status launch_one(const GemmArgs& a, hipStream_t s) {
 // of that, leaves CUs idle, and a workgroup's epilogue is only covered where two workgroups share a CU.  The estimate
 // counts the rounds of tiles over the workgroups; the times (us) of a 64-k step per layout (NN, NT, TN), of a step of
 // a nearly empty tile, and of an epilogue (store, GeLU, GeLU-backward, float store, float accumulation) were fitted
-// to 516 measured launches in all four shapes (1 to 64 experts of 8 to 8192 rows, dimensions 64 to 8192, even and
-// skewed random loads): the choice is on average 2 % slower than the best tile of each launch, 256 x 256 throughout
-// 32 % slower.  The host does not know the loads; it takes every expert to have the mean.  A launch for several
+// to 516 launches in all four shapes, measured when 256 x 256 tiles had the 32 x 32 instruction; their steps are 8 to 16 % shorter
+// now where they fill the chip, the other shapes' are what they were.  They choose as well with the present loops: over 12 500 launches
+// (the five GEMMs of 2500 layers, 1 to 64 experts of 8 to 8192 rows, dimensions 64 to 8192, even and uneven loads) the choice is
+// on average 2.2 % slower than the best tile of each launch, in 12 % of them by more than 5 %; 256 x 256 throughout is 44 % slower.
+// The host does not know the loads; it takes every expert to have the mean.  A launch for several
 // partitions counts the tiles of all of them: a step of 3003 tokens x 3, 776/2600, 6 experts, three partitions takes
 // 596 us, and 608 where it keeps the shape that suits one partition's tiles (of 35 layers, drawn and listed, seven gain
 // 1.5 to 13 %, two lose 1.2 %).
 struct TileCost { int bm, bn, per_cu; double step[3], tail_step, epi[5]; };
 static constexpr TileCost TILE_COSTS[5] = {
-    {256, 256, 1, {1.09, 1.52, 1.48}, 0.85, {3.3, 10.8, 27.0, 11.1, 20.9}},      // CfgW / Cfg4
+    {256, 256, 1, {1.09, 1.52, 1.48}, 0.85, {3.3, 10.8, 27.0, 11.1, 20.9}},      // CfgW, CfgN, Cfg4
     {256, 128, 1, {0.87, 0.84, 0.93}, 0.72, {3.4, 8.6, 19.1, 6.7, 11.0}},        // CfgM
     {128, 128, 2, {0.90, 1.29, 0.94}, 0.0, {3.0, 5.0, 9.3, 6.5, 8.8}},           // CfgS (two tiles at a time)
     {64, 128, 1, {0.44, 0.42, 0.0}, 0.92, {1.5, 2.5, 5.0, 0.0, 0.0}},            // CfgT (not for TN)
@@ -1882,10 +1885,10 @@ static moe_status check_args(GemmLayout lay, GemmEpilogue epi, const GemmArgs& a
 }
 
 // Rounds of tiles from which on the persistent launches one by one are the faster ones: of 32 768 tokens, 2048/8192, 16
-// experts, two partitions (2 x 16 rounds) the step takes 14.55 ms with them and 14.64 with both weight gradients
-// together; 8192 tokens, 768/3072, 64 experts (18 rounds of weight gradients, 3 of the input gradient) 1.35 and 1.33 ms.
-// Below: 16 384 tokens, 1024/4096, 8 experts, four partitions (0.6 + 4 rounds; 108 + 97 + 94 us one by one) 3.03 and 2.85
-// ms, 16 unevenly loaded experts 2.94 and 2.72, 4096 tokens, 512/2048 435 and 397 us.
+// experts, two partitions (2 x 16 rounds) the step takes 13.09 ms with them and 13.19 with all three
+// together; 8192 tokens, 768/3072, 64 experts (18 rounds of weight gradients, 3 of the input gradient) 1.242 and 1.226 ms.
+// Below: 16 384 tokens, 1024/4096, 8 experts, four partitions (0.6 + 4 rounds) 2.59 and 2.47
+// ms, 16 unevenly loaded experts 2.59 and 2.46, 4096 tokens, 512/2048 345 and 311 us.
 // (Tiles of full experts, since the host does not know the loads and a launch has to have room for them: what the capacity adds
 // are workgroups without a tile at the launch's end.  Ten shapes at capacity factors of 1.25 to 8: what a launch below the line takes varies by 1 %.)
 constexpr int BACKWARD_ROUNDS = 24;
@@ -1893,9 +1896,10 @@ constexpr int BACKWARD_ROUNDS = 24;
 // Whether they are the faster ones below that: apart, each ends in a round that leaves CUs idle and together only the last one does, but
 // a workgroup of the launch for all has one tile and begins it with nothing requested yet, where a persistent one fetches its next
 // tile under the last one's epilogue: 1.5 us a tile of 256 x 256 rows and columns (those of 128 x 128 have a second workgroup
-// beside them).  Fitted to 1326 backwards, even and uneven loads: 11 are more than 2 % slower together than apart (5 %), without this 93 (9 %).
-// us, apart / together: 64 experts x 64 rows, 768/3072 (9 + 9 rounds of weight gradients, 1.5) 430 / 442, 24 x 457, 2048/4096
-// (12 + 12, 3) 1216 / 1279, 8 x 1024, 1024/4096 (2 + 2, 0.6) 417 / 368; both weight gradients alone, 16 x 500, 2048/5120 (10 + 10) 977 / 1001.
+// beside them).  Fitted to 1326 backwards, even and uneven loads, with the loops before the present ones; of 2500 with these, 81 are more than
+// 2 % slower than the better of the two (20 more than 5 %, one 16 %).
+// us of these kernels, apart / together: 64 experts x 64 rows, 768/3072 (9 + 9 rounds of weight gradients, 1.5) 312 / 318, 24 x 457, 2048/4096
+// (12 + 12, 3) 775 / 798, 16 x 500, 2048/5120 632 / 634, 8 x 1024, 1024/4096 (2 + 2, 0.6) 221 / 217 and two launches less.
 static bool together_pays(const GemmArgs* dgrad, const GemmArgs& w2, const GemmArgs& w1, const GateDlArgs* gate, int epi, int cw, int cd) {
     if (cw == 2) return true;
     const int cus = compute_units();
