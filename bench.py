@@ -7,7 +7,8 @@ expert FFN forward, combine, then the backward pass (moe_layer_step).  Prints on
 JSON line with the whole-step throughput, the roofline of the dominant kernel
 (the bf16 MFMA grouped GEMM) measured with HIP events inside the timed region,
 the HBM-bound permutation kernels beside it, workspace bytes per memory-reuse
-mode, and the CPU oracle timed on a bounded sample of the same workload.
+mode, and the CPU oracle timed on a bounded sample of the same workload.  The short
+runs of other configurations (--no-sweep: none) are a second JSON line on stderr.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload large] [--n 2] [--reuse 2]
 """
@@ -324,6 +325,22 @@ def granularity_report(args, shape, inp, reuse):
     return out
 
 
+# the reports of the runs beside the timed one: several times as long as the rest together
+DETAILS = ("interference_and_cost_model", "gpt_partitions_by_mode", "gathered_first_gemm", "other_workloads",
+           "adaptive_granularity")
+
+
+def report_lines(out):
+    """The result as one JSON line, short enough to be found whole in the last few thousand bytes of a log, and the
+    other runs' reports as another (None if there are none)."""
+    line = {k_: v for k_, v in out.items() if k_ not in DETAILS}
+    details = {k_: out[k_] for k_ in DETAILS if out.get(k_)}
+    if "measured" in line.get("memory_bytes", {}):
+        details["memory_measured"] = line["memory_bytes"]["measured"]
+        line["memory_bytes"] = {k_: v for k_, v in line["memory_bytes"].items() if k_ != "measured"}
+    return json.dumps(line), json.dumps(details) if details else None
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -408,7 +425,10 @@ def main():
         out["adaptive_granularity"] = granularity_report(args, shape, inp, args.reuse)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(shape, inp, args.cpu_tokens)
-    print(json.dumps(out))
+    line, details = report_lines(out)
+    if details:
+        print(details, file=sys.stderr, flush=True)
+    print(line)
 
 
 if __name__ == "__main__":
